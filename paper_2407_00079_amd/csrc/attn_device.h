@@ -73,6 +73,19 @@ __device__ __forceinline__ void dma16(const char* vaddr, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                :: "v"(vaddr), "s"(lds_base) : "m0", "memory");
 }
+// The chunks of a page (1 KiB each, contiguous in the pool and in LDS): the immediate offset of the instruction advances
+// the global and the LDS address alike, so one base and one M0 serve all of them.
+template <int CHUNKS>
+__device__ __forceinline__ void dma16_page(const char* sbase, const uint32_t (&voff)[CHUNKS], uint32_t lds_base) {
+  static_assert(CHUNKS == 2 || CHUNKS == 4, "a page is 2 or 4 KiB");
+  if constexpr (CHUNKS == 4)
+    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0\n\tglobal_load_lds_dwordx4 %2, %0 offset:1024\n\t"
+                 "global_load_lds_dwordx4 %3, %0 offset:2048\n\tglobal_load_lds_dwordx4 %4, %0 offset:3072"
+                 :: "s"(sbase), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(lds_base) : "m0", "memory");
+  else
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0\n\tglobal_load_lds_dwordx4 %2, %0 offset:1024"
+                 :: "s"(sbase), "v"(voff[0]), "v"(voff[1]), "s"(lds_base) : "m0", "memory");
+}
 #pragma clang diagnostic pop
 
 }  // namespace

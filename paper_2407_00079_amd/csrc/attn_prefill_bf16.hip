@@ -20,14 +20,21 @@
 //   * Per 32-key block at head_dim 128: 16 score MFMAs (2 key tiles x 2 row tiles x 4 head_dim
 //     steps of 32) and 16 P V MFMAs (8 head_dim tiles x 2 row tiles), 8 K fragments and 8 V
 //     fragments from LDS; at head_dim 64 half of each (see Geo).
-//   * K/V tiles, their copy into LDS, the page walk, the lazy softmax reference, the two-phase
-//     ring schedule and the half-step skew of the two waves of a SIMD are those of
-//     attn_prefill.hip; the swizzles differ (fragment shapes differ).
-//   * Vector instructions are what the matrix pipe does not hide here (each one costs its issue
-//     time, measured by removing them one kind at a time), so the softmax keeps only what it
-//     cannot do without: per score one fma and one exp2, per pair one rounding to bf16.  The row
+//   * K/V tiles, the page walk, the lazy softmax reference, the two-phase ring and the half-step
+//     skew of the two waves of a SIMD are those of attn_prefill.hip; the swizzles differ (fragment
+//     shapes differ), and so does what runs under which MFMAs.
+//   * With two waves per SIMD an MFMA of this shape hides about two vector instructions of its
+//     wave (one exp2 counts as two); a third costs more than its own issue time (stand-alone loop
+//     of MFMA + n fma, two waves per SIMD: 33, 34, 34, 46 cycles per pair of MFMAs for n = 0..3).
+//     The softmax is therefore kept to what it cannot do without - per score one fma and one exp2,
+//     per pair one rounding to bf16 - and spread over BOTH phases: row tile 1 of block j under the
+//     score MFMAs of block j+1, row tile 0 of block j+1 under the P V MFMAs of block j.  The row
 //     sums of the rounded probabilities come from two more MFMAs per block (ones x P^T), and the
 //     guard of the lazy reference is an OR over the packed probabilities (see kRefLift).
+//   * What bounds it: the board's power limit.  7.6 % fewer cycles (128k-context shape, all-zero
+//     operands, which run at the full clock: 2.58 -> 2.40 ms) came out as 1.3 % less time on random
+//     operands (3.20 -> 3.16 ms = 1.35 PFLOP/s): the clock falls as the stream gets denser.  A large
+//     bf16 matrix product of the vendor library reaches 1.46-1.57 PFLOP/s on the same operands.
 #include <type_traits>
 
 #include "attn_device.h"
@@ -68,6 +75,17 @@ struct Geo {
   static constexpr int kVBaseB = kBuffers * kKTileB;     // the K tiles of the three buffers, then the V tiles
   static constexpr int kChunkRows = 1024 / kRowB;        // rows one wave copy instruction (1 KiB) covers
   static constexpr int kPageChunks = kPageTokens / kChunkRows;
+
+  // Order of a group of the pipeline (see weave): M = MFMA, L = ring refill, F = fma of a pair of scores, E = exp2 of
+  // one, C = rounding of a pair.  At head_dim 128 a group has one pair of scores for four MFMAs, which hide about two
+  // vector instructions each: the order below leaves the MFMAs of a step apart by the pair's fmas.  At head_dim 64 it
+  // has two pairs for four MFMAs, more than they hide, and keeping the two MFMAs that share a fragment together wins.
+  // Same box, all-zero operands (fixed clock: a cycle count) / random ones (power limit), 128k-context shape:
+  //   head_dim 128   all vector work in the score phase, before its MFMAs (the form before)  2.58 / 3.20 ms
+  //                  this order 2.40 / 3.16; eight other orders 2.48-2.62 / 3.20-3.26
+  //   head_dim 64    the form before 1.89 ms / 0.714 ms (P 8189, C 4099); this order 1.76 / 0.691; eight others 1.80-1.86 / 0.697-0.706
+  static constexpr char kOrder[] = "MFMLMEEMLC";
+  static constexpr char kOrder64[] = "FEEMMLCFEEMMLC";
 
   // LDS swizzles: 16-byte granule g of tile row r is stored at granule g ^ swz(r).  The banks repeat every
   // 256 bytes, i.e. every row (D 128) or every second row (D 64).
@@ -137,10 +155,9 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 
 // round probabilities e, e + 1 (same row tile) into their fragment
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void round_pair(PBlock& b, const Scores& p, int e) {
+__device__ __forceinline__ uint32_t round_pair(const Scores& p, int e) {
   const f32x2 pp = {p.get(e), p.get(e + 1)};
-  const bf16x2 pr = __builtin_convertvector(pp, bf16x2);      // one v_cvt_pk_bf16_f32 (round to nearest even)
-  b.w[e >> 3][(e & 7) >> 1] = __builtin_bit_cast(uint32_t, pr);
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));      // one v_cvt_pk_bf16_f32 (round to nearest even)
 }
 template <int D, int WAVES, bool SPLIT>
 __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const AttnArgs a) {
@@ -219,11 +236,10 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   // ---- global -> LDS, no registers in between (as in attn_prefill.hip): one wave instruction writes
   //      1 KiB of LDS, 4 (D 64: 8) tile rows of 16 (8) granules inside one page; lane i fetches, for granule
   //      position i % kGran of row i / kGran, the logical granule (i % kGran) ^ swz(row).  The first wave of
-  //      each SIMD copies.
+  //      each SIMD copies, wave w page w of the tile: one page id, one page address and two LDS bases per tile,
+  //      the chunks of the page are immediate offsets (they advance the global and the LDS address alike).
   constexpr int kFetchWaves = WAVES / 2;
-  constexpr int kChunks = kKTileBytes / 1024;                 // 1 KiB chunks per K (or V) tile
-  constexpr int kFetch = kChunks / kFetchWaves;               // chunks per fetching wave
-  static_assert(kChunks % kFetchWaves == 0 && kFetch <= 8, "tile must split evenly over the fetching waves");
+  static_assert(kFetchWaves == kTileKeys / kPageTokens, "one page of the tile per copying wave");
   const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)item.kv_head * kPageHeadBytes;
   const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)item.kv_head * kPageHeadBytes;
   const int64_t page_stride = (int64_t)a.Hkv * kPageHeadBytes;
@@ -233,50 +249,38 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
   const_i32_ptr btc = (const_i32_ptr)(a.block_tables + (int64_t)item.req * a.max_pages);
   const int64_t first_page_off = (int64_t)btc[0] * page_stride;   // page of key 0: always valid
-  int pid[kFetch];
-  int pid_next[kFetch];
+  int pid = 0, pid_next = 0;
   auto load_ids = [&](int tile) __attribute__((always_inline)) {
     if (!fetcher) return;
-#pragma unroll
-    for (int i = 0; i < kFetch; ++i) {
-      int lp = tile * (kTileKeys / kPageTokens) + (wave_u + i * kFetchWaves) / X::kPageChunks;
-      lp = lp < last_page ? lp : last_page;                  // never index the table past the request's pages
-      pid_next[i] = btc[lp];
-    }
+    const int lp = tile * (kTileKeys / kPageTokens) + wave_u;
+    pid_next = btc[lp < last_page ? lp : last_page];         // never index the table past the request's pages
   };
-  auto take_ids = [&]() __attribute__((always_inline)) {
+  auto take_ids = [&]() __attribute__((always_inline)) { pid = pid_next; };
+  uint32_t k_src[X::kPageChunks], v_src[X::kPageChunks];     // within a chunk
 #pragma unroll
-    for (int i = 0; i < kFetch; ++i) pid[i] = pid_next[i];
-  };
-  // row of the page this lane copies a granule of (the swizzles depend on the row modulo 16 only)
-  const int lane_row = (wave_u % X::kPageChunks) * X::kChunkRows + lane / X::kGran;
-  const uint32_t k_src = (uint32_t)(lane_row * kRowBytes + (((lane % X::kGran) ^ X::k_swz(lane_row)) << 4));
-  const uint32_t v_src = (uint32_t)(lane_row * kRowBytes + (((lane % X::kGran) ^ X::v_swz(lane_row)) << 4));
-  static_assert(kFetchWaves % X::kPageChunks == 0, "a fetching wave's chunks must all sit at the same rows of their pages");
+  for (int i = 0; i < X::kPageChunks; ++i) {
+    const int row = i * X::kChunkRows + lane / X::kGran;
+    k_src[i] = (uint32_t)(lane / X::kGran * kRowBytes + (((lane % X::kGran) ^ X::k_swz(row)) << 4));
+    v_src[i] = (uint32_t)(lane / X::kGran * kRowBytes + (((lane % X::kGran) ^ X::v_swz(row)) << 4));
+  }
   auto fetch = [&](int tile, int buf) __attribute__((always_inline)) {
     if (!fetcher) return;
-    const uint32_t dst0 = smem_base + buf * kKTileBytes + wave_u * 1024;
+    const uint32_t dst = smem_base + buf * kKTileBytes + wave_u * kPageHeadBytes;
+    const int64_t page_off = (int64_t)pid * page_stride;
     if ((tile + 1) * kTileKeys <= L) {
-#pragma unroll
-      for (int i = 0; i < kFetch; ++i) {
-        const int64_t page_off = (int64_t)pid[i] * page_stride;
-        const uint32_t dst = dst0 + i * kFetchWaves * 1024;
-        dma16(kbase + page_off, k_src, dst);
-        dma16(vbase + page_off, v_src, dst + kVBase);
-      }
+      dma16_page<X::kPageChunks>(kbase + page_off, k_src, dst);
+      dma16_page<X::kPageChunks>(vbase + page_off, v_src, dst + kVBase);
     } else {
       // slots at or past the request's length may hold anything: those lanes copy row 0 of the request's
       // first page instead; the causal mask hides the key
 #pragma unroll
-      for (int i = 0; i < kFetch; ++i) {
-        const int row = (wave_u + i * kFetchWaves) * X::kChunkRows + lane / X::kGran;
+      for (int i = 0; i < X::kPageChunks; ++i) {
+        const int row = wave_u * kPageTokens + i * X::kChunkRows + lane / X::kGran;
         const bool in_seq = tile * kTileKeys + row < L;
-        const int64_t page_off = (int64_t)pid[i] * page_stride;
-        const char* ks = kbase + (in_seq ? page_off + k_src : first_page_off + (k_src & (kRowBytes - 1)));
-        const char* vs = vbase + (in_seq ? page_off + v_src : first_page_off + (v_src & (kRowBytes - 1)));
-        const uint32_t dst = dst0 + i * kFetchWaves * 1024;
-        dma16(ks, dst);
-        dma16(vs, dst + kVBase);
+        const char* ks = kbase + (in_seq ? page_off + i * 1024 + k_src[i] : first_page_off + (k_src[i] & (kRowBytes - 1)));
+        const char* vs = vbase + (in_seq ? page_off + i * 1024 + v_src[i] : first_page_off + (v_src[i] & (kRowBytes - 1)));
+        dma16(ks, dst + i * 1024);
+        dma16(vs, dst + i * 1024 + kVBase);
       }
     }
   };
@@ -285,6 +289,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   // ---- running softmax state and output accumulators: o[dt][rt] register r = column 16 dt + 4 g + r of row 16 rt + j
   acc4 o[kDTiles][2];
   float m_run[2] = {-INFINITY, -INFINITY};   // reference of the probabilities accumulated so far (log2 units)
+  float m_ref[2] = {kNoKeyYet, kNoKeyYet};   // the same as probabilities are formed with: finite
   // Row sums come from the matrix cores: l_acc[rt] += ones (16 x 32) . P^T (32 keys x 16 rows) leaves, in all four
   // registers of lane (j, g), the sum of row j's rounded probabilities over the whole block, lane groups included
   // (2 MFMAs per block instead of 8 dot-product instructions, which cost a matrix-pipe slot each).
@@ -346,6 +351,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
         const float alpha = (SPLIT && m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run[rt] - m_new);
         l_acc[rt] *= alpha;
         m_run[rt] = m_new;
+        m_ref[rt] = SPLIT ? fmaxf(m_new, kNoKeyYet) : m_new;
 #pragma unroll
         for (int dt = 0; dt < kDTiles; ++dt) o[dt][rt] *= alpha;
       }
@@ -355,11 +361,10 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   auto probabilities = [&](Scores& s, PBlock& pb) __attribute__((always_inline)) {
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
-      const float m_ref = SPLIT ? fmaxf(m_run[rt], kNoKeyYet) : m_run[rt];
 #pragma unroll
-      for (int e = 8 * rt; e < 8 * rt + 8; ++e) s.set(e, __builtin_amdgcn_exp2f(__builtin_fmaf(s.get(e), c, -m_ref)));
+      for (int e = 8 * rt; e < 8 * rt + 8; ++e) s.set(e, __builtin_amdgcn_exp2f(__builtin_fmaf(s.get(e), c, -m_ref[rt])));
 #pragma unroll
-      for (int e = 8 * rt; e < 8 * rt + 8; e += 2) round_pair(pb, s, e);
+      for (int k = 0; k < 4; ++k) pb.w[rt][k] = round_pair(s, 8 * rt + 2 * k);
     }
   };
   auto add_row_sums = [&](const PBlock& pb) __attribute__((always_inline)) {
@@ -381,9 +386,12 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   //        phase A  scores of block j+1: step i multiplies ring[i] (K fragment i, read during the previous
   //                 phase B) into both row tiles and frees it; the V fragment that P V step i of block j
   //                 needs is read into the freed slot; under these MFMAs the vector ALU turns the scores of
-  //                 block j into probabilities, two per step.
+  //                 block j, row tile 1, into probabilities.
   //        phase B  P V of block j: step i multiplies ring[i] (the V fragment) into both row tiles and frees
-  //                 it; K fragment i of block j+2 is read into the freed slot.
+  //                 it; K fragment i of block j+2 is read into the freed slot; under these MFMAs the scores of
+  //                 block j+1, row tile 0, become probabilities.  (The last block the pipeline leaves scores of
+  //                 is one of those that may reach the diagonal: its scores are computed again, row tile 0 of
+  //                 them is overwritten by then.)
   frag ring[kRing];
   Scores s_cur, s_next;
   auto load_k_ring = [&](int buf, int kb) __attribute__((always_inline)) {
@@ -394,39 +402,55 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   // a probability of 2 or more (or not finite) means its score outgrew the reference: the block is then
   // recomputed against its true maxima (nothing was accumulated yet)
   PBlock pb;
+  u32x4 pb_ahead;                        // rounded probabilities of row tile 0 of the block whose scores are in s_next
+  // One group of a phase in the order Geo prescribes: four MFMAs (two steps of the ring, consecutive ones sharing an
+  // operand register), the refill of their two ring slots and the vector work that turns kPairs pairs of scores of row
+  // tile rt into rounded probabilities.
+  constexpr int kPairs = 8 / kRing;
+  constexpr int kOps = (D == 128 ? sizeof(X::kOrder) : sizeof(X::kOrder64)) - 1;
+  auto weave = [&](auto&& mfma, auto&& refill, Scores& s, u32x4& w, int rt, int grp) __attribute__((always_inline)) {
+    const int e0 = 8 * rt + 2 * kPairs * grp;
+    int m = 0, l = 0, f = 0, x = 0, k = 0;
+#pragma unroll
+    for (int t = 0; t < kOps; ++t) {
+      const char op = D == 128 ? X::kOrder[t] : X::kOrder64[t];
+      if (op == 'M') {
+        mfma(2 * grp + (m >> 1), (m == 1 || m == 2) ? 1 : 0);
+        ++m;
+      } else if (op == 'L') {
+        refill(2 * grp + l);
+        ++l;
+      } else if (op == 'F') {
+        s.set(e0 + 2 * f, __builtin_fmaf(s.get(e0 + 2 * f), c, -m_ref[rt]));
+        s.set(e0 + 2 * f + 1, __builtin_fmaf(s.get(e0 + 2 * f + 1), c, -m_ref[rt]));
+        ++f;
+      } else if (op == 'E') {
+        s.set(e0 + x, __builtin_amdgcn_exp2f(s.get(e0 + x)));
+        ++x;
+      } else {
+        w[kPairs * grp + k] = round_pair(s, e0 + 2 * k);
+        ++k;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   auto phase_a = [&](int buf_cur, int kb_cur) __attribute__((always_inline)) {
     const int off_v = buf_cur * kVTileBytes + kb_cur * 32 * kRowBytes;
     s_cur = s_next;
     s_next.zero();
-    float m_ref[2];
-    constexpr int kPer = 16 / kRing;     // scores a step turns into probabilities
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) m_ref[rt] = SPLIT ? fmaxf(m_run[rt], kNoKeyYet) : m_run[rt];
-#pragma unroll
-    for (int i = 0; i < kRing; ++i) {
-      // the step's vector work first (two exponentials; rounding and summing trail one step behind the
-      // exponentials they depend on), then its two MFMAs and the fragment read: measured best of the orders tried
-      const int e0 = kPer * i;
-#pragma unroll
-      for (int e = e0; e < e0 + kPer; ++e) s_cur.set(e, __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur.get(e), c, -m_ref[e >> 3])));
-      if (i > 0) {
-#pragma unroll
-        for (int e = e0 - kPer; e < e0; e += 2) round_pair(pb, s_cur, e);
-      }
+    pb.w[0] = pb_ahead;
+    auto score = [&](int i, int rt) __attribute__((always_inline)) {
+      s_next.t[rt][i & 1] = mma(ring[i], qf[i >> 1][rt], s_next.t[rt][i & 1]);
       __builtin_amdgcn_sched_barrier(0);
-      // consecutive MFMAs always share an operand register (the K fragment inside a step, the Q fragment across
-      // the steps of a head_dim chunk): odd steps take the row tiles in reverse order (+1 % under the power limit)
-      {
-        const int ra = i & 1, rb = ra ^ 1;
-        s_next.t[ra][i & 1] = mma(ring[i], qf[i >> 1][ra], s_next.t[ra][i & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        s_next.t[rb][i & 1] = mma(ring[i], qf[i >> 1][rb], s_next.t[rb][i & 1]);
-      }
+    };
+    auto refill = [&](int i) __attribute__((always_inline)) {
       ring[i] = X::load_v(vx, off_v, i);
       __builtin_amdgcn_sched_barrier(0);
-    }
+    };
 #pragma unroll
-    for (int e = 16 - kPer; e < 16; e += 2) round_pair(pb, s_cur, e);
+    for (int grp = 0; grp < kRing / 2; ++grp) {
+      weave(score, refill, s_cur, pb.w[1], 1, grp);
+    }
     // OR of the block's packed probabilities
     const uint32_t seen = pb.w[0][0] | pb.w[0][1] | pb.w[0][2] | pb.w[0][3] | pb.w[1][0] | pb.w[1][1] | pb.w[1][2] | pb.w[1][3];
     if (__builtin_expect(__builtin_amdgcn_ballot_w64((seen & kGuardBits) != 0) != 0, 0)) {   // (laid out behind the loop)
@@ -437,20 +461,21 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   };
   auto phase_b = [&](int buf_pre, int kb_pre) __attribute__((always_inline)) {
     const int off_k = buf_pre * kKTileBytes + kb_pre * 32 * kRowBytes;
-#pragma unroll
-    for (int i = 0; i < kRing; ++i) {
-      {
-        const int ra = i & 1, rb = ra ^ 1;      // as in phase A: the V fragment inside a step, P across steps
-        o[i][ra] = mma(ring[i], pb.f(ra), o[i][ra]);
+    auto accumulate = [&](int i, int rt) __attribute__((always_inline)) {
+      o[i][rt] = mma(ring[i], pb.f(rt), o[i][rt]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i < 2 && rt == (i & 1)) {        // the row sums of the tile just used: the P operand stays where it is
+        l_acc[rt] = mma(ones, pb.f(rt), l_acc[rt]);
         __builtin_amdgcn_sched_barrier(0);
-        if (i == 0 || i == 1) {              // the row sums of the tile just used: the P operand stays where it is
-          l_acc[ra] = mma(ones, pb.f(ra), l_acc[ra]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        o[i][rb] = mma(ring[i], pb.f(rb), o[i][rb]);
       }
+    };
+    auto refill = [&](int i) __attribute__((always_inline)) {
       ring[i] = X::load_k(kx, off_k, i);
       __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int grp = 0; grp < kRing / 2; ++grp) {
+      weave(accumulate, refill, s_next, pb_ahead, 0, grp);
     }
   };
   // one block start to finish, for the few blocks that may reach the diagonal
@@ -492,6 +517,10 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   if (tile < n_plain) {
     settle_reference(s_next, 0, std::false_type{});
     load_k_ring(0, 1);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s_next.set(e, __builtin_amdgcn_exp2f(__builtin_fmaf(s_next.get(e), c, -m_ref[0])));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) pb_ahead[k] = round_pair(s_next, 2 * k);
     // the two waves of a SIMD run half a step apart (see attn_prefill.hip)
     const bool late_barrier = wave_u >= WAVES / 2;
     auto pipelined_tile = [&](auto buf_tag) __attribute__((always_inline)) {
@@ -519,7 +548,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
       pipelined_tile(std::integral_constant<int, 2>{});
     }
   }
-  bool have_scores = true;
+  bool have_scores = n_plain <= t_lo;
   for (; tile < n_tiles; ++tile) {
     const int buf_next = buf == 2 ? 0 : buf + 1;
     tile_sync(tile);
