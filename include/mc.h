@@ -30,7 +30,9 @@
  *     HOST slots the library owns.  Such a call may allocate a slot with
  *     hipHostMalloc (the first calls, or a list larger than any before), and
  *     with 256 uploads in flight it waits for the oldest: these calls are not
- *     for stream capture.  The run calls (mc_prefill_attn_run, _run_split,
+ *     for stream capture.  mc_prefill_attn_paged and mc_prefill_attn_auto upload only
+ *     for batches of more than 63 requests with new tokens; smaller ones travel as a
+ *     kernel argument.  The run calls (mc_prefill_attn_run, _run_split,
  *     mc_kv_append_run), pack / unpack and the merge upload nothing, allocate
  *     nothing and never wait.  Calls may come from several host threads.
  *   - Page ids that live in device memory cannot be range-checked without a
@@ -104,10 +106,11 @@ size_t mc_prefill_attn_workspace_bytes(const mc_attn_params* p, int32_t batch,
  *   lse          dev  [total_new_tokens, Hq] fp32, or NULL
  *   workspace    dev  >= mc_prefill_attn_workspace_bytes(...), 16-byte aligned;
  *                     in use until the enqueued work has finished.  A workspace of at least
- *                     mc_prefill_attn_auto_workspace_bytes(...) lets the call run over key slices
- *                     + merge (as mc_prefill_attn_auto does) whenever whole rows would leave
- *                     compute units idle: a small chunk behind a long prefix, or a number of work
- *                     items just above a multiple of the 256 compute units.  The result is the
+ *                     mc_prefill_attn_auto_workspace_bytes(...) lets the call run over pieces of the
+ *                     keys + merge (as mc_prefill_attn_auto does) whenever whole rows would leave
+ *                     compute units idle: a small chunk behind a long prefix, few short rows, or a
+ *                     number of work items just above a multiple of the 256 compute units (the last
+ *                     ones are cut then, the rest stay whole rows).  The result is the
  *                     same to the tolerance of the two forms, not bit for bit; callers that need
  *                     one fixed form pass the minimal workspace (always whole rows) or call
  *                     mc_prefill_attn_paged_split themselves.
@@ -172,15 +175,18 @@ int32_t mc_prefill_attn_suggest_kv_splits(const mc_attn_params* p, const int32_t
                                           const int32_t* new_lens, int32_t batch);
 
 /*
- * mc_prefill_attn_paged with the choice between the whole-row form and key slices + merge made
- * by the library: it takes the slice count mc_prefill_attn_suggest_kv_splits gives for the
- * lengths and, when that is above 1, runs mc_prefill_attn_paged_split and mc_attn_merge_lse on
- * partial buffers it places in the workspace.  Same arguments, same result (to the tolerance of
- * the two forms) as mc_prefill_attn_paged; the workspace is larger:
+ * mc_prefill_attn_paged with the choice between whole rows and pieces of the keys + merge made
+ * by the library: the row tiles of the lengths are cut where the estimated time of the launch and
+ * the merge is least, into partial buffers it places in the workspace (batches of more than 63
+ * requests with new tokens: the slice count of mc_prefill_attn_suggest_kv_splits for all rows).
+ * Same arguments, same result (to the tolerance of the two forms) as mc_prefill_attn_paged; the
+ * workspace is larger:
  *
  *   workspace  dev  >= mc_prefill_attn_auto_workspace_bytes(...) for the same params and lengths
- *                   (work list + request table + kv_splits * rows * (head_dim + 1) floats),
- *                   16-byte aligned; 0 is returned for arguments the call would reject
+ *                   (work list + request table + kv_splits * rows * (head_dim + 1) floats for the
+ *                   suggested slice count; with a suggestion of 1, what the cut of few short rows
+ *                   needs, and a smaller workspace runs whole rows), 16-byte aligned; 0 is
+ *                   returned for arguments the call would reject
  */
 size_t mc_prefill_attn_auto_workspace_bytes(const mc_attn_params* p, const int32_t* prefix_lens,
                                             const int32_t* new_lens, int32_t batch);
@@ -192,16 +198,17 @@ mc_status mc_prefill_attn_auto(const mc_attn_params* p, const void* q, const voi
 /*
  * mc_prefill_attn_paged for callers that cannot allocate: code under HIP graph capture, serving
  * loops and harnesses that forbid hipMalloc.  Same arguments without the workspace, same result
- * (the same kernel over the same work list).  The work list and request table live in a fixed
+ * (the same kernel over the same row tiles).  Up to 63 requests with new tokens travel as a kernel
+ * argument.  Beyond that the work list and request table live in a fixed
  * device array inside the library (MC_NOALLOC_MAX_ITEMS * 16 + MC_NOALLOC_MAX_BATCH * 16 bytes
  * = 514 KiB per GPU, held until the process ends) and are built ON the device by a small kernel
  * that receives the lengths as a kernel argument: the call allocates nothing (device, pinned or
- * host heap), uploads nothing and never waits; it enqueues two kernels on `hip_stream`.
+ * host heap), uploads nothing and never waits; it enqueues one or two kernels on `hip_stream`.
  *
  * Limits: batch <= MC_NOALLOC_MAX_BATCH and at most MC_NOALLOC_MAX_ITEMS work items
  * (sum over requests of Hkv * ceil(C_r * Hq / Hkv / 256)); beyond them the call returns
- * MC_ERR_RANGE and enqueues nothing.  Every call on a GPU uses that GPU's one array: calls whose
- * device work may overlap (different streams without an ordering between them) race on it; calls
+ * MC_ERR_RANGE and enqueues nothing.  Every call with more than 63 such requests uses its GPU's one
+ * array: such calls whose device work may overlap (different streams without an ordering between them) race on it; calls
  * on one stream, or ordered by events, are safe.  The first call on a device looks the array's
  * address up (hipGetSymbolAddress) and should be made outside stream capture.
  */

@@ -35,6 +35,49 @@ constexpr float kRescaleSlack = 8.0f;  // log2 units the running max may lag beh
 // exp2(-inf) = 0 instead of exp2(-inf + inf) = NaN; a row with a finite score has a finite reference
 constexpr float kNoKeyYet = -1e30f;
 
+// How a launch describes its work: whole rows or uniform key slices from a list in device memory, or classes from the
+// kernel argument.
+enum Form { kWhole = 0, kSlices = 1, kClasses = 2 };
+
+// One workgroup's work, whatever described it.  The key tiles are cut into `pieces` (classes) or the request's tiles
+// into a.kv_splits slices of which this is number `piece` (slices); `part_row` + stacked row (classes) or + output row
+// (slices) is where a partial result goes.
+struct Work {
+  int32_t req, kv_head, row0, q_off, prefix, chunk;
+  int32_t piece, pieces;
+  int64_t part_row;
+};
+
+__device__ __forceinline__ Work work_of(const AttnItem& item, const AttnReq& rq, int64_t rows_total) {
+  return Work{item.req, item.kv_head, item.row0, rq.q_off, rq.prefix, rq.chunk, item.slice, 1, (int64_t)item.slice * rows_total};
+}
+
+// the class of workgroup (or merge block) wg: the last one whose first is not past it
+__device__ __forceinline__ int class_of(const AttnClasses& t, int wg) {
+  const int lane = threadIdx.x & 63;
+  const int first = t.first[lane];
+  return __popcll(__builtin_amdgcn_ballot_w64(lane < t.n && first <= wg)) - 1;
+}
+__device__ __forceinline__ int class_rows(const AttnClass& k, int G) {
+  const int all = k.chunk * G, hi = (k.tile_hi + 1) * kAttnTileRows;
+  return (all < hi ? all : hi) - k.tile_lo * kAttnTileRows;
+}
+__device__ __forceinline__ Work work_of(const AttnClasses& t, int wg, int Hkv, int G) {
+  const int at = class_of(t, wg);
+  const AttnClass k = t.c[at];
+  const int local = wg - t.first[at];
+  const int head = local % Hkv, rest = local / Hkv;
+  const int piece = rest % k.pieces, row0 = (k.tile_hi - rest / k.pieces) * kAttnTileRows;
+  const int64_t part = (int64_t)k.part_base + (int64_t)(piece * Hkv + head) * class_rows(k, G) - k.tile_lo * kAttnTileRows;
+  return Work{k.req, head, row0, k.q_off, k.prefix, k.chunk, piece, k.pieces, part};
+}
+// key tiles [lo, hi) of the n a row tile sees that piece `piece` of `pieces` covers
+__device__ __forceinline__ void piece_tiles(int n, int piece, int pieces, int* lo, int* hi) {
+  const int each = n / pieces, more = n - each * pieces;
+  *lo = piece * each + (piece < more ? piece : more);
+  *hi = *lo + each + (piece < more ? 1 : 0);
+}
+
 // Combine a value with the one held by lane ^ 32.  v_permlane32_swap exchanges the upper
 // half of its first register with the lower half of its second, so after it every lane
 // holds its own value in one register and its partner's in the other; max and sum do not

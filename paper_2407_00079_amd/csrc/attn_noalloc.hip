@@ -1,11 +1,13 @@
 // mc_prefill_attn_paged_noalloc: the whole-row attention call for callers that cannot allocate
 // (code under HIP graph capture, serving loops and harnesses that forbid hipMalloc).
 //
-// mc_prefill_attn_paged keeps its work list and request table in a caller-supplied workspace and
-// uploads them from pinned host memory.  Here both live in a file-scope device array, and the
-// list is BUILT ON THE DEVICE by a small kernel that gets the batch's lengths as a kernel
-// argument: no workspace, no upload, no allocation of any kind (no hipMalloc, hipHostMalloc or
-// hipFree; no host heap either).  The attention kernel is the one every other entry point runs.
+// Batches of up to kMaxAttnClasses - 1 requests are described by classes in the kernel argument, as
+// in mc_prefill_attn_paged: no list at all, one launch.  For larger ones mc_prefill_attn_paged keeps
+// its work list and request table in a caller-supplied workspace and uploads them from pinned host
+// memory; here both live in a file-scope device array, and the list is BUILT ON THE DEVICE by a
+// small kernel that gets the batch's lengths as a kernel argument: no workspace, no upload, no
+// allocation of any kind (no hipMalloc, hipHostMalloc or hipFree; no host heap either).  The
+// attention kernel is the one every other entry point runs.
 //
 // The list the kernel writes is the list mc::host::build_work_list makes, item for item: the
 // items of each of the 8 per-XCD lists in order of falling key count (ties in enumeration order),
@@ -176,6 +178,27 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
   if (st != MC_OK) return st;
   const int64_t n_items = count_items(p, new_lens, batch);
   if (batch > kMaxBatch || n_items > kMaxItems) return MC_ERR_RANGE;   // beyond the fixed scratch array
+
+  ClassPlan plan;
+  if (plan_classes(p, prefix_lens, new_lens, batch, 0, &plan)) {
+    // few enough requests to travel as a kernel argument: no list at all
+    AttnArgs args = {};
+    args.q = q;
+    args.k_pool = k_pool;
+    args.v_pool = v_pool;
+    args.block_tables = block_tables;
+    args.out = out;
+    args.lse = lse;
+    args.Hq = p->num_q_heads;
+    args.Hkv = p->num_kv_heads;
+    args.G = p->num_q_heads / p->num_kv_heads;
+    args.max_pages = max_pages_per_req;
+    args.head_dim = p->head_dim;
+    args.scale_log2e = attn_scale_log2e(p);
+    args.n_items = plan.n_wgs;
+    return launch_attn_classes(p->dtype, args, plan.classes, reinterpret_cast<hipStream_t>(hip_stream)) == hipSuccess
+               ? MC_OK : MC_ERR_HIP;
+  }
 
   char* base = reinterpret_cast<char*>(scratch_of_current_device());
   if (base == nullptr) return MC_ERR_HIP;

@@ -119,12 +119,13 @@ struct F32 {
 // ---------------------------------------------------------------------------
 // kernel
 // ---------------------------------------------------------------------------
-// SPLIT: the work item covers only slice item.slice of the request's keys (whole 64-key tiles,
+// SPLIT: the work item covers only slice work.slice of the request's keys (whole 64-key tiles,
 // ceil(tiles / kv_splits) per slice) and writes a PARTIAL result - the normalised fp32 output
 // over its keys and their log-sum-exp (-inf where the slice holds no key the row may see) - for
 // mc_attn_merge_lse to combine (paper Section 5.1: attention is associative over key slices).
-template <class T, int WAVES, bool SPLIT>
-__global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs a) {
+template <class T, int WAVES, Form FORM>
+__device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
+  constexpr bool SPLIT = FORM != kWhole;       // the result may be partial
   __shared__ __attribute__((aligned(16))) char smem[kBuffers * (kKTileBytes + kVTileBytes)];
   constexpr int kTileRows = WAVES * 32;
 
@@ -133,59 +134,59 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs
   const int wave = tid >> 6;
   const int half = lane >> 5;
 
-  const AttnItem item = a.items[blockIdx.x];
-  const AttnReq rq = a.reqs[item.req];
   const int G = a.G;
-  const int P = rq.prefix;
-  const int L = rq.prefix + rq.chunk;
-  const int n_rows = rq.chunk * G;
-  const int last_page = rq.pages - 1;
+  const int P = work.prefix;
+  const int L = work.prefix + work.chunk;
+  const int n_rows = work.chunk * G;
+  const int last_page = (L - 1) / kPageTokens;
 
   // A wave of the second half (these copy no tiles) whose 32 rows all lie past the end of the chunk
   // has nothing to do: it ends here, and the workgroup's barriers then wait for the surviving
   // waves only.  Small chunks (a 16-token chunk of an 8-head group fills 4 of 8 waves) then
   // spend no MFMA work on rows that are never stored.
-  if (wave >= WAVES / 2 && item.row0 + wave * 32 >= n_rows) return;
+  if (wave >= WAVES / 2 && work.row0 + wave * 32 >= n_rows) return;
 
   // ---- this lane's query row: its Q fragments stay in registers for the whole KV loop
   typename T::frag qf[T::kQKSteps];
-  int row = item.row0 + wave * 32 + (lane & 31);
+  int row = work.row0 + wave * 32 + (lane & 31);
   const bool live = row < n_rows;
   row = live ? row : n_rows - 1;                // dead rows recompute the last row, never stored
   const int tok = row / G;                      // token index inside the chunk
-  const int qhead = item.kv_head * G + (row - tok * G);
+  const int qhead = work.kv_head * G + (row - tok * G);
   {
-    const char* qrow = reinterpret_cast<const char*>(a.q) + ((int64_t)(rq.q_off + tok) * a.Hq + qhead) * kRowBytes;
+    const char* qrow = reinterpret_cast<const char*>(a.q) + ((int64_t)(work.q_off + tok) * a.Hq + qhead) * kRowBytes;
 #pragma unroll
     for (int kk = 0; kk < T::kQKSteps; ++kk) qf[kk] = T::load_q(qrow, kk, half);
   }
 
   // ---- keys this workgroup needs, and how many leading tiles need no mask
-  const int tok_first = item.row0 / G;
-  int tok_last = (item.row0 + kTileRows - 1) / G;
-  tok_last = tok_last < rq.chunk - 1 ? tok_last : rq.chunk - 1;
+  const int tok_first = work.row0 / G;
+  int tok_last = (work.row0 + kTileRows - 1) / G;
+  tok_last = tok_last < work.chunk - 1 ? tok_last : work.chunk - 1;
   const int kv_end = P + tok_last + 1;                       // <= L
   int n_tiles = (kv_end + kTileKeys - 1) / kTileKeys;        // tiles [t_lo, n_tiles) are this item's
   int t_lo = 0;
-  if (SPLIT) {
+  if (FORM == kSlices) {
     const int per = ((L + kTileKeys - 1) / kTileKeys + a.kv_splits - 1) / a.kv_splits;
-    t_lo = item.slice * per;
+    t_lo = work.piece * per;
     n_tiles = n_tiles < t_lo + per ? n_tiles : t_lo + per;
   }
+  if (FORM == kClasses) piece_tiles(n_tiles, work.piece, work.pieces, &t_lo, &n_tiles);
   int n_free = (P + tok_first + 1) / kTileKeys;              // every key of these tiles is visible to every row
   n_free = n_free < n_tiles ? n_free : n_tiles;
   // where this lane's row goes: the output itself, or this slice's plane of the partials
-  const int64_t orow_idx = (int64_t)(rq.q_off + tok) * a.Hq + qhead;
+  const int64_t orow_idx = (int64_t)(work.q_off + tok) * a.Hq + qhead;
+  const int64_t prow = work.part_row + (FORM == kClasses ? (int64_t)row : orow_idx);
   if (SPLIT && t_lo >= n_tiles) {
     // no key of the slice is visible to any row of the tile
     if (live) {
-      char* orow = reinterpret_cast<char*>(a.o_parts) + ((int64_t)item.slice * a.rows_total + orow_idx) * (T::kD * 4);
+      char* orow = reinterpret_cast<char*>(a.o_parts) + prow * (T::kD * 4);
 #pragma unroll
       for (int db = 0; db < T::kDBlocks; ++db)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
           *reinterpret_cast<f32x4*>(orow + (db * 32 + q4 * 8 + half * 4) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (half == 0) a.lse_parts[(int64_t)item.slice * a.rows_total + orow_idx] = -INFINITY;
+      if (half == 0) a.lse_parts[prow] = -INFINITY;
     }
     return;
   }
@@ -201,8 +202,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs
   constexpr int kChunks = kTileKeys / 4;                      // 1 KiB chunks per K (or V) tile
   constexpr int kFetch = kChunks / kFetchWaves;               // chunks per fetching wave
   static_assert(kChunks % kFetchWaves == 0 && kFetch <= 8, "tile must split evenly over the fetching waves");
-  const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)item.kv_head * kPageHeadBytes;
-  const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)item.kv_head * kPageHeadBytes;
+  const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadBytes;
+  const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)work.kv_head * kPageHeadBytes;
   const int64_t page_stride = (int64_t)a.Hkv * kPageHeadBytes;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t smem_base = (uint32_t)(uintptr_t)(MC_LDS char*)smem;
@@ -210,7 +211,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs
   // The block table is read through the scalar cache (it is constant while the kernel runs),
   // one tile AHEAD of the K/V loads that need it, so no wave ever waits for a page id.
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-  const_i32_ptr btc = (const_i32_ptr)(a.block_tables + (int64_t)item.req * a.max_pages);
+  const_i32_ptr btc = (const_i32_ptr)(a.block_tables + (int64_t)work.req * a.max_pages);
   const int64_t first_page_off = (int64_t)btc[0] * page_stride;   // page of key 0: always valid
   int pid[kFetch];
 
@@ -508,7 +509,8 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs
   const float l_run = sum_with_other_half(l_sum);
 
   // ---- epilogue: normalise, round, store; lane holds 4 consecutive columns per (db, r/4)
-  if (live && !SPLIT) {
+  const bool final_rows = FORM == kWhole || (FORM == kClasses && work.pieces == 1);
+  if (live && final_rows) {
     const float inv = 1.0f / l_run;
     char* orow = reinterpret_cast<char*>(a.out) + orow_idx * kRowBytes;
 #pragma unroll
@@ -521,10 +523,10 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs
       }
     if (a.lse != nullptr && half == 0) a.lse[orow_idx] = (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
   }
-  if (live && SPLIT) {
+  if (live && !final_rows) {
     // partial result in fp32; a row that saw no key of the slice has l = 0: zeros and -inf
     const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
-    char* orow = reinterpret_cast<char*>(a.o_parts) + ((int64_t)item.slice * a.rows_total + orow_idx) * (T::kD * 4);
+    char* orow = reinterpret_cast<char*>(a.o_parts) + prow * (T::kD * 4);
 #pragma unroll
     for (int db = 0; db < T::kDBlocks; ++db)
 #pragma unroll
@@ -532,73 +534,138 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs
         *reinterpret_cast<f32x4*>(orow + (db * 32 + q4 * 8 + half * 4) * 4) =
             f32x4{o[db][q4 * 4 + 0] * inv, o[db][q4 * 4 + 1] * inv, o[db][q4 * 4 + 2] * inv, o[db][q4 * 4 + 3] * inv};
     if (half == 0)
-      a.lse_parts[(int64_t)item.slice * a.rows_total + orow_idx] =
+      a.lse_parts[prow] =
           l_run > 0.f ? (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
   }
+}
+
+template <class T, int WAVES, bool SPLIT>
+__global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs a) {
+  const AttnItem item = a.items[blockIdx.x];
+  attn_body<T, WAVES, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
+}
+
+template <class T, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void attn_prefill_classes_kernel(const AttnArgs a, const AttnClasses t) {
+  attn_body<T, WAVES, kClasses>(a, work_of(t, blockIdx.x, a.Hkv, a.G));
 }
 
 // ---------------------------------------------------------------------------
 // merge of partial results (paper Section 5.1: attention is associative over key slices):
 //   lse = log sum_s exp(lse_s),  out = sum_s exp(lse_s - lse) o_s
-// A thread owns 4 consecutive columns of one row and every SL-th part, starting at its split
-// lane; a part whose lse is -inf has weight 0 and is not read.  D / 4 * SL threads per row, rows
-// packed into 256-thread workgroups.  SL = 1 walks all parts in one thread (many rows, few
-// parts); SL = 8 shortens the chain of dependent loads eightfold and adds the lanes' partial
-// sums through LDS (few rows, many parts: small chunks against long prefixes).
+// Bound by HBM, and for few rows by the latency of dependent loads.  A thread owns 4 consecutive columns of one row and
+// every SL-th part, starting at its split lane; D / 4 * SL threads per row, rows packed into 256-thread workgroups.
+// SL = 1 walks all parts in one thread (many rows, few parts); SL = 8 shortens the chain and adds the lanes' sums
+// through LDS (few rows, many parts: small chunks against long prefixes).  A lane takes its parts four at a time, their
+// log-sum-exps and their columns loaded together, against the largest lse it has seen (rescaled when that grows): one
+// round trip to memory per four parts, where taking the maximum of all lse first made it two.  A part whose lse is -inf
+// has weight 0 whatever its columns hold.
 // ---------------------------------------------------------------------------
+template <typename T, int SL>
+struct Merge {
+  static constexpr int kThreadsPerRow = T::kD / 4;
+  static constexpr int kRows = 256 / (kThreadsPerRow * SL);     // rows of one workgroup
+  struct Shared {
+    float m[kRows][SL], z[kRows][SL];
+    f32x4 part[kRows][SL][kThreadsPerRow];
+  };
+  // parts of one row: part s is row `first` + s * stride of o_parts and lse_parts; `dst` its row of out and lse
+  static __device__ __forceinline__ void row(Shared& sh, const float* __restrict__ o_parts, const float* __restrict__ lse_parts,
+                                             int64_t first, int64_t stride, int parts, bool live, int64_t dst,
+                                             void* __restrict__ out, float* __restrict__ lse) {
+    const int rl = threadIdx.x / (kThreadsPerRow * SL);
+    const int sl = (threadIdx.x / kThreadsPerRow) % SL;
+    const int cl = threadIdx.x % kThreadsPerRow;
+    float m = -INFINITY, z = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int kBatch = 4;
+    for (int s0 = sl; s0 < parts; s0 += kBatch * SL) {
+      float l[kBatch];
+      f32x4 v[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int s = s0 + u * SL;
+        const int64_t at = first + (int64_t)(s < parts ? s : s0) * stride;
+        l[u] = lse_parts[at];
+        v[u] = *reinterpret_cast<const f32x4*>(o_parts + at * T::kD + cl * 4);
+        if (s >= parts) l[u] = -INFINITY;
+      }
+      float top = m;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) top = fmaxf(top, l[u]);
+      if (top == -INFINITY) continue;
+      const float keep = __expf(m - top);
+      acc *= keep;
+      z *= keep;
+      m = top;
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const float w = __expf(l[u] - top);
+        if (w == 0.f) continue;                    // also a part without keys, whose columns may hold anything
+        z += w;
+        acc += w * v[u];
+      }
+    }
+    if constexpr (SL > 1) {
+      if (cl == 0) {
+        sh.m[rl][sl] = m;
+        sh.z[rl][sl] = z;
+      }
+      sh.part[rl][sl][cl] = acc;
+      __syncthreads();
+      if (sl != 0) return;
+#pragma unroll
+      for (int t = 1; t < SL; ++t) m = fmaxf(m, sh.m[rl][t]);
+      z = 0.f;
+      acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (m != -INFINITY) {
+#pragma unroll
+        for (int t = 0; t < SL; ++t) {
+          const float w = __expf(sh.m[rl][t] - m);
+          z += w * sh.z[rl][t];
+          acc += w * sh.part[rl][t][cl];
+        }
+      }
+    }
+    if (!live) return;
+    if (m != -INFINITY) acc *= 1.0f / z;
+    T::store4(reinterpret_cast<char*>(out) + dst * T::kOutRowBytes, cl * 4, acc[0], acc[1], acc[2], acc[3]);
+    if (lse != nullptr && cl == 0) lse[dst] = m != -INFINITY ? m + __logf(z) : -INFINITY;
+  }
+};
+
 template <typename T, int SL>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ o_parts,
                                                          const float* __restrict__ lse_parts, int kv_splits,
                                                          int64_t rows, void* __restrict__ out,
                                                          float* __restrict__ lse) {
-  constexpr int kThreadsPerRow = T::kD / 4;
-  constexpr int kRows = 256 / (kThreadsPerRow * SL);     // rows of one workgroup
-  __shared__ float red[kRows][SL];
-  __shared__ f32x4 part[kRows][SL][kThreadsPerRow];
-  const int rl = threadIdx.x / (kThreadsPerRow * SL);
-  const int sl = (threadIdx.x / kThreadsPerRow) % SL;
-  const int cl = threadIdx.x % kThreadsPerRow;
-  const int col = cl * 4;
-  const int64_t row_raw = (int64_t)blockIdx.x * kRows + rl;
-  const bool live = row_raw < rows;
-  const int64_t row = live ? row_raw : rows - 1;         // rows past the end compute the last row again and store nothing
-  float m = -INFINITY;
-  for (int s = sl; s < kv_splits; s += SL) m = fmaxf(m, lse_parts[(int64_t)s * rows + row]);
-  if constexpr (SL > 1) {
-    if (cl == 0) red[rl][sl] = m;
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < SL; ++t) m = fmaxf(m, red[rl][t]);
-    __syncthreads();
-  }
-  float z = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (m != -INFINITY) {
-    for (int s = sl; s < kv_splits; s += SL) {
-      const float w = __expf(lse_parts[(int64_t)s * rows + row] - m);
-      if (w == 0.f) continue;
-      z += w;
-      const f32x4 v = *reinterpret_cast<const f32x4*>(o_parts + ((int64_t)s * rows + row) * T::kD + col);
-      acc += w * v;
-    }
-  }
-  if constexpr (SL > 1) {
-    if (cl == 0) red[rl][sl] = z;
-    part[rl][sl][cl] = acc;
-    __syncthreads();
-    if (sl != 0) return;
-    z = 0.f;
-    acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < SL; ++t) {
-      z += red[rl][t];
-      acc += part[rl][t][cl];
-    }
-  }
-  if (!live) return;
-  if (m != -INFINITY) acc *= 1.0f / z;
-  T::store4(reinterpret_cast<char*>(out) + row * T::kOutRowBytes, col, acc[0], acc[1], acc[2], acc[3]);
-  if (lse != nullptr && col == 0) lse[row] = m != -INFINITY ? m + __logf(z) : -INFINITY;
+  typedef Merge<T, SL> M;
+  __shared__ typename M::Shared sh;
+  const int64_t raw = (int64_t)blockIdx.x * M::kRows + threadIdx.x / (M::kThreadsPerRow * SL);
+  const bool live = raw < rows;
+  const int64_t row = live ? raw : rows - 1;             // rows past the end compute the last row again and store nothing
+  M::row(sh, o_parts, lse_parts, row, rows, kv_splits, live, row, out, lse);
+}
+
+// the classes that were cut into pieces; t.first counts workgroups of this launch
+template <typename T, int SL>
+__global__ __launch_bounds__(256) void attn_merge_classes_kernel(const float* __restrict__ o_parts,
+                                                                 const float* __restrict__ lse_parts, const AttnClasses t,
+                                                                 int Hq, int Hkv, void* __restrict__ out,
+                                                                 float* __restrict__ lse) {
+  typedef Merge<T, SL> M;
+  __shared__ typename M::Shared sh;
+  const int at = class_of(t, blockIdx.x);
+  const AttnClass k = t.c[at];
+  const int G = Hq / Hkv;
+  const int rows_head = class_rows(k, G), rows = rows_head * Hkv;
+  const int raw = ((int)blockIdx.x - t.first[at]) * M::kRows + threadIdx.x / (M::kThreadsPerRow * SL);
+  const bool live = raw < rows;
+  const int r = live ? raw : rows - 1;
+  const int head = r / rows_head, row = k.tile_lo * kAttnTileRows + (r - head * rows_head);
+  const int tok = row / G;
+  const int64_t dst = (int64_t)(k.q_off + tok) * Hq + head * G + (row - tok * G);
+  M::row(sh, o_parts, lse_parts, (int64_t)k.part_base + r, rows, k.pieces, live, dst, out, lse);
 }
 
 }  // namespace
@@ -609,6 +676,60 @@ hipError_t launch_attn(int dtype, const AttnArgs& args, hipStream_t stream) {
   if (dtype == MC_DTYPE_BF16) return launch_attn_bf16(args, stream);
   if (split) attn_prefill_kernel<F32, kWaves, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
   else attn_prefill_kernel<F32, kWaves, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+  return hipGetLastError();
+}
+
+hipError_t launch_attn_classes(int dtype, const AttnArgs& args, const AttnClasses& t, hipStream_t stream) {
+  (void)hipGetLastError();
+  if (dtype == MC_DTYPE_BF16) return launch_attn_bf16_classes(args, t, stream);
+  attn_prefill_classes_kernel<F32, kWaves><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+  return hipGetLastError();
+}
+
+// Parts from which a row gets eight split lanes: below, one thread's four loads in flight cover all parts.
+constexpr int kWideParts = 8;
+
+template <typename T, int SL>
+static void enqueue_merge_classes(const float* o_parts, const float* lse_parts, AttnClasses t, int Hq, int Hkv, void* out,
+                                  float* lse, hipStream_t stream) {
+  int n = 0;
+  const int G = Hq / Hkv;
+  for (int i = 0; i < t.n; ++i) {
+    t.first[i] = n;
+    const AttnClass& k = t.c[i];
+    const int all = k.chunk * G, hi = (k.tile_hi + 1) * kAttnTileRows;
+    const int rows = ((all < hi ? all : hi) - k.tile_lo * kAttnTileRows) * Hkv;
+    n += (rows + Merge<T, SL>::kRows - 1) / Merge<T, SL>::kRows;
+  }
+  attn_merge_classes_kernel<T, SL><<<n, 256, 0, stream>>>(o_parts, lse_parts, t, Hq, Hkv, out, lse);
+}
+
+hipError_t launch_attn_merge_classes(int dtype, int head_dim, const float* o_parts, const float* lse_parts,
+                                     const AttnClasses& all, int Hq, int Hkv, void* out, float* lse, hipStream_t stream) {
+  (void)hipGetLastError();
+  AttnClasses t;
+  t.n = 0;
+  int most = 0;
+  for (int i = 0; i < all.n; ++i)
+    if (all.c[i].pieces > 1) {
+      t.c[t.n++] = all.c[i];
+      most = all.c[i].pieces > most ? all.c[i].pieces : most;
+    }
+  if (t.n == 0) return hipSuccess;
+  for (int i = t.n; i < kMaxAttnClasses; ++i) t.first[i] = 0;
+  const bool wide = most >= kWideParts;
+  if (dtype == MC_DTYPE_BF16 && head_dim == 128) {
+    if (wide) enqueue_merge_classes<Bf16<128>, 8>(o_parts, lse_parts, t, Hq, Hkv, out, lse, stream);
+    else enqueue_merge_classes<Bf16<128>, 1>(o_parts, lse_parts, t, Hq, Hkv, out, lse, stream);
+  } else if (dtype == MC_DTYPE_BF16 && head_dim == 64) {
+    if (wide) enqueue_merge_classes<Bf16<64>, 8>(o_parts, lse_parts, t, Hq, Hkv, out, lse, stream);
+    else enqueue_merge_classes<Bf16<64>, 1>(o_parts, lse_parts, t, Hq, Hkv, out, lse, stream);
+  } else if (dtype == MC_DTYPE_F32 && head_dim == 64) {
+    if (wide) enqueue_merge_classes<F32, 8>(o_parts, lse_parts, t, Hq, Hkv, out, lse, stream);
+    else enqueue_merge_classes<F32, 1>(o_parts, lse_parts, t, Hq, Hkv, out, lse, stream);
+  } else {
+    return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -623,7 +744,7 @@ static void enqueue_merge(const float* o_parts, const float* lse_parts, int kv_s
 hipError_t launch_attn_merge(int dtype, int head_dim, const float* o_parts, const float* lse_parts, int kv_splits,
                              int64_t rows, void* out, float* lse, hipStream_t stream) {
   (void)hipGetLastError();
-  const bool wide = kv_splits >= 8;   // enough parts to give each of 8 split lanes one
+  const bool wide = kv_splits >= kWideParts;
   if (dtype == MC_DTYPE_BF16 && head_dim == 128) {
     if (wide) enqueue_merge<Bf16<128>, 8>(o_parts, lse_parts, kv_splits, rows, out, lse, stream);
     else enqueue_merge<Bf16<128>, 1>(o_parts, lse_parts, kv_splits, rows, out, lse, stream);

@@ -159,8 +159,9 @@ __device__ __forceinline__ uint32_t round_pair(const Scores& p, int e) {
   const f32x2 pp = {p.get(e), p.get(e + 1)};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));      // one v_cvt_pk_bf16_f32 (round to nearest even)
 }
-template <int D, int WAVES, bool SPLIT>
-__global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const AttnArgs a) {
+template <int D, int WAVES, Form FORM>
+__device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& work) {
+  constexpr bool SPLIT = FORM != kWhole;       // the result may be partial
   typedef Geo<D> X;
   // (these names hide the 256-byte-row constants of attn_device.h inside this kernel)
   constexpr int kD = D, kSteps = X::kSteps, kDTiles = X::kDTiles, kRing = X::kRing, kRowBytes = X::kRowB,
@@ -176,47 +177,47 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   const int g = lane >> 4;        // lane group: which 4 + 4 keys of a block
   const int j = lane & 15;        // row inside a row tile
 
-  const AttnItem item = a.items[blockIdx.x];
-  const AttnReq rq = a.reqs[item.req];
   const int G = a.G;
-  const int P = rq.prefix;
-  const int L = rq.prefix + rq.chunk;
-  const int n_rows = rq.chunk * G;
-  const int last_page = rq.pages - 1;
+  const int P = work.prefix;
+  const int L = work.prefix + work.chunk;
+  const int n_rows = work.chunk * G;
+  const int last_page = (L - 1) / kPageTokens;
 
   // a wave of the second half (these copy no tiles) whose 32 rows all lie past the end of the chunk ends here
-  if (wave >= WAVES / 2 && item.row0 + wave * 32 >= n_rows) return;
+  if (wave >= WAVES / 2 && work.row0 + wave * 32 >= n_rows) return;
 
   // ---- this lane's two query rows: their Q fragments stay in registers for the whole KV loop
   frag qf[kSteps][2];
   bool live[2];
   int tok[2];
-  int64_t orow_idx[2];
+  int64_t orow_idx[2], prow[2];                   // rows of the output and of the partial results
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
-    int row = item.row0 + wave * 32 + rt * 16 + j;
+    int row = work.row0 + wave * 32 + rt * 16 + j;
     live[rt] = row < n_rows;
     row = live[rt] ? row : n_rows - 1;            // dead rows recompute the last row, never stored
     tok[rt] = row / G;
-    const int qhead = item.kv_head * G + (row - tok[rt] * G);
-    orow_idx[rt] = (int64_t)(rq.q_off + tok[rt]) * a.Hq + qhead;
+    const int qhead = work.kv_head * G + (row - tok[rt] * G);
+    orow_idx[rt] = (int64_t)(work.q_off + tok[rt]) * a.Hq + qhead;
+    prow[rt] = work.part_row + (FORM == kClasses ? (int64_t)row : orow_idx[rt]);
     const char* qrow = reinterpret_cast<const char*>(a.q) + orow_idx[rt] * kRowBytes;
 #pragma unroll
     for (int c = 0; c < kSteps; ++c) qf[c][rt] = *reinterpret_cast<const frag*>(qrow + c * 64 + g * 16);
   }
 
   // ---- keys this workgroup needs, and how many leading tiles need no mask
-  const int tok_first = item.row0 / G;
-  int tok_last = (item.row0 + kTileRows - 1) / G;
-  tok_last = tok_last < rq.chunk - 1 ? tok_last : rq.chunk - 1;
+  const int tok_first = work.row0 / G;
+  int tok_last = (work.row0 + kTileRows - 1) / G;
+  tok_last = tok_last < work.chunk - 1 ? tok_last : work.chunk - 1;
   const int kv_end = P + tok_last + 1;                       // <= L
   int n_tiles = (kv_end + kTileKeys - 1) / kTileKeys;        // tiles [t_lo, n_tiles) are this item's
   int t_lo = 0;
-  if (SPLIT) {
+  if (FORM == kSlices) {
     const int per = ((L + kTileKeys - 1) / kTileKeys + a.kv_splits - 1) / a.kv_splits;
-    t_lo = item.slice * per;
+    t_lo = work.piece * per;
     n_tiles = n_tiles < t_lo + per ? n_tiles : t_lo + per;
   }
+  if (FORM == kClasses) piece_tiles(n_tiles, work.piece, work.pieces, &t_lo, &n_tiles);
   int n_free = (P + tok_first + 1) / kTileKeys;              // every key of these tiles is visible to every row
   n_free = n_free < n_tiles ? n_free : n_tiles;
   if (SPLIT && t_lo >= n_tiles) {
@@ -224,11 +225,11 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
       if (live[rt]) {
-        char* orow = reinterpret_cast<char*>(a.o_parts) + ((int64_t)item.slice * a.rows_total + orow_idx[rt]) * (kD * 4);
+        char* orow = reinterpret_cast<char*>(a.o_parts) + prow[rt] * (kD * 4);
 #pragma unroll
         for (int dt = 0; dt < kDTiles; ++dt)
           *reinterpret_cast<f32x4*>(orow + (dt * 16 + g * 4) * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (g == 0) a.lse_parts[(int64_t)item.slice * a.rows_total + orow_idx[rt]] = -INFINITY;
+        if (g == 0) a.lse_parts[prow[rt]] = -INFINITY;
       }
     return;
   }
@@ -240,14 +241,14 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   //      the chunks of the page are immediate offsets (they advance the global and the LDS address alike).
   constexpr int kFetchWaves = WAVES / 2;
   static_assert(kFetchWaves == kTileKeys / kPageTokens, "one page of the tile per copying wave");
-  const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)item.kv_head * kPageHeadBytes;
-  const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)item.kv_head * kPageHeadBytes;
+  const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadBytes;
+  const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)work.kv_head * kPageHeadBytes;
   const int64_t page_stride = (int64_t)a.Hkv * kPageHeadBytes;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t smem_base = (uint32_t)(uintptr_t)(MC_LDS char*)smem;
   const bool fetcher = wave_u < kFetchWaves;
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-  const_i32_ptr btc = (const_i32_ptr)(a.block_tables + (int64_t)item.req * a.max_pages);
+  const_i32_ptr btc = (const_i32_ptr)(a.block_tables + (int64_t)work.req * a.max_pages);
   const int64_t first_page_off = (int64_t)btc[0] * page_stride;   // page of key 0: always valid
   int pid = 0, pid_next = 0;
   auto load_ids = [&](int tile) __attribute__((always_inline)) {
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
   for (int rt = 0; rt < 2; ++rt) {
     const float l_run = l_acc[rt][0];
     if (!live[rt]) continue;
-    if (!SPLIT) {
+    if (FORM == kWhole || (FORM == kClasses && work.pieces == 1)) {
       const float inv = 1.0f / l_run;
       char* orow = reinterpret_cast<char*>(a.out) + orow_idx[rt] * kRowBytes;
 #pragma unroll
@@ -578,19 +579,38 @@ __global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const Att
     } else {
       // partial result in fp32; a row that saw no key of the slice has l = 0: zeros and -inf
       const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
-      char* orow = reinterpret_cast<char*>(a.o_parts) + ((int64_t)item.slice * a.rows_total + orow_idx[rt]) * (kD * 4);
+      char* orow = reinterpret_cast<char*>(a.o_parts) + prow[rt] * (kD * 4);
 #pragma unroll
       for (int dt = 0; dt < kDTiles; ++dt)
         *reinterpret_cast<f32x4*>(orow + (dt * 16 + g * 4) * 4) =
             f32x4{o[dt][rt][0] * inv, o[dt][rt][1] * inv, o[dt][rt][2] * inv, o[dt][rt][3] * inv};
       if (g == 0)
-        a.lse_parts[(int64_t)item.slice * a.rows_total + orow_idx[rt]] =
+        a.lse_parts[prow[rt]] =
             l_run > 0.f ? (m_run[rt] + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
     }
   }
 }
 
+template <int D, int WAVES, bool SPLIT>
+__global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const AttnArgs a) {
+  const AttnItem item = a.items[blockIdx.x];
+  attn_bf16_body<D, WAVES, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
+}
+
+template <int D, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_classes_kernel(const AttnArgs a, const AttnClasses t) {
+  attn_bf16_body<D, WAVES, kClasses>(a, work_of(t, blockIdx.x, a.Hkv, a.G));
+}
+
 }  // namespace
+
+hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream) {
+  (void)hipGetLastError();
+  if (args.head_dim == 128) attn_prefill_bf16_classes_kernel<128, kWaves><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+  else if (args.head_dim == 64) attn_prefill_bf16_classes_kernel<64, kWaves><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
 
 hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t stream) {
   (void)hipGetLastError();   // drop any stale error of earlier, unrelated runtime calls

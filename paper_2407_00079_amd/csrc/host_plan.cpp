@@ -8,6 +8,10 @@
 namespace mc {
 namespace host {
 
+namespace {
+constexpr int64_t kComputeUnits = 256;   // MI355X
+}  // namespace
+
 mc_status check_params(const mc_attn_params* p) {
   if (p == nullptr) return MC_ERR_NULL;
   if (p->num_q_heads <= 0 || p->num_kv_heads <= 0 || p->head_dim <= 0 || p->page_size <= 0 || p->num_pages <= 0)
@@ -173,7 +177,6 @@ int32_t suggest_kv_splits(const mc_attn_params* p, const int32_t* prefix_lens, c
                           int32_t batch) {
   if (check_params(p) != MC_OK || batch < 0) return 0;
   if (batch > 0 && (prefix_lens == nullptr || new_lens == nullptr)) return 0;
-  constexpr int64_t kComputeUnits = 256;   // MI355X
   constexpr int64_t kMinTilesPerSlice = 8;
   const int64_t G = p->num_q_heads / p->num_kv_heads;
   int64_t items = 0, most_tiles = 0;
@@ -205,23 +208,237 @@ int32_t suggest_kv_splits(const mc_attn_params* p, const int32_t* prefix_lens, c
   return best;
 }
 
+namespace {
+
+// Time of a workgroup in microseconds, for weighing cuts against each other: a part that does not depend on the keys
+// (start, Q fragments, first tiles, epilogue) and one per 64-key tile.
+struct TileCost {
+  double fixed, tile;
+};
+TileCost tile_cost_of(const mc_attn_params* p) {
+  if (p->dtype == MC_DTYPE_F32) return {4.0, 7.0};
+  return p->head_dim == 128 ? TileCost{4.0, 1.65} : TileCost{4.0, 0.95};
+}
+// the merge launch, and bytes of partial results written and read per microsecond
+constexpr double kMergeFixed = 4.0, kPartBytesPerUs = 3.0e6;
+
+// A set of row tiles of one request: `items` workgroups if uncut, `tiles` key tiles each on average.
+struct Run {
+  int active;               // which of the requests with new tokens, in launch order
+  int64_t tile_lo, tile_hi;
+  int64_t items, rows;
+  double mean;
+  int64_t longest;
+};
+
+// End of the last workgroup if the runs' pieces are handed to the compute units in order, each to the one free first
+// (runs are few, so the units are kept as groups that are free at the same time).
+class Units {
+ public:
+  void place(int64_t n, double dur) {
+    while (n > 0) {
+      int at = 0;
+      for (int i = 1; i < used_; ++i)
+        if (t_[i] < t_[at]) at = i;
+      const int64_t k = n < count_[at] ? n : count_[at];
+      const double end = t_[at] + dur;
+      end_ = end > end_ ? end : end_;
+      count_[at] -= k;
+      if (count_[at] == 0) {
+        --used_;
+        t_[at] = t_[used_];
+        count_[at] = count_[used_];
+      }
+      add(end, k);
+      n -= k;
+    }
+  }
+  double end() const { return end_; }
+
+ private:
+  void add(double t, int64_t k) {
+    for (int i = 0; i < used_; ++i)
+      if (t_[i] > t - 0.01 && t_[i] < t + 0.01) {
+        count_[i] += k;
+        return;
+      }
+    if (used_ == kGroups) {                 // merge into the nearest: an estimate
+      int at = 0;
+      for (int i = 1; i < used_; ++i)
+        if (std::fabs(t_[i] - t) < std::fabs(t_[at] - t)) at = i;
+      count_[at] += k;
+      return;
+    }
+    t_[used_] = t;
+    count_[used_++] = k;
+  }
+  static constexpr int kGroups = 16;
+  int used_ = 1;
+  double t_[kGroups] = {0.0};
+  int64_t count_[kGroups] = {kComputeUnits};
+  double end_ = 0.0;
+};
+
+int64_t key_tiles(int64_t prefix, int64_t chunk, int64_t G, int64_t row_tile) {
+  const int64_t last = std::min<int64_t>(chunk - 1, (row_tile * kAttnTileRows + kAttnTileRows - 1) / G);
+  return (prefix + last + 1 + kAttnTileKeys - 1) / kAttnTileKeys;
+}
+
+Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk, int64_t lo, int64_t hi) {
+  const int64_t G = p->num_q_heads / p->num_kv_heads;
+  Run run;
+  run.active = active;
+  run.tile_lo = lo;
+  run.tile_hi = hi;
+  run.items = (hi - lo + 1) * p->num_kv_heads;
+  run.rows = (std::min<int64_t>(chunk * G, (hi + 1) * kAttnTileRows) - lo * kAttnTileRows) * p->num_kv_heads;
+  run.longest = key_tiles(prefix, chunk, G, hi);
+  run.mean = 0.5 * (double)(run.longest + key_tiles(prefix, chunk, G, lo));
+  return run;
+}
+
+}  // namespace
+
+// The cut.  The first `whole` workgroups of the launch order stay uncut - a multiple of the compute units, so that they
+// fill whole rounds - and every row tile behind them is cut into pieces of at most `longest / k` key tiles.  Both are
+// chosen together, by the estimated end of the last workgroup plus what the merge costs.  What that gives: a small chunk
+// behind a long prefix is cut until it fills the chip; a launch just above a whole number of rounds is cut only where it
+// would run a last, mostly empty round; few short row tiles are cut into pieces of one or two key tiles.
+// Measured, one call with its append (uniform slices of all rows or none before / this cut now): P 6144, C 811 and 328,
+// 64/8 heads (296 row tiles: 6 slices / 256 whole tiles and 40 in 6 pieces) 342 / 220 us; P 256, C 128, fp32, 4/1 heads
+// (2 row tiles: whole / 6 pieces) 73 / 33 us; P 131056, C 16, 64/8 heads (32 slices / 32 pieces) 125 / 118 us.
+bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                  int64_t max_part_rows, ClassPlan* plan) {
+  const int64_t G = p->num_q_heads / p->num_kv_heads, Hkv = p->num_kv_heads;
+  struct Active {
+    int32_t req, q_off, prefix, chunk;
+  } act[kMaxAttnClasses];
+  int n = 0;
+  int64_t q_off = 0, items = 0;
+  for (int32_t r = 0; r < batch; ++r) {
+    if (new_lens[r] > 0) {
+      if (n == kMaxAttnClasses - 1) return false;      // one request may take two classes
+      act[n++] = {r, (int32_t)q_off, prefix_lens[r], new_lens[r]};
+      items += Hkv * ((new_lens[r] * G + kAttnTileRows - 1) / kAttnTileRows);
+    }
+    q_off += new_lens[r];
+  }
+  if (items > INT32_MAX) return false;
+  std::sort(act, act + n, [](const Active& a, const Active& b) {
+    if (a.prefix != b.prefix) return a.prefix > b.prefix;
+    return a.chunk != b.chunk ? a.chunk > b.chunk : a.req < b.req;
+  });
+
+  // runs of the launch order when the first `whole` workgroups are kept apart; returns how many runs those are
+  Run runs[kMaxAttnClasses];
+  int n_runs = 0;
+  auto lay_out = [&](int64_t whole) {
+    n_runs = 0;
+    int uncut = 0;
+    for (int i = 0; i < n; ++i) {
+      const int64_t P = act[i].prefix, C = act[i].chunk;
+      const int64_t tiles = (C * G + kAttnTileRows - 1) / kAttnTileRows;
+      const int64_t keep = std::min<int64_t>(tiles, whole / Hkv);
+      if (keep > 0) {
+        runs[n_runs] = make_run(p, i, P, C, tiles - keep, tiles - 1);
+        ++n_runs;
+        uncut = n_runs;
+        whole -= keep * Hkv;
+      }
+      if (keep < tiles) {
+        runs[n_runs] = make_run(p, i, P, C, 0, tiles - keep - 1);
+        ++n_runs;
+        whole = 0;
+      }
+    }
+    return uncut;
+  };
+  auto pieces_of = [](const Run& run, double len) {
+    int64_t k = (int64_t)std::ceil((double)run.longest / len - 1e-9);
+    k = k < 1 ? 1 : k;
+    return k < MC_MAX_KV_SPLITS ? k : (int64_t)MC_MAX_KV_SPLITS;
+  };
+
+  int64_t best_whole = items;
+  double best_len = 0.0;
+  if (max_part_rows > 0 && items < 4 * kComputeUnits) {
+    // From four full rounds on the launch order (short row tiles last) balances the tail by itself.
+    const TileCost cost = tile_cost_of(p);
+    double best = 0.0;
+    for (int64_t rounds = 0; rounds * kComputeUnits < items; ++rounds) {
+      const int uncut = lay_out(rounds * kComputeUnits);
+      int64_t longest = 0;
+      for (int i = uncut; i < n_runs; ++i) longest = std::max(longest, runs[i].longest);
+      for (int64_t k = 1; k <= longest && k <= MC_MAX_KV_SPLITS; k += k < 8 ? 1 : k < 32 ? 2 : k < 64 ? 4 : 16) {
+        const double len = (double)longest / (double)k;
+        // more than four rounds of pieces: the tail is short by then, a finer cut only adds partial results
+        int64_t n_pieces = 0;
+        for (int i = uncut; i < n_runs; ++i) n_pieces += runs[i].items * pieces_of(runs[i], len);
+        if (k > 1 && n_pieces > 4 * kComputeUnits) break;
+        Units units;
+        int64_t part_rows = 0;
+        for (int i = 0; i < uncut; ++i) units.place(runs[i].items, cost.fixed + cost.tile * runs[i].mean);
+        for (int i = uncut; i < n_runs; ++i) {
+          const int64_t c = pieces_of(runs[i], len);
+          units.place(runs[i].items * c, cost.fixed + cost.tile * std::ceil(runs[i].mean / (double)c));
+          if (c > 1) part_rows += c * runs[i].rows;
+        }
+        if (part_rows > max_part_rows) continue;
+        double t = units.end();
+        if (part_rows > 0) t += kMergeFixed + 2.0 * (double)part_rows * (double)(p->head_dim + 1) * 4.0 / kPartBytesPerUs;
+        if (best == 0.0 || t < best) {
+          best = t;
+          best_whole = rounds * kComputeUnits;
+          best_len = len;
+        }
+      }
+    }
+  }
+  const int uncut = lay_out(best_whole);
+  AttnClasses& t = plan->classes;
+  t.n = n_runs;
+  int64_t wg = 0;
+  plan->part_rows = 0;
+  plan->most_pieces = 1;
+  for (int i = 0; i < n_runs; ++i) {
+    const Run& run = runs[i];
+    const Active& of = act[run.active];
+    const int64_t pieces = i < uncut || best_len == 0.0 ? 1 : pieces_of(run, best_len);
+    t.first[i] = (int32_t)wg;
+    t.c[i] = AttnClass{of.req, of.q_off, of.prefix, of.chunk, (int32_t)run.tile_lo, (int32_t)run.tile_hi,
+                       (int32_t)pieces, (int32_t)plan->part_rows};
+    wg += run.items * pieces;
+    if (pieces > 1) plan->part_rows += pieces * run.rows;
+    plan->most_pieces = std::max<int32_t>(plan->most_pieces, (int32_t)pieces);
+  }
+  if (wg > INT32_MAX || plan->part_rows > INT32_MAX) return false;
+  for (int i = n_runs; i < kMaxAttnClasses; ++i) {
+    t.first[i] = 0;
+    t.c[i] = AttnClass{};
+  }
+  plan->n_wgs = (int32_t)wg;
+  return true;
+}
+
 bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                  AutoLayout* lay) {
   const int32_t s = suggest_kv_splits(p, prefix_lens, new_lens, batch);
   if (s <= 0) return false;
   int64_t total_new = 0;
   for (int32_t r = 0; r < batch; ++r) total_new += new_lens[r];
+  const int64_t rows = total_new * p->num_q_heads;
   lay->kv_splits = s;
-  if (s == 1) {
-    lay->list_bytes = list_bytes(p, batch, total_new);
+  lay->list_bytes = list_bytes(p, batch, total_new, s);
+  // a launch of few workgroups may be cut finer than the suggestion goes: at most 64 parts of a row
+  lay->by_classes = plan_classes(p, prefix_lens, new_lens, batch, (s > 1 ? s : 64) * rows, &lay->plan);
+  const int64_t part_rows = s > 1 ? s * rows : lay->by_classes ? lay->plan.part_rows : 0;
+  if (part_rows == 0) {
     lay->o_off = lay->lse_off = lay->total = lay->list_bytes;
     return true;
   }
-  const size_t rows = (size_t)total_new * (size_t)p->num_q_heads;
-  lay->list_bytes = list_bytes(p, batch, total_new, s);
   lay->o_off = (lay->list_bytes + 255) & ~(size_t)255;
-  lay->lse_off = (lay->o_off + (size_t)s * rows * (size_t)p->head_dim * sizeof(float) + 255) & ~(size_t)255;
-  lay->total = lay->lse_off + (size_t)s * rows * sizeof(float);
+  lay->lse_off = (lay->o_off + (size_t)part_rows * (size_t)p->head_dim * sizeof(float) + 255) & ~(size_t)255;
+  lay->total = lay->lse_off + (size_t)part_rows * sizeof(float);
   return true;
 }
 

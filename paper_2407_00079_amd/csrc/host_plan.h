@@ -62,11 +62,29 @@ mc_status plan_items(const mc_attn_params* p, const int32_t* prefix_lens, const 
 int32_t suggest_kv_splits(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens,
                           int32_t batch);
 
+// What a one-shot attention call of a small batch launches: classes of row tiles (mc_types.h), no list in device memory.
+// Requests in order of falling prefix (their cheapest row tile), row tiles from the last one down, so that what starts
+// last is short.  With max_part_rows > 0 row tiles may be cut along the keys into pieces whose partial results take at
+// most that many rows: the cut with the least estimated time is taken, which may be none.
+// false: more requests with new tokens than a launch has classes for.
+struct ClassPlan {
+  AttnClasses classes;
+  int32_t n_wgs;          // workgroups of the attention launch
+  int32_t most_pieces;    // 1: nothing is cut, no partial results, no merge
+  int64_t part_rows;      // rows of partial results
+};
+bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                  int64_t max_part_rows, ClassPlan* plan);
+
 // Workspace of the automatic form: [work list + request table | o_parts | lse_parts], each part
-// starting at a multiple of 256 bytes.
+// starting at a multiple of 256 bytes.  The partial results have room for kv_splits parts of every row (kv_splits > 1)
+// or for what the class plan cuts (kv_splits == 1: by whole rows there is nothing to gain from uniform slices, but a
+// launch of few workgroups is cut all the same); without either the workspace is the minimal one.
 struct AutoLayout {
   int32_t kv_splits;
   size_t list_bytes, o_off, lse_off, total;
+  bool by_classes;        // plan says what to launch; false: uniform slices or whole rows from a list
+  ClassPlan plan;
 };
 bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                  AutoLayout* lay);

@@ -194,7 +194,7 @@ mc_status launch_planned_attn(const mc_attn_params* p, const mc_attn_plan* plan,
   return MC_OK;
 }
 
-// One-shot form: every check first (a rejected call enqueues nothing), then upload and launch.
+// One-shot form from a list: every check first (a rejected call enqueues nothing), then upload and launch.
 mc_status attn_enqueue(const mc_attn_params* p, const void* q, const void* k_pool, const void* v_pool,
                        const int32_t* block_tables, int32_t max_pages_per_req, const int32_t* prefix_lens,
                        const int32_t* new_lens, int32_t batch, void* out, float* lse, int32_t kv_splits,
@@ -222,6 +222,79 @@ mc_status attn_enqueue(const mc_attn_params* p, const void* q, const void* k_poo
                              lse_parts, workspace, stream);
 }
 
+// Launch of a class plan, then the merge of what it cut.  Nothing is uploaded: the classes travel as kernel arguments.
+mc_status launch_class_plan(const mc_attn_params* p, const ClassPlan& plan, const void* q, const void* k_pool,
+                            const void* v_pool, const int32_t* block_tables, int32_t max_pages_per_req, void* out,
+                            float* lse, float* o_parts, float* lse_parts, hipStream_t stream) {
+  mc::AttnArgs args = {};
+  args.q = q;
+  args.k_pool = k_pool;
+  args.v_pool = v_pool;
+  args.block_tables = block_tables;
+  args.out = out;
+  args.lse = lse;
+  args.Hq = p->num_q_heads;
+  args.Hkv = p->num_kv_heads;
+  args.G = p->num_q_heads / p->num_kv_heads;
+  args.max_pages = max_pages_per_req;
+  args.head_dim = p->head_dim;
+  args.scale_log2e = attn_scale_log2e(p);
+  args.n_items = plan.n_wgs;
+  args.o_parts = o_parts;
+  args.lse_parts = lse_parts;
+  if (mc::launch_attn_classes(p->dtype, args, plan.classes, stream) != hipSuccess) return MC_ERR_HIP;
+  if (plan.most_pieces > 1 &&
+      mc::launch_attn_merge_classes(p->dtype, p->head_dim, o_parts, lse_parts, plan.classes, p->num_q_heads,
+                                    p->num_kv_heads, out, lse, stream) != hipSuccess)
+    return MC_ERR_HIP;
+  return MC_OK;
+}
+
+// One-shot whole-row attention, over pieces of the keys where the workspace has room for partial results.  need_room:
+// the caller asked for the automatic form, so a workspace without that room is refused where uniform slices pay.
+mc_status attn_one_shot(const mc_attn_params* p, const void* q, const void* k_pool, const void* v_pool,
+                        const int32_t* block_tables, int32_t max_pages_per_req, const int32_t* prefix_lens,
+                        const int32_t* new_lens, int32_t batch, void* out, float* lse, void* workspace,
+                        size_t workspace_bytes, void* hip_stream, bool need_room) {
+  mc_status st = check_params(p);
+  if (st != MC_OK) return st;
+  if (batch < 0 || max_pages_per_req < 0) return MC_ERR_SHAPE;
+  if (batch == 0) return MC_OK;
+  if (prefix_lens == nullptr || new_lens == nullptr) return MC_ERR_NULL;
+  int64_t total_new = 0;
+  int32_t need_pages = 0;
+  st = check_lens(p, prefix_lens, new_lens, batch, &total_new, &need_pages);
+  if (st != MC_OK) return st;
+  if (total_new == 0) return MC_OK;
+  st = check_attn_buffers(false, q, k_pool, v_pool, block_tables, batch, max_pages_per_req, need_pages, out, lse,
+                          nullptr, nullptr, workspace);
+  if (st != MC_OK) return st;
+  st = check_list_range(p, batch, total_new, 0);
+  if (st != MC_OK) return st;
+  if (workspace == nullptr || workspace_bytes < list_bytes(p, batch, total_new)) return MC_ERR_WORKSPACE;
+  AutoLayout lay;
+  if (!auto_layout(p, prefix_lens, new_lens, batch, &lay)) return MC_ERR_SHAPE;
+  const bool room = workspace_bytes >= lay.total;
+  if (need_room && lay.kv_splits > 1 && !room) return MC_ERR_WORKSPACE;
+  char* ws = reinterpret_cast<char*>(workspace);
+  float* o_parts = reinterpret_cast<float*>(ws + lay.o_off);
+  float* lse_parts = reinterpret_cast<float*>(ws + lay.lse_off);
+  if (lay.by_classes) {
+    if (!room && lay.plan.most_pieces > 1 && !plan_classes(p, prefix_lens, new_lens, batch, 0, &lay.plan)) return MC_ERR_RANGE;
+    return launch_class_plan(p, lay.plan, q, k_pool, v_pool, block_tables, max_pages_per_req, out, lse, o_parts,
+                             lse_parts, reinterpret_cast<hipStream_t>(hip_stream));
+  }
+  // more requests than a launch has classes for: from a list
+  if (lay.kv_splits == 1 || !room)
+    return attn_enqueue(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, out, lse,
+                        0, nullptr, nullptr, workspace, workspace_bytes, hip_stream);
+  st = attn_enqueue(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, nullptr,
+                    nullptr, lay.kv_splits, o_parts, lse_parts, workspace, lay.list_bytes, hip_stream);
+  if (st != MC_OK) return st;
+  return mc_attn_merge_lse(o_parts, lse_parts, lay.kv_splits, total_new * p->num_q_heads, p->head_dim, (int32_t)p->dtype,
+                           out, lse, hip_stream);
+}
+
 }  // namespace
 
 extern "C" {
@@ -230,16 +303,8 @@ mc_status mc_prefill_attn_paged(const mc_attn_params* p, const void* q, const vo
                                 const int32_t* block_tables, int32_t max_pages_per_req,
                                 const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, void* out,
                                 float* lse, void* workspace, size_t workspace_bytes, void* hip_stream) {
-  // A launch that would leave compute units idle (a small chunk behind a long prefix, or a work-item count just
-  // above a multiple of the compute units) runs over key slices + merge when the caller's workspace has room
-  // for the partial results; with the minimal workspace it runs whole-row.
-  AutoLayout lay;
-  if (workspace != nullptr && batch > 0 && prefix_lens != nullptr && new_lens != nullptr &&
-      auto_layout(p, prefix_lens, new_lens, batch, &lay) && lay.kv_splits > 1 && workspace_bytes >= lay.total)
-    return mc_prefill_attn_auto(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch,
-                                out, lse, workspace, workspace_bytes, hip_stream);
-  return attn_enqueue(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, out, lse,
-                      0, nullptr, nullptr, workspace, workspace_bytes, hip_stream);
+  return attn_one_shot(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, out, lse,
+                       workspace, workspace_bytes, hip_stream, false);
 }
 
 size_t mc_prefill_attn_split_workspace_bytes(const mc_attn_params* p, int32_t batch, int64_t total_new_tokens,
@@ -269,25 +334,8 @@ mc_status mc_prefill_attn_auto(const mc_attn_params* p, const void* q, const voi
                                const int32_t* block_tables, int32_t max_pages_per_req,
                                const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, void* out,
                                float* lse, void* workspace, size_t workspace_bytes, void* hip_stream) {
-  AutoLayout lay;
-  if (!auto_layout(p, prefix_lens, new_lens, batch, &lay) || lay.kv_splits == 1)
-    // one slice, or arguments the whole-row call will name the fault of
-    return attn_enqueue(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, out, lse,
-                        0, nullptr, nullptr, workspace, workspace_bytes, hip_stream);
-  if (out == nullptr) return MC_ERR_NULL;
-  if (!aligned16(out) || !aligned4(lse) || !aligned16(workspace)) return MC_ERR_ALIGN;
-  if (workspace == nullptr || workspace_bytes < lay.total) return MC_ERR_WORKSPACE;
-  char* ws = reinterpret_cast<char*>(workspace);
-  float* o_parts = reinterpret_cast<float*>(ws + lay.o_off);
-  float* lse_parts = reinterpret_cast<float*>(ws + lay.lse_off);
-  mc_status st = attn_enqueue(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch,
-                              nullptr, nullptr, lay.kv_splits, o_parts, lse_parts, workspace, lay.list_bytes,
-                              hip_stream);
-  if (st != MC_OK) return st;
-  int64_t total_new = 0;
-  for (int32_t r = 0; r < batch; ++r) total_new += new_lens[r];
-  return mc_attn_merge_lse(o_parts, lse_parts, lay.kv_splits, total_new * p->num_q_heads, p->head_dim, (int32_t)p->dtype,
-                           out, lse, hip_stream);
+  return attn_one_shot(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, out, lse,
+                       workspace, workspace_bytes, hip_stream, true);
 }
 
 mc_status mc_prefill_attn_prepare(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens,

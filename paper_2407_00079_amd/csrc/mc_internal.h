@@ -35,6 +35,14 @@ hipError_t launch_attn(int dtype, const AttnArgs& args, hipStream_t stream);
 // the bf16 instantiation (attn_prefill_bf16.hip), reached through launch_attn
 hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t stream);
 
+// the same over args.n_items workgroups described by classes (args.items, reqs and kv_splits unused)
+hipError_t launch_attn_classes(int dtype, const AttnArgs& args, const AttnClasses& t, hipStream_t stream);
+hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream);
+
+// enqueue the merge of the classes that were cut into pieces (nothing if none was)
+hipError_t launch_attn_merge_classes(int dtype, int head_dim, const float* o_parts, const float* lse_parts,
+                                     const AttnClasses& all, int Hq, int Hkv, void* out, float* lse, hipStream_t stream);
+
 // enqueue the merge of kv_splits partial results over `rows` rows into out (dtype) and lse (or null)
 hipError_t launch_attn_merge(int dtype, int head_dim, const float* o_parts, const float* lse_parts, int kv_splits, int64_t rows,
                              void* out, float* lse, hipStream_t stream);

@@ -22,6 +22,29 @@ struct AttnReq {
   int32_t pages;   // ceil((P_r + C_r) / S): entries of the block-table row that may be read
 };
 
+// A run of row tiles of one request that are all cut into the same number of pieces along the keys: what an attention
+// launch of a small batch is described with.  A launch has at most a few dozen of them, so they travel as a kernel
+// argument (no list in device memory, no upload); every workgroup finds its class and its place in it by arithmetic.
+// What that is worth: the upload of a list cost a copy kernel of 4 us and gaps of 5-6 us up to 16 KiB, gaps of 20-30 us
+// above (copy engine); P 8189, C 4099 (1032 workgroups, head_dim 64) went from 699 to 688 us with it gone.
+// Workgroups of a class, from its first one on: KV heads fastest (consecutive workgroups land on different XCDs, so an
+// XCD keeps the K/V stream of one head), then pieces, then row tiles from tile_hi down to tile_lo (most keys first).
+// pieces == 1: the tile's output is final.  pieces > 1: piece i covers tiles [i n / pieces, (i + 1) n / pieces) of the n
+// key tiles the row tile sees (the first n % pieces pieces one more than the rest) and writes row x of head g to row
+// part_base + (i Hkv + g) rows + x of the partial results, rows = the class's stacked rows per head.
+struct AttnClass {
+  int32_t req, q_off, prefix, chunk;
+  int32_t tile_lo, tile_hi;
+  int32_t pieces;
+  int32_t part_base;
+};
+constexpr int kMaxAttnClasses = 64;          // one lane of a wave each when a workgroup looks for its class
+struct AttnClasses {
+  int32_t n;
+  int32_t first[kMaxAttnClasses];            // first workgroup of each class (of the attention launch or of the merge)
+  AttnClass c[kMaxAttnClasses];
+};
+
 // rows of stacked queries one attention workgroup covers (8 waves of 32 rows, both dtypes)
 constexpr int kAttnTileRows = 256;
 // keys of one LDS tile; key slices of the split form are whole tiles

@@ -1,0 +1,79 @@
+"""The classes a one-shot attention call of a small batch is described with (csrc/host_plan.cpp: plan_classes; no GPU):
+every row tile of every (request, KV head) once, partial rows disjoint and inside the room given, launch order."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2407_00079_amd", "csrc")
+ROWS, KEYS = 256, 64
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("classes") / "class_plan_driver")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-fsanitize=address,undefined", "-I", os.path.join(ROOT, "include"),
+                    "-I", CSRC, "-o", exe, os.path.join(ROOT, "tests", "class_plan_driver.cpp"),
+                    os.path.join(CSRC, "host_plan.cpp")], check=True)
+    return exe
+
+
+def plan(driver, Hq, Hkv, D, dtype, room, prefix, new):
+    line = " ".join(str(x) for x in [Hq, Hkv, D, dtype, room, len(prefix), *prefix, *new]) + "\n"
+    out = subprocess.run([driver], input=line, capture_output=True, text=True, check=True).stdout.split()
+    if out == ["none"]:
+        return None
+    v = [int(x) for x in out]
+    names = ("first", "req", "q_off", "prefix", "chunk", "tile_lo", "tile_hi", "pieces", "part_base")
+    return dict(n_wgs=v[1], most_pieces=v[2], part_rows=v[3],
+                classes=[dict(zip(names, v[4 + 9 * i:13 + 9 * i])) for i in range(v[0])])
+
+
+BATCHES = [
+    (64, 8, 128, 0, [131056], [16]),                  # few rows, long prefix: cut to fill the chip
+    (64, 8, 128, 0, [6144, 6144], [811, 328]),        # 296 row tiles: one round and a bit
+    (8, 1, 128, 0, [120832], [10240]),                # 320 row tiles of one head
+    (64, 8, 128, 0, [8192], [8192]),                  # many full rounds: nothing cut
+    (4, 1, 64, 1, [256], [128]),                      # two short row tiles
+    (12, 3, 128, 0, [999, 1, 0], [130, 0, 257]),      # heads that do not divide the units, an empty request
+    (16, 16, 64, 0, [5], [40]),
+    (8, 2, 128, 0, [0] * 63, [1] * 63),               # as many requests as there is room for
+    (16, 2, 128, 0, [700, 0, 33, 1500, 260], [300, 77, 0, 130, 1]),
+    (64, 1, 128, 0, [3, 40000], [70, 1500]),
+]
+
+
+@pytest.mark.parametrize("room_parts", [0, 1, 2, 7, 64])
+@pytest.mark.parametrize("Hq,Hkv,D,dtype,prefix,new", BATCHES)
+def test_classes_cover_every_tile_once(driver, Hq, Hkv, D, dtype, prefix, new, room_parts):
+    G, total = Hq // Hkv, sum(new)
+    room = room_parts * total * Hq
+    p = plan(driver, Hq, Hkv, D, dtype, room, prefix, new)
+    assert p["part_rows"] <= room and (p["most_pieces"] > 1) == (p["part_rows"] > 0)
+    wg, parts, seen = 0, 0, {}
+    for c in p["classes"]:
+        r = c["req"]
+        assert (c["q_off"], c["prefix"], c["chunk"]) == (sum(new[:r]), prefix[r], new[r])
+        assert c["first"] == wg and 1 <= c["pieces"] <= 256 and 0 <= c["tile_lo"] <= c["tile_hi"]
+        wg += (c["tile_hi"] - c["tile_lo"] + 1) * Hkv * c["pieces"]
+        rows = min(new[r] * G, (c["tile_hi"] + 1) * ROWS) - c["tile_lo"] * ROWS
+        if c["pieces"] > 1:                            # [part_base, part_base + pieces Hkv rows): one block after another
+            assert c["part_base"] == parts
+            parts += c["pieces"] * Hkv * rows
+        for t in range(c["tile_lo"], c["tile_hi"] + 1):
+            assert (r, t) not in seen
+            seen[r, t] = c["pieces"]
+    assert wg == p["n_wgs"] and parts == p["part_rows"]
+    assert set(seen) == {(r, t) for r in range(len(new)) for t in range(-(-new[r] * G // ROWS))}
+    mins = [c["prefix"] for c in p["classes"]]
+    assert mins == sorted(mins, reverse=True)          # what starts last is short
+
+
+def test_cuts_that_matter(driver):
+    assert plan(driver, 64, 8, 128, 0, 32 * 16 * 64, [131056], [16])["most_pieces"] == 32
+    p = plan(driver, 64, 8, 128, 0, 6 * 1139 * 64, [6144, 6144], [811, 328])
+    assert p["classes"][0]["pieces"] == 1 and p["most_pieces"] > 1          # a whole round stays whole, the rest is cut
+    assert plan(driver, 4, 1, 64, 1, 64 * 512, [256], [128])["n_wgs"] >= 8  # two row tiles become more workgroups
+    assert plan(driver, 64, 8, 128, 0, 1 << 40, [8192], [8192])["most_pieces"] == 1
+    assert plan(driver, 8, 2, 128, 0, 0, [0] * 64, [1] * 64) is None        # more requests than classes
