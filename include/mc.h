@@ -24,17 +24,17 @@
  *     touched.  MC_ERR_HIP means the HIP runtime refused a step of the call:
  *     steps of the same call that were enqueued before it (an upload, a copy,
  *     the first of two kernels) stay enqueued, so the outputs are undefined.
- *   - The calls that take host lengths or offsets and hand them to a kernel
- *     (mc_prefill_attn_paged, _paged_split, _auto, _prepare, mc_kv_append_paged,
- *     mc_prefix_hash, mc_prefix_match) upload them from a small ring of pinned
- *     HOST slots the library owns.  Such a call may allocate a slot with
- *     hipHostMalloc (the first calls, or a list larger than any before), and
- *     with 256 uploads in flight it waits for the oldest: these calls are not
- *     for stream capture.  mc_prefill_attn_paged and mc_prefill_attn_auto upload only
- *     for batches of more than 63 requests with new tokens; smaller ones travel as a
- *     kernel argument.  The run calls (mc_prefill_attn_run, _run_split,
- *     mc_kv_append_run), pack / unpack and the merge upload nothing, allocate
- *     nothing and never wait.  Calls may come from several host threads.
+ *   - The calls that take host lengths or offsets hand them to a kernel as an
+ *     argument where they are few: mc_prefill_attn_paged and mc_prefill_attn_auto up
+ *     to 63 requests with new tokens, mc_kv_append_paged up to 64 requests,
+ *     mc_prefix_hash and mc_prefix_match up to 64 requests and 64 instances.
+ *     Longer tables, and the lists of _paged_split and _prepare, are uploaded
+ *     from a small ring of pinned HOST slots the library owns.  A call that uploads
+ *     may allocate a slot with hipHostMalloc (the first calls, or a list larger than
+ *     any before), and with 256 uploads in flight it waits for the oldest: such
+ *     calls are not for stream capture.  The run calls (mc_prefill_attn_run,
+ *     _run_split, mc_kv_append_run), pack / unpack and the merge upload nothing,
+ *     allocate nothing and never wait.  Calls may come from several host threads.
  *   - Page ids that live in device memory cannot be range-checked without a
  *     sync: an id outside [0, num_pages) is undefined behaviour.
  *   - No exceptions cross this boundary.

@@ -132,30 +132,48 @@ __global__ __launch_bounds__(256) void kv_check_page_ids_kernel(const int32_t* _
 }
 
 // Append (paper Section 3 step 2: the chunk's new KVCache is kept in the request's pages):
-// one thread moves one 16-byte granule of one (token, KV head) row of K and of V.  The request
-// of a token is found by bisection of the per-request table; a row has 1 << gran_shift granules
-// (256 bytes for bf16 head_dim 128 and fp32 head_dim 64, 128 bytes for bf16 head_dim 64).
-__global__ __launch_bounds__(256) void kv_append_kernel(const u32x4* __restrict__ k_new, const u32x4* __restrict__ v_new,
-                                                        u32x4* __restrict__ k_pool, u32x4* __restrict__ v_pool,
-                                                        const int32_t* __restrict__ block_tables, int32_t max_pages,
-                                                        const AttnReq* __restrict__ reqs, int32_t batch,
-                                                        int64_t total_vecs, int32_t Hkv, int32_t gran_shift) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= total_vecs) return;
-  const int gran = (int)(idx & ((1 << gran_shift) - 1));
-  const int64_t row = idx >> gran_shift;        // (token, head)
-  const int g = (int)(row % Hkv);
-  const int32_t tok = (int32_t)(row / Hkv);
-  int lo = 0, hi = batch - 1;                   // last request with q_off <= tok and at least one token
+// one thread moves one 16-byte granule of one (token, KV head) row of K and of V; a row has 1 << gran_shift granules
+// (256 bytes for bf16 head_dim 128 and fp32 head_dim 64, 128 bytes for bf16 head_dim 64).  The request of a token is the
+// last one that starts at or before it: requests without new tokens share their start with the next one, and the last of
+// such a run is the one that owns the token.
+__device__ __forceinline__ int owner_of(const AttnReq* reqs, int batch, int32_t tok) {
+  int lo = 0, hi = batch - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (reqs[mid].q_off <= tok) lo = mid; else hi = mid - 1;
   }
-  // requests without new tokens share their q_off with the next one: bisection lands on the
-  // last of such a run, which is the one that owns the token
-  const AttnReq rq = reqs[lo];
+  return lo;
+}
+// a table in the kernel argument: each lane looks at one request for the wave's first token, and the threads whose token
+// lies in a later request (few waves have any) walk on from there
+__device__ __forceinline__ int owner_of(const AttnReqTable& t, int batch, int32_t tok) {
+  const int lane = threadIdx.x & 63;
+  const int32_t first = __builtin_amdgcn_readfirstlane(tok);
+  int r = __popcll(__builtin_amdgcn_ballot_w64(lane < batch && t.r[lane].q_off <= first)) - 1;
+  while (r + 1 < batch && t.r[r + 1].q_off <= tok) ++r;
+  return r;
+}
+__device__ __forceinline__ AttnReq req_at(const AttnReq* reqs, int i) { return reqs[i]; }
+__device__ __forceinline__ AttnReq req_at(const AttnReqTable& t, int i) { return t.r[i]; }
+
+template <typename Reqs>      // const AttnReq* or AttnReqTable
+__global__ __launch_bounds__(256) void kv_append_kernel(const u32x4* __restrict__ k_new, const u32x4* __restrict__ v_new,
+                                                        u32x4* __restrict__ k_pool, u32x4* __restrict__ v_pool,
+                                                        const int32_t* __restrict__ block_tables, int32_t max_pages,
+                                                        const Reqs reqs, int32_t batch, int64_t total_vecs, int32_t Hkv,
+                                                        int32_t gran_shift) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  // threads past the end stay for the search (it looks at one request per lane) with the last granule's token
+  const int64_t at = idx < total_vecs ? idx : total_vecs - 1;
+  const int gran = (int)(at & ((1 << gran_shift) - 1));
+  const int64_t row = at >> gran_shift;         // (token, head)
+  const int g = (int)(row % Hkv);
+  const int32_t tok = (int32_t)(row / Hkv);
+  const int owner = owner_of(reqs, batch, tok);
+  if (idx >= total_vecs) return;
+  const AttnReq rq = req_at(reqs, owner);
   const int32_t pos = rq.prefix + (tok - rq.q_off);
-  const int64_t page = block_tables[(int64_t)lo * max_pages + (pos >> 4)];
+  const int64_t page = block_tables[(int64_t)owner * max_pages + (pos >> 4)];
   const int64_t dst = ((((page * Hkv + g) << 4) + (pos & 15)) << gran_shift) + gran;
   k_pool[dst] = k_new[idx];
   v_pool[dst] = v_new[idx];
@@ -179,14 +197,20 @@ hipError_t launch_kv_check_page_ids(const int32_t* page_ids, int64_t n, int64_t 
 }
 
 hipError_t launch_kv_append(const void* k_new, const void* v_new, void* k_pool, void* v_pool,
-                            const int32_t* block_tables, int32_t max_pages, const AttnReq* reqs, int32_t batch,
-                            int64_t total_new, int32_t Hkv, int32_t row_bytes, hipStream_t stream) {
+                            const int32_t* block_tables, int32_t max_pages, const AttnReq* reqs, const AttnReqTable* arg,
+                            int32_t batch, int64_t total_new, int32_t Hkv, int32_t row_bytes, hipStream_t stream) {
   const int32_t gran_shift = row_bytes == 256 ? 4 : 3;      // 256- or 128-byte rows
   const int64_t total_vecs = (total_new * Hkv) << gran_shift;
+  const unsigned blocks = (unsigned)((total_vecs + 255) / 256);
   (void)hipGetLastError();
-  kv_append_kernel<<<(unsigned)((total_vecs + 255) / 256), 256, 0, stream>>>(
-      (const u32x4*)k_new, (const u32x4*)v_new, (u32x4*)k_pool, (u32x4*)v_pool, block_tables, max_pages, reqs, batch,
-      total_vecs, Hkv, gran_shift);
+  if (arg != nullptr)
+    kv_append_kernel<AttnReqTable><<<blocks, 256, 0, stream>>>(
+        (const u32x4*)k_new, (const u32x4*)v_new, (u32x4*)k_pool, (u32x4*)v_pool, block_tables, max_pages, *arg, batch,
+        total_vecs, Hkv, gran_shift);
+  else
+    kv_append_kernel<const AttnReq*><<<blocks, 256, 0, stream>>>(
+        (const u32x4*)k_new, (const u32x4*)v_new, (u32x4*)k_pool, (u32x4*)v_pool, block_tables, max_pages, reqs, batch,
+        total_vecs, Hkv, gran_shift);
   return hipGetLastError();
 }
 

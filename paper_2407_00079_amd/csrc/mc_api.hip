@@ -92,6 +92,35 @@ class StagingRing {
 
 StagingRing g_staging;
 
+// enqueue the upload of `bytes` of host data to `dst` through a pinned slot
+mc_status upload(void* dst, const void* src, size_t bytes, hipStream_t stream) {
+  int slot = -1;
+  void* host = g_staging.acquire(bytes, &slot);
+  if (host == nullptr) return MC_ERR_HIP;
+  std::memcpy(host, src, bytes);
+  if (hipMemcpyAsync(dst, host, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) {
+    g_staging.abandon(slot);
+    return MC_ERR_HIP;
+  }
+  return g_staging.release_after(slot, stream) ? MC_OK : MC_ERR_HIP;
+}
+
+// Two offset tables for a prefix call: in `arg` if they fit, else uploaded to the workspace back to back.
+mc_status place_tables(const int64_t* a, size_t n_a, const int64_t* b, size_t n_b, void* workspace, hipStream_t stream,
+                       mc::OffsetTables* arg, mc::PrefixTables* out) {
+  if (n_a <= mc::kMaxArgEntries + 1 && n_b <= mc::kMaxArgEntries + 1) {
+    std::memcpy(arg->a, a, sizeof(int64_t) * n_a);
+    std::memcpy(arg->b, b, sizeof(int64_t) * n_b);
+    *out = {nullptr, nullptr, arg};
+    return MC_OK;
+  }
+  std::vector<int64_t> both(a, a + n_a);
+  both.insert(both.end(), b, b + n_b);
+  const int64_t* dev = reinterpret_cast<const int64_t*>(workspace);
+  *out = {dev, dev + n_a, nullptr};
+  return upload(workspace, both.data(), sizeof(int64_t) * both.size(), stream);
+}
+
 }  // namespace
 
 extern "C" {
@@ -416,7 +445,7 @@ mc_status mc_kv_append_run(const mc_attn_params* p, const mc_attn_plan* plan, co
   if (workspace == nullptr) return MC_ERR_WORKSPACE;
   const char* ws = reinterpret_cast<const char*>(workspace);
   if (mc::launch_kv_append(k_new, v_new, k_pool, v_pool, block_tables, max_pages_per_req,
-                           reinterpret_cast<const mc::AttnReq*>(ws + plan->reqs_offset), plan->batch, total_new,
+                           reinterpret_cast<const mc::AttnReq*>(ws + plan->reqs_offset), nullptr, plan->batch, total_new,
                            p->num_kv_heads, row_bytes_of(p), reinterpret_cast<hipStream_t>(hip_stream)) != hipSuccess)
     return MC_ERR_HIP;
   return MC_OK;
@@ -483,24 +512,24 @@ mc_status mc_kv_append_paged(const mc_attn_params* p, const void* k_new, const v
   if (workspace == nullptr || workspace_bytes < mc_kv_append_workspace_bytes(batch)) return MC_ERR_WORKSPACE;
 
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  const size_t up_bytes = sizeof(mc::AttnReq) * (size_t)batch;
-  int slot = -1;
-  mc::AttnReq* host = reinterpret_cast<mc::AttnReq*>(g_staging.acquire(up_bytes, &slot));
-  if (host == nullptr) return MC_ERR_HIP;
+  mc::AttnReqTable arg = {};
+  std::vector<mc::AttnReq> list;
+  const bool in_arg = batch <= mc::kMaxArgEntries;
+  if (!in_arg) list.resize((size_t)batch);
+  mc::AttnReq* reqs = in_arg ? arg.r : list.data();
   int64_t q_off = 0;
   for (int32_t r = 0; r < batch; ++r) {
-    host[r] = {(int32_t)q_off, prefix_lens[r], new_lens[r],
+    reqs[r] = {(int32_t)q_off, prefix_lens[r], new_lens[r],
                (int32_t)(((int64_t)prefix_lens[r] + new_lens[r] + p->page_size - 1) / p->page_size)};
     q_off += new_lens[r];
   }
-  if (hipMemcpyAsync(workspace, host, up_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) {
-    g_staging.abandon(slot);
-    return MC_ERR_HIP;
+  if (!in_arg) {
+    st = upload(workspace, list.data(), sizeof(mc::AttnReq) * list.size(), stream);
+    if (st != MC_OK) return st;
   }
-  if (!g_staging.release_after(slot, stream)) return MC_ERR_HIP;
   if (mc::launch_kv_append(k_new, v_new, k_pool, v_pool, block_tables, max_pages_per_req,
-                           reinterpret_cast<const mc::AttnReq*>(workspace), batch, total_new, p->num_kv_heads,
-                           row_bytes_of(p), stream) != hipSuccess)
+                           reinterpret_cast<const mc::AttnReq*>(workspace), in_arg ? &arg : nullptr, batch, total_new,
+                           p->num_kv_heads, row_bytes_of(p), stream) != hipSuccess)
     return MC_ERR_HIP;
   return MC_OK;
 }
@@ -610,9 +639,7 @@ mc_status mc_prefix_hash(const int32_t* tokens, const int64_t* tok_offsets, int3
   if (batch < 0 || block_tokens <= 0) return MC_ERR_SHAPE;
   if (batch == 0) return MC_OK;
   if (tok_offsets == nullptr) return MC_ERR_NULL;
-  std::vector<int64_t> tab(2 * ((size_t)batch + 1));
-  int64_t* key_off = tab.data() + batch + 1;
-  key_off[0] = 0;
+  std::vector<int64_t> key_off((size_t)batch + 1);
   int64_t max_blocks = 0;
   for (int32_t r = 0; r < batch; ++r) {
     const int64_t len = tok_offsets[r + 1] - tok_offsets[r];
@@ -629,22 +656,12 @@ mc_status mc_prefix_hash(const int32_t* tokens, const int64_t* tok_offsets, int3
     return MC_ERR_ALIGN;
   if (max_blocks > (1 << 26) - 8) return MC_ERR_RANGE;   // four blocks per workgroup along grid x
   if (workspace == nullptr || workspace_bytes < mc_prefix_hash_workspace_bytes(batch)) return MC_ERR_WORKSPACE;
-  std::memcpy(tab.data(), tok_offsets, sizeof(int64_t) * ((size_t)batch + 1));
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  const size_t up = sizeof(int64_t) * tab.size();
-  int slot = -1;
-  void* host = g_staging.acquire(up, &slot);
-  if (host == nullptr) return MC_ERR_HIP;
-  std::memcpy(host, tab.data(), up);
-  if (hipMemcpyAsync(workspace, host, up, hipMemcpyHostToDevice, stream) != hipSuccess) {
-    g_staging.abandon(slot);
-    return MC_ERR_HIP;
-  }
-  if (!g_staging.release_after(slot, stream)) return MC_ERR_HIP;
-  const int64_t* dev_tab = reinterpret_cast<const int64_t*>(workspace);
-  if (mc::launch_prefix_hash(tokens, dev_tab, dev_tab + batch + 1, batch, block_tokens, max_blocks, keys, stream) !=
-      hipSuccess)
-    return MC_ERR_HIP;
+  mc::OffsetTables arg = {};
+  mc::PrefixTables tables;
+  const mc_status st = place_tables(tok_offsets, (size_t)batch + 1, key_off.data(), (size_t)batch + 1, workspace, stream, &arg, &tables);
+  if (st != MC_OK) return st;
+  if (mc::launch_prefix_hash(tokens, tables, batch, block_tokens, max_blocks, keys, stream) != hipSuccess) return MC_ERR_HIP;
   return MC_OK;
 }
 
@@ -676,21 +693,11 @@ mc_status mc_prefix_match(const uint64_t* keys, const int64_t* key_offsets, int3
   if (batch > 65535) return MC_ERR_RANGE;   // the match grid's second dimension
   if (workspace == nullptr || workspace_bytes < mc_prefix_match_workspace_bytes(batch, n_inst)) return MC_ERR_WORKSPACE;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-  const size_t n_tab = (size_t)batch + 1 + (size_t)n_inst + 1;
-  const size_t up = sizeof(int64_t) * n_tab;
-  int slot = -1;
-  int64_t* host = reinterpret_cast<int64_t*>(g_staging.acquire(up, &slot));
-  if (host == nullptr) return MC_ERR_HIP;
-  std::memcpy(host, key_offsets, sizeof(int64_t) * ((size_t)batch + 1));
-  std::memcpy(host + batch + 1, cache_offsets, sizeof(int64_t) * ((size_t)n_inst + 1));
-  if (hipMemcpyAsync(workspace, host, up, hipMemcpyHostToDevice, stream) != hipSuccess) {
-    g_staging.abandon(slot);
-    return MC_ERR_HIP;
-  }
-  if (!g_staging.release_after(slot, stream)) return MC_ERR_HIP;
-  const int64_t* dev_tab = reinterpret_cast<const int64_t*>(workspace);
-  if (mc::launch_prefix_match(keys, dev_tab, batch, cache_keys, dev_tab + batch + 1, n_inst, prefix_len, best_len,
-                              best_inst, stream) != hipSuccess)
+  mc::OffsetTables arg = {};
+  mc::PrefixTables tables;
+  const mc_status st = place_tables(key_offsets, (size_t)batch + 1, cache_offsets, (size_t)n_inst + 1, workspace, stream, &arg, &tables);
+  if (st != MC_OK) return st;
+  if (mc::launch_prefix_match(keys, tables, batch, cache_keys, n_inst, prefix_len, best_len, best_inst, stream) != hipSuccess)
     return MC_ERR_HIP;
   return MC_OK;
 }

@@ -60,18 +60,25 @@ hipError_t launch_kv_page_order(const int32_t* page_ids, int64_t n, int32_t* ord
 hipError_t launch_kv_check_page_ids(const int32_t* page_ids, int64_t n, int64_t num_pages, int32_t* report,
                                     hipStream_t stream);
 
-// enqueue the scatter of total_new tokens' K/V rows (row_bytes = 256 or 128 per KV head) into their page slots
+// enqueue the scatter of total_new tokens' K/V rows (row_bytes = 256 or 128 per KV head) into their page slots; the
+// request table is in device memory (reqs) or, for at most kMaxArgEntries requests, travels with the launch (arg)
 hipError_t launch_kv_append(const void* k_new, const void* v_new, void* k_pool, void* v_pool,
-                            const int32_t* block_tables, int32_t max_pages, const AttnReq* reqs, int32_t batch,
-                            int64_t total_new, int32_t Hkv, int32_t row_bytes, hipStream_t stream);
+                            const int32_t* block_tables, int32_t max_pages, const AttnReq* reqs, const AttnReqTable* arg,
+                            int32_t batch, int64_t total_new, int32_t Hkv, int32_t row_bytes, hipStream_t stream);
 
-// enqueue digest + chain kernels (offset tables on the device; max_blocks = most blocks of any request)
-hipError_t launch_prefix_hash(const int32_t* tokens, const int64_t* tok_off, const int64_t* key_off, int batch,
-                              int block_tokens, int64_t max_blocks, uint64_t* keys, hipStream_t stream);
+// The offset tables of a prefix call: both in device memory or, if `arg` is set, both in it (at most kMaxArgEntries + 1
+// entries each; they then travel with the launch).
+struct PrefixTables {
+  const int64_t *a, *b;
+  const OffsetTables* arg;
+};
 
-// enqueue match + best kernels over batch requests and n_inst instances (offset tables on the device)
-hipError_t launch_prefix_match(const uint64_t* keys, const int64_t* key_off, int batch, const uint64_t* cache_keys,
-                               const int64_t* cache_off, int n_inst, int32_t* prefix_len, int32_t* best_len,
-                               int32_t* best_inst, hipStream_t stream);
+// enqueue digest + chain kernels (tables: token offsets, key offsets; max_blocks = most blocks of any request)
+hipError_t launch_prefix_hash(const int32_t* tokens, const PrefixTables& tables, int batch, int block_tokens,
+                              int64_t max_blocks, uint64_t* keys, hipStream_t stream);
+
+// enqueue match + best kernels over batch requests and n_inst instances (tables: key offsets, cache offsets)
+hipError_t launch_prefix_match(const uint64_t* keys, const PrefixTables& tables, int batch, const uint64_t* cache_keys,
+                               int n_inst, int32_t* prefix_len, int32_t* best_len, int32_t* best_inst, hipStream_t stream);
 
 }  // namespace mc

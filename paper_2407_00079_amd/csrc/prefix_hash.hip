@@ -24,19 +24,24 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {
   return x ^ (x >> 31);
 }
 
+// offset tables in device memory; OffsetTables (same member names) is the form that travels with the launch
+struct TablePtrs {
+  const int64_t* __restrict__ a;
+  const int64_t* __restrict__ b;
+};
+
 // Blocks of one request sit along blockIdx.x (four per workgroup, one wave each), requests along
 // blockIdx.y: no search for the owner of a block, and the offset tables are read by scalar loads.
-__global__ __launch_bounds__(256) void prefix_digest_kernel(const int32_t* __restrict__ tokens,
-                                                            const int64_t* __restrict__ tok_off,
-                                                            const int64_t* __restrict__ key_off, int batch,
+template <typename Tables>     // a: token offsets, b: key offsets
+__global__ __launch_bounds__(256) void prefix_digest_kernel(const int32_t* __restrict__ tokens, const Tables off, int batch,
                                                             int block_tokens, uint64_t* __restrict__ keys) {
   const int lane = threadIdx.x & 63;
   const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   for (int r = blockIdx.y; r < batch; r += gridDim.y) {
-    const int64_t k0 = key_off[r];
-    if (b >= key_off[r + 1] - k0) continue;              // whole wave skips together
-    const int64_t t0 = tok_off[r];
-    const int64_t left = tok_off[r + 1] - t0 - b * block_tokens;
+    const int64_t k0 = off.b[r];
+    if (b >= off.b[r + 1] - k0) continue;                // whole wave skips together
+    const int64_t t0 = off.a[r];
+    const int64_t left = off.a[r + 1] - t0 - b * block_tokens;
     const int nb = left < block_tokens ? (int)left : block_tokens;
     const int32_t* t = tokens + t0 + b * block_tokens;
     uint64_t sum = 0;
@@ -61,11 +66,11 @@ __global__ __launch_bounds__(256) void prefix_digest_kernel(const int32_t* __res
 // One wave per request.  The chain itself is sequential, but its loads and stores need not be:
 // the wave reads 64 digests at once, walks them lane by lane with wave-uniform (scalar unit)
 // arithmetic, each lane keeping the key of its own block, and writes the 64 keys back at once.
-__global__ __launch_bounds__(64) void prefix_chain_kernel(const int64_t* __restrict__ key_off, int batch,
-                                                          uint64_t* __restrict__ keys) {
+template <typename Tables>
+__global__ __launch_bounds__(64) void prefix_chain_kernel(const Tables off, int batch, uint64_t* __restrict__ keys) {
   const int lane = threadIdx.x;
   for (int r = blockIdx.x; r < batch; r += gridDim.x) {
-    const int64_t k0 = key_off[r], nk = key_off[r + 1] - k0;
+    const int64_t k0 = off.b[r], nk = off.b[r + 1] - k0;
     uint64_t prev = 0;
     for (int64_t base = 0; base < nk; base += 64) {
       const int64_t i = base + lane;
@@ -86,16 +91,15 @@ __global__ __launch_bounds__(64) void prefix_chain_kernel(const int64_t* __restr
   }
 }
 
+template <typename Tables>     // a: key offsets, b: cache offsets
 __global__ __launch_bounds__(256) void prefix_match_kernel(const uint64_t* __restrict__ keys,
-                                                           const int64_t* __restrict__ key_off,
-                                                           const uint64_t* __restrict__ cache_keys,
-                                                           const int64_t* __restrict__ cache_off, int n_inst,
-                                                           int32_t* __restrict__ prefix_len) {
+                                                           const uint64_t* __restrict__ cache_keys, const Tables off,
+                                                           int n_inst, int32_t* __restrict__ prefix_len) {
   __shared__ int first_miss;
   const int inst = blockIdx.x, r = blockIdx.y;
-  const int64_t k0 = key_off[r], nk = key_off[r + 1] - k0;
-  const uint64_t* c = cache_keys + cache_off[inst];
-  const int64_t nc = cache_off[inst + 1] - cache_off[inst];
+  const int64_t k0 = off.a[r], nk = off.a[r + 1] - k0;
+  const uint64_t* c = cache_keys + off.b[inst];
+  const int64_t nc = off.b[inst + 1] - off.b[inst];
   if (threadIdx.x == 0) first_miss = (int)nk;
   __syncthreads();
   for (int64_t base = 0; base < nk; base += 256) {
@@ -135,25 +139,43 @@ __global__ __launch_bounds__(64) void prefix_best_kernel(const int32_t* __restri
 
 }  // namespace
 
-hipError_t launch_prefix_hash(const int32_t* tokens, const int64_t* tok_off, const int64_t* key_off, int batch,
-                              int block_tokens, int64_t max_blocks, uint64_t* keys, hipStream_t stream) {
-  (void)hipGetLastError();
+namespace {
+
+template <typename Tables>
+hipError_t hash_with(const int32_t* tokens, const Tables& off, int batch, int block_tokens, int64_t max_blocks,
+                     uint64_t* keys, hipStream_t stream) {
   const unsigned req_rows = batch < 65535 ? (unsigned)batch : 65535u;   // the kernels stride over the rest
-  prefix_digest_kernel<<<dim3((unsigned)((max_blocks + 3) / 4), req_rows), 256, 0, stream>>>(
-      tokens, tok_off, key_off, batch, block_tokens, keys);
-  prefix_chain_kernel<<<req_rows, 64, 0, stream>>>(key_off, batch, keys);
+  prefix_digest_kernel<Tables><<<dim3((unsigned)((max_blocks + 3) / 4), req_rows), 256, 0, stream>>>(tokens, off, batch,
+                                                                                                    block_tokens, keys);
+  prefix_chain_kernel<Tables><<<req_rows, 64, 0, stream>>>(off, batch, keys);
   return hipGetLastError();
 }
 
-hipError_t launch_prefix_match(const uint64_t* keys, const int64_t* key_off, int batch, const uint64_t* cache_keys,
-                               const int64_t* cache_off, int n_inst, int32_t* prefix_len, int32_t* best_len,
-                               int32_t* best_inst, hipStream_t stream) {
-  (void)hipGetLastError();
+template <typename Tables>
+hipError_t match_with(const uint64_t* keys, const Tables& off, int batch, const uint64_t* cache_keys, int n_inst,
+                      int32_t* prefix_len, int32_t* best_len, int32_t* best_inst, hipStream_t stream) {
   if (n_inst > 0)
-    prefix_match_kernel<<<dim3((unsigned)n_inst, (unsigned)batch), 256, 0, stream>>>(keys, key_off, cache_keys,
-                                                                                     cache_off, n_inst, prefix_len);
+    prefix_match_kernel<Tables><<<dim3((unsigned)n_inst, (unsigned)batch), 256, 0, stream>>>(keys, cache_keys, off, n_inst,
+                                                                                            prefix_len);
   prefix_best_kernel<<<(unsigned)((batch + 63) / 64), 64, 0, stream>>>(prefix_len, batch, n_inst, best_len, best_inst);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefix_hash(const int32_t* tokens, const PrefixTables& tables, int batch, int block_tokens,
+                              int64_t max_blocks, uint64_t* keys, hipStream_t stream) {
+  (void)hipGetLastError();
+  if (tables.arg != nullptr) return hash_with(tokens, *tables.arg, batch, block_tokens, max_blocks, keys, stream);
+  return hash_with(tokens, TablePtrs{tables.a, tables.b}, batch, block_tokens, max_blocks, keys, stream);
+}
+
+hipError_t launch_prefix_match(const uint64_t* keys, const PrefixTables& tables, int batch, const uint64_t* cache_keys,
+                               int n_inst, int32_t* prefix_len, int32_t* best_len, int32_t* best_inst, hipStream_t stream) {
+  (void)hipGetLastError();
+  if (tables.arg != nullptr)
+    return match_with(keys, *tables.arg, batch, cache_keys, n_inst, prefix_len, best_len, best_inst, stream);
+  return match_with(keys, TablePtrs{tables.a, tables.b}, batch, cache_keys, n_inst, prefix_len, best_len, best_inst, stream);
 }
 
 }  // namespace mc
