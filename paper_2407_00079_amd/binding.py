@@ -7,6 +7,7 @@ raises.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Optional
@@ -134,14 +135,51 @@ def status_string(status: int) -> str:
 
 
 def _dev_ptr(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _nbytes(t) -> int:
+    return 0 if t is None else t.numel() * t.element_size()
 
 
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream) or None
+        return _current_stream() or None
+    return stream.cuda_stream or None
+
+
+def _current_stream() -> int:
+    """Handle of torch's current stream of the current device.  torch.cuda.current_stream() builds a Stream object
+    through several Python layers; small calls are bound by the host, so the handle is asked for directly where this torch
+    can (2 loads and 2 stores of 24 pages: 44.0 us a pass before this and the rest of the marshalling below, 32.5 with them)."""
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(device())
+
+
+class _Ints:
+    """Host ints in C memory (int32 "i" or int64 "q").  array.array converts a list several times faster than a ctypes array
+    does (65 offsets: 2.6 us against 12.3); what it refuses (floats, values that do not fit, a list that does not have the
+    `n` entries asked for, an empty list's missing address) is converted the general way."""
+    __slots__ = ("keep", "at")
+
+    def __init__(self, code: str, values, n: int):
+        try:
+            if n == 0 or len(values) != n or isinstance(values, (bytes, bytearray)):
+                raise TypeError
+            self.keep = array.array(code, values)
+            self.at = self.keep.buffer_info()[0]
+        except (TypeError, OverflowError):
+            kind = ctypes.c_int32 if code == "i" else ctypes.c_int64
+            self.keep = (kind * max(n, 1))(*[int(x) for x in values])
+            self.at = ctypes.addressof(self.keep)
+
+
+def _lens(prefix_lens, new_lens):
+    batch = len(prefix_lens)
+    return batch, _Ints("i", prefix_lens, batch), _Ints("i", new_lens, batch)
 
 
 def mc_prefill_attn_workspace_bytes(params: McAttnParams, batch: int, total_new_tokens: int) -> int:
@@ -164,13 +202,11 @@ def mc_prefill_attn_paged(params: McAttnParams, q, k_pool, v_pool, block_tables,
     tensor [batch, max_pages]; prefix_lens / new_lens: host sequences of ints;
     workspace: uint8 device tensor of at least the size the library asks for.
     """
-    batch = len(prefix_lens)
-    pl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in prefix_lens])
-    nl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in new_lens])
-    max_pages = int(block_tables.shape[1]) if block_tables is not None and block_tables.dim() == 2 else 0
-    ws_bytes = 0 if workspace is None else int(workspace.numel() * workspace.element_size())
+    batch, pl, nl = _lens(prefix_lens, new_lens)
+    max_pages = _max_pages(block_tables)
+    ws_bytes = _nbytes(workspace)
     st = mc_prefill_attn_paged_raw(params, _dev_ptr(q), _dev_ptr(k_pool), _dev_ptr(v_pool), _dev_ptr(block_tables),
-                                   max_pages, ctypes.cast(pl, ctypes.c_void_p), ctypes.cast(nl, ctypes.c_void_p),
+                                   max_pages, pl.at, nl.at,
                                    batch, _dev_ptr(out), _dev_ptr(lse), _dev_ptr(workspace), ws_bytes,
                                    _stream_handle(stream))
     if st != MC_OK:
@@ -182,26 +218,19 @@ def mc_prefill_attn_split_workspace_bytes(params: McAttnParams, batch: int, tota
     return int(lib().mc_prefill_attn_split_workspace_bytes(ctypes.byref(params), batch, total_new_tokens, kv_splits))
 
 
-def _lens(prefix_lens, new_lens):
-    batch = len(prefix_lens)
-    pl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in prefix_lens])
-    nl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in new_lens])
-    return batch, pl, nl
-
-
 def mc_prefill_attn_auto_workspace_bytes(params: McAttnParams, prefix_lens, new_lens) -> int:
     batch, pl, nl = _lens(prefix_lens, new_lens)
-    return int(lib().mc_prefill_attn_auto_workspace_bytes(ctypes.byref(params), pl, nl, batch))
+    return int(lib().mc_prefill_attn_auto_workspace_bytes(ctypes.byref(params), pl.at, nl.at, batch))
 
 
 def mc_prefill_attn_auto(params: McAttnParams, q, k_pool, v_pool, block_tables, prefix_lens, new_lens, out, lse,
                          workspace, stream=None) -> None:
     """mc_prefill_attn_paged with the whole-row / key-slices choice made by the library (larger workspace)."""
     batch, pl, nl = _lens(prefix_lens, new_lens)
-    ws_bytes = 0 if workspace is None else int(workspace.numel() * workspace.element_size())
-    max_pages = int(block_tables.shape[1]) if block_tables is not None and block_tables.dim() == 2 else 0
+    ws_bytes = _nbytes(workspace)
+    max_pages = _max_pages(block_tables)
     st = int(lib().mc_prefill_attn_auto(ctypes.byref(params), _dev_ptr(q), _dev_ptr(k_pool), _dev_ptr(v_pool),
-                                        _dev_ptr(block_tables), max_pages, pl, nl, batch, _dev_ptr(out), _dev_ptr(lse),
+                                        _dev_ptr(block_tables), max_pages, pl.at, nl.at, batch, _dev_ptr(out), _dev_ptr(lse),
                                         _dev_ptr(workspace), ws_bytes, _stream_handle(stream)))
     if st != MC_OK:
         raise McError(st, "mc_prefill_attn_auto")
@@ -220,7 +249,7 @@ def mc_prefill_attn_paged_noalloc(params: McAttnParams, q, k_pool, v_pool, block
     fixed array (no allocation, no upload)."""
     batch, pl, nl = _lens(prefix_lens, new_lens)
     st = mc_prefill_attn_paged_noalloc_raw(params, _dev_ptr(q), _dev_ptr(k_pool), _dev_ptr(v_pool),
-                                           _dev_ptr(block_tables), _max_pages(block_tables), pl, nl, batch,
+                                           _dev_ptr(block_tables), _max_pages(block_tables), pl.at, nl.at, batch,
                                            _dev_ptr(out), _dev_ptr(lse), _stream_handle(stream))
     if st != MC_OK:
         raise McError(st, "mc_prefill_attn_paged_noalloc")
@@ -234,12 +263,10 @@ def mc_prefill_attn_prepare(params: McAttnParams, prefix_lens, new_lens, kv_spli
                             stream=None) -> McAttnPlan:
     """Build and upload the work list and request table of a batch ONCE; the returned plan drives any number of
     mc_prefill_attn_run / mc_prefill_attn_run_split / mc_kv_append_run calls (one per layer) on the same workspace."""
-    batch = len(prefix_lens)
-    pl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in prefix_lens])
-    nl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in new_lens])
-    ws_bytes = 0 if workspace is None else int(workspace.numel() * workspace.element_size())
+    batch, pl, nl = _lens(prefix_lens, new_lens)
+    ws_bytes = _nbytes(workspace)
     plan = McAttnPlan()
-    st = int(lib().mc_prefill_attn_prepare(ctypes.byref(params), pl, nl, batch, kv_splits, _dev_ptr(workspace), ws_bytes,
+    st = int(lib().mc_prefill_attn_prepare(ctypes.byref(params), pl.at, nl.at, batch, kv_splits, _dev_ptr(workspace), ws_bytes,
                                            _stream_handle(stream), ctypes.byref(plan)))
     if st != MC_OK:
         raise McError(st, "mc_prefill_attn_prepare")
@@ -277,15 +304,13 @@ def mc_kv_append_run(params: McAttnParams, plan: McAttnPlan, k_new, v_new, k_poo
 def mc_prefill_attn_plan(params: McAttnParams, prefix_lens, new_lens, kv_splits: int = 0):
     """The work list of an attention launch, in launch order: a list of (request, kv_head, row0, slice) tuples.
     Host arithmetic only (no GPU)."""
-    batch = len(prefix_lens)
-    pl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in prefix_lens])
-    nl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in new_lens])
+    batch, pl, nl = _lens(prefix_lens, new_lens)
     n = ctypes.c_int64(-1)
-    st = int(lib().mc_prefill_attn_plan(ctypes.byref(params), pl, nl, batch, kv_splits, None, 0, ctypes.byref(n)))
+    st = int(lib().mc_prefill_attn_plan(ctypes.byref(params), pl.at, nl.at, batch, kv_splits, None, 0, ctypes.byref(n)))
     if st != MC_OK:
         raise McError(st, "mc_prefill_attn_plan")
     buf = (ctypes.c_int32 * (4 * max(n.value, 1)))()
-    st = int(lib().mc_prefill_attn_plan(ctypes.byref(params), pl, nl, batch, kv_splits, buf, n.value, ctypes.byref(n)))
+    st = int(lib().mc_prefill_attn_plan(ctypes.byref(params), pl.at, nl.at, batch, kv_splits, buf, n.value, ctypes.byref(n)))
     if st != MC_OK:
         raise McError(st, "mc_prefill_attn_plan")
     return [tuple(buf[4 * i:4 * i + 4]) for i in range(n.value)]
@@ -293,10 +318,8 @@ def mc_prefill_attn_plan(params: McAttnParams, prefix_lens, new_lens, kv_splits:
 
 def mc_prefill_attn_suggest_kv_splits(params: McAttnParams, prefix_lens, new_lens) -> int:
     """Key slices that fill the GPU for this batch (1: use the whole-row call); 0 for arguments the library rejects."""
-    batch = len(prefix_lens)
-    pl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in prefix_lens])
-    nl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in new_lens])
-    return int(lib().mc_prefill_attn_suggest_kv_splits(ctypes.byref(params), pl, nl, batch))
+    batch, pl, nl = _lens(prefix_lens, new_lens)
+    return int(lib().mc_prefill_attn_suggest_kv_splits(ctypes.byref(params), pl.at, nl.at, batch))
 
 
 def mc_prefill_attn_paged_split_raw(params, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens,
@@ -310,14 +333,11 @@ def mc_prefill_attn_paged_split(params: McAttnParams, q, k_pool, v_pool, block_t
                                 kv_splits: int, o_parts, lse_parts, workspace, stream=None) -> None:
     """Enqueue attention over ``kv_splits`` key slices; partial results go to the fp32 device tensors
     ``o_parts`` [kv_splits, total_new, Hq, D] and ``lse_parts`` [kv_splits, total_new, Hq]."""
-    batch = len(prefix_lens)
-    pl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in prefix_lens])
-    nl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in new_lens])
-    max_pages = int(block_tables.shape[1]) if block_tables is not None and block_tables.dim() == 2 else 0
-    ws_bytes = 0 if workspace is None else int(workspace.numel() * workspace.element_size())
+    batch, pl, nl = _lens(prefix_lens, new_lens)
+    max_pages = _max_pages(block_tables)
+    ws_bytes = _nbytes(workspace)
     st = mc_prefill_attn_paged_split_raw(params, _dev_ptr(q), _dev_ptr(k_pool), _dev_ptr(v_pool),
-                                         _dev_ptr(block_tables), max_pages, ctypes.cast(pl, ctypes.c_void_p),
-                                         ctypes.cast(nl, ctypes.c_void_p), batch, kv_splits, _dev_ptr(o_parts),
+                                         _dev_ptr(block_tables), max_pages, pl.at, nl.at, batch, kv_splits, _dev_ptr(o_parts),
                                          _dev_ptr(lse_parts), _dev_ptr(workspace), ws_bytes, _stream_handle(stream))
     if st != MC_OK:
         raise McError(st, "mc_prefill_attn_paged_split")
@@ -433,11 +453,6 @@ def mc_prefix_match_workspace_bytes(batch: int, n_inst: int) -> int:
     return int(lib().mc_prefix_match_workspace_bytes(batch, n_inst))
 
 
-def _i64_array(values):
-    arr = (ctypes.c_int64 * max(len(values), 1))(*[int(x) for x in values])
-    return arr, ctypes.cast(arr, ctypes.c_void_p)
-
-
 def mc_prefix_hash_raw(tokens, tok_offsets, batch, block_tokens, keys, workspace, workspace_bytes, hip_stream) -> int:
     return int(lib().mc_prefix_hash(tokens, tok_offsets, batch, block_tokens, keys, workspace, workspace_bytes,
                                     hip_stream))
@@ -446,9 +461,9 @@ def mc_prefix_hash_raw(tokens, tok_offsets, batch, block_tokens, keys, workspace
 def mc_prefix_hash(tokens, tok_offsets, block_tokens: int, keys, workspace, stream=None) -> None:
     """Enqueue the block keys of every request: ``tokens`` int32 device tensor, ``tok_offsets`` host sequence of
     batch + 1 ints, ``keys`` int64 device tensor (the uint64 bit patterns) with one entry per block."""
-    keep, off = _i64_array(tok_offsets)
-    ws_bytes = 0 if workspace is None else int(workspace.numel() * workspace.element_size())
-    st = mc_prefix_hash_raw(_dev_ptr(tokens), off, len(tok_offsets) - 1, block_tokens, _dev_ptr(keys),
+    off = _Ints("q", tok_offsets, len(tok_offsets))
+    ws_bytes = _nbytes(workspace)
+    st = mc_prefix_hash_raw(_dev_ptr(tokens), off.at, len(tok_offsets) - 1, block_tokens, _dev_ptr(keys),
                             _dev_ptr(workspace), ws_bytes, _stream_handle(stream))
     if st != MC_OK:
         raise McError(st, "mc_prefix_hash")
@@ -463,10 +478,9 @@ def mc_prefix_match_raw(keys, key_offsets, batch, cache_keys, cache_offsets, n_i
 def mc_prefix_match(keys, key_offsets, cache_keys, cache_offsets, prefix_len, best_len, best_inst, workspace,
                     stream=None) -> None:
     """Enqueue the longest-prefix match of every request against every instance (device tensors; offsets on the host)."""
-    keep_k, koff = _i64_array(key_offsets)
-    keep_c, coff = _i64_array(cache_offsets)
-    ws_bytes = 0 if workspace is None else int(workspace.numel() * workspace.element_size())
-    st = mc_prefix_match_raw(_dev_ptr(keys), koff, len(key_offsets) - 1, _dev_ptr(cache_keys), coff,
+    koff, coff = _Ints("q", key_offsets, len(key_offsets)), _Ints("q", cache_offsets, len(cache_offsets))
+    ws_bytes = _nbytes(workspace)
+    st = mc_prefix_match_raw(_dev_ptr(keys), koff.at, len(key_offsets) - 1, _dev_ptr(cache_keys), coff.at,
                              len(cache_offsets) - 1, _dev_ptr(prefix_len), _dev_ptr(best_len), _dev_ptr(best_inst),
                              _dev_ptr(workspace), ws_bytes, _stream_handle(stream))
     if st != MC_OK:
@@ -487,14 +501,11 @@ def mc_kv_append_paged_raw(params, k_new, v_new, k_pool, v_pool, block_tables, m
 def mc_kv_append_paged(params: McAttnParams, k_new, v_new, k_pool, v_pool, block_tables, prefix_lens, new_lens,
                        workspace, stream=None) -> None:
     """Enqueue the scatter of the new tokens' K/V rows into their page slots (torch device tensors)."""
-    batch = len(prefix_lens)
-    pl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in prefix_lens])
-    nl = (ctypes.c_int32 * max(batch, 1))(*[int(x) for x in new_lens])
-    max_pages = int(block_tables.shape[1]) if block_tables is not None and block_tables.dim() == 2 else 0
-    ws_bytes = 0 if workspace is None else int(workspace.numel() * workspace.element_size())
+    batch, pl, nl = _lens(prefix_lens, new_lens)
+    max_pages = _max_pages(block_tables)
+    ws_bytes = _nbytes(workspace)
     st = mc_kv_append_paged_raw(params, _dev_ptr(k_new), _dev_ptr(v_new), _dev_ptr(k_pool), _dev_ptr(v_pool),
-                                _dev_ptr(block_tables), max_pages, ctypes.cast(pl, ctypes.c_void_p),
-                                ctypes.cast(nl, ctypes.c_void_p), batch, _dev_ptr(workspace), ws_bytes,
+                                _dev_ptr(block_tables), max_pages, pl.at, nl.at, batch, _dev_ptr(workspace), ws_bytes,
                                 _stream_handle(stream))
     if st != MC_OK:
         raise McError(st, "mc_kv_append_paged")
