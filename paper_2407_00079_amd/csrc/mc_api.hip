@@ -661,7 +661,7 @@ mc_status mc_prefix_hash(const int32_t* tokens, const int64_t* tok_offsets, int3
   mc::PrefixTables tables;
   const mc_status st = place_tables(tok_offsets, (size_t)batch + 1, key_off.data(), (size_t)batch + 1, workspace, stream, &arg, &tables);
   if (st != MC_OK) return st;
-  if (mc::launch_prefix_hash(tokens, tables, batch, block_tokens, max_blocks, keys, stream) != hipSuccess) return MC_ERR_HIP;
+  if (mc::launch_prefix_hash(tokens, tables, batch, block_tokens, max_blocks, total_blocks, keys, stream) != hipSuccess) return MC_ERR_HIP;
   return MC_OK;
 }
 

@@ -73,9 +73,10 @@ struct PrefixTables {
   const OffsetTables* arg;
 };
 
-// enqueue digest + chain kernels (tables: token offsets, key offsets; max_blocks = most blocks of any request)
+// enqueue the kernels that turn tokens into keys (tables: token offsets, key offsets; max_blocks = most blocks of any
+// request, total_blocks = all of them)
 hipError_t launch_prefix_hash(const int32_t* tokens, const PrefixTables& tables, int batch, int block_tokens,
-                              int64_t max_blocks, uint64_t* keys, hipStream_t stream);
+                              int64_t max_blocks, int64_t total_blocks, uint64_t* keys, hipStream_t stream);
 
 // enqueue match + best kernels over batch requests and n_inst instances (tables: key offsets, cache offsets)
 hipError_t launch_prefix_match(const uint64_t* keys, const PrefixTables& tables, int batch, const uint64_t* cache_keys,

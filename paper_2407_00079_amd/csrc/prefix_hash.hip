@@ -3,11 +3,11 @@
 // and by its prefix).  The paper fixes the block size (512 tokens), not the hash; the one used
 // here is stated in include/mc.h.  Integer work, bit-exact against the CPU oracle.
 //
-//   digest kernel  one wave per block: every lane mixes its tokens (position-salted), the 64
-//                  partial sums are added across the wave, lane 0 finalises.  Blocks are
-//                  independent, so a batch of long prompts fills the GPU.
-//   chain kernel   one wave per request walks its digests in order and turns them into keys in
-//                  place (the only sequential part: one mix per block, on the scalar unit).
+//   A block's digest is one wave's work (64 partial sums of position-salted mixes, added across the wave) and blocks are
+//   independent; the chain that turns a request's digests into keys is sequential, one mix per block.
+//   short kernel   requests of few blocks, one workgroup each: digests into LDS, then one wave chains them.
+//   stage kernel   longer ones: digests of one range of blocks (four per workgroup) beside the chain of another range
+//                  (one wave per request), so that a queue's first blocks are chained while its later ones are digested.
 //   match kernel   one workgroup per (instance, request): thread t looks keys t, t + 256, ... up
 //                  in the instance's ascending key array by bisection; the smallest index that
 //                  misses is the prefix length.
@@ -30,63 +30,123 @@ struct TablePtrs {
   const int64_t* __restrict__ b;
 };
 
-// Blocks of one request sit along blockIdx.x (four per workgroup, one wave each), requests along
-// blockIdx.y: no search for the owner of a block, and the offset tables are read by scalar loads.
-template <typename Tables>     // a: token offsets, b: key offsets
-__global__ __launch_bounds__(256) void prefix_digest_kernel(const int32_t* __restrict__ tokens, const Tables off, int batch,
-                                                            int block_tokens, uint64_t* __restrict__ keys) {
-  const int lane = threadIdx.x & 63;
-  const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  for (int r = blockIdx.y; r < batch; r += gridDim.y) {
-    const int64_t k0 = off.b[r];
-    if (b >= off.b[r + 1] - k0) continue;                // whole wave skips together
-    const int64_t t0 = off.a[r];
-    const int64_t left = off.a[r + 1] - t0 - b * block_tokens;
-    const int nb = left < block_tokens ? (int)left : block_tokens;
-    const int32_t* t = tokens + t0 + b * block_tokens;
-    uint64_t sum = 0;
-    int j = lane;
-    for (; j + 7 * 64 < nb; j += 8 * 64) {                // eight loads in flight per lane
-      int32_t v[8];
+// Digest of a block of nb tokens, by a whole wave (every lane gets it).  Bound by the vector ALU: about 26 instructions
+// per token and lane, six of them 32-bit multiplies at a quarter of the rate (16384 blocks of 512 tokens: 12 us).
+__device__ __forceinline__ uint64_t digest_of(const int32_t* __restrict__ t, int nb, int lane) {
+  uint64_t sum = 0;
+  int j = lane;
+  for (; j + 7 * 64 < nb; j += 8 * 64) {                  // eight loads in flight per lane
+    int32_t v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = t[j + 64 * u];
+    for (int u = 0; u < 8; ++u) v[u] = t[j + 64 * u];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) sum += mix64((uint64_t)(uint32_t)v[u] + ((uint64_t)(j + 64 * u) << 32));
-    }
-    for (; j < nb; j += 64) sum += mix64((uint64_t)(uint32_t)t[j] + ((uint64_t)j << 32));
+    for (int u = 0; u < 8; ++u) sum += mix64((uint64_t)(uint32_t)v[u] + ((uint64_t)(j + 64 * u) << 32));
+  }
+  for (; j < nb; j += 64) sum += mix64((uint64_t)(uint32_t)t[j] + ((uint64_t)j << 32));
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const uint32_t lo = __shfl_xor((uint32_t)sum, d, 64), hi = __shfl_xor((uint32_t)(sum >> 32), d, 64);
-      sum += ((uint64_t)hi << 32) | lo;
-    }
-    if (lane == 0) keys[k0 + b] = mix64(sum + (uint64_t)nb);
+  for (int d = 32; d >= 1; d >>= 1) {
+    const uint32_t lo = __shfl_xor((uint32_t)sum, d, 64), hi = __shfl_xor((uint32_t)(sum >> 32), d, 64);
+    sum += ((uint64_t)hi << 32) | lo;
+  }
+  return mix64(sum + (uint64_t)nb);
+}
+
+constexpr uint64_t kFirstSalt = 0x243F6A8885A308D3ull;
+__device__ __forceinline__ uint64_t salt_after(uint64_t key) { return ((key << 23) | (key >> 41)) * 0x9E3779B97F4A7C15ull; }
+
+// A link of the chain with the block's digest in lane LANE, whose key goes to the same lane of (lo, hi).  (A lane known at
+// compile time is an immediate for both lane moves; v_writelane has no builtin.)
+template <int LANE>
+__device__ __forceinline__ void chain_link(uint64_t digest, uint64_t& salt, uint32_t& lo, uint32_t& hi) {
+  const uint32_t dl = __builtin_amdgcn_readlane((uint32_t)digest, LANE);
+  const uint32_t dh = __builtin_amdgcn_readlane((uint32_t)(digest >> 32), LANE);
+  const uint64_t key = mix64((((uint64_t)dh << 32) | dl) ^ salt);
+  salt = salt_after(key);
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)key), "n"(LANE));
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(key >> 32)), "n"(LANE));
+}
+template <int LANE>
+__device__ __forceinline__ void chain_four(uint64_t digest, uint64_t& salt, uint32_t& lo, uint32_t& hi) {
+  chain_link<LANE>(digest, salt, lo, hi);
+  chain_link<LANE + 1>(digest, salt, lo, hi);
+  chain_link<LANE + 2>(digest, salt, lo, hi);
+  chain_link<LANE + 3>(digest, salt, lo, hi);
+}
+
+__device__ __forceinline__ int64_t uniform64(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Blocks [lo, hi) of a request from digests in `from` to keys in `to` (the same array, or LDS and the keys), by one wave,
+// 16 blocks a turn.  Bound by the issue of one wave's scalar instructions, about 6 cycles each whatever they are, so a
+// link is nothing but the hash: no first-block case, no lane compare, no counter
+// (34 instructions, 97 ns; 47 and 118 ns with them: 256 links 30 -> 25 us).
+__device__ __forceinline__ void chain_range(const uint64_t* from, uint64_t* to, int64_t lo, int64_t hi, uint64_t salt, int lane) {
+  uint64_t ahead = lane < 16 && lo + lane < hi ? from[lo + lane] : 0;
+  for (int64_t base = lo; base < hi; base += 16) {
+    const uint64_t digest = ahead;
+    const int64_t i = base + lane;
+    ahead = lane < 16 && i + 16 < hi ? from[i + 16] : 0;  // in flight while these are chained
+    uint32_t kl = 0, kh = 0;
+    chain_four<0>(digest, salt, kl, kh);                  // (links past the end lead nowhere: nothing follows them)
+    if (base + 4 < hi) chain_four<4>(digest, salt, kl, kh);
+    if (base + 8 < hi) chain_four<8>(digest, salt, kl, kh);
+    if (base + 12 < hi) chain_four<12>(digest, salt, kl, kh);
+    if (lane < 16 && i < hi) to[i] = ((uint64_t)kh << 32) | kl;
   }
 }
 
-// One wave per request.  The chain itself is sequential, but its loads and stores need not be:
-// the wave reads 64 digests at once, walks them lane by lane with wave-uniform (scalar unit)
-// arithmetic, each lane keeping the key of its own block, and writes the 64 keys back at once.
+constexpr int kShortBlocks = 32;       // most blocks of a request the short kernel takes (see hash_with)
+
+template <typename Tables>     // a: token offsets, b: key offsets
+__global__ __launch_bounds__(1024) void prefix_short_kernel(const int32_t* __restrict__ tokens, const Tables off, int batch,
+                                                            int block_tokens, uint64_t* __restrict__ keys) {
+  __shared__ uint64_t digests[kShortBlocks];
+  const int lane = threadIdx.x & 63;
+  for (int r = blockIdx.x; r < batch; r += gridDim.x) {
+    const int64_t k0 = off.b[r], t0 = off.a[r], len = off.a[r + 1] - t0;
+    const int nk = (int)(off.b[r + 1] - k0);
+    for (int b = threadIdx.x >> 6; b < nk; b += blockDim.x >> 6) {
+      const int64_t at = (int64_t)b * block_tokens, left = len - at;
+      const uint64_t d = digest_of(tokens + t0 + at, left < block_tokens ? (int)left : block_tokens, lane);
+      if (lane == 0) digests[b] = d;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) chain_range(digests, keys + k0, 0, nk, kFirstSalt, lane);
+    __syncthreads();
+  }
+}
+
+// A range of blocks [lo, hi); of a request, those of them it has.
+struct Blocks {
+  int64_t lo, hi;
+};
+
+// Requests sit along blockIdx.x.  Row 0 of the grid, where `chains` says so, chains blocks `chain` of its request (their
+// digests are complete, and the key before them); the other rows digest blocks `digest`, four per workgroup and turn.
 template <typename Tables>
-__global__ __launch_bounds__(64) void prefix_chain_kernel(const Tables off, int batch, uint64_t* __restrict__ keys) {
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(256) void prefix_stage_kernel(const int32_t* __restrict__ tokens, const Tables off, int batch,
+                                                           int block_tokens, const Blocks digest, const Blocks chain,
+                                                           const int chains, uint64_t* keys) {
+  const int lane = threadIdx.x & 63;
+  const int row = (int)blockIdx.y - chains;
   for (int r = blockIdx.x; r < batch; r += gridDim.x) {
     const int64_t k0 = off.b[r], nk = off.b[r + 1] - k0;
-    uint64_t prev = 0;
-    for (int64_t base = 0; base < nk; base += 64) {
-      const int64_t i = base + lane;
-      const uint64_t digest = i < nk ? keys[k0 + i] : 0;
-      const int m = nk - base < 64 ? (int)(nk - base) : 64;
-      uint64_t mine = 0;
-      for (int j = 0; j < m; ++j) {
-        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)digest, j);
-        const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(digest >> 32), j);
-        const uint64_t d = ((uint64_t)hi << 32) | lo;
-        const uint64_t salt = base + j == 0 ? 0x243F6A8885A308D3ull
-                                            : ((prev << 23) | (prev >> 41)) * 0x9E3779B97F4A7C15ull;
-        prev = mix64(d ^ salt);
-        if (lane == j) mine = prev;
-      }
-      if (i < nk) keys[k0 + i] = mine;
+    if (row < 0) {
+      if (threadIdx.x >= 64) return;
+      const int64_t hi = nk < chain.hi ? nk : chain.hi;
+      if (chain.lo >= hi) continue;
+      const uint64_t salt = chain.lo == 0 ? kFirstSalt : salt_after((uint64_t)uniform64((int64_t)keys[k0 + chain.lo - 1]));
+      chain_range(keys + k0, keys + k0, chain.lo, hi, salt, lane);
+      continue;
+    }
+    const int64_t t0 = off.a[r], len = off.a[r + 1] - t0;
+    const int64_t hi = nk < digest.hi ? nk : digest.hi;
+    for (int64_t b = digest.lo + (int64_t)row * 4 + (threadIdx.x >> 6); b < hi; b += (int64_t)(gridDim.y - chains) * 4) {
+      const int64_t at = b * block_tokens, left = len - at;
+      const uint64_t d = digest_of(tokens + t0 + at, left < block_tokens ? (int)left : block_tokens, lane);
+      if (lane == 0) keys[k0 + b] = d;
     }
   }
 }
@@ -141,13 +201,39 @@ __global__ __launch_bounds__(64) void prefix_best_kernel(const int32_t* __restri
 
 namespace {
 
+// Costs the split of a queue of long prompts rests on (512-token blocks, measured): one link of a chain, and the digest of
+// one block when the whole chip digests.  A rough figure does: the line only moves work between launches.
+constexpr double kChainNs = 95.0, kDigestNs = 0.64;
+
 template <typename Tables>
 hipError_t hash_with(const int32_t* tokens, const Tables& off, int batch, int block_tokens, int64_t max_blocks,
-                     uint64_t* keys, hipStream_t stream) {
-  const unsigned req_rows = batch < 65535 ? (unsigned)batch : 65535u;   // the kernels stride over the rest
-  prefix_digest_kernel<Tables><<<dim3((unsigned)((max_blocks + 3) / 4), req_rows), 256, 0, stream>>>(tokens, off, batch,
-                                                                                                    block_tokens, keys);
-  prefix_chain_kernel<Tables><<<req_rows, 64, 0, stream>>>(off, batch, keys);
+                     int64_t total_blocks, uint64_t* keys, hipStream_t stream) {
+  const unsigned cols = batch < 65535 ? (unsigned)batch : 65535u;          // the kernels stride over the rest
+  // Few blocks per request: one launch.  On one compute unit a block's digest takes 0.16 us, so beyond 32 of them (two
+  // turns of the 16 waves) the chip-wide digests win back what their own launch costs.  14 blocks: 3.0 + 3.5 us and a
+  // launch between them, now 5.0 us; keys and match of that prompt 18.2 -> 14.8 us a pass.
+  if (max_blocks <= kShortBlocks) {
+    const unsigned waves = max_blocks < 16 ? (unsigned)max_blocks : 16u;
+    prefix_short_kernel<Tables><<<cols, waves * 64, 0, stream>>>(tokens, off, batch, block_tokens, keys);
+    return hipGetLastError();
+  }
+  // Long prompts: digests, then chains.  Where the digests of the whole queue take longer than another launch costs (about
+  // 4 us), the chains of the first blocks run beside the digests of the rest: `first` is where both take equally long.
+  // 64 prompts of 256 blocks: 12 + 30 us, now 6 + 11 + 20 (59.9 -> 54.7 us a pass with the match; 54.8 with first = 112
+  // instead of 64).
+  const double digest_ns = kDigestNs * (double)total_blocks;
+  int64_t first = (int64_t)(digest_ns / (kChainNs + kDigestNs * batch)) & ~(int64_t)15;
+  if (digest_ns < 4000.0 || first == 0 || first + 32 > max_blocks) first = max_blocks;
+  auto stage = [&](Blocks digest, Blocks chain) {
+    const int chains = chain.lo < chain.hi ? 1 : 0;
+    const int64_t quads = (digest.hi - digest.lo + 3) / 4;
+    const unsigned rows = (unsigned)(quads < 8192 ? quads : 8192);         // and over these
+    prefix_stage_kernel<Tables><<<dim3(cols, rows + chains), rows > 0 ? 256 : 64, 0, stream>>>(
+        tokens, off, batch, block_tokens, digest, chain, chains, keys);
+  };
+  stage({0, first}, {0, 0});
+  if (first < max_blocks) stage({first, max_blocks}, {0, first});
+  stage({0, 0}, {first < max_blocks ? first : 0, max_blocks});
   return hipGetLastError();
 }
 
@@ -164,10 +250,10 @@ hipError_t match_with(const uint64_t* keys, const Tables& off, int batch, const 
 }  // namespace
 
 hipError_t launch_prefix_hash(const int32_t* tokens, const PrefixTables& tables, int batch, int block_tokens,
-                              int64_t max_blocks, uint64_t* keys, hipStream_t stream) {
+                              int64_t max_blocks, int64_t total_blocks, uint64_t* keys, hipStream_t stream) {
   (void)hipGetLastError();
-  if (tables.arg != nullptr) return hash_with(tokens, *tables.arg, batch, block_tokens, max_blocks, keys, stream);
-  return hash_with(tokens, TablePtrs{tables.a, tables.b}, batch, block_tokens, max_blocks, keys, stream);
+  if (tables.arg != nullptr) return hash_with(tokens, *tables.arg, batch, block_tokens, max_blocks, total_blocks, keys, stream);
+  return hash_with(tokens, TablePtrs{tables.a, tables.b}, batch, block_tokens, max_blocks, total_blocks, keys, stream);
 }
 
 hipError_t launch_prefix_match(const uint64_t* keys, const PrefixTables& tables, int batch, const uint64_t* cache_keys,
