@@ -676,9 +676,12 @@ mc_status mc_prefix_match(const uint64_t* keys, const int64_t* key_offsets, int3
   if (batch == 0) return MC_OK;
   if (key_offsets == nullptr || cache_offsets == nullptr) return MC_ERR_NULL;
   if (key_offsets[0] < 0 || cache_offsets[0] < 0) return MC_ERR_SHAPE;
+  int64_t max_keys = 0;
   for (int32_t r = 0; r < batch; ++r) {
     if (key_offsets[r + 1] < key_offsets[r]) return MC_ERR_SHAPE;
-    if (key_offsets[r + 1] - key_offsets[r] > INT32_MAX) return MC_ERR_RANGE;
+    const int64_t n = key_offsets[r + 1] - key_offsets[r];
+    if (n > INT32_MAX) return MC_ERR_RANGE;
+    max_keys = n > max_keys ? n : max_keys;
   }
   for (int32_t i = 0; i < n_inst; ++i)
     if (cache_offsets[i + 1] < cache_offsets[i]) return MC_ERR_SHAPE;
@@ -697,7 +700,7 @@ mc_status mc_prefix_match(const uint64_t* keys, const int64_t* key_offsets, int3
   mc::PrefixTables tables;
   const mc_status st = place_tables(key_offsets, (size_t)batch + 1, cache_offsets, (size_t)n_inst + 1, workspace, stream, &arg, &tables);
   if (st != MC_OK) return st;
-  if (mc::launch_prefix_match(keys, tables, batch, cache_keys, n_inst, prefix_len, best_len, best_inst, stream) != hipSuccess)
+  if (mc::launch_prefix_match(keys, tables, batch, max_keys, cache_keys, n_inst, prefix_len, best_len, best_inst, stream) != hipSuccess)
     return MC_ERR_HIP;
   return MC_OK;
 }

@@ -78,8 +78,10 @@ struct PrefixTables {
 hipError_t launch_prefix_hash(const int32_t* tokens, const PrefixTables& tables, int batch, int block_tokens,
                               int64_t max_blocks, int64_t total_blocks, uint64_t* keys, hipStream_t stream);
 
-// enqueue match + best kernels over batch requests and n_inst instances (tables: key offsets, cache offsets)
-hipError_t launch_prefix_match(const uint64_t* keys, const PrefixTables& tables, int batch, const uint64_t* cache_keys,
-                               int n_inst, int32_t* prefix_len, int32_t* best_len, int32_t* best_inst, hipStream_t stream);
+// enqueue the prefix match over batch requests and n_inst instances (tables: key offsets, cache offsets; max_keys = most
+// keys of any request)
+hipError_t launch_prefix_match(const uint64_t* keys, const PrefixTables& tables, int batch, int64_t max_keys,
+                               const uint64_t* cache_keys, int n_inst, int32_t* prefix_len, int32_t* best_len,
+                               int32_t* best_inst, hipStream_t stream);
 
 }  // namespace mc
