@@ -19,6 +19,21 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;              // waves of a workgroup: two per SIMD, 32 stacked rows each
 static_assert(kWaves * 32 == kAttnTileRows, "the host cuts the work list into tiles of kAttnTileRows rows");
+// Which waves do what.  Full tiles (256 rows): all eight compute, the first of each SIMD copies tiles besides (it wins the
+// issue arbitration and would idle at the tile barrier).  Few rows (128): the first of each SIMD computes, the second only
+// copies; a copy instruction holds its wave for about 130 cycles, which a lone computing wave has no one to hide behind
+// (16 tokens at 128k, 64/8 heads: 115 us a call with four waves that do both, 97 with four and four).
+// Full tiles / few rows, one call, bf16 head_dim 128, 64/8 heads unless said: P 131056, C 16 111 / 96 us; P 131056, C 1
+// 101 / 86; P 1000, C 100 28 / 22; P 256, C 128 17 / 13; P 30000, C 300 245 / 275; head_dim 64, P 131056, C 16 69 / 60;
+// fp32, 4/1 heads, P 256, C 128 24 / 17, P 6955, C 200 80 / 46.
+enum Rows { kFullRows = 0, kFewRows = 1 };
+constexpr int kFetchWaves = 4;
+template <Rows R>
+constexpr int kTileRowsOf = R == kFewRows ? kAttnFewRows : kAttnTileRows;
+template <Rows R>
+__device__ __forceinline__ bool wave_copies(int wave) { return R == kFewRows ? wave >= kFetchWaves : wave < kFetchWaves; }
+template <Rows R>
+__device__ __forceinline__ bool wave_computes(int wave) { return R == kFullRows || wave < kFetchWaves; }
 constexpr int kTileKeys = kAttnTileKeys;   // keys per LDS tile = 4 pages of 16
 constexpr int kPageTokens = 16;
 constexpr int kRowBytes = 256;         // one K or V row: 128 bf16 or 64 f32
@@ -26,6 +41,7 @@ constexpr int kPageHeadBytes = kPageTokens * kRowBytes;   // 4 KiB, contiguous i
 constexpr int kKTileBytes = kTileKeys * kRowBytes;        // 16 KiB; rows dense, granules swizzled
 constexpr int kVTileBytes = kTileKeys * kRowBytes;
 constexpr int kBuffers = 3;
+constexpr int kDeepBuffers = 4;        // 128 KiB of 256-byte rows, of 160 KiB a compute unit has
 // LDS: the K tiles of the three buffers, then the V tiles.  Every tile starts at a multiple of
 // 16 KiB, so the XOR constants of the swizzle (< 256) never reach a tile base, and the offset of
 // any fragment from its lane's base register stays below the 64 KiB a ds_read immediate can hold.
@@ -46,10 +62,11 @@ struct Work {
   int32_t req, kv_head, row0, q_off, prefix, chunk;
   int32_t piece, pieces;
   int64_t part_row;
+  bool once;                             // every K and V row of the launch is read once and they outgrow the caches
 };
 
 __device__ __forceinline__ Work work_of(const AttnItem& item, const AttnReq& rq, int64_t rows_total) {
-  return Work{item.req, item.kv_head, item.row0, rq.q_off, rq.prefix, rq.chunk, item.slice, 1, (int64_t)item.slice * rows_total};
+  return Work{item.req, item.kv_head, item.row0, rq.q_off, rq.prefix, rq.chunk, item.slice, 1, (int64_t)item.slice * rows_total, false};
 }
 
 // the class of workgroup (or merge block) wg: the last one whose first is not past it
@@ -58,18 +75,19 @@ __device__ __forceinline__ int class_of(const AttnClasses& t, int wg) {
   const int first = t.first[lane];
   return __popcll(__builtin_amdgcn_ballot_w64(lane < t.n && first <= wg)) - 1;
 }
-__device__ __forceinline__ int class_rows(const AttnClass& k, int G) {
-  const int all = k.chunk * G, hi = (k.tile_hi + 1) * kAttnTileRows;
-  return (all < hi ? all : hi) - k.tile_lo * kAttnTileRows;
+__device__ __forceinline__ int class_rows(const AttnClass& k, int G, int tile_rows) {
+  const int all = k.chunk * G, hi = (k.tile_hi + 1) * tile_rows;
+  return (all < hi ? all : hi) - k.tile_lo * tile_rows;
 }
+template <int TILE_ROWS>
 __device__ __forceinline__ Work work_of(const AttnClasses& t, int wg, int Hkv, int G) {
   const int at = class_of(t, wg);
   const AttnClass k = t.c[at];
   const int local = wg - t.first[at];
   const int head = local % Hkv, rest = local / Hkv;
-  const int piece = rest % k.pieces, row0 = (k.tile_hi - rest / k.pieces) * kAttnTileRows;
-  const int64_t part = (int64_t)k.part_base + (int64_t)(piece * Hkv + head) * class_rows(k, G) - k.tile_lo * kAttnTileRows;
-  return Work{k.req, head, row0, k.q_off, k.prefix, k.chunk, piece, k.pieces, part};
+  const int piece = rest % k.pieces, row0 = (k.tile_hi - rest / k.pieces) * TILE_ROWS;
+  const int64_t part = (int64_t)k.part_base + (int64_t)(piece * Hkv + head) * class_rows(k, G, TILE_ROWS) - k.tile_lo * TILE_ROWS;
+  return Work{k.req, head, row0, k.q_off, k.prefix, k.chunk, piece, k.pieces, part, t.once != 0};
 }
 // key tiles [lo, hi) of the n a row tile sees that piece `piece` of `pieces` covers
 __device__ __forceinline__ void piece_tiles(int n, int piece, int pieces, int* lo, int* hi) {
@@ -117,18 +135,29 @@ __device__ __forceinline__ void dma16(const char* vaddr, uint32_t lds_base) {
                :: "v"(vaddr), "s"(lds_base) : "m0", "memory");
 }
 // The chunks of a page (1 KiB each, contiguous in the pool and in LDS): the immediate offset of the instruction advances
-// the global and the LDS address alike, so one base and one M0 serve all of them.
-template <int CHUNKS>
+// the global and the LDS address alike, so one base and one M0 serve all of them.  ONCE: the bytes are not read again soon.
+#define MC_COPY_PAGE_4(HINT)                                                                                              \
+  asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" HINT "\n\t"                              \
+               "global_load_lds_dwordx4 %2, %0 offset:1024" HINT "\n\tglobal_load_lds_dwordx4 %3, %0 offset:2048" HINT    \
+               "\n\tglobal_load_lds_dwordx4 %4, %0 offset:3072" HINT                                                      \
+               :: "s"(sbase), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(lds_base) : "m0", "memory")
+#define MC_COPY_PAGE_2(HINT)                                                                                              \
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0" HINT "\n\t"                              \
+               "global_load_lds_dwordx4 %2, %0 offset:1024" HINT                                                          \
+               :: "s"(sbase), "v"(voff[0]), "v"(voff[1]), "s"(lds_base) : "m0", "memory")
+template <bool ONCE, int CHUNKS>
 __device__ __forceinline__ void dma16_page(const char* sbase, const uint32_t (&voff)[CHUNKS], uint32_t lds_base) {
   static_assert(CHUNKS == 2 || CHUNKS == 4, "a page is 2 or 4 KiB");
-  if constexpr (CHUNKS == 4)
-    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0\n\tglobal_load_lds_dwordx4 %2, %0 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %3, %0 offset:2048\n\tglobal_load_lds_dwordx4 %4, %0 offset:3072"
-                 :: "s"(sbase), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(lds_base) : "m0", "memory");
-  else
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0\n\tglobal_load_lds_dwordx4 %2, %0 offset:1024"
-                 :: "s"(sbase), "v"(voff[0]), "v"(voff[1]), "s"(lds_base) : "m0", "memory");
+  if constexpr (CHUNKS == 4) {
+    if constexpr (ONCE) MC_COPY_PAGE_4(" nt");
+    else MC_COPY_PAGE_4("");
+  } else {
+    if constexpr (ONCE) MC_COPY_PAGE_2(" nt");
+    else MC_COPY_PAGE_2("");
+  }
 }
+#undef MC_COPY_PAGE_4
+#undef MC_COPY_PAGE_2
 #pragma clang diagnostic pop
 
 }  // namespace

@@ -31,8 +31,11 @@
 //     on the chunk's diagonal take the masked, max-first path.
 //   * Two waves per SIMD, half a step apart: while one wave's softmax occupies the
 //     vector ALU under its score MFMAs, the other wave's P V MFMAs keep the matrix
-//     pipe busy.  Waves of the second half whose rows lie past the chunk's end exit
+//     pipe busy.  Waves that copy nothing and whose rows lie past the chunk's end exit
 //     at once (the barriers count surviving waves only).
+//   * Launches of few or short row tiles take 128 rows per workgroup: one wave of each SIMD
+//     computes, the other only copies tiles (see Rows).  Twice the workgroups to cut, half the
+//     matrix work on a workgroup's critical path, and the copies off it.
 #include <type_traits>
 
 #include "attn_device.h"
@@ -123,11 +126,11 @@ struct F32 {
 // ceil(tiles / kv_splits) per slice) and writes a PARTIAL result - the normalised fp32 output
 // over its keys and their log-sum-exp (-inf where the slice holds no key the row may see) - for
 // mc_attn_merge_lse to combine (paper Section 5.1: attention is associative over key slices).
-template <class T, int WAVES, Form FORM>
+template <class T, Rows ROWS, Form FORM>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   constexpr bool SPLIT = FORM != kWhole;       // the result may be partial
   __shared__ __attribute__((aligned(16))) char smem[kBuffers * (kKTileBytes + kVTileBytes)];
-  constexpr int kTileRows = WAVES * 32;
+  constexpr int kTileRows = kTileRowsOf<ROWS>;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -140,11 +143,11 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   const int n_rows = work.chunk * G;
   const int last_page = (L - 1) / kPageTokens;
 
-  // A wave of the second half (these copy no tiles) whose 32 rows all lie past the end of the chunk
-  // has nothing to do: it ends here, and the workgroup's barriers then wait for the surviving
-  // waves only.  Small chunks (a 16-token chunk of an 8-head group fills 4 of 8 waves) then
-  // spend no MFMA work on rows that are never stored.
-  if (wave >= WAVES / 2 && work.row0 + wave * 32 >= n_rows) return;
+  // A wave that copies no tiles and whose 32 rows all lie past the end of the chunk has nothing to
+  // do: it ends here, and the workgroup's barriers then wait for the surviving waves only.
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const bool fetcher = wave_copies<ROWS>(wave_u);
+  if (!fetcher && work.row0 + wave_u * 32 >= n_rows) return;
 
   // ---- this lane's query row: its Q fragments stay in registers for the whole KV loop
   typename T::frag qf[T::kQKSteps];
@@ -179,7 +182,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   const int64_t prow = work.part_row + (FORM == kClasses ? (int64_t)row : orow_idx);
   if (SPLIT && t_lo >= n_tiles) {
     // no key of the slice is visible to any row of the tile
-    if (live) {
+    if (live && wave_computes<ROWS>(wave_u)) {
       char* orow = reinterpret_cast<char*>(a.o_parts) + prow * (T::kD * 4);
 #pragma unroll
       for (int db = 0; db < T::kDBlocks; ++db)
@@ -194,20 +197,16 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   // ---- global -> LDS, no registers in between.  One wave instruction writes 1 KiB of LDS (lane i
   //      its 16 bytes at +16*i): 4 tile rows x 16 granules, all inside one page.  Lane i fetches,
   //      for LDS granule position i%16 of row i/16, the logical granule (i%16) ^ swz(row).
-  //      Only the first half of the waves issue copies: they are the first wave of each SIMD, win
-  //      the issue arbitration against the second wave and would otherwise idle at the tile
-  //      barrier, and a copy instruction holds its wave for ~130 cycles.  Fetching wave w copies
+  //      One wave of each SIMD issues copies (which: see Rows).  Fetching wave w copies
   //      chunks w, w + kFetchWaves, ... of the tile (chunk c = rows 4c..4c+3, page c/4).
-  constexpr int kFetchWaves = WAVES / 2;
   constexpr int kChunks = kTileKeys / 4;                      // 1 KiB chunks per K (or V) tile
   constexpr int kFetch = kChunks / kFetchWaves;               // chunks per fetching wave
   static_assert(kChunks % kFetchWaves == 0 && kFetch <= 8, "tile must split evenly over the fetching waves");
   const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadBytes;
   const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)work.kv_head * kPageHeadBytes;
   const int64_t page_stride = (int64_t)a.Hkv * kPageHeadBytes;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int fetch_wave = wave_u & (kFetchWaves - 1);
   const uint32_t smem_base = (uint32_t)(uintptr_t)(MC_LDS char*)smem;
-  const bool fetcher = wave_u < kFetchWaves;
   // The block table is read through the scalar cache (it is constant while the kernel runs),
   // one tile AHEAD of the K/V loads that need it, so no wave ever waits for a page id.
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
@@ -221,7 +220,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
     if (!fetcher) return;
 #pragma unroll
     for (int i = 0; i < kFetch; ++i) {
-      int lp = tile * (kTileKeys / kPageTokens) + (wave_u + i * kFetchWaves) / 4;
+      int lp = tile * (kTileKeys / kPageTokens) + (fetch_wave + i * kFetchWaves) / 4;
       lp = lp < last_page ? lp : last_page;                  // never index the table past the request's pages
       pid_next[i] = btc[lp];
     }
@@ -232,14 +231,14 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   };
   // Per-lane byte offset inside a (page, head) block: the same for every chunk of a wave, because
   // a wave's chunks are 16 rows (one page) apart and both swizzles depend on row % 16 only.
-  const int lane_row = (wave_u & 3) * 4 + (lane >> 4);       // row of the page this lane copies a granule of
+  const int lane_row = (fetch_wave & 3) * 4 + (lane >> 4);       // row of the page this lane copies a granule of
   const uint32_t k_src = (uint32_t)(lane_row * kRowBytes + (((lane & 15) ^ T::k_swz(lane_row)) << 4));
   const uint32_t v_src = (uint32_t)(lane_row * kRowBytes + (((lane & 15) ^ T::v_swz(lane_row)) << 4));
   static_assert(kFetchWaves % 4 == 0, "a fetching wave's chunks must all sit at the same rows of their pages");
   // enqueue the copy of tile `tile` (page ids in pid[]) into LDS buffer `buf`
   auto fetch = [&](int tile, int buf) __attribute__((always_inline)) {
     if (!fetcher) return;
-    const uint32_t dst0 = smem_base + buf * kKTileBytes + wave_u * 1024;
+    const uint32_t dst0 = smem_base + buf * kKTileBytes + fetch_wave * 1024;
     if ((tile + 1) * kTileKeys <= L) {
       // whole tile inside the sequence: scalar page base + constant lane offset
 #pragma unroll
@@ -254,7 +253,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
       // those lanes copy row 0 of the request's first page instead; the causal mask hides the key.
 #pragma unroll
       for (int i = 0; i < kFetch; ++i) {
-        const int row = (wave_u + i * kFetchWaves) * 4 + (lane >> 4);
+        const int row = (fetch_wave + i * kFetchWaves) * 4 + (lane >> 4);
         const bool in_seq = tile * kTileKeys + row < L;
         const int64_t page_off = (int64_t)pid[i] * page_stride;
         const char* ks = kbase + (in_seq ? page_off + k_src : first_page_off + (k_src & 255));
@@ -429,25 +428,27 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
     pv_block(buf, kb, pb);
   };
 
-  load_ids(t_lo);
-  take_ids();
-  fetch(t_lo, 0);
-  load_ids(t_lo + 1);
-  take_ids();
-  if (n_tiles > t_lo + 1) {
-    fetch(t_lo + 1, 1);
-    load_ids(t_lo + 2);
+  // the first two tiles; everything issued so far (also the Q fragments) has landed: inside the loop the vector-memory
+  // counter only ever counts the tile copies
+  auto first_copies = [&]() __attribute__((always_inline)) {
+    load_ids(t_lo);
     take_ids();
-  }
-  // everything issued so far has landed (Q fragments, tiles 0 and 1): inside the loop the
-  // vector-memory counter only ever counts the tile copies
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
+    fetch(t_lo, 0);
+    load_ids(t_lo + 1);
+    take_ids();
+    if (n_tiles > t_lo + 1) {
+      fetch(t_lo + 1, 1);
+      load_ids(t_lo + 2);
+      take_ids();
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  };
   int buf = 0;
   // One tile = barrier, enqueue the copy of tile + 2, two blocks.  After the barrier tile + 1 is
   // visible to every wave (it was enqueued a whole tile ago) and no wave reads tile - 1 any
   // more, so that buffer takes tile + 2.
-  auto tile_sync = [&](int tile) __attribute__((always_inline)) {
+  auto copy_sync = [&](int tile) __attribute__((always_inline)) {
     const bool ahead = tile + 2 < n_tiles;
     if (ahead) load_ids(tile + 3);
     copies_landed();
@@ -457,6 +458,23 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
       take_ids();
     }
   };
+  auto tile_sync = [&](int tile) __attribute__((always_inline)) {
+    if constexpr (ROWS == kFullRows) copy_sync(tile);
+    else __syncthreads();
+  };
+  if constexpr (ROWS == kFewRows) {
+    if (fetcher) {
+      first_copies();
+      for (int tile = t_lo; tile < n_tiles; ++tile) {
+        copy_sync(tile);
+        buf = buf == 2 ? 0 : buf + 1;
+      }
+      return;
+    }
+    __syncthreads();
+  } else {
+    first_copies();
+  }
   int tile = t_lo;
   // tiles every key of which is visible to every row go through the pipeline (never the last
   // tile: the pipeline always computes the scores of one block ahead)
@@ -465,14 +483,14 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   if (tile < n_plain) {
     settle_reference(s_next, 0, std::false_type{});
     load_k_ring(0, 1);
-    // The two waves of a SIMD run half a step apart: the second one (waves WAVES/2 ..) passes the
+    // The two waves of a SIMD run half a step apart: the second one (waves kFetchWaves ..) passes the
     // tile barrier between the two phases of the tile's first step instead of before it.  When
     // the barrier opens one wave of each SIMD starts a phase A (a dependent MFMA chain under
     // heavy vector work) and the other a phase B (independent MFMAs, no vector work), so the
     // matrix pipe always has an MFMA that is ready and the vector ALU is never wanted twice.
     // Safe because phase A of a tile's first step reads nothing of the tile before it and
     // nothing of the tile after it, and every wave still passes one barrier per tile.
-    const bool late_barrier = wave_u >= WAVES / 2;
+    const bool late_barrier = ROWS == kFullRows && wave_u >= kFetchWaves;
     // The loop body is written out for the three buffers in turn, so that inside it every tile
     // offset is a compile-time constant and goes into the LDS instructions' immediate fields.
     auto pipelined_tile = [&](auto buf_tag) __attribute__((always_inline)) {
@@ -539,15 +557,15 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   }
 }
 
-template <class T, int WAVES, bool SPLIT>
-__global__ __launch_bounds__(WAVES * 64) void attn_prefill_kernel(const AttnArgs a) {
+template <class T, bool SPLIT>
+__global__ __launch_bounds__(kWaves * 64) void attn_prefill_kernel(const AttnArgs a) {
   const AttnItem item = a.items[blockIdx.x];
-  attn_body<T, WAVES, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
+  attn_body<T, kFullRows, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
 }
 
-template <class T, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void attn_prefill_classes_kernel(const AttnArgs a, const AttnClasses t) {
-  attn_body<T, WAVES, kClasses>(a, work_of(t, blockIdx.x, a.Hkv, a.G));
+template <class T, Rows ROWS>
+__global__ __launch_bounds__(kWaves * 64) void attn_prefill_classes_kernel(const AttnArgs a, const AttnClasses t) {
+  attn_body<T, ROWS, kClasses>(a, work_of<kTileRowsOf<ROWS>>(t, blockIdx.x, a.Hkv, a.G));
 }
 
 // ---------------------------------------------------------------------------
@@ -658,11 +676,11 @@ __global__ __launch_bounds__(256) void attn_merge_classes_kernel(const float* __
   const int at = class_of(t, blockIdx.x);
   const AttnClass k = t.c[at];
   const int G = Hq / Hkv;
-  const int rows_head = class_rows(k, G), rows = rows_head * Hkv;
+  const int rows_head = class_rows(k, G, t.rows), rows = rows_head * Hkv;
   const int raw = ((int)blockIdx.x - t.first[at]) * M::kRows + threadIdx.x / (M::kThreadsPerRow * SL);
   const bool live = raw < rows;
   const int r = live ? raw : rows - 1;
-  const int head = r / rows_head, row = k.tile_lo * kAttnTileRows + (r - head * rows_head);
+  const int head = r / rows_head, row = k.tile_lo * t.rows + (r - head * rows_head);
   const int tok = row / G;
   const int64_t dst = (int64_t)(k.q_off + tok) * Hq + head * G + (row - tok * G);
   M::row(sh, o_parts, lse_parts, (int64_t)k.part_base + r, rows, k.pieces, live, dst, out, lse);
@@ -674,15 +692,16 @@ hipError_t launch_attn(int dtype, const AttnArgs& args, hipStream_t stream) {
   (void)hipGetLastError();   // drop any stale error of earlier, unrelated runtime calls
   const bool split = args.kv_splits > 0;
   if (dtype == MC_DTYPE_BF16) return launch_attn_bf16(args, stream);
-  if (split) attn_prefill_kernel<F32, kWaves, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-  else attn_prefill_kernel<F32, kWaves, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+  if (split) attn_prefill_kernel<F32, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+  else attn_prefill_kernel<F32, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_classes(int dtype, const AttnArgs& args, const AttnClasses& t, hipStream_t stream) {
   (void)hipGetLastError();
   if (dtype == MC_DTYPE_BF16) return launch_attn_bf16_classes(args, t, stream);
-  attn_prefill_classes_kernel<F32, kWaves><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+  if (t.rows == kAttnFewRows) attn_prefill_classes_kernel<F32, kFewRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+  else attn_prefill_classes_kernel<F32, kFullRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
   return hipGetLastError();
 }
 
@@ -697,8 +716,8 @@ static void enqueue_merge_classes(const float* o_parts, const float* lse_parts, 
   for (int i = 0; i < t.n; ++i) {
     t.first[i] = n;
     const AttnClass& k = t.c[i];
-    const int all = k.chunk * G, hi = (k.tile_hi + 1) * kAttnTileRows;
-    const int rows = ((all < hi ? all : hi) - k.tile_lo * kAttnTileRows) * Hkv;
+    const int all = k.chunk * G, hi = (k.tile_hi + 1) * t.rows;
+    const int rows = ((all < hi ? all : hi) - k.tile_lo * t.rows) * Hkv;
     n += (rows + Merge<T, SL>::kRows - 1) / Merge<T, SL>::kRows;
   }
   attn_merge_classes_kernel<T, SL><<<n, 256, 0, stream>>>(o_parts, lse_parts, t, Hq, Hkv, out, lse);
@@ -709,6 +728,8 @@ hipError_t launch_attn_merge_classes(int dtype, int head_dim, const float* o_par
   (void)hipGetLastError();
   AttnClasses t;
   t.n = 0;
+  t.rows = all.rows;
+  t.once = all.once;
   int most = 0;
   for (int i = 0; i < all.n; ++i)
     if (all.c[i].pieces > 1) {

@@ -72,7 +72,6 @@ struct Geo {
   static_assert(kRing == 2 * kSteps, "both phases walk the ring once");
   static constexpr int kPageHeadB = kPageTokens * kRowB; // one (page, KV head), contiguous in the pool
   static constexpr int kKTileB = kTileKeys * kRowB;      // a K (or V) tile in LDS; rows dense, granules swizzled
-  static constexpr int kVBaseB = kBuffers * kKTileB;     // the K tiles of the three buffers, then the V tiles
   static constexpr int kChunkRows = 1024 / kRowB;        // rows one wave copy instruction (1 KiB) covers
   static constexpr int kPageChunks = kPageTokens / kChunkRows;
 
@@ -159,17 +158,24 @@ __device__ __forceinline__ uint32_t round_pair(const Scores& p, int e) {
   const f32x2 pp = {p.get(e), p.get(e + 1)};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(pp, bf16x2));      // one v_cvt_pk_bf16_f32 (round to nearest even)
 }
-template <int D, int WAVES, Form FORM>
+template <int D, Rows ROWS, Form FORM>
 __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& work) {
   constexpr bool SPLIT = FORM != kWhole;       // the result may be partial
   typedef Geo<D> X;
   // (these names hide the 256-byte-row constants of attn_device.h inside this kernel)
   constexpr int kD = D, kSteps = X::kSteps, kDTiles = X::kDTiles, kRing = X::kRing, kRowBytes = X::kRowB,
-                kPageHeadBytes = X::kPageHeadB, kKTileBytes = X::kKTileB, kVTileBytes = X::kKTileB, kVBase = X::kVBaseB;
+                kPageHeadBytes = X::kPageHeadB, kKTileBytes = X::kKTileB, kVTileBytes = X::kKTileB;
+  // Tiles in LDS.  Two computing waves per SIMD keep the matrix pipe busy for longer than a copy takes: three buffers, a
+  // tile's copy has one tile's time to land.  One is done with a tile sooner than its copy (launches of few rows stream K
+  // and V at the memory's rate): four, two to three tiles in flight (16 tokens at 128k, 64/8 heads: 103.5 us a call with
+  // three buffers, 97 with four or five; a short call, 1000 + 16 tokens: 16.9, 17.0, 17.4).
+  constexpr int kBufs = ROWS == kFullRows ? kBuffers : kDeepBuffers;
+  constexpr int kAhead = kBufs - 1;
+  constexpr int kVBase = kBufs * kKTileBytes;            // the K tiles of the buffers, then the V tiles
   // tile bases are multiples of 8 KiB from a 256-byte aligned start: the XOR constants of the swizzle (< 256)
   // never reach a tile base
-  __shared__ __attribute__((aligned(256))) char smem[kBuffers * (kKTileBytes + kVTileBytes)];
-  constexpr int kTileRows = WAVES * 32;
+  __shared__ __attribute__((aligned(256))) char smem[kBufs * (kKTileBytes + kVTileBytes)];
+  constexpr int kTileRows = kTileRowsOf<ROWS>;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -183,8 +189,10 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   const int n_rows = work.chunk * G;
   const int last_page = (L - 1) / kPageTokens;
 
-  // a wave of the second half (these copy no tiles) whose 32 rows all lie past the end of the chunk ends here
-  if (wave >= WAVES / 2 && work.row0 + wave * 32 >= n_rows) return;
+  // a wave that copies no tiles and whose 32 rows all lie past the end of the chunk ends here
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const bool fetcher = wave_copies<ROWS>(wave_u);
+  if (!fetcher && work.row0 + wave_u * 32 >= n_rows) return;
 
   // ---- this lane's two query rows: their Q fragments stay in registers for the whole KV loop
   frag qf[kSteps][2];
@@ -224,7 +232,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
     // no key of the slice is visible to any row of the tile
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
-      if (live[rt]) {
+      if (live[rt] && wave_computes<ROWS>(wave_u)) {
         char* orow = reinterpret_cast<char*>(a.o_parts) + prow[rt] * (kD * 4);
 #pragma unroll
         for (int dt = 0; dt < kDTiles; ++dt)
@@ -236,24 +244,22 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
 
   // ---- global -> LDS, no registers in between (as in attn_prefill.hip): one wave instruction writes
   //      1 KiB of LDS, 4 (D 64: 8) tile rows of 16 (8) granules inside one page; lane i fetches, for granule
-  //      position i % kGran of row i / kGran, the logical granule (i % kGran) ^ swz(row).  The first wave of
-  //      each SIMD copies, wave w page w of the tile: one page id, one page address and two LDS bases per tile,
+  //      position i % kGran of row i / kGran, the logical granule (i % kGran) ^ swz(row).  One wave of each
+  //      SIMD copies (which: see Rows), each one page of the tile: one page id, one page address and two LDS bases per tile,
   //      the chunks of the page are immediate offsets (they advance the global and the LDS address alike).
-  constexpr int kFetchWaves = WAVES / 2;
   static_assert(kFetchWaves == kTileKeys / kPageTokens, "one page of the tile per copying wave");
   const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadBytes;
   const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)work.kv_head * kPageHeadBytes;
   const int64_t page_stride = (int64_t)a.Hkv * kPageHeadBytes;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int fetch_wave = wave_u & (kFetchWaves - 1);
   const uint32_t smem_base = (uint32_t)(uintptr_t)(MC_LDS char*)smem;
-  const bool fetcher = wave_u < kFetchWaves;
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
   const_i32_ptr btc = (const_i32_ptr)(a.block_tables + (int64_t)work.req * a.max_pages);
   const int64_t first_page_off = (int64_t)btc[0] * page_stride;   // page of key 0: always valid
   int pid = 0, pid_next = 0;
   auto load_ids = [&](int tile) __attribute__((always_inline)) {
     if (!fetcher) return;
-    const int lp = tile * (kTileKeys / kPageTokens) + wave_u;
+    const int lp = tile * (kTileKeys / kPageTokens) + fetch_wave;
     pid_next = btc[lp < last_page ? lp : last_page];         // never index the table past the request's pages
   };
   auto take_ids = [&]() __attribute__((always_inline)) { pid = pid_next; };
@@ -266,17 +272,22 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   }
   auto fetch = [&](int tile, int buf) __attribute__((always_inline)) {
     if (!fetcher) return;
-    const uint32_t dst = smem_base + buf * kKTileBytes + wave_u * kPageHeadBytes;
+    const uint32_t dst = smem_base + buf * kKTileBytes + fetch_wave * kPageHeadBytes;
     const int64_t page_off = (int64_t)pid * page_stride;
     if ((tile + 1) * kTileKeys <= L) {
-      dma16_page<X::kPageChunks>(kbase + page_off, k_src, dst);
-      dma16_page<X::kPageChunks>(vbase + page_off, v_src, dst + kVBase);
+      if (ROWS == kFewRows && work.once) {
+        dma16_page<true>(kbase + page_off, k_src, dst);
+        dma16_page<true>(vbase + page_off, v_src, dst + kVBase);
+      } else {
+        dma16_page<false>(kbase + page_off, k_src, dst);
+        dma16_page<false>(vbase + page_off, v_src, dst + kVBase);
+      }
     } else {
       // slots at or past the request's length may hold anything: those lanes copy row 0 of the request's
       // first page instead; the causal mask hides the key
 #pragma unroll
       for (int i = 0; i < X::kPageChunks; ++i) {
-        const int row = wave_u * kPageTokens + i * X::kChunkRows + lane / X::kGran;
+        const int row = fetch_wave * kPageTokens + i * X::kChunkRows + lane / X::kGran;
         const bool in_seq = tile * kTileKeys + row < L;
         const char* ks = kbase + (in_seq ? page_off + i * 1024 + k_src[i] : first_page_off + (k_src[i] & (kRowBytes - 1)));
         const char* vs = vbase + (in_seq ? page_off + i * 1024 + v_src[i] : first_page_off + (v_src[i] & (kRowBytes - 1)));
@@ -285,7 +296,12 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
       }
     }
   };
-  auto copies_landed = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0x0F70); };
+  // wait until all but the last `tiles` tiles this wave has enqueued have landed (vmcnt only)
+  auto copies_landed = [&](auto tiles) __attribute__((always_inline)) {
+    constexpr int n = decltype(tiles)::value * 2 * X::kPageChunks;
+    static_assert(n < 64, "vmcnt");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | (n >> 4 << 14));
+  };
 
   // ---- running softmax state and output accumulators: o[dt][rt] register r = column 16 dt + 4 g + r of row 16 rt + j
   acc4 o[kDTiles][2];
@@ -489,29 +505,61 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
     pv_block(buf, kb, pbl);
   };
 
-  load_ids(t_lo);
-  take_ids();
-  fetch(t_lo, 0);
-  load_ids(t_lo + 1);
-  take_ids();
-  if (n_tiles > t_lo + 1) {
-    fetch(t_lo + 1, 1);
-    load_ids(t_lo + 2);
+  // The copies of the first tiles; everything enqueued so far (also the Q fragments) has landed, those of the rest of the
+  // buffers are on their way.
+  auto first_copies = [&]() __attribute__((always_inline)) {
+    load_ids(t_lo);
     take_ids();
-  }
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
+    fetch(t_lo, 0);
+    load_ids(t_lo + 1);
+    take_ids();
+    if (n_tiles > t_lo + 1) {
+      fetch(t_lo + 1, 1);
+      load_ids(t_lo + 2);
+      take_ids();
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+#pragma unroll
+    for (int i = 2; i < kAhead; ++i)
+      if (n_tiles > t_lo + i) {
+        fetch(t_lo + i, i);
+        load_ids(t_lo + i + 1);
+        take_ids();
+      }
+  };
+  // Tile `tile` begins: the copy of the next one has landed everywhere (the scores run a block ahead), the buffer of the
+  // one before is free and takes tile + kAhead, whose ids were loaded a tile ago.
   int buf = 0;
-  auto tile_sync = [&](int tile) __attribute__((always_inline)) {
-    const bool ahead = tile + 2 < n_tiles;
-    if (ahead) load_ids(tile + 3);
-    copies_landed();
+  auto copy_sync = [&](int tile) __attribute__((always_inline)) {
+    const bool ahead = tile + kAhead < n_tiles;
+    if (ahead) load_ids(tile + kAhead + 1);
+    // enqueued so far: tiles up to tile + kAhead - 1, as far as there are any
+    if (kAhead > 2 && tile + kAhead - 1 < n_tiles) copies_landed(std::integral_constant<int, kAhead - 2>{});
+    else copies_landed(std::integral_constant<int, 0>{});
     __syncthreads();
     if (ahead) {
-      fetch(tile + 2, buf == 0 ? 2 : buf - 1);   // (tile + 2) % 3, ids loaded one tile ago
+      fetch(tile + kAhead, buf == 0 ? kBufs - 1 : buf - 1);
       take_ids();
     }
   };
+  auto tile_sync = [&](int tile) __attribute__((always_inline)) {
+    if constexpr (ROWS == kFullRows) copy_sync(tile);
+    else __syncthreads();
+  };
+  if constexpr (ROWS == kFewRows) {
+    if (fetcher) {
+      first_copies();
+      for (int tile = t_lo; tile < n_tiles; ++tile) {
+        copy_sync(tile);
+        buf = buf == kBufs - 1 ? 0 : buf + 1;
+      }
+      return;
+    }
+    __syncthreads();
+  } else {
+    first_copies();
+  }
   int tile = t_lo;
   const int n_plain = n_free < n_tiles - 1 ? n_free : n_tiles - 1;
   qk_block(0, 0, s_next);
@@ -523,9 +571,13 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
 #pragma unroll
     for (int k = 0; k < 4; ++k) pb_ahead[k] = round_pair(s_next, 2 * k);
     // the two waves of a SIMD run half a step apart (see attn_prefill.hip)
-    const bool late_barrier = wave_u >= WAVES / 2;
+    // (few rows: the waves that would be late only copy.  The compiler is not told: with the barrier unconditional the
+    // phases become one basic block, in which it keeps 28 registers too many alive and spills 52.)
+    int w = wave_u;
+    if constexpr (ROWS == kFewRows) asm volatile("" : "+s"(w));
+    const bool late_barrier = w >= kFetchWaves;
     auto pipelined_tile = [&](auto buf_tag) __attribute__((always_inline)) {
-      constexpr int b = decltype(buf_tag)::value, bn = (b + 1) % kBuffers;
+      constexpr int b = decltype(buf_tag)::value, bn = (b + 1) % kBufs;
       buf = b;
       if (!late_barrier) tile_sync(tile);
       phase_a(b, 0);
@@ -547,11 +599,15 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
       pipelined_tile(std::integral_constant<int, 1>{});
       if (tile >= n_plain) break;
       pipelined_tile(std::integral_constant<int, 2>{});
+      if constexpr (kBufs == 4) {
+        if (tile >= n_plain) break;
+        pipelined_tile(std::integral_constant<int, 3>{});
+      }
     }
   }
   bool have_scores = n_plain <= t_lo;
   for (; tile < n_tiles; ++tile) {
-    const int buf_next = buf == 2 ? 0 : buf + 1;
+    const int buf_next = buf == kBufs - 1 ? 0 : buf + 1;
     tile_sync(tile);
     plain_block(buf, 0, tile * kTileKeys, s_next, have_scores);
     have_scores = false;
@@ -591,24 +647,31 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   }
 }
 
-template <int D, int WAVES, bool SPLIT>
-__global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_kernel(const AttnArgs a) {
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(kWaves * 64) void attn_prefill_bf16_kernel(const AttnArgs a) {
   const AttnItem item = a.items[blockIdx.x];
-  attn_bf16_body<D, WAVES, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
+  attn_bf16_body<D, kFullRows, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
 }
 
-template <int D, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void attn_prefill_bf16_classes_kernel(const AttnArgs a, const AttnClasses t) {
-  attn_bf16_body<D, WAVES, kClasses>(a, work_of(t, blockIdx.x, a.Hkv, a.G));
+template <int D, Rows ROWS>
+__global__ __launch_bounds__(kWaves * 64) void attn_prefill_bf16_classes_kernel(const AttnArgs a, const AttnClasses t) {
+  attn_bf16_body<D, ROWS, kClasses>(a, work_of<kTileRowsOf<ROWS>>(t, blockIdx.x, a.Hkv, a.G));
 }
 
 }  // namespace
 
 hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream) {
   (void)hipGetLastError();
-  if (args.head_dim == 128) attn_prefill_bf16_classes_kernel<128, kWaves><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
-  else if (args.head_dim == 64) attn_prefill_bf16_classes_kernel<64, kWaves><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
-  else return hipErrorInvalidValue;
+  const bool few = t.rows == kAttnFewRows;
+  if (args.head_dim == 128) {
+    if (few) attn_prefill_bf16_classes_kernel<128, kFewRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+    else attn_prefill_bf16_classes_kernel<128, kFullRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+  } else if (args.head_dim == 64) {
+    if (few) attn_prefill_bf16_classes_kernel<64, kFewRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+    else attn_prefill_bf16_classes_kernel<64, kFullRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+  } else {
+    return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -616,11 +679,11 @@ hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t stream) {
   (void)hipGetLastError();   // drop any stale error of earlier, unrelated runtime calls
   const bool split = args.kv_splits > 0;
   if (args.head_dim == 128) {
-    if (split) attn_prefill_bf16_kernel<128, kWaves, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-    else attn_prefill_bf16_kernel<128, kWaves, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+    if (split) attn_prefill_bf16_kernel<128, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+    else attn_prefill_bf16_kernel<128, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
   } else if (args.head_dim == 64) {
-    if (split) attn_prefill_bf16_kernel<64, kWaves, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-    else attn_prefill_bf16_kernel<64, kWaves, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+    if (split) attn_prefill_bf16_kernel<64, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+    else attn_prefill_bf16_kernel<64, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
   } else {
     return hipErrorInvalidValue;
   }

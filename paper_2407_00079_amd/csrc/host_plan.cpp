@@ -215,9 +215,11 @@ namespace {
 struct TileCost {
   double fixed, tile;
 };
-TileCost tile_cost_of(const mc_attn_params* p) {
-  if (p->dtype == MC_DTYPE_F32) return {4.0, 7.0};
-  return p->head_dim == 128 ? TileCost{4.0, 1.65} : TileCost{4.0, 0.95};
+TileCost tile_cost_of(const mc_attn_params* p, int64_t tile_rows) {
+  const bool few = tile_rows == kAttnFewRows;
+  if (p->dtype == MC_DTYPE_F32) return {4.0, few ? 3.6 : 7.0};
+  if (p->head_dim == 128) return {4.0, few ? 1.2 : 1.65};
+  return {4.0, few ? 0.7 : 0.95};
 }
 // the merge launch, and bytes of partial results written and read per microsecond
 constexpr double kMergeFixed = 4.0, kPartBytesPerUs = 3.0e6;
@@ -279,21 +281,21 @@ class Units {
   double end_ = 0.0;
 };
 
-int64_t key_tiles(int64_t prefix, int64_t chunk, int64_t G, int64_t row_tile) {
-  const int64_t last = std::min<int64_t>(chunk - 1, (row_tile * kAttnTileRows + kAttnTileRows - 1) / G);
+int64_t key_tiles(int64_t prefix, int64_t chunk, int64_t G, int64_t row_tile, int64_t tile_rows) {
+  const int64_t last = std::min<int64_t>(chunk - 1, (row_tile * tile_rows + tile_rows - 1) / G);
   return (prefix + last + 1 + kAttnTileKeys - 1) / kAttnTileKeys;
 }
 
-Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk, int64_t lo, int64_t hi) {
+Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk, int64_t lo, int64_t hi, int64_t tile_rows) {
   const int64_t G = p->num_q_heads / p->num_kv_heads;
   Run run;
   run.active = active;
   run.tile_lo = lo;
   run.tile_hi = hi;
   run.items = (hi - lo + 1) * p->num_kv_heads;
-  run.rows = (std::min<int64_t>(chunk * G, (hi + 1) * kAttnTileRows) - lo * kAttnTileRows) * p->num_kv_heads;
-  run.longest = key_tiles(prefix, chunk, G, hi);
-  run.mean = 0.5 * (double)(run.longest + key_tiles(prefix, chunk, G, lo));
+  run.rows = (std::min<int64_t>(chunk * G, (hi + 1) * tile_rows) - lo * tile_rows) * p->num_kv_heads;
+  run.longest = key_tiles(prefix, chunk, G, hi, tile_rows);
+  run.mean = 0.5 * (double)(run.longest + key_tiles(prefix, chunk, G, lo, tile_rows));
   return run;
 }
 
@@ -303,7 +305,9 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 // fill whole rounds - and every row tile behind them is cut into pieces of at most `longest / k` key tiles.  Both are
 // chosen together, by the estimated end of the last workgroup plus what the merge costs.  What that gives: a small chunk
 // behind a long prefix is cut until it fills the chip; a launch just above a whole number of rounds is cut only where it
-// would run a last, mostly empty round; few short row tiles are cut into pieces of one or two key tiles.
+// would run a last, mostly empty round; few short row tiles are cut into pieces of one or two key tiles.  Row tiles of 256
+// and of 128 rows (see Rows in attn_device.h) are both tried: the larger ones share each key tile among twice the rows and
+// win wherever there are enough of them.
 // Measured, one call with its append (uniform slices of all rows or none before / this cut now): P 6144, C 811 and 328,
 // 64/8 heads (296 row tiles: 6 slices / 256 whole tiles and 40 in 6 pieces) 342 / 220 us; P 256, C 128, fp32, 4/1 heads
 // (2 row tiles: whole / 6 pieces) 73 / 33 us; P 131056, C 16, 64/8 heads (32 slices / 32 pieces) 125 / 118 us.
@@ -314,16 +318,20 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
     int32_t req, q_off, prefix, chunk;
   } act[kMaxAttnClasses];
   int n = 0;
-  int64_t q_off = 0, items = 0;
+  int64_t q_off = 0;
   for (int32_t r = 0; r < batch; ++r) {
     if (new_lens[r] > 0) {
       if (n == kMaxAttnClasses - 1) return false;      // one request may take two classes
       act[n++] = {r, (int32_t)q_off, prefix_lens[r], new_lens[r]};
-      items += Hkv * ((new_lens[r] * G + kAttnTileRows - 1) / kAttnTileRows);
     }
     q_off += new_lens[r];
   }
-  if (items > INT32_MAX) return false;
+  auto items_of = [&](int64_t tile_rows) {
+    int64_t items = 0;
+    for (int i = 0; i < n; ++i) items += Hkv * ((act[i].chunk * G + tile_rows - 1) / tile_rows);
+    return items;
+  };
+  if (items_of(kAttnTileRows) > INT32_MAX) return false;
   std::sort(act, act + n, [](const Active& a, const Active& b) {
     if (a.prefix != b.prefix) return a.prefix > b.prefix;
     return a.chunk != b.chunk ? a.chunk > b.chunk : a.req < b.req;
@@ -332,21 +340,21 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   // runs of the launch order when the first `whole` workgroups are kept apart; returns how many runs those are
   Run runs[kMaxAttnClasses];
   int n_runs = 0;
-  auto lay_out = [&](int64_t whole) {
+  auto lay_out = [&](int64_t whole, int64_t tile_rows) {
     n_runs = 0;
     int uncut = 0;
     for (int i = 0; i < n; ++i) {
       const int64_t P = act[i].prefix, C = act[i].chunk;
-      const int64_t tiles = (C * G + kAttnTileRows - 1) / kAttnTileRows;
+      const int64_t tiles = (C * G + tile_rows - 1) / tile_rows;
       const int64_t keep = std::min<int64_t>(tiles, whole / Hkv);
       if (keep > 0) {
-        runs[n_runs] = make_run(p, i, P, C, tiles - keep, tiles - 1);
+        runs[n_runs] = make_run(p, i, P, C, tiles - keep, tiles - 1, tile_rows);
         ++n_runs;
         uncut = n_runs;
         whole -= keep * Hkv;
       }
       if (keep < tiles) {
-        runs[n_runs] = make_run(p, i, P, C, 0, tiles - keep - 1);
+        runs[n_runs] = make_run(p, i, P, C, 0, tiles - keep - 1, tile_rows);
         ++n_runs;
         whole = 0;
       }
@@ -359,14 +367,15 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
     return k < MC_MAX_KV_SPLITS ? k : (int64_t)MC_MAX_KV_SPLITS;
   };
 
-  int64_t best_whole = items;
-  double best_len = 0.0;
-  if (max_part_rows > 0 && items < 4 * kComputeUnits) {
+  int64_t best_rows = kAttnTileRows, best_whole = items_of(kAttnTileRows);
+  double best_len = 0.0, best = 0.0;
+  for (const int64_t tile_rows : {(int64_t)kAttnTileRows, (int64_t)kAttnFewRows}) {
     // From four full rounds on the launch order (short row tiles last) balances the tail by itself.
-    const TileCost cost = tile_cost_of(p);
-    double best = 0.0;
+    const int64_t items = items_of(tile_rows);
+    if (items >= 4 * kComputeUnits) continue;
+    const TileCost cost = tile_cost_of(p, tile_rows);
     for (int64_t rounds = 0; rounds * kComputeUnits < items; ++rounds) {
-      const int uncut = lay_out(rounds * kComputeUnits);
+      const int uncut = lay_out(rounds * kComputeUnits, tile_rows);
       int64_t longest = 0;
       for (int i = uncut; i < n_runs; ++i) longest = std::max(longest, runs[i].longest);
       for (int64_t k = 1; k <= longest && k <= MC_MAX_KV_SPLITS; k += k < 8 ? 1 : k < 32 ? 2 : k < 64 ? 4 : 16) {
@@ -374,7 +383,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         // more than four rounds of pieces: the tail is short by then, a finer cut only adds partial results
         int64_t n_pieces = 0;
         for (int i = uncut; i < n_runs; ++i) n_pieces += runs[i].items * pieces_of(runs[i], len);
-        if (k > 1 && n_pieces > 4 * kComputeUnits) break;
+        if (k > 1 && (n_pieces > 4 * kComputeUnits || max_part_rows == 0)) break;
         Units units;
         int64_t part_rows = 0;
         for (int i = 0; i < uncut; ++i) units.place(runs[i].items, cost.fixed + cost.tile * runs[i].mean);
@@ -388,15 +397,27 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         if (part_rows > 0) t += kMergeFixed + 2.0 * (double)part_rows * (double)(p->head_dim + 1) * 4.0 / kPartBytesPerUs;
         if (best == 0.0 || t < best) {
           best = t;
+          best_rows = tile_rows;
           best_whole = rounds * kComputeUnits;
           best_len = len;
         }
       }
     }
   }
-  const int uncut = lay_out(best_whole);
+  const int uncut = lay_out(best_whole, best_rows);
   AttnClasses& t = plan->classes;
   t.n = n_runs;
+  t.rows = (int32_t)best_rows;
+  // One row tile per head reads every K and V row once.  If they outgrow the last-level cache, the next layer finds none of
+  // them there anyway, and a hint that they need not be kept helps: 16 tokens at 128k (64/8 heads, 537 MB) 106.5 us a
+  // call without it, 97 with it.  What would stay in the cache is better left there (8192 + 16 tokens, 34 MB, the same call
+  // repeated: 21.5 us without the hint, 23.6 with it).
+  int64_t kv_bytes = 0, most_rows = 0;
+  for (int i = 0; i < n; ++i) {
+    kv_bytes += 2 * ((int64_t)act[i].prefix + act[i].chunk) * Hkv * p->head_dim * (p->dtype == MC_DTYPE_BF16 ? 2 : 4);
+    most_rows = std::max(most_rows, act[i].chunk * G);
+  }
+  t.once = most_rows <= best_rows && kv_bytes > ((int64_t)256 << 20) ? 1 : 0;
   int64_t wg = 0;
   plan->part_rows = 0;
   plan->most_pieces = 1;

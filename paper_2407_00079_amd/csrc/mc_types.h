@@ -41,6 +41,8 @@ struct AttnClass {
 constexpr int kMaxAttnClasses = 64;          // one lane of a wave each when a workgroup looks for its class
 struct AttnClasses {
   int32_t n;
+  int32_t rows;                              // stacked rows of a row tile: kAttnTileRows or kAttnFewRows
+  int32_t once;                              // K and V are read once and outgrow the caches
   int32_t first[kMaxAttnClasses];            // first workgroup of each class (of the attention launch or of the merge)
   AttnClass c[kMaxAttnClasses];
 };
@@ -61,6 +63,8 @@ struct OffsetTables {
 
 // rows of stacked queries one attention workgroup covers (8 waves of 32 rows, both dtypes)
 constexpr int kAttnTileRows = 256;
+// ... and of the form for launches whose row tiles are few or short: 4 waves compute (one per SIMD), 4 copy tiles
+constexpr int kAttnFewRows = 128;
 // keys of one LDS tile; key slices of the split form are whole tiles
 constexpr int kAttnTileKeys = 64;
 // 16-byte vectors of a page one copy workgroup moves (512 threads, one vector each)

@@ -1,6 +1,6 @@
 // Prints the class plan of each batch read from stdin, one line per plan (tests/test_class_plan.py checks them).
 // input:  Hq Hkv D dtype max_part_rows batch P... C...
-// output: n n_wgs most_pieces part_rows [first req q_off prefix chunk tile_lo tile_hi pieces part_base]...
+// output: n n_wgs most_pieces part_rows tile_rows [first req q_off prefix chunk tile_lo tile_hi pieces part_base]...
 #include <cstdio>
 #include <vector>
 
@@ -21,7 +21,7 @@ int main() {
       std::printf("none\n");
       continue;
     }
-    std::printf("%d %d %d %lld", plan.classes.n, plan.n_wgs, plan.most_pieces, (long long)plan.part_rows);
+    std::printf("%d %d %d %lld %d", plan.classes.n, plan.n_wgs, plan.most_pieces, (long long)plan.part_rows, plan.classes.rows);
     for (int i = 0; i < plan.classes.n; ++i) {
       const mc::AttnClass& k = plan.classes.c[i];
       std::printf(" %d %d %d %d %d %d %d %d %d", plan.classes.first[i], k.req, k.q_off, k.prefix, k.chunk, k.tile_lo, k.tile_hi,

@@ -7,7 +7,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2407_00079_amd", "csrc")
-ROWS, KEYS = 256, 64
+ROWS, FEW_ROWS, KEYS = 256, 128, 64
 
 
 @pytest.fixture(scope="module")
@@ -26,8 +26,8 @@ def plan(driver, Hq, Hkv, D, dtype, room, prefix, new):
         return None
     v = [int(x) for x in out]
     names = ("first", "req", "q_off", "prefix", "chunk", "tile_lo", "tile_hi", "pieces", "part_base")
-    return dict(n_wgs=v[1], most_pieces=v[2], part_rows=v[3],
-                classes=[dict(zip(names, v[4 + 9 * i:13 + 9 * i])) for i in range(v[0])])
+    return dict(n_wgs=v[1], most_pieces=v[2], part_rows=v[3], rows=v[4],
+                classes=[dict(zip(names, v[5 + 9 * i:14 + 9 * i])) for i in range(v[0])])
 
 
 BATCHES = [
@@ -51,6 +51,8 @@ def test_classes_cover_every_tile_once(driver, Hq, Hkv, D, dtype, prefix, new, r
     room = room_parts * total * Hq
     p = plan(driver, Hq, Hkv, D, dtype, room, prefix, new)
     assert p["part_rows"] <= room and (p["most_pieces"] > 1) == (p["part_rows"] > 0)
+    ROWS = p["rows"]
+    assert ROWS in (256, FEW_ROWS)
     wg, parts, seen = 0, 0, {}
     for c in p["classes"]:
         r = c["req"]

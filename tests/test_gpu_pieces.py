@@ -22,6 +22,10 @@ CASES = [
     (W.BF16, 12, 3, 128, [2000, 3], [40, 86]),                # groups of 4 heads, three KV heads
     (W.BF16, 16, 2, 64, [1500, 31], [17, 129]),               # 128-byte rows
     (W.BF16, 64, 8, 128, [127, 128], [1000, 60]),             # one full round of row tiles and a rest that is cut
+    (W.BF16, 8, 1, 128, [40000], [9]),                        # 72 rows: a wave without rows; pieces of several key tiles
+    (W.BF16, 16, 1, 128, [9000, 63, 320], [8, 1, 5]),         # 128-row tiles exactly full and nearly empty
+    (W.BF16, 64, 8, 64, [9999], [17]),                        # 136 rows: two row tiles, the second of 8 rows
+    (W.F32, 8, 2, 64, [3000], [33]),
 ]
 
 
@@ -43,3 +47,18 @@ def test_pieces_match_oracle(oracle, dtype, Hq, Hkv, D, prefix, new):
     assert np.abs(lse - ref_lse).max() <= TOL[dtype]["lse_abs"]
     first = (guard + need + 3) // 4 * 4
     assert torch.isnan(buf[:guard].view(torch.float32)).all() and torch.isnan(buf[first:first + guard].view(torch.float32)).all()
+
+
+@pytest.mark.parametrize("dtype,D,tiles", [(W.BF16, 128, n) for n in (1, 2, 3, 4, 5, 6, 7, 11)] + [(W.BF16, 64, 6), (W.F32, 64, 5)])
+def test_few_rows_without_room(oracle, dtype, D, tiles):
+    """No room for partial results: one workgroup per KV head walks all key tiles, as many as there are LDS buffers and
+    around that; rows for one, two and four of its waves."""
+    for new in (1, 7, 16):
+        print(f"few rows case {dtype} D={D} tiles={tiles} new={new}", flush=True)
+        case = W.make_attn_case(72 + tiles, dtype, 16, 2, D, 16, [64 * tiles - new - 3], [new], 4 * tiles + 3)
+        dc = DeviceCase(case)
+        dc.run()
+        out, lse = dc.result()
+        ref_out, ref_lse, _ = oracle.case_full(case)
+        check_close(out, ref_out, dtype, "few rows")
+        assert np.abs(lse - ref_lse).max() <= TOL[dtype]["lse_abs"]
