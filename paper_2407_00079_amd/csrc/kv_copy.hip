@@ -64,40 +64,41 @@ __global__ __launch_bounds__(kThreads) void kv_copy_kernel(const u32x4* __restri
 }
 
 // order[r] = the list position whose pool page is the r-th smallest (ties: lower position first),
-// i.e. the rank of the 64-bit key (page id, list position).  Rank by counting, the keys staged
-// through LDS in chunks and read back two per LDS instruction, one compare per key:
-// O(n^2 / threads), meant to be run once per request - the list is the same for every layer.
-// Slots past the end of the list hold the largest key and count nothing.
+// i.e. the rank of the 64-bit key (page id, list position).  Rank by counting, the ids staged
+// through LDS in chunks: O(n^2) compares, meant to be run once per request - the list is the same
+// for every layer.  LANES threads share a position, each counting every LANES-th group of four
+// keys, so that short lists fill the chip too (2048 ids: 8 workgroups and 26 us with one thread a
+// position, 128 and about 7 us with 16).  Slots past the end of the list hold the largest id at
+// positions behind all others and count nothing.
+constexpr int kOrderChunk = 1024;
+template <int LANES>
 __global__ __launch_bounds__(256) void kv_page_order_kernel(const int32_t* __restrict__ page_ids, int64_t n,
                                                             int32_t* __restrict__ order) {
-  typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-  __shared__ u64x2 chunk[512];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  __shared__ u32x4 chunk[kOrderChunk / 4];
+  const int part = threadIdx.x % LANES;
+  const int64_t i = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
   // ids are not negative and positions stay below 2^20: (id << 32) | position orders as the pair does
   const uint64_t mine = i < n ? ((uint64_t)(uint32_t)page_ids[i] << 32) | (uint64_t)i : 0;
-  int64_t rank = 0;
-  for (int64_t base = 0; base < n; base += 1024) {
+  int rank = 0;
+  for (int64_t base = 0; base < n; base += kOrderChunk) {
     __syncthreads();
+    const int64_t at = base + threadIdx.x * 4;
+    u32x4 ids;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      u64x2 v;
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const int64_t at = base + (threadIdx.x + h * 256) * 2 + e;
-        v[e] = at < n ? ((uint64_t)(uint32_t)page_ids[at] << 32) | (uint64_t)at : ~0ull;
-      }
-      chunk[threadIdx.x + h * 256] = v;
-    }
+    for (int e = 0; e < 4; ++e) ids[e] = at + e < n ? (uint32_t)page_ids[at + e] : ~0u;
+    chunk[threadIdx.x] = ids;
     __syncthreads();
-    int r = 0;
 #pragma unroll 8
-    for (int t = 0; t < 512; ++t) {
-      const u64x2 o = chunk[t];
-      r += (o[0] < mine) + (o[1] < mine);
+    for (int t = part; t < kOrderChunk / 4; t += LANES) {
+      const u32x4 o = chunk[t];
+      const uint32_t pos = (uint32_t)base + 4 * t;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rank += (((uint64_t)o[e] << 32) | (pos + e)) < mine;
     }
-    rank += r;
   }
-  if (i < n) order[rank] = (int32_t)i;
+#pragma unroll
+  for (int d = LANES / 2; d >= 1; d >>= 1) rank += __shfl_xor(rank, d, 64);
+  if (i < n && part == 0) order[rank] = (int32_t)i;
 }
 
 // Range check of a page id list (debugging aid): a one-thread kernel resets the report, then every
@@ -183,7 +184,11 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const u32x4* __restrict_
 
 hipError_t launch_kv_page_order(const int32_t* page_ids, int64_t n, int32_t* order, hipStream_t stream) {
   (void)hipGetLastError();
-  kv_page_order_kernel<<<(unsigned)((n + 255) / 256), 256, 0, stream>>>(page_ids, n, order);
+  // as many threads a position as it takes to fill 256 compute units; every workgroup stages the whole list, so not more
+  auto blocks = [&](int per) { return (unsigned)((n + per - 1) / per); };
+  if (n <= 8192) kv_page_order_kernel<16><<<blocks(16), 256, 0, stream>>>(page_ids, n, order);
+  else if (n <= 32768) kv_page_order_kernel<4><<<blocks(64), 256, 0, stream>>>(page_ids, n, order);
+  else kv_page_order_kernel<1><<<blocks(256), 256, 0, stream>>>(page_ids, n, order);
   return hipGetLastError();
 }
 
