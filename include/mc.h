@@ -247,7 +247,8 @@ typedef struct {
   int32_t need_pages;         /* most pages any request with new tokens spans */
   int64_t total_new_tokens;
   int64_t reqs_offset;        /* byte offset of the request table in the workspace */
-  int32_t num_q_heads, num_kv_heads, dtype, reserved;   /* of the params it was prepared with */
+  int32_t num_q_heads, num_kv_heads, dtype,             /* of the params it was prepared with */
+      reserved;                                         /* how the list is launched */
 } mc_attn_plan;
 
 mc_status mc_prefill_attn_prepare(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens,

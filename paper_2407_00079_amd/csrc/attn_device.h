@@ -19,21 +19,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;              // waves of a workgroup: two per SIMD, 32 stacked rows each
 static_assert(kWaves * 32 == kAttnTileRows, "the host cuts the work list into tiles of kAttnTileRows rows");
-// Which waves do what.  Full tiles (256 rows): all eight compute, the first of each SIMD copies tiles besides (it wins the
-// issue arbitration and would idle at the tile barrier).  Few rows (128): the first of each SIMD computes, the second only
-// copies; a copy instruction holds its wave for about 130 cycles, which a lone computing wave has no one to hide behind
-// (16 tokens at 128k, 64/8 heads: 115 us a call with four waves that do both, 97 with four and four).
-// Full tiles / few rows, one call, bf16 head_dim 128, 64/8 heads unless said: P 131056, C 16 111 / 96 us; P 131056, C 1
-// 101 / 86; P 1000, C 100 28 / 22; P 256, C 128 17 / 13; P 30000, C 300 245 / 275; head_dim 64, P 131056, C 16 69 / 60;
-// fp32, 4/1 heads, P 256, C 128 24 / 17, P 6955, C 200 80 / 46.
-enum Rows { kFullRows = 0, kFewRows = 1 };
-constexpr int kFetchWaves = 4;
-template <Rows R>
-constexpr int kTileRowsOf = R == kFewRows ? kAttnFewRows : kAttnTileRows;
-template <Rows R>
-__device__ __forceinline__ bool wave_copies(int wave) { return R == kFewRows ? wave >= kFetchWaves : wave < kFetchWaves; }
-template <Rows R>
-__device__ __forceinline__ bool wave_computes(int wave) { return R == kFullRows || wave < kFetchWaves; }
 constexpr int kTileKeys = kAttnTileKeys;   // keys per LDS tile = 4 pages of 16
 constexpr int kPageTokens = 16;
 constexpr int kRowBytes = 256;         // one K or V row: 128 bf16 or 64 f32
@@ -51,6 +36,22 @@ constexpr float kRescaleSlack = 8.0f;  // log2 units the running max may lag beh
 // exp2(-inf) = 0 instead of exp2(-inf + inf) = NaN; a row with a finite score has a finite reference
 constexpr float kNoKeyYet = -1e30f;
 
+// Which waves do what.  Full tiles (256 rows): all eight compute, the first of each SIMD copies tiles besides (it wins the
+// issue arbitration and would idle at the tile barrier).  Few rows (128): the first of each SIMD computes, the second only
+// copies; a copy instruction holds its wave for about 130 cycles, which a lone computing wave has no one to hide behind
+// (16 tokens at 128k, 64/8 heads: 115 us a call with four waves that do both, 97 with four and four).
+// Full tiles / few rows, one call, bf16 head_dim 128, 64/8 heads unless said: P 131056, C 16 111 / 96 us; P 131056, C 1
+// 101 / 86; P 1000, C 100 28 / 22; P 256, C 128 17 / 13; P 30000, C 300 245 / 275; head_dim 64, P 131056, C 16 69 / 60;
+// fp32, 4/1 heads, P 256, C 128 24 / 17, P 6955, C 200 80 / 46.
+enum Rows { kFullRows = 0, kFewRows = 1 };
+constexpr int kFetchWaves = 4;
+template <Rows R>
+constexpr int kTileRowsOf = R == kFewRows ? kAttnFewRows : kAttnTileRows;
+template <Rows R>
+__device__ __forceinline__ bool wave_copies(int wave) { return R == kFewRows ? wave >= kFetchWaves : wave < kFetchWaves; }
+template <Rows R>
+__device__ __forceinline__ bool wave_computes(int wave) { return R == kFullRows || wave < kFetchWaves; }
+
 // How a launch describes its work: whole rows or uniform key slices from a list in device memory, or classes from the
 // kernel argument.
 enum Form { kWhole = 0, kSlices = 1, kClasses = 2 };
@@ -65,8 +66,14 @@ struct Work {
   bool once;                             // every K and V row of the launch is read once and they outgrow the caches
 };
 
-__device__ __forceinline__ Work work_of(const AttnItem& item, const AttnReq& rq, int64_t rows_total) {
-  return Work{item.req, item.kv_head, item.row0, rq.q_off, rq.prefix, rq.chunk, item.slice, 1, (int64_t)item.slice * rows_total, false};
+// list launches; workgroups n_items .. take the second halves of the items' row tiles (few rows only)
+template <Rows R, typename Args>
+__device__ __forceinline__ Work work_of(const Args& a, int wg) {
+  const bool second = R == kFewRows && wg >= a.n_items;
+  const AttnItem item = a.items[second ? wg - a.n_items : wg];
+  const AttnReq rq = a.reqs[item.req];
+  return Work{item.req, item.kv_head, item.row0 + (second ? kAttnFewRows : 0), rq.q_off, rq.prefix, rq.chunk, item.slice, 1,
+              (int64_t)item.slice * a.rows_total, a.once != 0};
 }
 
 // the class of workgroup (or merge block) wg: the last one whose first is not past it

@@ -557,10 +557,11 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   }
 }
 
-template <class T, bool SPLIT>
+template <class T, Rows ROWS, bool SPLIT>
 __global__ __launch_bounds__(kWaves * 64) void attn_prefill_kernel(const AttnArgs a) {
-  const AttnItem item = a.items[blockIdx.x];
-  attn_body<T, kFullRows, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
+  const Work work = work_of<ROWS>(a, blockIdx.x);
+  if (ROWS == kFewRows && work.row0 >= work.chunk * a.G) return;      // a second half without rows
+  attn_body<T, ROWS, SPLIT ? kSlices : kWhole>(a, work);
 }
 
 template <class T, Rows ROWS>
@@ -688,12 +689,17 @@ __global__ __launch_bounds__(256) void attn_merge_classes_kernel(const float* __
 
 }  // namespace
 
+template <Rows ROWS>
+static void enqueue_f32_list(const AttnArgs& args, hipStream_t stream) {
+  const int wgs = args.n_items << args.halves;
+  if (args.kv_splits > 0) attn_prefill_kernel<F32, ROWS, true><<<wgs, kWaves * 64, 0, stream>>>(args);
+  else attn_prefill_kernel<F32, ROWS, false><<<wgs, kWaves * 64, 0, stream>>>(args);
+}
+
 hipError_t launch_attn(int dtype, const AttnArgs& args, hipStream_t stream) {
   (void)hipGetLastError();   // drop any stale error of earlier, unrelated runtime calls
-  const bool split = args.kv_splits > 0;
   if (dtype == MC_DTYPE_BF16) return launch_attn_bf16(args, stream);
-  if (split) attn_prefill_kernel<F32, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-  else attn_prefill_kernel<F32, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
+  args.few_rows ? enqueue_f32_list<kFewRows>(args, stream) : enqueue_f32_list<kFullRows>(args, stream);
   return hipGetLastError();
 }
 

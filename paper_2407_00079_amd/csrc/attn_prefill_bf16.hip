@@ -647,10 +647,11 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   }
 }
 
-template <int D, bool SPLIT>
+template <int D, Rows ROWS, bool SPLIT>
 __global__ __launch_bounds__(kWaves * 64) void attn_prefill_bf16_kernel(const AttnArgs a) {
-  const AttnItem item = a.items[blockIdx.x];
-  attn_bf16_body<D, kFullRows, SPLIT ? kSlices : kWhole>(a, work_of(item, a.reqs[item.req], a.rows_total));
+  const Work work = work_of<ROWS>(a, blockIdx.x);
+  if (ROWS == kFewRows && work.row0 >= work.chunk * a.G) return;      // a second half without rows
+  attn_bf16_body<D, ROWS, SPLIT ? kSlices : kWhole>(a, work);
 }
 
 template <int D, Rows ROWS>
@@ -660,33 +661,31 @@ __global__ __launch_bounds__(kWaves * 64) void attn_prefill_bf16_classes_kernel(
 
 }  // namespace
 
+template <int D, Rows ROWS>
+static void enqueue_list(const AttnArgs& args, hipStream_t stream) {
+  const int wgs = args.n_items << args.halves;
+  if (args.kv_splits > 0) attn_prefill_bf16_kernel<D, ROWS, true><<<wgs, kWaves * 64, 0, stream>>>(args);
+  else attn_prefill_bf16_kernel<D, ROWS, false><<<wgs, kWaves * 64, 0, stream>>>(args);
+}
+template <int D, Rows ROWS>
+static void enqueue_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream) {
+  attn_prefill_bf16_classes_kernel<D, ROWS><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
+}
+
 hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream) {
   (void)hipGetLastError();
   const bool few = t.rows == kAttnFewRows;
-  if (args.head_dim == 128) {
-    if (few) attn_prefill_bf16_classes_kernel<128, kFewRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
-    else attn_prefill_bf16_classes_kernel<128, kFullRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
-  } else if (args.head_dim == 64) {
-    if (few) attn_prefill_bf16_classes_kernel<64, kFewRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
-    else attn_prefill_bf16_classes_kernel<64, kFullRows><<<args.n_items, kWaves * 64, 0, stream>>>(args, t);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (args.head_dim == 128) few ? enqueue_classes<128, kFewRows>(args, t, stream) : enqueue_classes<128, kFullRows>(args, t, stream);
+  else if (args.head_dim == 64) few ? enqueue_classes<64, kFewRows>(args, t, stream) : enqueue_classes<64, kFullRows>(args, t, stream);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t stream) {
   (void)hipGetLastError();   // drop any stale error of earlier, unrelated runtime calls
-  const bool split = args.kv_splits > 0;
-  if (args.head_dim == 128) {
-    if (split) attn_prefill_bf16_kernel<128, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-    else attn_prefill_bf16_kernel<128, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-  } else if (args.head_dim == 64) {
-    if (split) attn_prefill_bf16_kernel<64, true><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-    else attn_prefill_bf16_kernel<64, false><<<args.n_items, kWaves * 64, 0, stream>>>(args);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (args.head_dim == 128) args.few_rows ? enqueue_list<128, kFewRows>(args, stream) : enqueue_list<128, kFullRows>(args, stream);
+  else if (args.head_dim == 64) args.few_rows ? enqueue_list<64, kFewRows>(args, stream) : enqueue_list<64, kFullRows>(args, stream);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

@@ -140,6 +140,37 @@ int64_t count_items(const mc_attn_params* p, const int32_t* new_lens, int32_t ba
   return n;
 }
 
+bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, int64_t tile_rows) {
+  const int64_t G = p->num_q_heads / p->num_kv_heads;
+  for (int32_t r = 0; r < batch; ++r)
+    if (new_lens[r] * G > tile_rows) return false;
+  return true;
+}
+
+// One row tile per head reads every K and V row once.  If they outgrow the last-level cache, the next layer finds none of
+// them there anyway, and a hint that they need not be kept helps: 16 tokens at 128k (64/8 heads, 537 MB) 106.5 us a
+// call without it, 97 with it.  What would stay in the cache is better left there (8192 + 16 tokens, 34 MB, the same call
+// repeated: 21.5 us without the hint, 23.6 with it).
+bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                int64_t tile_rows) {
+  constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
+  if (!few_rows(p, new_lens, batch, tile_rows)) return false;
+  int64_t keys = 0;
+  for (int32_t r = 0; r < batch; ++r)
+    if (new_lens[r] > 0) keys += (int64_t)prefix_lens[r] + new_lens[r];
+  return 2 * keys * p->num_kv_heads * p->head_dim * (p->dtype == MC_DTYPE_BF16 ? 2 : 4) > kLastLevelBytes;
+}
+
+// 128-row workgroups where no row tile has more rows, and where two of them per item still run side by side (an item's two
+// halves read K and V twice, which costs less than a compute unit left idle).  Measured, planned, append + attention, 256
+// rows / now, us: P 131056, C 16, 64/8 heads 2024 / 1493; 16 requests of P 4000, C 1 73 / 52; P 8192, C 300, 64/8
+// heads (80 items in halves) 169 / 117, fp32, 4/1 heads 1024 / 517.
+int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t n_items) {
+  if (few_rows(p, new_lens, batch, kAttnFewRows))
+    return reads_once(p, prefix_lens, new_lens, batch, kAttnFewRows) ? kListFewOnce : kListFew;
+  return 2 * n_items <= kComputeUnits ? kListHalves : 0;
+}
+
 mc_status check_plan(const mc_attn_params* p, const mc_attn_plan* plan, bool want_split) {
   if (plan == nullptr) return MC_ERR_NULL;
   if (plan->num_q_heads != p->num_q_heads || plan->num_kv_heads != p->num_kv_heads || plan->dtype != (int32_t)p->dtype ||
@@ -408,16 +439,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   AttnClasses& t = plan->classes;
   t.n = n_runs;
   t.rows = (int32_t)best_rows;
-  // One row tile per head reads every K and V row once.  If they outgrow the last-level cache, the next layer finds none of
-  // them there anyway, and a hint that they need not be kept helps: 16 tokens at 128k (64/8 heads, 537 MB) 106.5 us a
-  // call without it, 97 with it.  What would stay in the cache is better left there (8192 + 16 tokens, 34 MB, the same call
-  // repeated: 21.5 us without the hint, 23.6 with it).
-  int64_t kv_bytes = 0, most_rows = 0;
-  for (int i = 0; i < n; ++i) {
-    kv_bytes += 2 * ((int64_t)act[i].prefix + act[i].chunk) * Hkv * p->head_dim * (p->dtype == MC_DTYPE_BF16 ? 2 : 4);
-    most_rows = std::max(most_rows, act[i].chunk * G);
-  }
-  t.once = most_rows <= best_rows && kv_bytes > ((int64_t)256 << 20) ? 1 : 0;
+  t.once = reads_once(p, prefix_lens, new_lens, batch, best_rows) ? 1 : 0;
   int64_t wg = 0;
   plan->part_rows = 0;
   plan->most_pieces = 1;

@@ -53,6 +53,17 @@ void build_work_list(const mc_attn_params* p, const int32_t* prefix_lens, const 
 // number of whole-row work items of a batch (the size of the list build_work_list makes for kv_splits == 0)
 int64_t count_items(const mc_attn_params* p, const int32_t* new_lens, int32_t batch);
 
+// Every request's stacked rows of a KV head fit one row tile; and then, whether the K and V rows a launch reads (once each)
+// outgrow the last-level cache.
+bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
+bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
+
+// How a list of n_items workgroups is launched, kept in a plan: as row tiles of 256 rows (0) or by workgroups of 128 rows,
+// one per item or two.  Marks that no caller's own zeroed or filled struct holds by accident: a list of longer row tiles
+// launched one workgroup per item would leave rows out.
+constexpr int32_t kListFew = 0x4d434631, kListFewOnce = 0x4d434632, kListHalves = 0x4d434633;
+int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t n_items);
+
 // A plan handed back by the caller: made for these params, of the wanted form, not empty.
 mc_status check_plan(const mc_attn_params* p, const mc_attn_plan* plan, bool want_split);
 

@@ -190,7 +190,7 @@ mc_status prepare_attn(const mc_attn_params* p, const int32_t* prefix_lens, cons
   plan->num_q_heads = p->num_q_heads;
   plan->num_kv_heads = p->num_kv_heads;
   plan->dtype = (int32_t)p->dtype;
-  plan->reserved = 0;
+  plan->reserved = list_form(p, prefix_lens, new_lens, batch, plan->n_items);
   return MC_OK;
 }
 
@@ -215,6 +215,9 @@ mc_status launch_planned_attn(const mc_attn_params* p, const mc_attn_plan* plan,
   args.head_dim = p->head_dim;
   args.scale_log2e = attn_scale_log2e(p);
   args.n_items = plan->n_items;
+  args.halves = plan->reserved == kListHalves;
+  args.few_rows = args.halves || plan->reserved == kListFew || plan->reserved == kListFewOnce;
+  args.once = plan->reserved == kListFewOnce;
   args.kv_splits = plan->kv_splits;
   args.rows_total = plan->total_new_tokens * p->num_q_heads;
   args.o_parts = o_parts;

@@ -21,6 +21,9 @@ struct AttnArgs {
   int32_t head_dim;   // bf16: 128 or 64; fp32: 64
   float scale_log2e;  // softmax scale * log2(e): scores go through exp2
   int32_t n_items;
+  int32_t few_rows;    // list launches: 128-row workgroups, one per item (no item has more rows) or two (halves)
+  int32_t halves;
+  int32_t once;        // list launches: as AttnClasses::once
   // split launches (kv_splits > 0): partial results go to o_parts [kv_splits, rows_total, D] fp32 and
   // lse_parts [kv_splits, rows_total] instead of out / lse
   int32_t kv_splits;

@@ -52,8 +52,8 @@ def test_pieces_match_oracle(oracle, dtype, Hq, Hkv, D, prefix, new):
 @pytest.mark.parametrize("dtype,D,tiles", [(W.BF16, 128, n) for n in (1, 2, 3, 4, 5, 6, 7, 11)] + [(W.BF16, 64, 6), (W.F32, 64, 5)])
 def test_few_rows_without_room(oracle, dtype, D, tiles):
     """No room for partial results: one workgroup per KV head walks all key tiles, as many as there are LDS buffers and
-    around that; rows for one, two and four of its waves."""
-    for new in (1, 7, 16):
+    around that; rows for one, two and four of its waves, and for more than one workgroup."""
+    for new in (1, 7, 16, 33):                                # 33 tokens: a full row tile and one of 8 rows, in halves
         print(f"few rows case {dtype} D={D} tiles={tiles} new={new}", flush=True)
         case = W.make_attn_case(72 + tiles, dtype, 16, 2, D, 16, [64 * tiles - new - 3], [new], 4 * tiles + 3)
         dc = DeviceCase(case)
@@ -61,4 +61,21 @@ def test_few_rows_without_room(oracle, dtype, D, tiles):
         out, lse = dc.result()
         ref_out, ref_lse, _ = oracle.case_full(case)
         check_close(out, ref_out, dtype, "few rows")
+        assert np.abs(lse - ref_lse).max() <= TOL[dtype]["lse_abs"]
+        # the same from a prepared list, whole rows and key slices (some of them without a key a row may see)
+        p, args = dc.params, (dc.q, dc.k_pool, dc.v_pool, dc.block_tables)
+        dc.out.fill_(float("nan"))
+        dc.lse.fill_(float("nan"))
+        plan = B.mc_prefill_attn_prepare(p, case.prefix_lens.tolist(), case.new_lens.tolist(), 0, dc.workspace)
+        B.mc_prefill_attn_run(p, plan, *args, dc.out, dc.lse, dc.workspace)
+        check_close(dc.result()[0], ref_out, dtype, "few rows, planned")
+        ws = torch.empty(B.mc_prefill_attn_split_workspace_bytes(p, 1, new, 3), dtype=torch.uint8, device="cuda:0")
+        o_parts = torch.full((3, new, 16, D), float("nan"), dtype=torch.float32, device="cuda:0")
+        lse_parts = torch.full((3, new, 16), float("nan"), dtype=torch.float32, device="cuda:0")
+        plan = B.mc_prefill_attn_prepare(p, case.prefix_lens.tolist(), case.new_lens.tolist(), 3, ws)
+        B.mc_prefill_attn_run_split(p, plan, *args, o_parts, lse_parts, ws)
+        dc.out.fill_(float("nan"))
+        B.mc_attn_merge_lse(o_parts, lse_parts, 3, new * 16, D, int(p.dtype), dc.out, dc.lse)
+        out, lse = dc.result()
+        check_close(out, ref_out, dtype, "few rows, split")
         assert np.abs(lse - ref_lse).max() <= TOL[dtype]["lse_abs"]
