@@ -11,7 +11,7 @@
 //   match kernel   one workgroup per (instance, request): thread t looks keys t, t + 256, ... up
 //                  in the instance's ascending key array; the smallest index that misses is the
 //                  prefix length.
-//   best kernel    one thread per request scans its row of prefix lengths.
+//   best kernel    sixteen lanes per request scan its row of prefix lengths.
 //   small match    both of them for requests of few (key, instance) pairs, one workgroup each.
 #include "mc_internal.h"
 
@@ -255,21 +255,34 @@ __global__ __launch_bounds__(kSmallMatch) void prefix_small_match_kernel(const u
   }
 }
 
-__global__ __launch_bounds__(64) void prefix_best_kernel(const int32_t* __restrict__ prefix_len, int batch, int n_inst,
-                                                         int32_t* __restrict__ best_len,
-                                                         int32_t* __restrict__ best_inst) {
-  const int r = blockIdx.x * 64 + threadIdx.x;
-  if (r >= batch) return;
-  int32_t bl = 0, bi = n_inst > 0 ? 0 : -1;
-  for (int i = 0; i < n_inst; ++i) {
-    const int32_t l = prefix_len[(int64_t)r * n_inst + i];
-    if (l > bl) {
-      bl = l;
-      bi = i;
+// Sixteen lanes per request read its row of prefix lengths side by side (one thread a request read it one by one; 64
+// requests, 16 instances: a pass of keys and match 49.9 us before, 49.0 now).
+constexpr int kBestLanes = 16;
+__global__ __launch_bounds__(256) void prefix_best_kernel(const int32_t* __restrict__ prefix_len, int batch, int n_inst,
+                                                          int32_t* __restrict__ best_len,
+                                                          int32_t* __restrict__ best_inst) {
+  const int r = blockIdx.x * (256 / kBestLanes) + threadIdx.x / kBestLanes, part = threadIdx.x % kBestLanes;
+  int32_t len = 0, inst = n_inst > 0 ? 0 : -1;           // the longest, and of equals the first
+  if (r < batch)
+    for (int i = part; i < n_inst; i += kBestLanes) {
+      const int32_t l = prefix_len[(int64_t)r * n_inst + i];
+      if (l > len) {
+        len = l;
+        inst = i;
+      }
+    }
+#pragma unroll
+  for (int d = kBestLanes / 2; d >= 1; d >>= 1) {
+    const int32_t l = __shfl_xor(len, d, 64), i = __shfl_xor(inst, d, 64);
+    if (l > len || (l == len && i < inst)) {
+      len = l;
+      inst = i;
     }
   }
-  best_len[r] = bl;
-  best_inst[r] = bi;
+  if (r < batch && part == 0) {
+    best_len[r] = len;
+    best_inst[r] = inst;
+  }
 }
 
 }  // namespace
@@ -327,7 +340,8 @@ hipError_t match_with(const uint64_t* keys, const Tables& off, int batch, int64_
   if (n_inst > 0)
     prefix_match_kernel<Tables><<<dim3((unsigned)n_inst, (unsigned)batch), 256, 0, stream>>>(keys, cache_keys, off, n_inst,
                                                                                             prefix_len);
-  prefix_best_kernel<<<(unsigned)((batch + 63) / 64), 64, 0, stream>>>(prefix_len, batch, n_inst, best_len, best_inst);
+  const unsigned per = 256 / kBestLanes;
+  prefix_best_kernel<<<((unsigned)batch + per - 1) / per, 256, 0, stream>>>(prefix_len, batch, n_inst, best_len, best_inst);
   return hipGetLastError();
 }
 
