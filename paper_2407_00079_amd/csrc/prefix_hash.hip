@@ -155,7 +155,10 @@ __global__ __launch_bounds__(256) void prefix_stage_kernel(const int32_t* __rest
 // Does c[0 .. n), ascending, hold `key`?  Keys are hashes, spread evenly, so a probe tells not only on which side the key
 // lies but about how far: the first guess is off by some sqrt(n) / 2 places (220 of 200000), the next by the root of that,
 // and the rest is next to it: 4.6 probes instead of 18.  What has been read always brackets the key, so any ascending array
-// gives the right answer; where kGuesses do not close in (keys that are not spread evenly), the bracket is bisected.
+// gives the right answer; where kGuesses do not close in (keys that are far from evenly spread), the bracket is bisected.
+// Distances turn into places at the rate between the last two probes, so keys that fill parts of the range evenly are found
+// as fast (16 instances whose keys leave half the range empty, 64 requests: 16.2 us a call;
+// 26.9 at the mean rate of the whole array, 23.1 by bisection).
 // Distances go by the upper 32 bits of key differences: 64-bit conversions and windows of several keys a probe cost more
 // vector instructions than they save in loads (256 keys of 64 requests in 16 instances of 209000:
 // 16.6 us with them, 13.5 without; bisection 19.1).
@@ -165,22 +168,24 @@ __device__ __forceinline__ bool holds(const uint64_t* __restrict__ c, int64_t n,
   const uint64_t first = c[0], last = c[n - 1];
   if (key <= first || key >= last) return key == first || key == last;
   int64_t lo = 0, hi = n - 1;                            // c[lo] < key < c[hi]
-  if (n <= INT32_MAX) {
+  if (n <= (int64_t)1 << 30) {
     int l = 0, h = (int)n - 1;
-    const float per_key = (float)h / ((float)(uint32_t)((last - first) >> 32) + 1.f);
-    auto places = [&](uint64_t d) { return (int)((float)(uint32_t)(d >> 32) * per_key + 0.5f); };
-    int at = places(key - first);
+    float per_key = (float)h / ((float)(uint32_t)((last - first) >> 32) + 1.f);
+    auto upper = [](uint64_t x, uint64_t y) { return (float)(uint32_t)((x > y ? x - y : y - x) >> 32); };
+    int at = (int)fminf(upper(key, first) * per_key + 0.5f, (float)h), was = 0;
+    uint64_t v_was = first;
     for (int guess = 0; guess < kGuesses && h - l > 1; ++guess) {
       at = at <= l ? l + 1 : (at >= h ? h - 1 : at);
       const uint64_t v = c[at];
       if (v == key) return true;
-      if (v < key) {
-        l = at;
-        at += places(key - v);
-      } else {
-        h = at;
-        at -= places(v - key);
-      }
+      if (v < key) l = at; else h = at;
+      // places per key between the last two probes, where they are far enough apart to tell
+      const float span = upper(v, v_was), gone = (float)(at > was ? at - was : was - at);
+      if (gone >= 16.f && span > 0.f) per_key = gone * __builtin_amdgcn_rcpf(span);
+      was = at;
+      v_was = v;
+      const int off = (int)fminf(upper(key, v) * per_key + 0.5f, (float)h);
+      at = v < key ? at + off : at - off;
     }
     lo = l;
     hi = h;
