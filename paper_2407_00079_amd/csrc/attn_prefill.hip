@@ -286,7 +286,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
 #pragma unroll
   for (int i = 0; i < T::kVX; ++i) vx[i] = v_lane ^ T::v_xor(i);
 
-  // ---- building blocks that are NOT on the steady-state path (prologue, last block, rare recompute)
+  // ---- building blocks that are NOT on the steady-state path (last block, rare recompute)
   // S^T block = K Q^T for keys [32*kb, 32*kb+32) of the tile in LDS buffer `buf`, one K fragment
   // in flight at a time (it runs where registers are scarce)
   auto qk_block = [&](int buf, int kb, f32x16& s) __attribute__((always_inline)) {
@@ -337,14 +337,6 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
     for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], c, -m_ref));
     pb = T::round_p(p);
     return T::block_sum(pb);
-  };
-  // O^T += V^T P^T for the block's 32 keys, V fragments read just in time
-  auto pv_block = [&](int buf, int kb, const typename T::pblock& pb) __attribute__((always_inline)) {
-    const int off = buf * kVTileBytes + kb * 32 * kRowBytes;
-#pragma unroll
-    for (int st = 0; st < T::kPVSteps; ++st)
-#pragma unroll
-      for (int db = 0; db < T::kDBlocks; ++db) o[db] = T::mma(T::load_v(vx, off, st, db), T::p_frag(pb, st), o[db]);
   };
 
   // ---- KV loop.  Software pipeline over 32-key blocks, scheduled by hand: the order written
@@ -419,13 +411,25 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
     }
   };
   // One block start to finish, for the few blocks that may reach the diagonal: scores (unless the
-  // pipeline has left them in `s`), mask, true maxima and reference, probabilities, P V.
+  // pipeline has left them in `s`), mask, true maxima and reference, probabilities, P V.  The ring
+  // is free there: K fragments are read together, V fragments under the softmax.
+  auto scores_of = [&](int buf, int kb, f32x16& s) __attribute__((always_inline)) {
+    load_k_ring(buf, kb);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < kRing; ++i) s = T::mma(ring[i], qf[i], s);
+  };
   auto plain_block = [&](int buf, int kb, int key0, f32x16& s, bool have_scores) __attribute__((always_inline)) {
-    if (!have_scores) qk_block(buf, kb, s);
+    if (!have_scores) scores_of(buf, kb, s);
+    const int off = buf * kVTileBytes + kb * 32 * kRowBytes;
+#pragma unroll
+    for (int i = 0; i < kRing; ++i) ring[i] = T::load_v(vx, off, i / T::kDBlocks, i % T::kDBlocks);
     settle_reference(s, key0, std::true_type{});
     typename T::pblock pb;
     l_sum += probabilities(s, pb);
-    pv_block(buf, kb, pb);
+#pragma unroll
+    for (int i = 0; i < kRing; ++i) o[i % T::kDBlocks] = T::mma(ring[i], T::p_frag(pb, i / T::kDBlocks), o[i % T::kDBlocks]);
   };
 
   // the first two tiles; everything issued so far (also the Q fragments) has landed: inside the loop the vector-memory
@@ -479,7 +483,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   // tiles every key of which is visible to every row go through the pipeline (never the last
   // tile: the pipeline always computes the scores of one block ahead)
   const int n_plain = n_free < n_tiles - 1 ? n_free : n_tiles - 1;
-  qk_block(0, 0, s_next);
+  scores_of(0, 0, s_next);
   if (tile < n_plain) {
     settle_reference(s_next, 0, std::false_type{});
     load_k_ring(0, 1);

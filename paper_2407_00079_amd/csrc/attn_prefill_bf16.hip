@@ -328,7 +328,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
 #pragma unroll
   for (int i = 0; i < kDTiles; ++i) vx[i] = v_lane ^ (uint32_t)(i << 5);
 
-  // ---- building blocks that are NOT on the steady-state path (prologue, last blocks, rare recompute)
+  // ---- building blocks that are NOT on the steady-state path (last blocks, rare recompute)
   auto qk_block = [&](int buf, int kb, Scores& s) __attribute__((always_inline)) {
     const int off = buf * kKTileBytes + kb * 32 * kRowBytes;
     s.zero();
@@ -387,15 +387,6 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   auto add_row_sums = [&](const PBlock& pb) __attribute__((always_inline)) {
     l_acc[0] = mma(ones, pb.f(0), l_acc[0]);
     l_acc[1] = mma(ones, pb.f(1), l_acc[1]);
-  };
-  auto pv_block = [&](int buf, int kb, const PBlock& pb) __attribute__((always_inline)) {
-    const int off = buf * kVTileBytes + kb * 32 * kRowBytes;
-#pragma unroll
-    for (int dt = 0; dt < kDTiles; ++dt) {
-      const frag vf = X::load_v(vx, off, dt);
-      o[dt][0] = mma(vf, pb.f(0), o[dt][0]);
-      o[dt][1] = mma(vf, pb.f(1), o[dt][1]);
-    }
   };
 
   // ---- KV loop.  Software pipeline over 32-key blocks, scheduled by hand (the order written is the order
@@ -495,14 +486,32 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
       weave(accumulate, refill, s_next, pb_ahead, 0, grp);
     }
   };
-  // one block start to finish, for the few blocks that may reach the diagonal
+  // One block start to finish, for the few blocks that may reach the diagonal: the ring is free there, so the block's K
+  // fragments are read together, and its V fragments under the softmax.  (A fragment read just before its MFMAs cost its
+  // whole latency: one call, P 256, C 128, 64/8 heads 13.4 us, now 12.8; P 1000, C 16 17.0, 16.2.)
+  auto scores_of = [&](int buf, int kb, Scores& s) __attribute__((always_inline)) {
+    load_k_ring(buf, kb);
+    s.zero();
+#pragma unroll
+    for (int i = 0; i < kRing; ++i) {
+      s.t[0][i & 1] = mma(ring[i], qf[i >> 1][0], s.t[0][i & 1]);
+      s.t[1][i & 1] = mma(ring[i], qf[i >> 1][1], s.t[1][i & 1]);
+    }
+  };
   auto plain_block = [&](int buf, int kb, int key0, Scores& s, bool have_scores) __attribute__((always_inline)) {
-    if (!have_scores) qk_block(buf, kb, s);
+    if (!have_scores) scores_of(buf, kb, s);
+    const int off = buf * kVTileBytes + kb * 32 * kRowBytes;
+#pragma unroll
+    for (int dt = 0; dt < kDTiles; ++dt) ring[dt] = X::load_v(vx, off, dt);
     settle_reference(s, key0, std::true_type{});
     PBlock pbl;
     probabilities(s, pbl);
     add_row_sums(pbl);
-    pv_block(buf, kb, pbl);
+#pragma unroll
+    for (int dt = 0; dt < kDTiles; ++dt) {
+      o[dt][0] = mma(ring[dt], pbl.f(0), o[dt][0]);
+      o[dt][1] = mma(ring[dt], pbl.f(1), o[dt][1]);
+    }
   };
 
   // The copies of the first tiles; everything enqueued so far (also the Q fragments) has landed, those of the rest of the
@@ -562,7 +571,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   }
   int tile = t_lo;
   const int n_plain = n_free < n_tiles - 1 ? n_free : n_tiles - 1;
-  qk_block(0, 0, s_next);
+  scores_of(0, 0, s_next);
   if (tile < n_plain) {
     settle_reference(s_next, 0, std::false_type{});
     load_k_ring(0, 1);
