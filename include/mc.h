@@ -299,8 +299,9 @@ mc_status mc_prefill_attn_plan(const mc_attn_params* p, const int32_t* prefix_le
  *   out[t][:] = sum_s exp(lse_parts[s][t] - lse[t]) * o_parts[s][t][:]
  *
  *   o_parts    dev  [kv_splits, rows, head_dim] fp32
- *   lse_parts  dev  [kv_splits, rows] fp32; -inf marks a part without keys: weight 0, its
- *                   o_parts row is not read
+ *   lse_parts  dev  [kv_splits, rows] fp32; -inf marks a part without keys: it counts for
+ *                   nothing, whatever its o_parts row holds.  Every other part counts: one with a
+ *                   NaN makes the row NaN
  *   out        dev  [rows, head_dim] of `dtype` (bf16: rounded to nearest even)
  *   lse        dev  [rows] fp32, or NULL
  *

@@ -546,8 +546,10 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
     if (a.lse != nullptr && half == 0) a.lse[orow_idx] = (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
   }
   if (live && !final_rows) {
-    // partial result in fp32; a row that saw no key of the slice has l = 0: zeros and -inf
-    const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
+    // partial result in fp32; a row that saw no key of the slice has l = 0: zeros and -inf (and nothing else has: a NaN
+    // stays one)
+    const bool no_key = l_run == 0.f;
+    const float inv = no_key ? 0.f : 1.0f / l_run;
     char* orow = reinterpret_cast<char*>(a.o_parts) + prow * (T::kD * 4);
 #pragma unroll
     for (int db = 0; db < T::kDBlocks; ++db)
@@ -557,7 +559,7 @@ __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
             f32x4{o[db][q4 * 4 + 0] * inv, o[db][q4 * 4 + 1] * inv, o[db][q4 * 4 + 2] * inv, o[db][q4 * 4 + 3] * inv};
     if (half == 0)
       a.lse_parts[prow] =
-          l_run > 0.f ? (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
+          no_key ? -INFINITY : (m_run + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
   }
 }
 
@@ -582,7 +584,8 @@ __global__ __launch_bounds__(kWaves * 64) void attn_prefill_classes_kernel(const
 // through LDS (few rows, many parts: small chunks against long prefixes).  A lane takes its parts four at a time, their
 // log-sum-exps and their columns loaded together, against the largest lse it has seen (rescaled when that grows): one
 // round trip to memory per four parts, where taking the maximum of all lse first made it two.  A part whose lse is -inf
-// has weight 0 whatever its columns hold.
+// has weight 0 whatever its columns hold; nothing else is left out, so a NaN in a part (a NaN in Q or in a visible key)
+// reaches the output as it does from whole rows.
 // ---------------------------------------------------------------------------
 template <typename T, int SL>
 struct Merge {
@@ -616,15 +619,15 @@ struct Merge {
       float top = m;
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) top = fmaxf(top, l[u]);
-      if (top == -INFINITY) continue;
-      const float keep = __expf(m - top);
+      const float ref = finite_reference(top);
+      const float keep = __expf(m - ref);
       acc *= keep;
       z *= keep;
       m = top;
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
-        const float w = __expf(l[u] - top);
-        if (w == 0.f) continue;                    // also a part without keys, whose columns may hold anything
+        if (l[u] == -INFINITY) continue;           // a part without keys: its columns may hold anything
+        const float w = __expf(l[u] - ref);
         z += w;
         acc += w * v[u];
       }
@@ -641,20 +644,24 @@ struct Merge {
       for (int t = 1; t < SL; ++t) m = fmaxf(m, sh.m[rl][t]);
       z = 0.f;
       acc = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (m != -INFINITY) {
+      const float ref = finite_reference(m);
 #pragma unroll
-        for (int t = 0; t < SL; ++t) {
-          const float w = __expf(sh.m[rl][t] - m);
-          z += w * sh.z[rl][t];
-          acc += w * sh.part[rl][t][cl];
-        }
+      for (int t = 0; t < SL; ++t) {
+        const float w = __expf(sh.m[rl][t] - ref);
+        z += w * sh.z[rl][t];
+        acc += w * sh.part[rl][t][cl];
       }
     }
     if (!live) return;
-    if (m != -INFINITY) acc *= 1.0f / z;
+    // z is 0 only where no part has keys (the largest weight is 1), and NaN where any of them is
+    if (z != 0.f) acc *= 1.0f / z;
     T::store4(reinterpret_cast<char*>(out) + dst * T::kOutRowBytes, cl * 4, acc[0], acc[1], acc[2], acc[3]);
-    if (lse != nullptr && cl == 0) lse[dst] = m != -INFINITY ? m + __logf(z) : -INFINITY;
+    if (lse != nullptr && cl == 0) lse[dst] = z != 0.f ? m + __logf(z) : -INFINITY;
   }
+
+ private:
+  // weights are exp(lse - reference): with no part seen yet any finite one makes them 0 (and leaves a NaN a NaN)
+  static __device__ __forceinline__ float finite_reference(float top) { return top == -INFINITY ? 0.f : top; }
 };
 
 template <typename T, int SL>

@@ -642,8 +642,10 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
       if (a.lse != nullptr && g == 0)
         a.lse[orow_idx[rt]] = (m_run[rt] + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
     } else {
-      // partial result in fp32; a row that saw no key of the slice has l = 0: zeros and -inf
-      const float inv = l_run > 0.f ? 1.0f / l_run : 0.f;
+      // partial result in fp32; a row that saw no key of the slice has l = 0: zeros and -inf (and nothing else has: a NaN
+      // stays one)
+      const bool no_key = l_run == 0.f;
+      const float inv = no_key ? 0.f : 1.0f / l_run;
       char* orow = reinterpret_cast<char*>(a.o_parts) + prow[rt] * (kD * 4);
 #pragma unroll
       for (int dt = 0; dt < kDTiles; ++dt)
@@ -651,7 +653,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
             f32x4{o[dt][rt][0] * inv, o[dt][rt][1] * inv, o[dt][rt][2] * inv, o[dt][rt][3] * inv};
       if (g == 0)
         a.lse_parts[prow[rt]] =
-            l_run > 0.f ? (m_run[rt] + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f : -INFINITY;
+            no_key ? -INFINITY : (m_run[rt] + __builtin_amdgcn_logf(l_run)) * 0.6931471805599453f;
     }
   }
 }
