@@ -161,13 +161,21 @@ bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32
   return 2 * keys * p->num_kv_heads * p->head_dim * (p->dtype == MC_DTYPE_BF16 ? 2 : 4) > kLastLevelBytes;
 }
 
-// 128-row workgroups where no row tile has more rows, and where two of them per item still run side by side (an item's two
-// halves read K and V twice, which costs less than a compute unit left idle).  Measured, planned, append + attention, 256
-// rows / now, us: P 131056, C 16, 64/8 heads 2024 / 1493; 16 requests of P 4000, C 1 73 / 52; P 8192, C 300, 64/8
-// heads (80 items in halves) 169 / 117, fp32, 4/1 heads 1024 / 517.
-int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t n_items) {
+// 128-row workgroups where no row tile has more rows, and where the plan of a one-shot call without room for partial
+// results takes them (plan_classes), so that a prepared list computes what that call computes, bit for bit: the rows that
+// share a workgroup decide which of its key tiles need no mask, and with that the reference of the probabilities.  Lists a
+// class plan has no room for, and lists of key slices: where two workgroups per item still run side by side (an item's two
+// halves read K and V twice, which costs less than a compute unit left idle).
+// Measured, planned, 256 rows / 128, us: P 131056, C 16, 64/8 heads 2024 / 1493; 16 requests of P 4000, C 1 73 / 52;
+// P 8192, C 300, 64/8 heads (80 items) 169 / 117, fp32, 4/1 heads 1024 / 517; more items than half the units: 24 requests
+// of 16 tokens and one of 30, P 4000, 64/8 heads (200 items) 100 / 80; 3 requests, fp32, 12/3 heads (360 items) 754 / 684.
+int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                  int32_t kv_splits, int64_t n_items) {
   if (few_rows(p, new_lens, batch, kAttnFewRows))
     return reads_once(p, prefix_lens, new_lens, batch, kAttnFewRows) ? kListFewOnce : kListFew;
+  ClassPlan plan;
+  if (kv_splits == 0 && plan_classes(p, prefix_lens, new_lens, batch, 0, &plan))
+    return plan.classes.rows == kAttnFewRows ? kListHalves : 0;
   return 2 * n_items <= kComputeUnits ? kListHalves : 0;
 }
 
@@ -338,7 +346,7 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 // behind a long prefix is cut until it fills the chip; a launch just above a whole number of rounds is cut only where it
 // would run a last, mostly empty round; few short row tiles are cut into pieces of one or two key tiles.  Row tiles of 256
 // and of 128 rows (see Rows in attn_device.h) are both tried: the larger ones share each key tile among twice the rows and
-// win wherever there are enough of them.
+// win wherever there are enough of them.  (Where every request fits the smaller ones there are as many of either.)
 // Measured, one call with its append (uniform slices of all rows or none before / this cut now): P 6144, C 811 and 328,
 // 64/8 heads (296 row tiles: 6 slices / 256 whole tiles and 40 in 6 pieces) 342 / 220 us; P 256, C 128, fp32, 4/1 heads
 // (2 row tiles: whole / 6 pieces) 73 / 33 us; P 131056, C 16, 64/8 heads (32 slices / 32 pieces) 125 / 118 us.
@@ -363,6 +371,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
     return items;
   };
   if (items_of(kAttnTileRows) > INT32_MAX) return false;
+  const bool few = few_rows(p, new_lens, batch, kAttnFewRows);
   std::sort(act, act + n, [](const Active& a, const Active& b) {
     if (a.prefix != b.prefix) return a.prefix > b.prefix;
     return a.chunk != b.chunk ? a.chunk > b.chunk : a.req < b.req;
@@ -398,12 +407,12 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
     return k < MC_MAX_KV_SPLITS ? k : (int64_t)MC_MAX_KV_SPLITS;
   };
 
-  int64_t best_rows = kAttnTileRows, best_whole = items_of(kAttnTileRows);
+  int64_t best_rows = few ? kAttnFewRows : kAttnTileRows, best_whole = items_of(best_rows);
   double best_len = 0.0, best = 0.0;
   for (const int64_t tile_rows : {(int64_t)kAttnTileRows, (int64_t)kAttnFewRows}) {
     // From four full rounds on the launch order (short row tiles last) balances the tail by itself.
     const int64_t items = items_of(tile_rows);
-    if (items >= 4 * kComputeUnits) continue;
+    if (items >= 4 * kComputeUnits || (few && tile_rows != kAttnFewRows)) continue;
     const TileCost cost = tile_cost_of(p, tile_rows);
     for (int64_t rounds = 0; rounds * kComputeUnits < items; ++rounds) {
       const int uncut = lay_out(rounds * kComputeUnits, tile_rows);

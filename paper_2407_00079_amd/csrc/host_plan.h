@@ -62,7 +62,8 @@ bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32
 // one per item or two.  Marks that no caller's own zeroed or filled struct holds by accident: a list of longer row tiles
 // launched one workgroup per item would leave rows out.
 constexpr int32_t kListFew = 0x4d434631, kListFewOnce = 0x4d434632, kListHalves = 0x4d434633;
-int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t n_items);
+int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                  int32_t kv_splits, int64_t n_items);
 
 // A plan handed back by the caller: made for these params, of the wanted form, not empty.
 mc_status check_plan(const mc_attn_params* p, const mc_attn_plan* plan, bool want_split);

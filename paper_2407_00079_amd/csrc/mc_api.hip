@@ -190,7 +190,7 @@ mc_status prepare_attn(const mc_attn_params* p, const int32_t* prefix_lens, cons
   plan->num_q_heads = p->num_q_heads;
   plan->num_kv_heads = p->num_kv_heads;
   plan->dtype = (int32_t)p->dtype;
-  plan->reserved = list_form(p, prefix_lens, new_lens, batch, plan->n_items);
+  plan->reserved = list_form(p, prefix_lens, new_lens, batch, plan->kv_splits, plan->n_items);
   return MC_OK;
 }
 

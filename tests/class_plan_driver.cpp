@@ -1,6 +1,7 @@
 // Prints the class plan of each batch read from stdin, one line per plan (tests/test_class_plan.py checks them).
 // input:  Hq Hkv D dtype max_part_rows batch P... C...
 // output: n n_wgs most_pieces part_rows tile_rows [first req q_off prefix chunk tile_lo tile_hi pieces part_base]...
+//         and the rows of a workgroup of the prepared list of the batch
 #include <cstdio>
 #include <vector>
 
@@ -27,7 +28,8 @@ int main() {
       std::printf(" %d %d %d %d %d %d %d %d %d", plan.classes.first[i], k.req, k.q_off, k.prefix, k.chunk, k.tile_lo, k.tile_hi,
                   k.pieces, k.part_base);
     }
-    std::printf("\n");
+    const int32_t form = mc::host::list_form(&p, P.data(), C.data(), batch, 0, mc::host::count_items(&p, C.data(), batch));
+    std::printf(" %d\n", form == 0 ? mc::kAttnTileRows : mc::kAttnFewRows);
   }
   return 0;
 }

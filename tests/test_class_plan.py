@@ -26,7 +26,7 @@ def plan(driver, Hq, Hkv, D, dtype, room, prefix, new):
         return None
     v = [int(x) for x in out]
     names = ("first", "req", "q_off", "prefix", "chunk", "tile_lo", "tile_hi", "pieces", "part_base")
-    return dict(n_wgs=v[1], most_pieces=v[2], part_rows=v[3], rows=v[4],
+    return dict(n_wgs=v[1], most_pieces=v[2], part_rows=v[3], rows=v[4], list_rows=v[-1],
                 classes=[dict(zip(names, v[5 + 9 * i:14 + 9 * i])) for i in range(v[0])])
 
 
@@ -79,3 +79,21 @@ def test_cuts_that_matter(driver):
     assert plan(driver, 4, 1, 64, 1, 64 * 512, [256], [128])["n_wgs"] >= 8  # two row tiles become more workgroups
     assert plan(driver, 64, 8, 128, 0, 1 << 40, [8192], [8192])["most_pieces"] == 1
     assert plan(driver, 8, 2, 128, 0, 0, [0] * 64, [1] * 64) is None        # more requests than classes
+
+
+# batches on which the two rules once disagreed: more items than half the compute units, row tiles of mixed lengths; and
+# ones with more row tiles than are weighed against each other
+SAME_ROWS = [
+    (64, 8, 128, 0, [4000] * 25, [16] * 24 + [30]),
+    (12, 3, 64, 1, [74, 8, 2000], [6160, 900, 500]),
+    (4, 1, 128, 0, [91, 400, 3000, 16, 77, 1200, 9, 5], [443, 4000, 8000, 800, 400, 50, 1, 1]),
+    (16, 16, 128, 0, [22, 700], [6965, 300]),
+    (32, 32, 128, 0, [100] * 60, [40] * 60),
+    (64, 8, 128, 0, [8192], [8192]),
+]
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,dtype,prefix,new", BATCHES + SAME_ROWS)
+def test_prepared_lists_take_the_row_tiles_of_an_uncut_call(driver, Hq, Hkv, D, dtype, prefix, new):
+    p = plan(driver, Hq, Hkv, D, dtype, 0, prefix, new)
+    assert p["most_pieces"] == 1 and p["list_rows"] == p["rows"]

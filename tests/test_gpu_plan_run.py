@@ -1,5 +1,6 @@
 """GPU: prepare once, run per layer (mc_prefill_attn_prepare / _run / _run_split, mc_kv_append_run) gives bit for bit
-what the one-shot calls give, also when the runs are replayed from a HIP graph."""
+what the one-shot calls give (whole rows: with the minimal workspace, or without one), also when the runs are replayed
+from a HIP graph."""
 import numpy as np
 import pytest
 import torch
@@ -138,3 +139,32 @@ def test_layer_step_replays_from_a_hip_graph(oracle):
         assert torch.equal(got_lse, ref.lse)
         ref_out, ref_lse, _ = oracle.case_full(case)
         check_close(got_out.float().cpu().numpy().astype(np.float64), ref_out, W.BF16, f"replay {l}")
+
+
+# batches whose lists have more items than half the compute units and row tiles of mixed lengths (on the first four the
+# prepared list once took other row tiles than the one-shot calls), and one with more row tiles than are weighed
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,prefix,new", [
+    (W.F32, 12, 3, 64, [74, 8, 2000], [6160, 900, 500]),
+    (W.BF16, 4, 1, 128, [91, 400, 3000, 16, 77, 1200, 9, 5], [443, 4000, 8000, 800, 400, 50, 1, 1]),
+    (W.BF16, 16, 16, 128, [22, 700], [6965, 300]),
+    (W.BF16, 64, 8, 128, [4000] * 25, [16] * 24 + [30]),
+    (W.BF16, 16, 16, 128, [1500] * 40, [100] * 40),
+])
+def test_whole_rows_are_the_same_bits_however_the_call_is_driven(dtype, Hq, Hkv, D, prefix, new):
+    print(f"same bits case {dtype} Hq={Hq} Hkv={Hkv} D={D} batch={len(new)}", flush=True)
+    pages = sum(-(-(p + c) // 16) for p, c in zip(prefix, new)) + 5
+    dc = DeviceCase(W.make_attn_case(905, dtype, Hq, Hkv, D, 16, prefix, new, pages))
+    args = (dc.q, dc.k_pool, dc.v_pool, dc.block_tables)
+    # scores spread so widely that many blocks outgrow the reference of their rows
+    dc.run(scale=1.0)                                              # one shot, minimal workspace
+    want = [t.clone() for t in (dc.out, dc.lse)]
+    assert all(torch.isfinite(t.float()).all() for t in want)
+    plan_ws = torch.empty_like(dc.workspace)
+    plan = B.mc_prefill_attn_prepare(dc.params, prefix, new, 0, plan_ws)
+    for call in (lambda: B.mc_prefill_attn_run(dc.params, plan, *args, dc.out, dc.lse, plan_ws),
+                 lambda: B.mc_prefill_attn_paged_noalloc(dc.params, *args, prefix, new, dc.out, dc.lse)):
+        dc.out.fill_(float("nan"))
+        dc.lse.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        assert torch.equal(dc.out, want[0]) and torch.equal(dc.lse, want[1])
