@@ -263,55 +263,60 @@ TileCost tile_cost_of(const mc_attn_params* p, int64_t tile_rows) {
 // the merge launch, and bytes of partial results written and read per microsecond
 constexpr double kMergeFixed = 4.0, kPartBytesPerUs = 3.0e6;
 
-// A set of row tiles of one request: `items` workgroups if uncut, `tiles` key tiles each on average.
+// A set of row tiles of one request: `items` workgroups if uncut, of `shortest` to `longest` key tiles.
 struct Run {
   int active;               // which of the requests with new tokens, in launch order
   int64_t tile_lo, tile_hi;
   int64_t items, rows;
-  double mean;
-  int64_t longest;
+  int64_t shortest, longest;
+  double mean() const { return 0.5 * (double)(shortest + longest); }
+  // pieces of at most 1 / k of `of` key tiles each, and the key tiles of one of c pieces on average, rounded up
+  int64_t pieces(int64_t of, int64_t k) const { return std::min<int64_t>((longest * k + of - 1) / of, MC_MAX_KV_SPLITS); }
+  double mean_piece(int64_t c) const { return (double)((shortest + longest + 2 * c - 1) / (2 * c)); }
 };
 
 // End of the last workgroup if the runs' pieces are handed to the compute units in order, each to the one free first
-// (runs are few, so the units are kept as groups that are free at the same time).
+// (runs are few, so the units are kept as groups that are free at the same time, the first one first).
 class Units {
  public:
-  void place(int64_t n, double dur) {
+  // false as soon as a workgroup ends at `limit` or later
+  bool place(int64_t n, double dur, double limit) {
     while (n > 0) {
-      int at = 0;
-      for (int i = 1; i < used_; ++i)
-        if (t_[i] < t_[at]) at = i;
-      const int64_t k = n < count_[at] ? n : count_[at];
-      const double end = t_[at] + dur;
+      const int64_t k = n < count_[0] ? n : count_[0];
+      const double end = t_[0] + dur;
+      if (end >= limit) return false;
       end_ = end > end_ ? end : end_;
-      count_[at] -= k;
-      if (count_[at] == 0) {
+      count_[0] -= k;
+      if (count_[0] == 0) {
         --used_;
-        t_[at] = t_[used_];
-        count_[at] = count_[used_];
+        std::copy(t_ + 1, t_ + 1 + used_, t_);
+        std::copy(count_ + 1, count_ + 1 + used_, count_);
       }
       add(end, k);
       n -= k;
     }
+    return true;
   }
   double end() const { return end_; }
 
  private:
   void add(double t, int64_t k) {
-    for (int i = 0; i < used_; ++i)
-      if (t_[i] > t - 0.01 && t_[i] < t + 0.01) {
-        count_[i] += k;
-        return;
-      }
-    if (used_ == kGroups) {                 // merge into the nearest: an estimate
-      int at = 0;
-      for (int i = 1; i < used_; ++i)
-        if (std::fabs(t_[i] - t) < std::fabs(t_[at] - t)) at = i;
+    int at = used_;                         // the first group that is free later
+    while (at > 0 && t_[at - 1] > t) --at;
+    if (at > 0 && t - t_[at - 1] < 0.01) {
+      count_[at - 1] += k;
+    } else if (at < used_ && t_[at] - t < 0.01) {
       count_[at] += k;
-      return;
+    } else if (used_ == kGroups) {          // merge into the nearest: an estimate
+      const bool before = at > 0 && (at == used_ || t - t_[at - 1] <= t_[at] - t);
+      count_[before ? at - 1 : at] += k;
+    } else {
+      std::copy_backward(t_ + at, t_ + used_, t_ + used_ + 1);
+      std::copy_backward(count_ + at, count_ + used_, count_ + used_ + 1);
+      t_[at] = t;
+      count_[at] = k;
+      ++used_;
     }
-    t_[used_] = t;
-    count_[used_++] = k;
   }
   static constexpr int kGroups = 16;
   int used_ = 1;
@@ -334,7 +339,7 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
   run.items = (hi - lo + 1) * p->num_kv_heads;
   run.rows = (std::min<int64_t>(chunk * G, (hi + 1) * tile_rows) - lo * tile_rows) * p->num_kv_heads;
   run.longest = key_tiles(prefix, chunk, G, hi, tile_rows);
-  run.mean = 0.5 * (double)(run.longest + key_tiles(prefix, chunk, G, lo, tile_rows));
+  run.shortest = key_tiles(prefix, chunk, G, lo, tile_rows);
   return run;
 }
 
@@ -350,6 +355,9 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 // Measured, one call with its append (uniform slices of all rows or none before / this cut now): P 6144, C 811 and 328,
 // 64/8 heads (296 row tiles: 6 slices / 256 whole tiles and 40 in 6 pieces) 342 / 220 us; P 256, C 128, fp32, 4/1 heads
 // (2 row tiles: whole / 6 pieces) 73 / 33 us; P 131056, C 16, 64/8 heads (32 slices / 32 pieces) 125 / 118 us.
+// Every one-shot call pays for the search on the host, so a trial that the work alone puts behind the best is not placed, and
+// placing ends where the best does (same plans; host time of a call of 63 requests, 8/1 heads, C up to 300: 219 us with every
+// trial placed, 20 now; of 63 one-token requests 41 and 16; of one to three requests 1 us of planning).
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                   int64_t max_part_rows, ClassPlan* plan) {
   const int64_t G = p->num_q_heads / p->num_kv_heads, Hkv = p->num_kv_heads;
@@ -379,6 +387,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
 
   // runs of the launch order when the first `whole` workgroups are kept apart; returns how many runs those are
   Run runs[kMaxAttnClasses];
+  int64_t pieces[kMaxAttnClasses];
   int n_runs = 0;
   auto lay_out = [&](int64_t whole, int64_t tile_rows) {
     n_runs = 0;
@@ -401,14 +410,9 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
     }
     return uncut;
   };
-  auto pieces_of = [](const Run& run, double len) {
-    int64_t k = (int64_t)std::ceil((double)run.longest / len - 1e-9);
-    k = k < 1 ? 1 : k;
-    return k < MC_MAX_KV_SPLITS ? k : (int64_t)MC_MAX_KV_SPLITS;
-  };
-
   int64_t best_rows = few ? kAttnFewRows : kAttnTileRows, best_whole = items_of(best_rows);
-  double best_len = 0.0, best = 0.0;
+  int64_t best_of = 0, best_k = 1;
+  double best = 0.0;
   for (const int64_t tile_rows : {(int64_t)kAttnTileRows, (int64_t)kAttnFewRows}) {
     // From four full rounds on the launch order (short row tiles last) balances the tail by itself.
     const int64_t items = items_of(tile_rows);
@@ -418,29 +422,38 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       const int uncut = lay_out(rounds * kComputeUnits, tile_rows);
       int64_t longest = 0;
       for (int i = uncut; i < n_runs; ++i) longest = std::max(longest, runs[i].longest);
+      double kept = 0.0, least = 0.0;      // unit time of what stays whole, and of the rest before it is cut
+      for (int i = 0; i < uncut; ++i) kept += (double)runs[i].items * (cost.fixed + cost.tile * runs[i].mean());
+      for (int i = uncut; i < n_runs; ++i) least += (double)runs[i].items * cost.tile * runs[i].mean();
+      int64_t n_before = 0;
       for (int64_t k = 1; k <= longest && k <= MC_MAX_KV_SPLITS; k += k < 8 ? 1 : k < 32 ? 2 : k < 64 ? 4 : 16) {
-        const double len = (double)longest / (double)k;
-        // more than four rounds of pieces: the tail is short by then, a finer cut only adds partial results
-        int64_t n_pieces = 0;
-        for (int i = uncut; i < n_runs; ++i) n_pieces += runs[i].items * pieces_of(runs[i], len);
-        if (k > 1 && (n_pieces > 4 * kComputeUnits || max_part_rows == 0)) break;
-        Units units;
-        int64_t part_rows = 0;
-        for (int i = 0; i < uncut; ++i) units.place(runs[i].items, cost.fixed + cost.tile * runs[i].mean);
+        int64_t n_pieces = 0, part_rows = 0;
         for (int i = uncut; i < n_runs; ++i) {
-          const int64_t c = pieces_of(runs[i], len);
-          units.place(runs[i].items * c, cost.fixed + cost.tile * std::ceil(runs[i].mean / (double)c));
-          if (c > 1) part_rows += c * runs[i].rows;
+          pieces[i] = runs[i].pieces(longest, k);
+          n_pieces += runs[i].items * pieces[i];
+          if (pieces[i] > 1) part_rows += pieces[i] * runs[i].rows;
         }
+        // more than four rounds of pieces: the tail is short by then, a finer cut only adds partial results
+        if (k > 1 && (n_pieces > 4 * kComputeUnits || max_part_rows == 0)) break;
+        if (n_pieces == n_before) continue;                       // the same pieces
+        n_before = n_pieces;
+        double merge = 0.0;
+        if (part_rows > 0) merge = kMergeFixed + 2.0 * (double)part_rows * (double)(p->head_dim + 1) * 4.0 / kPartBytesPerUs;
+        // The work shared evenly is the least any placing takes, and it and the merge only grow with the pieces.
+        if (best > 0.0 && (kept + least + cost.fixed * (double)n_pieces) / kComputeUnits + merge >= best) break;
         if (part_rows > max_part_rows) continue;
-        double t = units.end();
-        if (part_rows > 0) t += kMergeFixed + 2.0 * (double)part_rows * (double)(p->head_dim + 1) * 4.0 / kPartBytesPerUs;
-        if (best == 0.0 || t < best) {
-          best = t;
-          best_rows = tile_rows;
-          best_whole = rounds * kComputeUnits;
-          best_len = len;
-        }
+        const double limit = best > 0.0 ? best - merge : HUGE_VAL;
+        Units units;
+        bool sooner = true;
+        for (int i = 0; i < uncut && sooner; ++i) sooner = units.place(runs[i].items, cost.fixed + cost.tile * runs[i].mean(), limit);
+        for (int i = uncut; i < n_runs && sooner; ++i)
+          sooner = units.place(runs[i].items * pieces[i], cost.fixed + cost.tile * runs[i].mean_piece(pieces[i]), limit);
+        if (!sooner) continue;
+        best = units.end() + merge;
+        best_rows = tile_rows;
+        best_whole = rounds * kComputeUnits;
+        best_of = longest;
+        best_k = k;
       }
     }
   }
@@ -455,13 +468,13 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   for (int i = 0; i < n_runs; ++i) {
     const Run& run = runs[i];
     const Active& of = act[run.active];
-    const int64_t pieces = i < uncut || best_len == 0.0 ? 1 : pieces_of(run, best_len);
+    const int64_t cut = i < uncut || best_of == 0 ? 1 : run.pieces(best_of, best_k);
     t.first[i] = (int32_t)wg;
     t.c[i] = AttnClass{of.req, of.q_off, of.prefix, of.chunk, (int32_t)run.tile_lo, (int32_t)run.tile_hi,
-                       (int32_t)pieces, (int32_t)plan->part_rows};
-    wg += run.items * pieces;
-    if (pieces > 1) plan->part_rows += pieces * run.rows;
-    plan->most_pieces = std::max<int32_t>(plan->most_pieces, (int32_t)pieces);
+                       (int32_t)cut, (int32_t)plan->part_rows};
+    wg += run.items * cut;
+    if (cut > 1) plan->part_rows += cut * run.rows;
+    plan->most_pieces = std::max<int32_t>(plan->most_pieces, (int32_t)cut);
   }
   if (wg > INT32_MAX || plan->part_rows > INT32_MAX) return false;
   for (int i = n_runs; i < kMaxAttnClasses; ++i) {
@@ -473,7 +486,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
 }
 
 bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                 AutoLayout* lay) {
+                 AutoLayout* lay, size_t available) {
   const int32_t s = suggest_kv_splits(p, prefix_lens, new_lens, batch);
   if (s <= 0) return false;
   int64_t total_new = 0;
@@ -481,16 +494,27 @@ bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int3
   const int64_t rows = total_new * p->num_q_heads;
   lay->kv_splits = s;
   lay->list_bytes = list_bytes(p, batch, total_new, s);
-  // a launch of few workgroups may be cut finer than the suggestion goes: at most 64 parts of a row
-  lay->by_classes = plan_classes(p, prefix_lens, new_lens, batch, (s > 1 ? s : 64) * rows, &lay->plan);
-  const int64_t part_rows = s > 1 ? s * rows : lay->by_classes ? lay->plan.part_rows : 0;
-  if (part_rows == 0) {
+  auto place = [&](int64_t part_rows) {
     lay->o_off = lay->lse_off = lay->total = lay->list_bytes;
+    if (part_rows > 0) {
+      lay->o_off = (lay->list_bytes + 255) & ~(size_t)255;
+      lay->lse_off = (lay->o_off + (size_t)part_rows * (size_t)p->head_dim * sizeof(float) + 255) & ~(size_t)255;
+      lay->total = lay->lse_off + (size_t)part_rows * sizeof(float);
+    }
+    lay->room = available >= lay->total;
+  };
+  auto plan_with = [&](int64_t max_part_rows) {
+    lay->by_classes = plan_classes(p, prefix_lens, new_lens, batch, max_part_rows, &lay->plan);
+  };
+  if (s > 1) {
+    place(s * rows);
+    plan_with(lay->room ? s * rows : 0);
     return true;
   }
-  lay->o_off = (lay->list_bytes + 255) & ~(size_t)255;
-  lay->lse_off = (lay->o_off + (size_t)part_rows * (size_t)p->head_dim * sizeof(float) + 255) & ~(size_t)255;
-  lay->total = lay->lse_off + (size_t)part_rows * sizeof(float);
+  // a launch of few workgroups may be cut all the same, and finer: at most 64 parts of a row
+  plan_with(available > lay->list_bytes ? 64 * rows : 0);
+  place(lay->by_classes ? lay->plan.part_rows : 0);
+  if (!lay->room) plan_with(0);
   return true;
 }
 

@@ -95,11 +95,12 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
 struct AutoLayout {
   int32_t kv_splits;
   size_t list_bytes, o_off, lse_off, total;
-  bool by_classes;        // plan says what to launch; false: uniform slices or whole rows from a list
+  bool room;              // the bytes that are available are enough for all of it
+  bool by_classes;        // plan says what to launch (without room: whole rows); false: uniform slices or whole rows from a list
   ClassPlan plan;
 };
 bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                 AutoLayout* lay);
+                 AutoLayout* lay, size_t available = SIZE_MAX);
 
 // arguments of a page copy (pack / unpack and their relatives): a, b source pair, c, d destination pair
 mc_status check_copy(const void* a, const void* b, int64_t num_pages, int64_t page_bytes, const int32_t* ids,

@@ -305,19 +305,16 @@ mc_status attn_one_shot(const mc_attn_params* p, const void* q, const void* k_po
   if (st != MC_OK) return st;
   if (workspace == nullptr || workspace_bytes < list_bytes(p, batch, total_new)) return MC_ERR_WORKSPACE;
   AutoLayout lay;
-  if (!auto_layout(p, prefix_lens, new_lens, batch, &lay)) return MC_ERR_SHAPE;
-  const bool room = workspace_bytes >= lay.total;
-  if (need_room && lay.kv_splits > 1 && !room) return MC_ERR_WORKSPACE;
+  if (!auto_layout(p, prefix_lens, new_lens, batch, &lay, workspace_bytes)) return MC_ERR_SHAPE;
+  if (need_room && lay.kv_splits > 1 && !lay.room) return MC_ERR_WORKSPACE;
   char* ws = reinterpret_cast<char*>(workspace);
   float* o_parts = reinterpret_cast<float*>(ws + lay.o_off);
   float* lse_parts = reinterpret_cast<float*>(ws + lay.lse_off);
-  if (lay.by_classes) {
-    if (!room && lay.plan.most_pieces > 1 && !plan_classes(p, prefix_lens, new_lens, batch, 0, &lay.plan)) return MC_ERR_RANGE;
+  if (lay.by_classes)
     return launch_class_plan(p, lay.plan, q, k_pool, v_pool, block_tables, max_pages_per_req, out, lse, o_parts,
                              lse_parts, reinterpret_cast<hipStream_t>(hip_stream));
-  }
   // more requests than a launch has classes for: from a list
-  if (lay.kv_splits == 1 || !room)
+  if (lay.kv_splits == 1 || !lay.room)
     return attn_enqueue(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, out, lse,
                         0, nullptr, nullptr, workspace, workspace_bytes, hip_stream);
   st = attn_enqueue(p, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens, new_lens, batch, nullptr,

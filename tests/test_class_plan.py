@@ -1,6 +1,7 @@
 """The classes a one-shot attention call of a small batch is described with (csrc/host_plan.cpp: plan_classes; no GPU):
 every row tile of every (request, KV head) once, partial rows disjoint and inside the room given, launch order."""
 import os
+import random
 import subprocess
 
 import pytest
@@ -97,3 +98,19 @@ SAME_ROWS = [
 def test_prepared_lists_take_the_row_tiles_of_an_uncut_call(driver, Hq, Hkv, D, dtype, prefix, new):
     p = plan(driver, Hq, Hkv, D, dtype, 0, prefix, new)
     assert p["most_pieces"] == 1 and p["list_rows"] == p["rows"]
+
+
+def test_planning_dozens_of_requests_costs_about_what_their_list_costs(tmp_path):
+    """A one-shot call plans its cut every time, and dozens of short requests are over in tens of microseconds.  Both batches
+    together: the plan takes about 3 times as long as the list; a search that places every trial took 14 times."""
+    exe = str(tmp_path / "plan_time_driver")
+    subprocess.run(["g++", "-O3", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", exe,
+                    os.path.join(ROOT, "tests", "plan_time_driver.cpp"), os.path.join(CSRC, "host_plan.cpp")], check=True)
+    rng = random.Random(4)
+    lines = []
+    for most_prefix, most_new in ((40000, 300), (2000, 1)):
+        prefix, new = [rng.randrange(most_prefix) for _ in range(63)], [rng.randint(1, most_new) for _ in range(63)]
+        lines.append(" ".join(str(x) for x in [8, 1, 128, 0, 63, *prefix, *new]))
+    out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout
+    plan_us, list_us = (sum(float(x) for x in out.split()[at::2]) for at in (0, 1))
+    assert plan_us <= 7 * list_us, (plan_us, list_us)
