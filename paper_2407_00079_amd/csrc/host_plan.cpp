@@ -518,6 +518,16 @@ bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int3
   return true;
 }
 
+// One launch saves 3 us; what it costs is that a request's digests share one compute unit.  They are bound by its vector
+// ALUs, so tokens decide, unless there are so few blocks that each has a SIMD to itself (as it has when the whole chip
+// digests).  One launch / digests and chains apart, us, one request: 32 blocks of 512 tokens 7.9 / 8.2, of 768 9.8 / 8.2, of
+// 4096 24.8 / 10.4, of 16384 82.1 / 20.4; 16 blocks of 1024 6.0 / 8.1, of 2048 8.5 / 8.0; 4 blocks of 16384 14.8 / 17.5, 6 of
+// them 23.4 / 18.2; 8 and 64 such requests alike.
+bool hash_in_one_launch(int64_t max_blocks, int64_t max_tokens) {
+  constexpr int64_t kShortTokens = 20 << 10, kSimds = 4;
+  return max_blocks <= kShortHashBlocks && (max_tokens <= kShortTokens || max_blocks <= kSimds);
+}
+
 mc_status check_copy(const void* a, const void* b, int64_t num_pages, int64_t page_bytes, const int32_t* ids,
                      int64_t n, const void* c, const void* d) {
   if (num_pages < 0 || page_bytes < 0 || n < 0) return MC_ERR_SHAPE;

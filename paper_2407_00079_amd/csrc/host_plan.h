@@ -102,6 +102,10 @@ struct AutoLayout {
 bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                  AutoLayout* lay, size_t available = SIZE_MAX);
 
+// Whether the prefix keys of a batch are made by one workgroup per request in one launch: most blocks and most tokens of
+// any request.
+bool hash_in_one_launch(int64_t max_blocks, int64_t max_tokens);
+
 // arguments of a page copy (pack / unpack and their relatives): a, b source pair, c, d destination pair
 mc_status check_copy(const void* a, const void* b, int64_t num_pages, int64_t page_bytes, const int32_t* ids,
                      int64_t n, const void* c, const void* d);

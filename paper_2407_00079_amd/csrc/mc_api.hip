@@ -640,13 +640,14 @@ mc_status mc_prefix_hash(const int32_t* tokens, const int64_t* tok_offsets, int3
   if (batch == 0) return MC_OK;
   if (tok_offsets == nullptr) return MC_ERR_NULL;
   std::vector<int64_t> key_off((size_t)batch + 1);
-  int64_t max_blocks = 0;
+  int64_t max_blocks = 0, max_tokens = 0;
   for (int32_t r = 0; r < batch; ++r) {
     const int64_t len = tok_offsets[r + 1] - tok_offsets[r];
     if (len < 0 || tok_offsets[r] < 0) return MC_ERR_SHAPE;
     const int64_t blocks = (len + block_tokens - 1) / block_tokens;
     key_off[r + 1] = key_off[r] + blocks;
     max_blocks = blocks > max_blocks ? blocks : max_blocks;
+    max_tokens = len > max_tokens ? len : max_tokens;
   }
   const int64_t total_blocks = key_off[batch];
   if (total_blocks == 0) return MC_OK;
@@ -661,7 +662,9 @@ mc_status mc_prefix_hash(const int32_t* tokens, const int64_t* tok_offsets, int3
   mc::PrefixTables tables;
   const mc_status st = place_tables(tok_offsets, (size_t)batch + 1, key_off.data(), (size_t)batch + 1, workspace, stream, &arg, &tables);
   if (st != MC_OK) return st;
-  if (mc::launch_prefix_hash(tokens, tables, batch, block_tokens, max_blocks, total_blocks, keys, stream) != hipSuccess) return MC_ERR_HIP;
+  if (mc::launch_prefix_hash(tokens, tables, batch, block_tokens, max_blocks, total_blocks,
+                             hash_in_one_launch(max_blocks, max_tokens), keys, stream) != hipSuccess)
+    return MC_ERR_HIP;
   return MC_OK;
 }
 

@@ -77,9 +77,10 @@ struct PrefixTables {
 };
 
 // enqueue the kernels that turn tokens into keys (tables: token offsets, key offsets; max_blocks = most blocks of any
-// request, total_blocks = all of them)
+// request, total_blocks = all of them, in_one_launch: no request has more than kShortHashBlocks and it pays)
 hipError_t launch_prefix_hash(const int32_t* tokens, const PrefixTables& tables, int batch, int block_tokens,
-                              int64_t max_blocks, int64_t total_blocks, uint64_t* keys, hipStream_t stream);
+                              int64_t max_blocks, int64_t total_blocks, bool in_one_launch, uint64_t* keys,
+                              hipStream_t stream);
 
 // enqueue the prefix match over batch requests and n_inst instances (tables: key offsets, cache offsets; max_keys = most
 // keys of any request)

@@ -61,6 +61,9 @@ struct OffsetTables {
   int64_t a[kMaxArgEntries + 1], b[kMaxArgEntries + 1];
 };
 
+// most blocks of a request whose keys one workgroup makes in one launch (its digests go through LDS)
+constexpr int kShortHashBlocks = 32;
+
 // rows of stacked queries one attention workgroup covers (8 waves of 32 rows, both dtypes)
 constexpr int kAttnTileRows = 256;
 // ... and of the form for launches whose row tiles are few or short: 4 waves compute (one per SIMD), 4 copy tiles

@@ -98,12 +98,10 @@ __device__ __forceinline__ void chain_range(const uint64_t* from, uint64_t* to, 
   }
 }
 
-constexpr int kShortBlocks = 32;       // most blocks of a request the short kernel takes (see hash_with)
-
 template <typename Tables>     // a: token offsets, b: key offsets
 __global__ __launch_bounds__(1024) void prefix_short_kernel(const int32_t* __restrict__ tokens, const Tables off, int batch,
                                                             int block_tokens, uint64_t* __restrict__ keys) {
-  __shared__ uint64_t digests[kShortBlocks];
+  __shared__ uint64_t digests[kShortHashBlocks];
   const int lane = threadIdx.x & 63;
   for (int r = blockIdx.x; r < batch; r += gridDim.x) {
     const int64_t k0 = off.b[r], t0 = off.a[r], len = off.a[r + 1] - t0;
@@ -294,18 +292,20 @@ __global__ __launch_bounds__(256) void prefix_best_kernel(const int32_t* __restr
 
 namespace {
 
-// Costs the split of a queue of long prompts rests on (512-token blocks, measured): one link of a chain, and the digest of
-// one block when the whole chip digests.  A rough figure does: the line only moves work between launches.
+// Costs the split of a queue of long prompts rests on: one link of a chain, and the digest of one block when the whole chip
+// digests - of 512 tokens, and of fewer about as much (a workgroup's start and the sum across the wave).  A rough figure does:
+// the line only moves work between launches.  64 prompts, as split here / not at all / best of eleven splits, us: 1024 blocks
+// of 16 tokens 92.5 / 101.9 / 91.7, 512 of 64 49.7 / 53.0 / 49.4, 256 of 512 31.3 / 32.7 / 30.4, 128 of 1024 22.6 / 21.5 /
+// 21.1, 64 of 2048 (not split) 16.0 / 15.9 / 15.9.
 constexpr double kChainNs = 95.0, kDigestNs = 0.64;
 
 template <typename Tables>
 hipError_t hash_with(const int32_t* tokens, const Tables& off, int batch, int block_tokens, int64_t max_blocks,
-                     int64_t total_blocks, uint64_t* keys, hipStream_t stream) {
+                     int64_t total_blocks, bool in_one_launch, uint64_t* keys, hipStream_t stream) {
   const unsigned cols = batch < 65535 ? (unsigned)batch : 65535u;          // the kernels stride over the rest
-  // Few blocks per request: one launch.  On one compute unit a block's digest takes 0.16 us, so beyond 32 of them (two
-  // turns of the 16 waves) the chip-wide digests win back what their own launch costs.  14 blocks: 3.0 + 3.5 us and a
-  // launch between them, now 5.0 us; keys and match of that prompt 18.2 -> 14.8 us a pass.
-  if (max_blocks <= kShortBlocks) {
+  // Few blocks and tokens per request: one launch.  14 blocks of 512 tokens: 3.0 + 3.5 us and a launch between them, now
+  // 5.0 us; keys and match of that prompt 18.2 -> 14.8 us a pass.
+  if (in_one_launch && max_blocks <= kShortHashBlocks) {
     const unsigned waves = max_blocks < 16 ? (unsigned)max_blocks : 16u;
     prefix_short_kernel<Tables><<<cols, waves * 64, 0, stream>>>(tokens, off, batch, block_tokens, keys);
     return hipGetLastError();
@@ -353,10 +353,12 @@ hipError_t match_with(const uint64_t* keys, const Tables& off, int batch, int64_
 }  // namespace
 
 hipError_t launch_prefix_hash(const int32_t* tokens, const PrefixTables& tables, int batch, int block_tokens,
-                              int64_t max_blocks, int64_t total_blocks, uint64_t* keys, hipStream_t stream) {
+                              int64_t max_blocks, int64_t total_blocks, bool in_one_launch, uint64_t* keys,
+                              hipStream_t stream) {
   (void)hipGetLastError();
-  if (tables.arg != nullptr) return hash_with(tokens, *tables.arg, batch, block_tokens, max_blocks, total_blocks, keys, stream);
-  return hash_with(tokens, TablePtrs{tables.a, tables.b}, batch, block_tokens, max_blocks, total_blocks, keys, stream);
+  if (tables.arg != nullptr)
+    return hash_with(tokens, *tables.arg, batch, block_tokens, max_blocks, total_blocks, in_one_launch, keys, stream);
+  return hash_with(tokens, TablePtrs{tables.a, tables.b}, batch, block_tokens, max_blocks, total_blocks, in_one_launch, keys, stream);
 }
 
 hipError_t launch_prefix_match(const uint64_t* keys, const PrefixTables& tables, int batch, int64_t max_keys,

@@ -112,6 +112,15 @@ static void test_rejections() {
   EXPECT(!auto_layout(&p, neg, C2, 1, &lay));
 }
 
+// Prefix keys in one launch: by blocks, and by tokens where blocks share a SIMD.
+static void test_hash_rule() {
+  EXPECT(hash_in_one_launch(1, 1) && hash_in_one_launch(14, 6955) && hash_in_one_launch(32, 32 * 512));
+  EXPECT(!hash_in_one_launch(33, 33 * 16) && !hash_in_one_launch(256, 131072));
+  EXPECT(hash_in_one_launch(32, 20480) && !hash_in_one_launch(32, 20481));
+  EXPECT(!hash_in_one_launch(32, 32 * 4096) && !hash_in_one_launch(8, 8 * 16384));      // blocks of many tokens
+  EXPECT(hash_in_one_launch(4, 4 * 16384) && !hash_in_one_launch(5, 5 * 16384));
+}
+
 // The slot bookkeeping, driven the way the staging ring drives it: `done` stands in for hipEventQuery.
 static void test_slot_ring() {
   SlotRing ring;
@@ -225,6 +234,7 @@ static int run_plans() {
 int main(int argc, char** argv) {
   if (argc > 1 && std::string(argv[1]) == "plan") return run_plans();
   test_rejections();
+  test_hash_rule();
   test_slot_ring();
   if (failures == 0) std::printf("selftest ok\n");
   return failures == 0 ? 0 : 1;

@@ -35,6 +35,19 @@ def test_keys_match_oracle(oracle, blocks):
     np.testing.assert_array_equal(gpu_keys(tokens, off, BT), ref)
 
 
+@pytest.mark.parametrize("block,lens", [
+    (640, [20480, 3, 0, 641]), (640, [20480, 20481]),                   # 32 blocks of one launch, and a token too many
+    (8192, [4 * 8192, 8192, 1]), (8192, [4 * 8192 + 1]),                # a SIMD for every block, and a block too many
+    (4096, [32 * 4096 - 7, 4096]), (1 << 20, [100, 0, 5000]),
+])
+def test_keys_of_long_blocks_match_oracle(oracle, block, lens):
+    print(f"prefix long blocks case block={block} lens={lens}", flush=True)
+    tokens = np.random.default_rng(block).integers(-5, 128000, size=sum(lens), dtype=np.int32)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    ref, _ = oracle.prefix_hash(tokens, off, block)
+    np.testing.assert_array_equal(gpu_keys(tokens, off, block), ref)
+
+
 def _caches(rng):
     top = (1 << 64) - 1
     yield np.zeros(0, dtype=np.uint64)
