@@ -179,6 +179,8 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
   const int64_t n_items = count_items(p, new_lens, batch);
   if (batch > kMaxBatch || n_items > kMaxItems) return MC_ERR_RANGE;   // beyond the fixed scratch array
 
+  // looked up by the first call whatever its size: a warm-up with a small batch prepares the capture of a large one
+  char* base = reinterpret_cast<char*>(scratch_of_current_device());
   ClassPlan plan;
   if (plan_classes(p, prefix_lens, new_lens, batch, 0, &plan)) {
     // few enough requests to travel as a kernel argument: no list at all
@@ -200,7 +202,6 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
                ? MC_OK : MC_ERR_HIP;
   }
 
-  char* base = reinterpret_cast<char*>(scratch_of_current_device());
   if (base == nullptr) return MC_ERR_HIP;
   AttnItem* items = reinterpret_cast<AttnItem*>(base);
   AttnReq* reqs = reinterpret_cast<AttnReq*>(base + kReqsOffset);

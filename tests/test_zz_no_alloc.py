@@ -1,6 +1,9 @@
 """mc_prefill_attn_paged_noalloc (work list built on the device in the library's fixed array: no workspace,
 no allocation, no upload) against mc_prefill_attn_paged, through the C ABI, on calls in a row that share the array."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -11,6 +14,7 @@ from paper_2407_00079_amd import workloads as W
 from gpu_util import DeviceCase, check_close, TOL
 
 pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def run_both(case):
@@ -62,6 +66,33 @@ def test_bf16_head_dim_64(oracle):
     same(d, want_o, want_l, W.BF16, "bf16, head_dim 64")
     ref, lse_ref, _ = oracle.case_full(case)
     check_close(d.out.float().cpu().numpy().astype(np.float64), ref, W.BF16, "bf16 head_dim 64 against the oracle")
+
+
+LOOKUP = """
+import os, torch
+from paper_2407_00079_amd import binding as B
+p = B.attn_params(2, 1, 128, 16, 128, "bf16")
+pool = torch.zeros(128, 1, 16, 128, dtype=torch.bfloat16, device="cuda:0")
+for batch in (1, 70):
+    q = torch.zeros(batch, 2, 128, dtype=torch.bfloat16, device="cuda:0")
+    table = torch.arange(batch, dtype=torch.int32, device="cuda:0").reshape(batch, 1)
+    torch.cuda.synchronize()
+    os.write(2, b"\\n<call of %d>\\n" % batch)
+    B.mc_prefill_attn_paged_noalloc(p, q, pool, pool, table, [0] * batch, [1] * batch, torch.empty_like(q), None)
+    torch.cuda.synchronize()
+os.write(2, b"\\n<end>\\n")
+"""
+
+
+def test_the_first_call_looks_the_array_up_whatever_its_size():
+    """A program warms up outside stream capture with whatever batch it has: the runtime calls of a later, larger one (the
+    first that needs the array) must not include the lookup.  Read from the runtime's own log of its API calls."""
+    env = dict(os.environ, AMD_LOG_LEVEL="3", AMD_LOG_MASK="1")
+    res = subprocess.run([sys.executable, "-c", LOOKUP], cwd=ROOT, env=env, capture_output=True, text=True, timeout=100)
+    assert res.returncode == 0, res.stderr[-2000:]
+    small, large = res.stderr.split("<call of 1>")[1].split("<end>")[0].split("<call of 70>")
+    assert "hipLaunchKernel" in small and "hipLaunchKernel" in large
+    assert "hipGetSymbolAddress" in small and "hipGetSymbolAddress" not in large
 
 
 def test_limits_and_noops():
