@@ -1,5 +1,6 @@
-"""mc_prefill_attn_paged_noalloc (work list built on the device in the library's fixed array: no workspace,
-no allocation, no upload) against mc_prefill_attn_paged, through the C ABI, on calls in a row that share the array."""
+"""mc_prefill_attn_paged_noalloc (no workspace, no allocation, no upload) against mc_prefill_attn_paged, through the C ABI.
+These batches travel as a kernel argument; test_gpu_large_batches.py has those whose work list is built on the device in the
+library's fixed array."""
 import ctypes
 import os
 import subprocess
@@ -33,15 +34,14 @@ def run_both(case):
 def same(d, want_o, want_l, dtype, what):
     got_o, got_l = d.out, d.lse
     assert torch.isfinite(got_o.float()).all() and torch.isfinite(got_l).all(), what
-    # the same kernel over the same work list: bit-identical; the tolerance of the parity tests is the bar
+    # the same kernel over the same row tiles: bit-identical; the tolerance of the parity tests is the bar
     check_close(got_o.float().cpu().numpy().astype(np.float64), want_o.float().cpu().numpy().astype(np.float64), dtype, what)
     assert float((got_l - want_l).abs().max()) <= TOL[dtype]["lse_abs"], what
     assert torch.equal(got_o, want_o) and torch.equal(got_l, want_l), what
 
 
 def test_two_calls_in_a_row_second_smaller(oracle):
-    # a ragged batch of five requests (several tiles per head, one empty request), then a smaller one: the second call
-    # finds the first call's longer list in the array and must not run any of it
+    # a ragged batch of five requests (several tiles per head, one empty request), then a smaller one
     big = W.make_attn_case(101, W.BF16, 32, 4, 128, 16, [700, 0, 33, 1500, 260], [300, 77, 0, 130, 1], 512)
     small = W.make_attn_case(102, W.BF16, 32, 4, 128, 16, [40], [19], 512)
     for case, name in ((big, "first call"), (small, "second, smaller call")):
