@@ -234,10 +234,10 @@ mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, const void* q, 
  *                   ordered after the prepare call (same stream, or an event)
  *   plan       HOST out: plain data the run calls take back; valid with these params only
  *
- * The run calls compute exactly what mc_prefill_attn_paged / mc_prefill_attn_paged_split /
- * mc_kv_append_paged compute for the lengths the plan was prepared with (those calls are
- * prepare + run in one), with the same argument rules; block tables need at least
- * plan->need_pages columns.  A plan for no new tokens is empty and its runs enqueue nothing.
+ * The run calls compute exactly what mc_prefill_attn_paged with the minimal workspace (whole
+ * rows) / mc_prefill_attn_paged_split / mc_kv_append_paged compute for the lengths the plan was
+ * prepared with, with the same argument rules; block tables need at least plan->need_pages
+ * columns.  A plan for no new tokens is empty and its runs enqueue nothing.
  * mc_kv_append_run takes either form of plan.
  */
 typedef struct {

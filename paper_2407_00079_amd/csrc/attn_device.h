@@ -63,7 +63,7 @@ struct Work {
   int32_t req, kv_head, row0, q_off, prefix, chunk;
   int32_t piece, pieces;
   int64_t part_row;
-  bool once;                             // every K and V row of the launch is read once and they outgrow the caches
+  bool once;                             // K and V are streamed (AttnClasses::once)
 };
 
 // list launches; workgroups n_items .. take the second halves of the items' row tiles (few rows only)

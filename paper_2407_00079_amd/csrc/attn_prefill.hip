@@ -122,10 +122,11 @@ struct F32 {
 // ---------------------------------------------------------------------------
 // kernel
 // ---------------------------------------------------------------------------
-// SPLIT: the work item covers only slice work.slice of the request's keys (whole 64-key tiles,
-// ceil(tiles / kv_splits) per slice) and writes a PARTIAL result - the normalised fp32 output
-// over its keys and their log-sum-exp (-inf where the slice holds no key the row may see) - for
-// mc_attn_merge_lse to combine (paper Section 5.1: attention is associative over key slices).
+// FORM kSlices: the work covers only slice work.piece of the request's keys (whole 64-key tiles,
+// ceil(tiles / kv_splits) per slice); kClasses: piece work.piece of work.pieces of the key tiles its row tile sees.  A row
+// tile that is not done whole gives a PARTIAL result - the normalised fp32 output over its keys and their log-sum-exp (-inf
+// where they hold none the row may see) - for the merge to combine (paper Section 5.1: attention is associative over key
+// slices).
 template <class T, Rows ROWS, Form FORM>
 __device__ __forceinline__ void attn_body(const AttnArgs& a, const Work& work) {
   constexpr bool SPLIT = FORM != kWhole;       // the result may be partial

@@ -31,10 +31,13 @@
 //     score MFMAs of block j+1, row tile 0 of block j+1 under the P V MFMAs of block j.  The row
 //     sums of the rounded probabilities come from two more MFMAs per block (ones x P^T), and the
 //     guard of the lazy reference is an OR over the packed probabilities (see kRefLift).
-//   * What bounds it: the board's power limit.  7.6 % fewer cycles (128k-context shape, all-zero
-//     operands, which run at the full clock: 2.58 -> 2.40 ms) came out as 1.3 % less time on random
-//     operands (3.20 -> 3.16 ms = 1.35 PFLOP/s): the clock falls as the stream gets denser.  A large
-//     bf16 matrix product of the vendor library reaches 1.46-1.57 PFLOP/s on the same operands.
+//   * What bounds it at head_dim 128: the board's power limit.  7.0 % less time on all-zero operands,
+//     which run at the full clock (128k-context shape, 2.58 -> 2.40 ms; 6.1 % fewer cycles by the
+//     counters), came out as 1.3 % less on random ones (3.20 -> 3.16 ms): the clock falls as the stream
+//     gets denser.  On one board: 1.36-1.37 PFLOP/s, where a large bf16 matrix product of the vendor
+//     library reaches 1.37-1.40; on zeros both reach 1.78-1.80.
+//   * At head_dim 64: the same vector work per block against half the MFMAs, 2.7 vector instructions
+//     per MFMA where two are hidden; the matrix pipe is busy 50.5 % of the cycles (1.02 PFLOP/s).
 #include <type_traits>
 
 #include "attn_device.h"

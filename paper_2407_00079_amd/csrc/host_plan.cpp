@@ -147,10 +147,14 @@ bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, i
   return true;
 }
 
-// One row tile per head reads every K and V row once.  If they outgrow the last-level cache, the next layer finds none of
-// them there anyway, and a hint that they need not be kept helps: 16 tokens at 128k (64/8 heads, 537 MB) 106.5 us a
-// call without it, 97 with it.  What would stay in the cache is better left there (8192 + 16 tokens, 34 MB, the same call
-// repeated: 21.5 us without the hint, 23.6 with it).
+// One row tile per head reads each of its request's K and V rows once.  If they outgrow the last-level cache, the next layer
+// finds none of them there anyway, and a hint that they need not be kept helps.  What would stay in the cache is better left
+// there.  64/8 heads, the same call repeated, us without / with the hint: 16 tokens behind 51k (210 MB) 44.7 / 48.3, 61k 51 / 54,
+// 74k (302 MB) 61 / 61, 82k 70 / 66, 98k 84 / 76, 128k 107 / 97; 16 requests behind 3840 each (252 MB) 51 / 53, 5120 73 / 66,
+// 16k 201 / 178.
+// Requests may share pages, which the host does not see: they are counted as if they were apart.  Those that do read them at
+// about the same time and find them in the caches either way: 16 requests on one 16k document 127 / 128, 32 on 8k 121 / 121,
+// 8 on 32k 129 / 129, 2 on 128k 148 / 149; the one clear loss of the shapes tried is 32 on 32k with 8/1 heads, 71.6 / 73.5.
 bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                 int64_t tile_rows) {
   constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;

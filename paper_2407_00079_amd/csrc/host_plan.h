@@ -53,8 +53,8 @@ void build_work_list(const mc_attn_params* p, const int32_t* prefix_lens, const 
 // number of whole-row work items of a batch (the size of the list build_work_list makes for kv_splits == 0)
 int64_t count_items(const mc_attn_params* p, const int32_t* new_lens, int32_t batch);
 
-// Every request's stacked rows of a KV head fit one row tile; and then, whether the K and V rows a launch reads (once each)
-// outgrow the last-level cache.
+// Every request's stacked rows of a KV head fit one row tile; and then, whether the K and V rows the requests read outgrow
+// the last-level cache.
 bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
 bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
 

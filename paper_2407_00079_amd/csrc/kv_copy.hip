@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kThreads) void kv_copy_kernel(const u32x4* __restri
 // through LDS in chunks: O(n^2) compares, meant to be run once per request - the list is the same
 // for every layer.  LANES threads share a position, each counting every LANES-th group of four
 // keys, so that short lists fill the chip too (2048 ids: 8 workgroups and 26 us with one thread a
-// position, 128 and about 7 us with 16).  Slots past the end of the list hold the largest id at
+// position, 128 and 5 us with 16).  Slots past the end of the list hold the largest id at
 // positions behind all others and count nothing.
 constexpr int kOrderChunk = 1024;
 template <int LANES>

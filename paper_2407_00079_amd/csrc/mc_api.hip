@@ -655,7 +655,7 @@ mc_status mc_prefix_hash(const int32_t* tokens, const int64_t* tok_offsets, int3
   if (!aligned4(tokens) || (reinterpret_cast<uintptr_t>(keys) & 7u) ||
       !aligned16(workspace))
     return MC_ERR_ALIGN;
-  if (max_blocks > (1 << 26) - 8) return MC_ERR_RANGE;   // four blocks per workgroup along grid x
+  if (max_blocks > (1 << 26) - 8) return MC_ERR_RANGE;   // the interface's limit (the kernels stride over blocks)
   if (workspace == nullptr || workspace_bytes < mc_prefix_hash_workspace_bytes(batch)) return MC_ERR_WORKSPACE;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
   mc::OffsetTables arg = {};

@@ -42,7 +42,7 @@ constexpr int kMaxAttnClasses = 64;          // one lane of a wave each when a w
 struct AttnClasses {
   int32_t n;
   int32_t rows;                              // stacked rows of a row tile: kAttnTileRows or kAttnFewRows
-  int32_t once;                              // K and V are read once and outgrow the caches
+  int32_t once;                              // K and V are streamed: one row tile per head, more bytes than the caches hold
   int32_t first[kMaxAttnClasses];            // first workgroup of each class (of the attention launch or of the merge)
   AttnClass c[kMaxAttnClasses];
 };
