@@ -266,6 +266,9 @@ TileCost tile_cost_of(const mc_attn_params* p, int64_t tile_rows) {
 }
 // the merge launch, and bytes of partial results written and read per microsecond
 constexpr double kMergeFixed = 4.0, kPartBytesPerUs = 3.0e6;
+double merge_time(const mc_attn_params* p, int64_t part_rows) {
+  return part_rows > 0 ? kMergeFixed + 2.0 * (double)part_rows * (double)(p->head_dim + 1) * 4.0 / kPartBytesPerUs : 0.0;
+}
 
 // A set of row tiles of one request: `items` workgroups if uncut, of `shortest` to `longest` key tiles.
 struct Run {
@@ -328,6 +331,34 @@ class Units {
   int64_t count_[kGroups] = {kComputeUnits};
   double end_ = 0.0;
 };
+
+// When a launch really ends.  Workgroup i goes to XCD i % 8 and there to shader engine (i / 8) % 4, whatever else is free: 32
+// queues of 8 compute units, and only inside a queue to the unit that is free first.  (One workgroup a unit, spinning for
+// given times, us measured / by this rule / by handing each to the first free unit of the chip: 10 of 1330, 246 of 900-960,
+// 236 of 430: 1761 / 1760 / 1388; 256 and 236: 1391 / 1390 / 1385; 354 of 290 instead of 236: 1520 / 1519 / 1506.)
+class Queues {
+ public:
+  // n workgroups next in launch order
+  void place(int64_t n, double dur) {
+    for (; n > 0; --n) {
+      double* t = t_[next_];
+      next_ = (next_ + 1) % kQueues;
+      int at = 0;
+      for (int u = 1; u < kUnits; ++u) at = t[u] < t[at] ? u : at;
+      t[at] += dur;
+      end_ = t[at] > end_ ? t[at] : end_;
+    }
+  }
+  double end() const { return end_; }
+
+ private:
+  static constexpr int kQueues = 32, kUnits = (int)kComputeUnits / kQueues;
+  double t_[kQueues][kUnits] = {{0.0}};
+  int next_ = 0;
+  double end_ = 0.0;
+};
+// how much sooner the plain cut has to end to be taken instead
+constexpr double kPlainSlack = 1.02;
 
 int64_t key_tiles(int64_t prefix, int64_t chunk, int64_t G, int64_t row_tile, int64_t tile_rows) {
   const int64_t last = std::min<int64_t>(chunk - 1, (row_tile * tile_rows + tile_rows - 1) / G);
@@ -441,8 +472,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         if (k > 1 && (n_pieces > 4 * kComputeUnits || max_part_rows == 0)) break;
         if (n_pieces == n_before) continue;                       // the same pieces
         n_before = n_pieces;
-        double merge = 0.0;
-        if (part_rows > 0) merge = kMergeFixed + 2.0 * (double)part_rows * (double)(p->head_dim + 1) * 4.0 / kPartBytesPerUs;
+        const double merge = merge_time(p, part_rows);
         // The work shared evenly is the least any placing takes, and it and the merge only grow with the pieces.
         if (best > 0.0 && (kept + least + cost.fixed * (double)n_pieces) / kComputeUnits + merge >= best) break;
         if (part_rows > max_part_rows) continue;
@@ -459,6 +489,50 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         best_of = longest;
         best_k = k;
       }
+    }
+  }
+  // The estimate hands every workgroup to the first free unit of the chip.  Where whole rounds are followed by a cut rest, the
+  // launch is also followed by where workgroups really go, beside the plain one: every row tile in as many pieces as
+  // suggest_kv_splits gives.  Behind a few long row tiles the rest may end later than that: P 55245, C 155 and P 33667, C 5816,
+  // 16/2 heads, us: a round whole and the rest in halves (estimated sooner) 1604, all rows in halves 1487; fp32, 8/1 heads, C
+  // 5575 and 3868 behind P 268 and 68 737, 507; C 6227, 12/3 heads 775, 561.  Of 66 batches it decides, most fp32, 44 gain up to
+  // 45 % where the plain one is ahead by the slack or more, and none loses.
+  if (best_k > 1 && best_whole > 0) {
+    // `limit` and more: as late as that or later
+    auto really_ends = [&](int64_t whole, int64_t tile_rows, int64_t of, int64_t k, double limit) {
+      const int uncut = lay_out(whole, tile_rows);
+      const TileCost cost = tile_cost_of(p, tile_rows);
+      int64_t part_rows = 0;
+      double work = 0.0;
+      for (int i = 0; i < n_runs; ++i) {
+        pieces[i] = i < uncut ? 1 : runs[i].pieces(of, k);
+        if (pieces[i] > 1) part_rows += pieces[i] * runs[i].rows;
+        work += (double)runs[i].items * ((double)pieces[i] * cost.fixed + cost.tile * runs[i].mean());
+      }
+      const double merge = merge_time(p, part_rows);
+      if (part_rows > max_part_rows || work / kComputeUnits + merge >= limit) return limit;
+      Queues queues;
+      for (int i = 0; i < n_runs; ++i) {
+        const Active& a = act[runs[i].active];
+        for (int64_t t = runs[i].tile_hi; t >= runs[i].tile_lo; --t) {
+          const int64_t tiles = key_tiles(a.prefix, a.chunk, G, t, tile_rows);
+          for (int64_t j = 0; j < pieces[i]; ++j)
+            queues.place(Hkv, cost.fixed + cost.tile * (double)(tiles / pieces[i] + (j < tiles % pieces[i] ? 1 : 0)));
+          if (queues.end() + merge >= limit) return limit;
+        }
+      }
+      return queues.end() + merge;
+    };
+    const double end = really_ends(best_whole, best_rows, best_of, best_k, HUGE_VAL) / kPlainSlack;
+    const int32_t plain = suggest_kv_splits(p, prefix_lens, new_lens, batch);
+    lay_out(0, kAttnTileRows);
+    int64_t longest = 0;
+    for (int i = 0; i < n_runs; ++i) longest = std::max(longest, runs[i].longest);
+    if (really_ends(0, kAttnTileRows, longest, plain, end) < end) {
+      best_whole = 0;
+      best_rows = kAttnTileRows;
+      best_of = longest;
+      best_k = plain;
     }
   }
   const int uncut = lay_out(best_whole, best_rows);

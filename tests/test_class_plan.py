@@ -1,5 +1,6 @@
 """The classes a one-shot attention call of a small batch is described with (csrc/host_plan.cpp: plan_classes; no GPU):
 every row tile of every (request, KV head) once, partial rows disjoint and inside the room given, launch order."""
+import heapq
 import os
 import random
 import subprocess
@@ -98,6 +99,52 @@ SAME_ROWS = [
 def test_prepared_lists_take_the_row_tiles_of_an_uncut_call(driver, Hq, Hkv, D, dtype, prefix, new):
     p = plan(driver, Hq, Hkv, D, dtype, 0, prefix, new)
     assert p["most_pieces"] == 1 and p["list_rows"] == p["rows"]
+
+
+def launch_end(workgroups):
+    """Workgroup i goes to XCD i % 8 and there to shader engine (i / 8) % 4: 32 queues of 8 compute units."""
+    ends = []
+    for q in range(32):
+        units = [0.0] * 8
+        for us in workgroups[q::32]:
+            heapq.heapreplace(units, units[0] + us)
+        ends.append(max(units))
+    return max(ends)
+
+
+def time_of(Hq, Hkv, D, dtype, rows, classes):
+    """The launch by where its workgroups go, every row tile with its own key tiles, at the costs the plan weighs by, and the
+    merge.  classes: (prefix, chunk, tile_lo, tile_hi, pieces)."""
+    G = Hq // Hkv
+    tile = (3.6 if rows == FEW_ROWS else 7.0) if dtype else (1.2 if rows == FEW_ROWS else 1.65)
+    workgroups, parts = [], 0
+    for prefix, chunk, lo, hi, pieces in classes:
+        if pieces > 1:
+            parts += pieces * Hkv * (min(chunk * G, (hi + 1) * rows) - lo * rows)
+        for t in range(hi, lo - 1, -1):
+            n = -(-(prefix + min(chunk - 1, (t * rows + rows - 1) // G) + 1) // KEYS)
+            for j in range(pieces):
+                workgroups += [4.0 + tile * (n // pieces + (j < n % pieces))] * Hkv
+    return launch_end(workgroups) + (4.0 + 2 * parts * (D + 1) * 4 / 3e6 if parts else 0.0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,dtype,prefix,new,splits", [
+    (16, 2, 128, 0, [55245, 33667], [155, 5816], 2),          # ten long row tiles before the rest
+    (8, 1, 64, 1, [243, 28, 268, 68], [5, 1, 5575, 3868], 6),
+    (12, 3, 64, 1, [0], [6227], 6),
+    (12, 3, 64, 1, [632, 140, 2277], [4887, 25, 1527], 5),
+    (8, 1, 64, 1, [0, 82], [5111, 35], 3),
+    (64, 8, 128, 0, [6144, 6144], [811, 328], 6),             # here the cut of the rest stays
+])
+def test_a_cut_rest_is_not_later_than_the_plain_cut(driver, Hq, Hkv, D, dtype, prefix, new, splits):
+    """suggest_kv_splits pieces (`splits`) of every row tile: what such a call ran before only the rest was cut."""
+    G, total = Hq // Hkv, sum(new)
+    p = plan(driver, Hq, Hkv, D, dtype, splits * total * Hq, prefix, new)
+    chosen = [tuple(c[k] for k in ("prefix", "chunk", "tile_lo", "tile_hi", "pieces")) for c in p["classes"]]
+    tiles = {r: -(-(prefix[r] + new[r]) // KEYS) for r in range(len(new))}
+    plain = [(prefix[r], new[r], 0, -(-new[r] * G // ROWS) - 1, -(-tiles[r] * splits // max(tiles.values())))
+             for r in sorted(tiles, key=lambda r: (-prefix[r], -new[r]))]
+    assert time_of(Hq, Hkv, D, dtype, p["rows"], chosen) <= 1.021 * time_of(Hq, Hkv, D, dtype, ROWS, plain)
 
 
 def test_planning_dozens_of_requests_costs_about_what_their_list_costs(tmp_path):
