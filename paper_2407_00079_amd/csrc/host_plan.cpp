@@ -495,8 +495,8 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   // launch is also followed by where workgroups really go, beside the plain one: every row tile in as many pieces as
   // suggest_kv_splits gives.  Behind a few long row tiles the rest may end later than that: P 55245, C 155 and P 33667, C 5816,
   // 16/2 heads, us: a round whole and the rest in halves (estimated sooner) 1604, all rows in halves 1487; fp32, 8/1 heads, C
-  // 5575 and 3868 behind P 268 and 68 737, 507; C 6227, 12/3 heads 775, 561.  Of 66 batches it decides, most fp32, 44 gain up to
-  // 45 % where the plain one is ahead by the slack or more, and none loses.
+  // 5575 and 3868 behind P 268 and 68 737, 507; C 6227, 12/3 heads 775, 561.  Of 66 batches where the plain one is ahead, most
+  // of them fp32, the 46 where it is by more than the slack gain up to 45 % and none loses; the rest are left as they are.
   if (best_k > 1 && best_whole > 0) {
     // `limit` and more: as late as that or later
     auto really_ends = [&](int64_t whole, int64_t tile_rows, int64_t of, int64_t k, double limit) {
