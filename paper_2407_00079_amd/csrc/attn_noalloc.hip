@@ -197,9 +197,11 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
     args.max_pages = max_pages_per_req;
     args.head_dim = p->head_dim;
     args.scale_log2e = attn_scale_log2e(p);
-    args.n_items = plan.n_wgs;
-    return launch_attn_classes(p->dtype, args, plan.classes, reinterpret_cast<hipStream_t>(hip_stream)) == hipSuccess
-               ? MC_OK : MC_ERR_HIP;
+    args.n_items = plan.narrow_wgs > 0 ? plan.narrow_wgs : plan.n_wgs;
+    const hipStream_t on = reinterpret_cast<hipStream_t>(hip_stream);
+    const hipError_t launched = plan.narrow_wgs > 0 ? launch_attn_narrow(p->dtype, args, &plan.narrow, on)
+                                                    : launch_attn_classes(p->dtype, args, plan.classes, on);
+    return launched == hipSuccess ? MC_OK : MC_ERR_HIP;
   }
 
   if (base == nullptr) return MC_ERR_HIP;

@@ -147,6 +147,13 @@ bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, i
   return true;
 }
 
+int64_t kv_bytes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch) {
+  int64_t keys = 0;
+  for (int32_t r = 0; r < batch; ++r)
+    if (new_lens[r] > 0) keys += (int64_t)prefix_lens[r] + new_lens[r];
+  return 2 * keys * p->num_kv_heads * p->head_dim * (p->dtype == MC_DTYPE_BF16 ? 2 : 4);
+}
+
 // One row tile per head reads each of its request's K and V rows once.  If they outgrow the last-level cache, the next layer
 // finds none of them there anyway, and a hint that they need not be kept helps.  What would stay in the cache is better left
 // there.  64/8 heads, the same call repeated, us without / with the hint: 16 tokens behind 51k (210 MB) 44.7 / 48.3, 61k 51 / 54,
@@ -158,16 +165,13 @@ bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, i
 bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                 int64_t tile_rows) {
   constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
-  if (!few_rows(p, new_lens, batch, tile_rows)) return false;
-  int64_t keys = 0;
-  for (int32_t r = 0; r < batch; ++r)
-    if (new_lens[r] > 0) keys += (int64_t)prefix_lens[r] + new_lens[r];
-  return 2 * keys * p->num_kv_heads * p->head_dim * (p->dtype == MC_DTYPE_BF16 ? 2 : 4) > kLastLevelBytes;
+  return few_rows(p, new_lens, batch, tile_rows) && kv_bytes(p, prefix_lens, new_lens, batch) > kLastLevelBytes;
 }
 
-// 128-row workgroups where no row tile has more rows, and where the plan of a one-shot call without room for partial
-// results takes them (plan_classes), so that a prepared list computes what that call computes, bit for bit: the rows that
-// share a workgroup decide which of its key tiles need no mask, and with that the reference of the probabilities.  Lists a
+// The narrow form where the plan of a one-shot call without room for partial results takes it (plan_classes), 128-row
+// workgroups where no row tile has more rows and where that plan takes them, so that a prepared list computes what that call
+// computes, bit for bit: the rows that share a workgroup decide which of its key tiles need no mask, and with that the
+// reference of the probabilities.  Lists a
 // class plan has no room for, and lists of key slices: where two workgroups per item still run side by side (an item's two
 // halves read K and V twice, which costs less than a compute unit left idle).
 // Measured, planned, 256 rows / 128, us: P 131056, C 16, 64/8 heads 2024 / 1493; 16 requests of P 4000, C 1 73 / 52;
@@ -175,11 +179,12 @@ bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32
 // of 16 tokens and one of 30, P 4000, 64/8 heads (200 items) 100 / 80; 3 requests, fp32, 12/3 heads (360 items) 754 / 684.
 int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                   int32_t kv_splits, int64_t n_items) {
+  ClassPlan plan;
+  const bool planned = kv_splits == 0 && plan_classes(p, prefix_lens, new_lens, batch, 0, &plan);
+  if (planned && plan.narrow_wgs > 0) return kListNarrow;
   if (few_rows(p, new_lens, batch, kAttnFewRows))
     return reads_once(p, prefix_lens, new_lens, batch, kAttnFewRows) ? kListFewOnce : kListFew;
-  ClassPlan plan;
-  if (kv_splits == 0 && plan_classes(p, prefix_lens, new_lens, batch, 0, &plan))
-    return plan.classes.rows == kAttnFewRows ? kListHalves : 0;
+  if (planned) return plan.classes.rows == kAttnFewRows ? kListHalves : 0;
   return 2 * n_items <= kComputeUnits ? kListHalves : 0;
 }
 
@@ -264,6 +269,36 @@ TileCost tile_cost_of(const mc_attn_params* p, int64_t tile_rows) {
   if (p->head_dim == 128) return {4.0, few ? 1.2 : 1.65};
   return {4.0, few ? 0.7 : 0.95};
 }
+// The same for the choice of the narrow form, fitted to 400 random launches of each form by themselves (median error 3-9 %):
+// the launch, a workgroup, a 64-key tile, and the merge with its time per MB of partial results.  (The costs above are for
+// weighing cuts of one form against each other; with these in their place 250 random calls got 1 % slower.)
+struct FormCost {
+  double launch, fixed, tile, merge, part_mb;
+};
+FormCost form_cost_of(const mc_attn_params* p, int64_t tile_rows) {
+  const bool few = tile_rows == kAttnFewRows, full = tile_rows == kAttnTileRows;
+  if (p->dtype == MC_DTYPE_F32)
+    return full ? FormCost{0, 9, 7.0, 3, 0.36} : few ? FormCost{0, 8.4, 3.8, 2.6, 0.36} : FormCost{0, 4.2, 0.58, 0, 0};
+  if (p->head_dim == 128)
+    return full ? FormCost{1, 4, 1.37, 3, 0.25} : few ? FormCost{2.1, 5.5, 0.72, 2, 0.31} : FormCost{0, 4.65, 0.315, 0, 0};
+  return full ? FormCost{1, 1, 0.94, 5, 0.25} : few ? FormCost{1.5, 4.2, 0.55, 2.6, 0.44} : FormCost{0, 4.2, 0.21, 0, 0};
+}
+// K and V bytes per microsecond: the most any form reads, and what the narrow one's time grows by beyond what the caches hold
+// (it has no tiles in flight beyond the next block, and row tiles of a request that do not run together read their keys again).
+constexpr double kReadPerUs = 6.2e6, kNarrowReadPerUs = 5.8e6, kNarrowMissPerUs = 8.0e6, kNarrowHeld = 128 << 20;
+// Launches of more narrow workgroups than this are not worth weighing: the other forms fill the chip (of 20 random launches of
+// more the estimate chose, the narrow form won 13 by 17 % on average and lost 7 by up to 20 %).
+constexpr int64_t kMostNarrow = 3 * kComputeUnits;
+
+// How much sooner the narrow form has to end than a cut, and than anything if it takes more than one round (the estimate's
+// errors), and if its rounds walk more keys than the XCDs' caches hold, at paces of their own (12/3 heads, C 1210 behind 32143:
+// 0.46 us a tile instead of 0.315, 382 -> 478 us).
+constexpr double kNarrowSlack = 1.06, kNarrowRoundsSlack = 1.12, kNarrowApartSlack = 1.3, kXcdCaches = 32 << 20;
+// Longest row tile the fp32 narrow form takes, in key tiles (4096 keys).  Beyond, whole rows are one long chain of roundings in
+// the other forms (6.3e-6 off 64 bits at 127262 keys, 1.0e-6 at 3000) and eight shorter ones here (2.3e-6, 4.5e-7): better, but
+// another result than such a call has given so far by more than a few roundings of its terms.
+constexpr int64_t kNarrowTilesF32 = 64;
+
 // the merge launch, and bytes of partial results written and read per microsecond
 constexpr double kMergeFixed = 4.0, kPartBytesPerUs = 3.0e6;
 double merge_time(const mc_attn_params* p, int64_t part_rows) {
@@ -533,6 +568,71 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       best_rows = kAttnTileRows;
       best_of = longest;
       best_k = plain;
+    }
+  }
+  // The narrow form, beside what has been chosen so far: no cut, no merge, the keys of a row tile at several times the pace,
+  // and, with so few rows a workgroup, more rounds of them.  Both are estimated row tile by row tile (in up to 16 steps a run).
+  const int64_t narrow_rows = p->dtype == MC_DTYPE_F32 ? kAttnNarrowRowsF32 : kAttnNarrowRows;
+  plan->narrow_wgs = 0;
+  const int64_t narrow_items = items_of(narrow_rows);
+  if (narrow_items <= kMostNarrow) {
+    auto place = [&](Units& units, const Run& run, int64_t cut, int64_t tile_rows, const FormCost& cost, double limit) {
+      const Active& a = act[run.active];
+      const int64_t step = (run.tile_hi - run.tile_lo) / 16 + 1;
+      for (int64_t hi = run.tile_hi; hi >= run.tile_lo; hi -= step) {
+        const int64_t lo = std::max(run.tile_lo, hi - step + 1);
+        const int64_t tiles = key_tiles(a.prefix, a.chunk, G, hi, tile_rows);
+        if (!units.place((hi - lo + 1) * Hkv * cut, cost.fixed + cost.tile * (double)((tiles + cut - 1) / cut), limit)) return false;
+      }
+      return true;
+    };
+    const double bytes = (double)kv_bytes(p, prefix_lens, new_lens, batch);
+    const FormCost cost = form_cost_of(p, best_rows);
+    const int uncut = lay_out(best_whole, best_rows);
+    Units chosen;
+    double part_rows = 0.0;
+    for (int i = 0; i < n_runs; ++i) {
+      const int64_t cut = i < uncut || best_of == 0 ? 1 : runs[i].pieces(best_of, best_k);
+      place(chosen, runs[i], cut, best_rows, cost, HUGE_VAL);
+      if (cut > 1) part_rows += (double)(cut * runs[i].rows);
+    }
+    const double merge = part_rows > 0.0 ? cost.merge + cost.part_mb * part_rows * (double)(p->head_dim + 1) * 8e-6 : 0.0;
+    double end = cost.launch + std::max(chosen.end(), bytes / kReadPerUs) + merge;
+    const FormCost narrow = form_cost_of(p, narrow_rows);
+    const double missed = std::max(0.0, bytes - kNarrowHeld) / kNarrowMissPerUs;
+    Units units;
+    // (a row tile of one key tile is one block for each of two waves: the 128-row form has that done as soon)
+    int64_t longest = 0;
+    for (int i = 0; i < n; ++i) longest = std::max(longest, (act[i].prefix + act[i].chunk + kAttnTileKeys - 1) / (int64_t)kAttnTileKeys);
+    if (narrow_items > kComputeUnits) end /= bytes > kXcdCaches ? kNarrowApartSlack : kNarrowRoundsSlack;
+    else if (merge > 0.0) end /= kNarrowSlack;
+    bool sooner = longest > 1 && (p->dtype != MC_DTYPE_F32 || longest <= kNarrowTilesF32) &&
+                  narrow.launch + bytes / kNarrowReadPerUs < end;
+    for (int i = 0; i < n && sooner; ++i) {
+      const int64_t last = (act[i].chunk * G - 1) / narrow_rows;
+      sooner = place(units, make_run(p, i, act[i].prefix, act[i].chunk, 0, last, narrow_rows), 1, narrow_rows, narrow,
+                     end - narrow.launch - missed);
+    }
+    if (sooner) {
+      AttnClasses& t = plan->narrow;
+      t.n = n;
+      t.rows = (int32_t)narrow_rows;
+      t.once = 0;
+      int64_t wg = 0;
+      for (int i = 0; i < kMaxAttnClasses; ++i) {
+        t.first[i] = i < n ? (int32_t)wg : 0;
+        t.c[i] = AttnClass{};
+        if (i >= n) continue;
+        const int64_t tiles = (act[i].chunk * G + narrow_rows - 1) / narrow_rows;
+        t.c[i] = AttnClass{act[i].req, act[i].q_off, act[i].prefix, act[i].chunk, 0, (int32_t)(tiles - 1), 1, 0};
+        wg += tiles * Hkv;
+      }
+      plan->narrow_wgs = (int32_t)wg;
+      if (max_part_rows == 0) {
+        best_rows = kAttnFewRows;
+        best_whole = items_of(best_rows);
+        best_of = 0;
+      }
     }
   }
   const int uncut = lay_out(best_whole, best_rows);

@@ -58,10 +58,12 @@ int64_t count_items(const mc_attn_params* p, const int32_t* new_lens, int32_t ba
 bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
 bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
 
-// How a list of n_items workgroups is launched, kept in a plan: as row tiles of 256 rows (0) or by workgroups of 128 rows,
-// one per item or two.  Marks that no caller's own zeroed or filled struct holds by accident: a list of longer row tiles
+// How a list of n_items workgroups is launched, kept in a plan: as row tiles of 256 rows (0), by workgroups of 128 rows, one
+// per item or two, or by those of the narrow form, as many per item as it may have rows for.  Marks that no caller's own zeroed or filled struct holds by accident: a list of longer row tiles
 // launched one workgroup per item would leave rows out.
-constexpr int32_t kListFew = 0x4d434631, kListFewOnce = 0x4d434632, kListHalves = 0x4d434633;
+constexpr int32_t kListFew = 0x4d434631, kListFewOnce = 0x4d434632, kListHalves = 0x4d434633, kListNarrow = 0x4d434634;
+// (items of a plan that is launched so: their workgroups have to be counted with 32 bits)
+constexpr int32_t kMostNarrowItems = INT32_MAX / (kAttnTileRows / kAttnNarrowRowsF32);
 int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                   int32_t kv_splits, int64_t n_items);
 
@@ -81,6 +83,10 @@ int32_t suggest_kv_splits(const mc_attn_params* p, const int32_t* prefix_lens, c
 // false: more requests with new tokens than a launch has classes for.
 struct ClassPlan {
   AttnClasses classes;
+  // Workgroups of the narrow form, if that is sooner (0: it is not); `narrow` are its classes, whole rows, and the launch takes
+  // them instead.  (Without room for partial results `classes` are then the whole rows of 128-row tiles.)
+  int32_t narrow_wgs;
+  AttnClasses narrow;
   int32_t n_wgs;          // workgroups of the attention launch
   int32_t most_pieces;    // 1: nothing is cut, no partial results, no merge
   int64_t part_rows;      // rows of partial results

@@ -222,8 +222,9 @@ mc_status launch_planned_attn(const mc_attn_params* p, const mc_attn_plan* plan,
   args.rows_total = plan->total_new_tokens * p->num_q_heads;
   args.o_parts = o_parts;
   args.lse_parts = lse_parts;
-  if (mc::launch_attn(p->dtype, args, stream) != hipSuccess) return MC_ERR_HIP;
-  return MC_OK;
+  const bool narrow = plan->reserved == kListNarrow && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
+  const hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, nullptr, stream) : mc::launch_attn(p->dtype, args, stream);
+  return st == hipSuccess ? MC_OK : MC_ERR_HIP;
 }
 
 // One-shot form from a list: every check first (a rejected call enqueues nothing), then upload and launch.
@@ -254,7 +255,7 @@ mc_status attn_enqueue(const mc_attn_params* p, const void* q, const void* k_poo
                              lse_parts, workspace, stream);
 }
 
-// Launch of a class plan, then the merge of what it cut.  Nothing is uploaded: the classes travel as kernel arguments.
+// Launch of a class plan, then the merge of what it cut; or of the narrow form, where the plan says so.  Nothing is uploaded: the classes travel as kernel arguments.
 mc_status launch_class_plan(const mc_attn_params* p, const ClassPlan& plan, const void* q, const void* k_pool,
                             const void* v_pool, const int32_t* block_tables, int32_t max_pages_per_req, void* out,
                             float* lse, float* o_parts, float* lse_parts, hipStream_t stream) {
@@ -271,9 +272,11 @@ mc_status launch_class_plan(const mc_attn_params* p, const ClassPlan& plan, cons
   args.max_pages = max_pages_per_req;
   args.head_dim = p->head_dim;
   args.scale_log2e = attn_scale_log2e(p);
-  args.n_items = plan.n_wgs;
+  args.n_items = plan.narrow_wgs > 0 ? plan.narrow_wgs : plan.n_wgs;
   args.o_parts = o_parts;
   args.lse_parts = lse_parts;
+  if (plan.narrow_wgs > 0)
+    return mc::launch_attn_narrow(p->dtype, args, &plan.narrow, stream) == hipSuccess ? MC_OK : MC_ERR_HIP;
   if (mc::launch_attn_classes(p->dtype, args, plan.classes, stream) != hipSuccess) return MC_ERR_HIP;
   if (plan.most_pieces > 1 &&
       mc::launch_attn_merge_classes(p->dtype, p->head_dim, o_parts, lse_parts, plan.classes, p->num_q_heads,

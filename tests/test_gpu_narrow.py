@@ -1,0 +1,55 @@
+"""GPU parity of the narrow form of the attention kernels (csrc/attn_narrow.hip: waves share out the keys of 32 or, fp32, 16
+rows), at the edges of its rows, key blocks and waves, against the oracle; whole rows are the same bits however the call is
+driven.  The pools hold NaN behind every request's last key."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2407_00079_amd import binding as B
+from paper_2407_00079_amd import workloads as W
+
+from gpu_util import TOL, DeviceCase, check_close
+
+pytestmark = pytest.mark.gpu
+
+NARROW = 0x4d434634                            # mc_attn_plan.reserved of a list that is launched so
+
+# dtype, Hq, Hkv, D, prefix, new
+CASES = [(W.BF16, 8, 1, 128, [keys - 4], [4]) for keys in (65, 95, 96, 97, 255, 256, 257, 288, 289, 511, 513, 545)]    # 32 rows; blocks per wave
+CASES += [(W.BF16, 8, 2, 64, [keys - 9], [9]) for keys in (66, 256, 257, 300)]                                       # 36 rows: a row tile of 4
+CASES += [(W.F32, 4, 1, 64, [keys - 5], [5]) for keys in (67, 96, 255, 256, 257, 290)]                               # 20 rows: 16 and 4
+CASES += [
+    (W.BF16, 8, 1, 128, [300], [1]),                          # 8 rows
+    (W.BF16, 16, 1, 128, [70], [2]),                          # exactly a row tile of 16 heads a group
+    (W.BF16, 64, 8, 128, [1023], [33]),                       # 264 rows: more than one item of the list, the last of 8 rows
+    (W.BF16, 12, 3, 128, [999, 1, 0], [130, 0, 257]),         # three heads, an empty request, no prefix: row tiles of one to five key tiles
+    (W.BF16, 16, 16, 64, [700, 81], [70, 1]),                 # one head a group
+    (W.F32, 12, 3, 64, [500, 31, 0], [17, 100, 40]),
+    (W.F32, 16, 16, 64, [4000], [3]),                         # just inside what fp32 takes
+]
+
+
+@pytest.mark.parametrize("q_scale", [1.0, 8.0])               # 8: references that are raised many times
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,prefix,new", CASES)
+def test_narrow_form_matches_oracle(oracle, dtype, Hq, Hkv, D, prefix, new, q_scale):
+    print(f"narrow case {dtype} Hq={Hq} Hkv={Hkv} D={D} prefix={prefix} new={new} q_scale={q_scale}", flush=True)
+    pages = sum(-(-(p + c) // 16) for p, c in zip(prefix, new)) + 5
+    case = W.make_attn_case(95, dtype, Hq, Hkv, D, 16, prefix, new, pages, q_scale=q_scale)
+    dc = DeviceCase(case)
+    plan_ws = torch.empty_like(dc.workspace)
+    plan = B.mc_prefill_attn_prepare(dc.params, prefix, new, 0, plan_ws)
+    assert plan.reserved == NARROW
+    args = (dc.q, dc.k_pool, dc.v_pool, dc.block_tables)
+    ref_out, ref_lse, _ = oracle.case_full(case)
+    first = None
+    for call in (lambda: B.mc_prefill_attn_run(dc.params, plan, *args, dc.out, dc.lse, plan_ws), dc.run,
+                 lambda: B.mc_prefill_attn_paged_noalloc(dc.params, *args, prefix, new, dc.out, dc.lse)):
+        dc.out.fill_(float("nan"))
+        dc.lse.fill_(float("nan"))
+        call()
+        out, lse = dc.result()
+        check_close(out, ref_out, dtype, "narrow")
+        assert np.abs(lse - ref_lse).max() <= TOL[dtype]["lse_abs"]
+        bits = dc.out.clone(), dc.lse.clone()
+        first = first or bits
+        assert torch.equal(bits[0], first[0]) and torch.equal(bits[1], first[1])
