@@ -7,7 +7,8 @@
 //   independent; the chain that turns a request's digests into keys is sequential, one mix per block.
 //   short kernel   requests of few blocks, one workgroup each: digests into LDS, then one wave chains them.
 //   stage kernel   longer ones: digests of one range of blocks (four per workgroup) beside the chain of another range
-//                  (one wave per request), so that a queue's first blocks are chained while its later ones are digested.
+//                  (one wave per request).
+//   pour kernel    a queue of them: a workgroup per request chains its first blocks while it digests the later ones.
 //   match kernel   one workgroup per (instance, request): thread t looks keys t, t + 256, ... up
 //                  in the instance's ascending key array; the smallest index that misses is the
 //                  prefix length.
@@ -83,7 +84,7 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
 // 16 blocks a turn.  Bound by the issue of one wave's scalar instructions, about 6 cycles each whatever they are, so a
 // link is nothing but the hash: no first-block case, no lane compare, no counter
 // (34 instructions, 97 ns; 47 and 118 ns with them: 256 links 30 -> 25 us).
-__device__ __forceinline__ void chain_range(const uint64_t* from, uint64_t* to, int64_t lo, int64_t hi, uint64_t salt, int lane) {
+__device__ __forceinline__ void chain_range(const uint64_t* from, uint64_t* to, int64_t lo, int64_t hi, uint64_t& salt, int lane) {
   uint64_t ahead = lane < 16 && lo + lane < hi ? from[lo + lane] : 0;
   for (int64_t base = lo; base < hi; base += 16) {
     const uint64_t digest = ahead;
@@ -112,7 +113,8 @@ __global__ __launch_bounds__(1024) void prefix_short_kernel(const int32_t* __res
       if (lane == 0) digests[b] = d;
     }
     __syncthreads();
-    if (threadIdx.x < 64) chain_range(digests, keys + k0, 0, nk, kFirstSalt, lane);
+    uint64_t salt = kFirstSalt;
+    if (threadIdx.x < 64) chain_range(digests, keys + k0, 0, nk, salt, lane);
     __syncthreads();
   }
 }
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(256) void prefix_stage_kernel(const int32_t* __rest
       if (threadIdx.x >= 64) return;
       const int64_t hi = nk < chain.hi ? nk : chain.hi;
       if (chain.lo >= hi) continue;
-      const uint64_t salt = chain.lo == 0 ? kFirstSalt : salt_after((uint64_t)uniform64((int64_t)keys[k0 + chain.lo - 1]));
+      uint64_t salt = chain.lo == 0 ? kFirstSalt : salt_after((uint64_t)uniform64((int64_t)keys[k0 + chain.lo - 1]));
       chain_range(keys + k0, keys + k0, chain.lo, hi, salt, lane);
       continue;
     }
@@ -147,6 +149,65 @@ __global__ __launch_bounds__(256) void prefix_stage_kernel(const int32_t* __rest
       const uint64_t d = digest_of(tokens + t0 + at, left < block_tokens ? (int)left : block_tokens, lane);
       if (lane == 0) keys[k0 + b] = d;
     }
+  }
+}
+
+// The rest of a queue of long prompts: blocks [0, first) of every request are digested; one workgroup a request chains them
+// in its first wave while the others digest the blocks behind them, into LDS, in order.  A group of 16 digests is complete when
+// its count says so; the chain waits for that, and only for waves of its own workgroup, which wait for nothing.
+// Bound by the chain where `first` is large enough (see hash_with): a compute unit digests a block of 512 tokens in 0.15 us, a
+// link takes 0.1.  Keys, launches of whole ranges before / this now, us: 64 prompts of 256 blocks of 512 tokens 31.0 / 28.6, 128
+// blocks 19.5 / 16.9; 200 prompts of 256 blocks 52.5 / 45.1; 128 of 59 20.9 / 17.1; 100 of 71 blocks of 128 tokens 21.1 / 18.0.
+constexpr int kPourBlocks = 4096;                         // most blocks of a request behind `first`
+template <typename Tables>
+__global__ __launch_bounds__(1024) void prefix_pour_kernel(const int32_t* __restrict__ tokens, const Tables off, int block_tokens,
+                                                           int64_t first, uint64_t* keys) {
+  __shared__ uint64_t digests[kPourBlocks];
+  __shared__ int done[kPourBlocks / 16];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+  const int r = blockIdx.x;
+  const int64_t k0 = off.b[r], nk = off.b[r + 1] - k0;
+  const int rest = nk > first ? (int)(nk - first) : 0;
+  for (int g = threadIdx.x; g < kPourBlocks / 16; g += blockDim.x) done[g] = 0;
+  __syncthreads();
+  if (wave > 0) {
+    const int64_t t0 = off.a[r], len = off.a[r + 1] - t0;
+    for (int b = wave - 1; b < rest; b += waves - 1) {
+      const int64_t at = (first + b) * block_tokens, left = len - at;
+      const uint64_t d = digest_of(tokens + t0 + at, left < block_tokens ? (int)left : block_tokens, lane);
+      if (lane == 0) {
+        digests[b] = d;
+        __hip_atomic_fetch_add(&done[b >> 4], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    return;
+  }
+  __builtin_amdgcn_s_setprio(3);                          // the chain is what the others are early for
+  uint64_t salt = kFirstSalt;
+  chain_range(keys + k0, keys + k0, 0, nk < first ? nk : first, salt, lane);
+  // The count and the digests of the next group are read before this one's links, the count first (a wave's LDS accesses keep
+  // their order): if it is complete by then, its digests are what has been read.
+  const volatile int* const counts = done;
+  const volatile uint64_t* const from = digests + (lane & 15);
+  int ready = counts[0];
+  uint64_t ahead = from[0];
+  for (int base = 0; base < rest; base += 16) {
+    const int n = rest - base < 16 ? rest - base : 16;
+    while (__builtin_amdgcn_readfirstlane(ready) < n) {
+      __builtin_amdgcn_s_sleep(1);
+      ready = counts[base >> 4];
+      ahead = from[base];
+    }
+    const uint64_t digest = ahead;
+    const int next = base + 16 < kPourBlocks ? base + 16 : base;
+    ready = counts[next >> 4];
+    ahead = from[next];
+    uint32_t kl = 0, kh = 0;
+    chain_four<0>(digest, salt, kl, kh);
+    if (n > 4) chain_four<4>(digest, salt, kl, kh);
+    if (n > 8) chain_four<8>(digest, salt, kl, kh);
+    if (n > 12) chain_four<12>(digest, salt, kl, kh);
+    if (lane < n) keys[k0 + first + base + lane] = ((uint64_t)kh << 32) | kl;
   }
 }
 
@@ -294,10 +355,15 @@ namespace {
 
 // Costs the split of a queue of long prompts rests on: one link of a chain, and the digest of one block when the whole chip
 // digests - of 512 tokens, and of fewer about as much (a workgroup's start and the sum across the wave).  A rough figure does:
-// the line only moves work between launches.  64 prompts, as split here / not at all / best of eleven splits, us: 1024 blocks
+// the line only moves work between launches.  64 prompts, split into ranges / not at all / best of eleven splits, us: 1024 blocks
 // of 16 tokens 92.5 / 101.9 / 91.7, 512 of 64 49.7 / 53.0 / 49.4, 256 of 512 31.3 / 32.7 / 30.4, 128 of 1024 22.6 / 21.5 /
 // 21.1, 64 of 2048 (not split) 16.0 / 15.9 / 15.9.
 constexpr double kChainNs = 95.0, kDigestNs = 0.64;
+// ... and a block's digest on the compute unit that chains its request, per token and for the block (256 tokens 133 ns, 512 186):
+// of 64, 80 and 110 for the block 80 was never behind launches of whole ranges (64 prompts of 512 blocks of 256 tokens 55.9,
+// 53.5, 51.8 us, 53.4 by ranges; 256 prompts of 118 blocks of 512 29.2, 29.2, 31.1, 35.6).
+constexpr double kUnitTokenNs = 0.207, kUnitBlockNs = 80.0;
+constexpr int kComputeUnits = 256;
 
 template <typename Tables>
 hipError_t hash_with(const int32_t* tokens, const Tables& off, int batch, int block_tokens, int64_t max_blocks,
@@ -310,11 +376,28 @@ hipError_t hash_with(const int32_t* tokens, const Tables& off, int batch, int bl
     prefix_short_kernel<Tables><<<cols, waves * 64, 0, stream>>>(tokens, off, batch, block_tokens, keys);
     return hipGetLastError();
   }
-  // Long prompts: digests, then chains.  Where the digests of the whole queue take longer than another launch costs (about
-  // 4 us), the chains of the first blocks run beside the digests of the rest: `first` is where both take equally long.
-  // 64 prompts of 256 blocks: 12 + 30 us, now 6 + 11 + 20 (59.9 -> 54.7 us a pass with the match; 54.8 with first = 112
-  // instead of 64).
+  // Long prompts.  Where the digests of the whole queue take longer than another launch costs (about 4 us), only the first of
+  // them get one; the rest are made beside the chain of their request, by its own compute unit.
   const double digest_ns = kDigestNs * (double)total_blocks;
+  if (digest_ns >= 4000.0 && batch <= kComputeUnits) {
+    const double unit_ns = kUnitBlockNs + kUnitTokenNs * block_tokens;
+    const double behind = unit_ns > kChainNs ? (double)max_blocks * kChainNs / unit_ns : (double)max_blocks;
+    const int64_t first = (max_blocks - (int64_t)behind + 15) & ~(int64_t)15;
+    if (first < max_blocks && max_blocks - first <= kPourBlocks) {
+      if (first > 0) {
+        const int64_t quads = (first + 3) / 4;
+        prefix_stage_kernel<Tables><<<dim3(cols, (unsigned)(quads < 8192 ? quads : 8192)), 256, 0, stream>>>(
+            tokens, off, batch, block_tokens, Blocks{0, first}, Blocks{0, 0}, 0, keys);
+      }
+      prefix_pour_kernel<Tables><<<cols, 1024, 0, stream>>>(tokens, off, block_tokens, first, keys);
+      return hipGetLastError();
+    }
+  }
+  // Digests, then chains.  In a queue of more requests than compute units, or of more blocks than the LDS has room for, the
+  // chains of the first blocks run beside the digests of the rest in a launch of their own: `first` is where both take equally
+  // long.
+  // 64 prompts of 256 blocks: 12 + 30 us unsplit, by ranges 6 + 11 + 20 (59.9 -> 54.7 us a pass with the match; 54.8 with
+  // first = 112 instead of 64).
   int64_t first = (int64_t)(digest_ns / (kChainNs + kDigestNs * batch)) & ~(int64_t)15;
   if (digest_ns < 4000.0 || first == 0 || first + 32 > max_blocks) first = max_blocks;
   auto stage = [&](Blocks digest, Blocks chain) {
