@@ -1,4 +1,4 @@
-"""ctypes binding of ``libmooncake_hip.so``: argument marshalling only.
+"""Binding of ``libmooncake_hip.so`` (ctypes, and ``_mccall.so`` for the calls that enqueue work): argument marshalling only.
 
 Function names and argument order are those of ``include/mc.h``.  torch is used
 for device memory and streams; every step of the path runs in the library's
@@ -56,7 +56,7 @@ _lib = None
 
 def lib():
     """The loaded library; raises if it was never built (run ``__graft_entry__.build()``)."""
-    global _lib
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_2407_00079_amd.build` "
@@ -126,8 +126,40 @@ def lib():
         l.mc_prefix_match.argtypes = [vp, vp, i32, vp, vp, i32, vp, vp, vp, vp, ctypes.c_size_t, vp]
         l.mc_attn_merge_lse.restype = ctypes.c_int
         l.mc_attn_merge_lse.argtypes = [vp, vp, i32, i64, i32, i32, vp, vp, vp]
+        try:
+            from . import _mccall
+        except ImportError as e:
+            raise RuntimeError("_mccall.so is missing: build it with `python -m paper_2407_00079_amd.build`") from e
+        for name in EXPORTS:
+            _address[name] = ctypes.cast(getattr(l, name), ctypes.c_void_p).value
+        _call = _mccall.call
         _lib = l
     return _lib
+
+
+_address: dict = {}            # of the library's functions
+_call = None                   # csrc/pycall.cpp
+
+
+def _enqueue(name: str, kinds: str, *args) -> None:
+    """The library's function ``name``; ``kinds`` says how each argument is handed over (csrc/pycall.cpp)."""
+    if _call is None:
+        lib()
+    st = _call(_address[name], kinds, *args)
+    if st != MC_OK:
+        raise McError(st, name)
+
+
+def _params(params):
+    if params is not None and not isinstance(params, McAttnParams):
+        raise TypeError(f"McAttnParams wanted, not {type(params).__name__}")
+    return params
+
+
+def _plan(plan):
+    if not isinstance(plan, McAttnPlan):
+        raise TypeError(f"McAttnPlan wanted, not {type(plan).__name__}")
+    return plan
 
 
 def status_string(status: int) -> str:
@@ -139,7 +171,7 @@ def _dev_ptr(t) -> Optional[int]:
 
 
 def _nbytes(t) -> int:
-    return 0 if t is None else t.numel() * t.element_size()
+    return 0 if t is None else t.nbytes
 
 
 def _stream_handle(stream) -> Optional[int]:
@@ -148,15 +180,26 @@ def _stream_handle(stream) -> Optional[int]:
     return stream.cuda_stream or None
 
 
+_raw_stream = _device = None
+
+
 def _current_stream() -> int:
     """Handle of torch's current stream of the current device.  torch.cuda.current_stream() builds a Stream object
     through several Python layers; small calls are bound by the host, so the handle is asked for directly where this torch
-    can (2 loads and 2 stores of 24 pages: 44.0 us a pass before this and the rest of the marshalling below, 32.5 with them)."""
+    can (0.15 us)."""
+    global _raw_stream, _device
+    if _raw_stream is not None:
+        return _raw_stream(_device())
     import torch
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
     if raw is None or device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
+    _raw_stream, _device = raw, device
     return raw(device())
+
+
+def _on(stream) -> int:
+    return _current_stream() if stream is None else stream.cuda_stream
 
 
 class _Ints:
@@ -175,6 +218,14 @@ class _Ints:
             kind = ctypes.c_int32 if code == "i" else ctypes.c_int64
             self.keep = (kind * max(n, 1))(*[int(x) for x in values])
             self.at = ctypes.addressof(self.keep)
+
+    def __index__(self):
+        return self.at
+
+
+def _ints(code: str, values, n: int):
+    """What stands for ``n`` host ints in a call: the list itself, which the call lays out, or its C copy."""
+    return values if type(values) is list and len(values) == n and n > 0 else _Ints(code, values, n)
 
 
 def _lens(prefix_lens, new_lens):
@@ -202,15 +253,10 @@ def mc_prefill_attn_paged(params: McAttnParams, q, k_pool, v_pool, block_tables,
     tensor [batch, max_pages]; prefix_lens / new_lens: host sequences of ints;
     workspace: uint8 device tensor of at least the size the library asks for.
     """
-    batch, pl, nl = _lens(prefix_lens, new_lens)
-    max_pages = _max_pages(block_tables)
-    ws_bytes = _nbytes(workspace)
-    st = mc_prefill_attn_paged_raw(params, _dev_ptr(q), _dev_ptr(k_pool), _dev_ptr(v_pool), _dev_ptr(block_tables),
-                                   max_pages, pl.at, nl.at,
-                                   batch, _dev_ptr(out), _dev_ptr(lse), _dev_ptr(workspace), ws_bytes,
-                                   _stream_handle(stream))
-    if st != MC_OK:
-        raise McError(st, "mc_prefill_attn_paged")
+    n = len(prefix_lens)
+    _enqueue("mc_prefill_attn_paged", "sppppiIIipppii", _params(params), q, k_pool, v_pool, block_tables,
+             _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, out, lse, workspace,
+             _nbytes(workspace), _on(stream))
 
 
 def mc_prefill_attn_split_workspace_bytes(params: McAttnParams, batch: int, total_new_tokens: int,
@@ -226,14 +272,10 @@ def mc_prefill_attn_auto_workspace_bytes(params: McAttnParams, prefix_lens, new_
 def mc_prefill_attn_auto(params: McAttnParams, q, k_pool, v_pool, block_tables, prefix_lens, new_lens, out, lse,
                          workspace, stream=None) -> None:
     """mc_prefill_attn_paged with the whole-row / key-slices choice made by the library (larger workspace)."""
-    batch, pl, nl = _lens(prefix_lens, new_lens)
-    ws_bytes = _nbytes(workspace)
-    max_pages = _max_pages(block_tables)
-    st = int(lib().mc_prefill_attn_auto(ctypes.byref(params), _dev_ptr(q), _dev_ptr(k_pool), _dev_ptr(v_pool),
-                                        _dev_ptr(block_tables), max_pages, pl.at, nl.at, batch, _dev_ptr(out), _dev_ptr(lse),
-                                        _dev_ptr(workspace), ws_bytes, _stream_handle(stream)))
-    if st != MC_OK:
-        raise McError(st, "mc_prefill_attn_auto")
+    n = len(prefix_lens)
+    _enqueue("mc_prefill_attn_auto", "sppppiIIipppii", _params(params), q, k_pool, v_pool, block_tables,
+             _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, out, lse, workspace,
+             _nbytes(workspace), _on(stream))
 
 
 def mc_prefill_attn_paged_noalloc_raw(params, q, k_pool, v_pool, block_tables, max_pages_per_req, prefix_lens,
@@ -247,16 +289,13 @@ def mc_prefill_attn_paged_noalloc(params: McAttnParams, q, k_pool, v_pool, block
                                   lse=None, stream=None) -> None:
     """mc_prefill_attn_paged without a workspace: the work list is built on the device in the library's own
     fixed array (no allocation, no upload)."""
-    batch, pl, nl = _lens(prefix_lens, new_lens)
-    st = mc_prefill_attn_paged_noalloc_raw(params, _dev_ptr(q), _dev_ptr(k_pool), _dev_ptr(v_pool),
-                                           _dev_ptr(block_tables), _max_pages(block_tables), pl.at, nl.at, batch,
-                                           _dev_ptr(out), _dev_ptr(lse), _stream_handle(stream))
-    if st != MC_OK:
-        raise McError(st, "mc_prefill_attn_paged_noalloc")
+    n = len(prefix_lens)
+    _enqueue("mc_prefill_attn_paged_noalloc", "sppppiIIippi", _params(params), q, k_pool, v_pool, block_tables,
+             _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, out, lse, _on(stream))
 
 
 def _max_pages(block_tables) -> int:
-    return int(block_tables.shape[1]) if block_tables is not None and block_tables.dim() == 2 else 0
+    return block_tables.size(1) if block_tables is not None and block_tables.dim() == 2 else 0
 
 
 def mc_prefill_attn_prepare(params: McAttnParams, prefix_lens, new_lens, kv_splits: int, workspace,
@@ -275,11 +314,8 @@ def mc_prefill_attn_prepare(params: McAttnParams, prefix_lens, new_lens, kv_spli
 
 def mc_prefill_attn_run(params: McAttnParams, plan: McAttnPlan, q, k_pool, v_pool, block_tables, out, lse, workspace,
                         stream=None) -> None:
-    st = int(lib().mc_prefill_attn_run(ctypes.byref(params), ctypes.byref(plan), _dev_ptr(q), _dev_ptr(k_pool),
-                                       _dev_ptr(v_pool), _dev_ptr(block_tables), _max_pages(block_tables),
-                                       _dev_ptr(out), _dev_ptr(lse), _dev_ptr(workspace), _stream_handle(stream)))
-    if st != MC_OK:
-        raise McError(st, "mc_prefill_attn_run")
+    _enqueue("mc_prefill_attn_run", "ssppppipppi", _params(params), _plan(plan), q, k_pool, v_pool, block_tables,
+             _max_pages(block_tables), out, lse, workspace, _on(stream))
 
 
 def mc_prefill_attn_run_split(params: McAttnParams, plan: McAttnPlan, q, k_pool, v_pool, block_tables, o_parts,
@@ -294,11 +330,8 @@ def mc_prefill_attn_run_split(params: McAttnParams, plan: McAttnPlan, q, k_pool,
 
 def mc_kv_append_run(params: McAttnParams, plan: McAttnPlan, k_new, v_new, k_pool, v_pool, block_tables, workspace,
                      stream=None) -> None:
-    st = int(lib().mc_kv_append_run(ctypes.byref(params), ctypes.byref(plan), _dev_ptr(k_new), _dev_ptr(v_new),
-                                    _dev_ptr(k_pool), _dev_ptr(v_pool), _dev_ptr(block_tables),
-                                    _max_pages(block_tables), _dev_ptr(workspace), _stream_handle(stream)))
-    if st != MC_OK:
-        raise McError(st, "mc_kv_append_run")
+    _enqueue("mc_kv_append_run", "sspppppipi", _params(params), _plan(plan), k_new, v_new, k_pool, v_pool, block_tables,
+             _max_pages(block_tables), workspace, _on(stream))
 
 
 def mc_prefill_attn_plan(params: McAttnParams, prefix_lens, new_lens, kv_splits: int = 0):
@@ -366,25 +399,17 @@ def mc_kv_unpack_layer_raw(k_in, v_in, num_pages, page_bytes, page_ids, n, k_poo
 
 def mc_kv_pack_layer(k_pool_layer, v_pool_layer, num_pages: int, page_bytes: int, page_ids, n: int,
                      k_out, v_out, stream=None) -> None:
-    st = mc_kv_pack_layer_raw(_dev_ptr(k_pool_layer), _dev_ptr(v_pool_layer), num_pages, page_bytes,
-                              _dev_ptr(page_ids), n, _dev_ptr(k_out), _dev_ptr(v_out), _stream_handle(stream))
-    if st != MC_OK:
-        raise McError(st, "mc_kv_pack_layer")
+    _enqueue("mc_kv_pack_layer", "ppiipippi", k_pool_layer, v_pool_layer, num_pages, page_bytes, page_ids, n, k_out, v_out, _on(stream))
 
 
 def mc_kv_unpack_layer(k_in, v_in, num_pages: int, page_bytes: int, page_ids, n: int,
                        k_pool_layer, v_pool_layer, stream=None) -> None:
-    st = mc_kv_unpack_layer_raw(_dev_ptr(k_in), _dev_ptr(v_in), num_pages, page_bytes, _dev_ptr(page_ids), n,
-                                _dev_ptr(k_pool_layer), _dev_ptr(v_pool_layer), _stream_handle(stream))
-    if st != MC_OK:
-        raise McError(st, "mc_kv_unpack_layer")
+    _enqueue("mc_kv_unpack_layer", "ppiipippi", k_in, v_in, num_pages, page_bytes, page_ids, n, k_pool_layer, v_pool_layer, _on(stream))
 
 
 def mc_kv_page_order(page_ids, n: int, order, stream=None) -> None:
     """Enqueue order[r] = position of the r-th smallest page id (int32 device tensors)."""
-    st = int(lib().mc_kv_page_order(_dev_ptr(page_ids), n, _dev_ptr(order), _stream_handle(stream)))
-    if st != MC_OK:
-        raise McError(st, "mc_kv_page_order")
+    _enqueue("mc_kv_page_order", "pipi", page_ids, n, order, _on(stream))
 
 
 def mc_kv_check_page_ids(page_ids, n: int, num_pages: int, report, stream=None) -> None:
@@ -397,20 +422,14 @@ def mc_kv_check_page_ids(page_ids, n: int, num_pages: int, report, stream=None) 
 
 def mc_kv_pack_layer_ordered(k_pool_layer, v_pool_layer, num_pages: int, page_bytes: int, page_ids, order, n: int,
                              k_out, v_out, stream=None) -> None:
-    st = int(lib().mc_kv_pack_layer_ordered(_dev_ptr(k_pool_layer), _dev_ptr(v_pool_layer), num_pages, page_bytes,
-                                            _dev_ptr(page_ids), _dev_ptr(order), n, _dev_ptr(k_out), _dev_ptr(v_out),
-                                            _stream_handle(stream)))
-    if st != MC_OK:
-        raise McError(st, "mc_kv_pack_layer_ordered")
+    _enqueue("mc_kv_pack_layer_ordered", "ppiippippi", k_pool_layer, v_pool_layer, num_pages, page_bytes, page_ids, order, n, k_out, v_out,
+             _on(stream))
 
 
 def mc_kv_unpack_layer_ordered(k_in, v_in, num_pages: int, page_bytes: int, page_ids, order, n: int, k_pool_layer,
                                v_pool_layer, stream=None) -> None:
-    st = int(lib().mc_kv_unpack_layer_ordered(_dev_ptr(k_in), _dev_ptr(v_in), num_pages, page_bytes,
-                                              _dev_ptr(page_ids), _dev_ptr(order), n, _dev_ptr(k_pool_layer),
-                                              _dev_ptr(v_pool_layer), _stream_handle(stream)))
-    if st != MC_OK:
-        raise McError(st, "mc_kv_unpack_layer_ordered")
+    _enqueue("mc_kv_unpack_layer_ordered", "ppiippippi", k_in, v_in, num_pages, page_bytes, page_ids, order, n, k_pool_layer, v_pool_layer,
+             _on(stream))
 
 
 def mc_kv_load_layer_raw(k_host, v_host, k_stage, v_stage, num_pages, page_bytes, page_ids, n, k_pool, v_pool,
@@ -461,12 +480,9 @@ def mc_prefix_hash_raw(tokens, tok_offsets, batch, block_tokens, keys, workspace
 def mc_prefix_hash(tokens, tok_offsets, block_tokens: int, keys, workspace, stream=None) -> None:
     """Enqueue the block keys of every request: ``tokens`` int32 device tensor, ``tok_offsets`` host sequence of
     batch + 1 ints, ``keys`` int64 device tensor (the uint64 bit patterns) with one entry per block."""
-    off = _Ints("q", tok_offsets, len(tok_offsets))
-    ws_bytes = _nbytes(workspace)
-    st = mc_prefix_hash_raw(_dev_ptr(tokens), off.at, len(tok_offsets) - 1, block_tokens, _dev_ptr(keys),
-                            _dev_ptr(workspace), ws_bytes, _stream_handle(stream))
-    if st != MC_OK:
-        raise McError(st, "mc_prefix_hash")
+    n = len(tok_offsets)
+    _enqueue("mc_prefix_hash", "pQiippii", tokens, _ints("q", tok_offsets, n), n - 1, block_tokens, keys, workspace,
+             _nbytes(workspace), _on(stream))
 
 
 def mc_prefix_match_raw(keys, key_offsets, batch, cache_keys, cache_offsets, n_inst, prefix_len, best_len, best_inst,
@@ -478,13 +494,9 @@ def mc_prefix_match_raw(keys, key_offsets, batch, cache_keys, cache_offsets, n_i
 def mc_prefix_match(keys, key_offsets, cache_keys, cache_offsets, prefix_len, best_len, best_inst, workspace,
                     stream=None) -> None:
     """Enqueue the longest-prefix match of every request against every instance (device tensors; offsets on the host)."""
-    koff, coff = _Ints("q", key_offsets, len(key_offsets)), _Ints("q", cache_offsets, len(cache_offsets))
-    ws_bytes = _nbytes(workspace)
-    st = mc_prefix_match_raw(_dev_ptr(keys), koff.at, len(key_offsets) - 1, _dev_ptr(cache_keys), coff.at,
-                             len(cache_offsets) - 1, _dev_ptr(prefix_len), _dev_ptr(best_len), _dev_ptr(best_inst),
-                             _dev_ptr(workspace), ws_bytes, _stream_handle(stream))
-    if st != MC_OK:
-        raise McError(st, "mc_prefix_match")
+    n, m = len(key_offsets), len(cache_offsets)
+    _enqueue("mc_prefix_match", "pQipQippppii", keys, _ints("q", key_offsets, n), n - 1, cache_keys,
+             _ints("q", cache_offsets, m), m - 1, prefix_len, best_len, best_inst, workspace, _nbytes(workspace), _on(stream))
 
 
 def mc_kv_append_workspace_bytes(batch: int) -> int:
@@ -501,14 +513,10 @@ def mc_kv_append_paged_raw(params, k_new, v_new, k_pool, v_pool, block_tables, m
 def mc_kv_append_paged(params: McAttnParams, k_new, v_new, k_pool, v_pool, block_tables, prefix_lens, new_lens,
                        workspace, stream=None) -> None:
     """Enqueue the scatter of the new tokens' K/V rows into their page slots (torch device tensors)."""
-    batch, pl, nl = _lens(prefix_lens, new_lens)
-    max_pages = _max_pages(block_tables)
-    ws_bytes = _nbytes(workspace)
-    st = mc_kv_append_paged_raw(params, _dev_ptr(k_new), _dev_ptr(v_new), _dev_ptr(k_pool), _dev_ptr(v_pool),
-                                _dev_ptr(block_tables), max_pages, pl.at, nl.at, batch, _dev_ptr(workspace), ws_bytes,
-                                _stream_handle(stream))
-    if st != MC_OK:
-        raise McError(st, "mc_kv_append_paged")
+    n = len(prefix_lens)
+    _enqueue("mc_kv_append_paged", "spppppiIIipii", _params(params), k_new, v_new, k_pool, v_pool, block_tables,
+             _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, workspace,
+             _nbytes(workspace), _on(stream))
 
 
 def attn_params(num_q_heads: int, num_kv_heads: int, head_dim: int, page_size: int, num_pages: int,

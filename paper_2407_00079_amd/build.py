@@ -1,9 +1,11 @@
-"""Build ``libmooncake_hip.so`` in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Build ``libmooncake_hip.so`` (hipcc for gfx950, cross-compiles without a GPU) and ``_mccall.so``, through which the binding
+calls it, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmooncake_hip.so")
+CALLER = os.path.join(PKG, "_mccall.so")
 # host_plan.cpp holds no device code: hipcc compiles it as plain C++
 SOURCES = ["mc_api.hip", "host_plan.cpp", "attn_prefill.hip", "attn_prefill_bf16.hip", "attn_narrow.hip", "attn_noalloc.hip", "kv_copy.hip", "prefix_hash.hip"]
 
@@ -34,13 +37,20 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_caller() -> None:
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", "-I",
+                    sysconfig.get_paths()["include"], "-o", CALLER, os.path.join(CSRC, "pycall.cpp")], check=True)
+
+
 def build(verbose: bool = False) -> str:
     """Compile every kernel source and link the shared library; returns its path."""
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        caller = ex.submit(_build_caller)
         objs = list(ex.map(_compile, SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    caller.result()
     if verbose:
         print("built", LIB)
     return LIB
