@@ -1,11 +1,13 @@
-// Narrow form of the attention kernels, whole rows only: a workgroup owns 32 (fp32: 16) stacked query rows of one (request,
+// Narrow form of the attention kernels: a workgroup owns 32 (fp32: 16) stacked query rows of one (request,
 // KV head) and its eight waves share out the KEYS of those rows, each walking every eighth 32-key block by itself; their
 // results meet in LDS once, at the end (paper Section 5.1: attention is associative over key slices).
 //
 // The other forms give each wave rows of its own, 128 or 256 a workgroup, and all of them every key: a launch of few rows
 // leaves most of the chip idle and walks its keys at the pace of one workgroup.  Here a workgroup walks them at the rate one
 // compute unit can load them.  No partial results in memory, so it is what callers without room for them run (prepared
-// plans, calls without a workspace, calls with the minimal one), and no merge launch, which short calls gain from.
+// plans, calls without a workspace, calls with the minimal one), and no merge launch, which short calls gain from.  Where there
+// is room its row tiles are cut into pieces as those of the other forms are, into fewer: a workgroup starts sooner (4.7 us with
+// its launch, 7.6 the 128-row form) and a piece of four key tiles takes about as long as one of a single tile.
 //
 //   * A wave's block is its own: no barrier in the loop, and no tile that others wait for.  K and V go from the pool to
 //     registers, the next block's K while this one's scores are formed, its V as soon as P V has let go of this one's; K is
@@ -23,7 +25,9 @@
 // hint: 0.53.  64 keys a block (head_dim 64): no change; two workgroups a compute unit (128 registers): 0.27 and fp32 0.73.
 // Whole calls before / now, us: planned, 64/8 heads, P 30000, C 90 350 / 148; P 131056, C 16 1490 / 908; 16/16 heads, P 7206,
 // C 200 93 / 41; head_dim 64, 64/8 heads, P 30000, C 90 301 / 104; fp32, 8/2 heads, P 2798, C 62 183 / 31; one call with room
-// for pieces, fp32, 4/1 heads, P 256, C 128, append included: 18.8 / 14.2.  When it is taken: plan_classes (host_plan.cpp).
+// for pieces, fp32, 4/1 heads, P 256, C 128, append included: 18.8 / 14.2.  450 random one-shot calls whose narrow row tiles may
+// be cut, against only whole ones: geometric mean x1.05 (fp32 x1.25), the slowest x0.96.  When it is taken: plan_classes
+// (host_plan.cpp).
 #include "attn_device.h"
 #include "mc_internal.h"
 
@@ -53,7 +57,7 @@ struct Narrow {
     float top = sh.m[0][row];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) top = fmaxf(top, sh.m[w][row]);
-    // every row sees key 0, so `top` is finite but for rows of NaN or -inf scores, whose sums are NaN
+    // (no wave has a key for the row: in a piece of the keys, or where every score is -inf or NaN)
     const float ref = top == -INFINITY ? 0.f : top;
     float l = 0.f, acc[kPer];
 #pragma unroll
@@ -67,6 +71,17 @@ struct Narrow {
     }
     const int at = work.row0 + row, tok = at / a.G;
     const int64_t dst = (int64_t)(work.q_off + tok) * a.Hq + work.kv_head * a.G + (at - tok * a.G);
+    if (work.pieces > 1) {
+      // partial result in fp32; a row that saw no key of the piece has l = 0: zeros and -inf
+      const float inv = l == 0.f ? 0.f : 1.0f / l;
+      const int64_t part = work.part_row + at;
+      float v __attribute__((ext_vector_type(kPer)));
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) v[e] = acc[e] * inv;
+      *reinterpret_cast<decltype(v)*>(a.o_parts + part * D + col) = v;
+      if (col == 0) a.lse_parts[part] = l == 0.f ? -INFINITY : (top + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+      return;
+    }
     const float inv = 1.0f / l;
     Out v __attribute__((ext_vector_type(kPer)));
 #pragma unroll
@@ -121,6 +136,16 @@ struct Walk {
     }
   }
 };
+
+// 32-key blocks [first, end) of the keys up to token tok_last that are the workgroup's: all of them, or its piece's key tiles
+__device__ __forceinline__ void blocks_of(const Work& work, int tok_last, int* first, int* end) {
+  constexpr int kBlocks = kTileKeys / 32;
+  const int keys = work.prefix + tok_last + 1, all = (keys + 31) / 32;
+  int lo, hi;
+  piece_tiles((keys + kTileKeys - 1) / kTileKeys, work.piece, work.pieces, &lo, &hi);
+  *first = lo * kBlocks;
+  *end = hi * kBlocks < all ? hi * kBlocks : all;
+}
 
 // A wave's K block on its way to fragments: loaded as it lies (a quarter of a wave takes 256 contiguous bytes; lanes that load
 // their own fragments read 16 rows at once), turned in the wave's own corner of LDS.  Rows dense, 16-byte granules swizzled
@@ -187,7 +212,8 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
   const int tok_first = work.row0 / G;
   int tok_last = (work.row0 + kRows - 1) / G;
   tok_last = tok_last < work.chunk - 1 ? tok_last : work.chunk - 1;
-  const int n_blocks = (work.prefix + tok_last + kBlockKeys) / kBlockKeys;
+  int first_block, n_blocks;
+  blocks_of(work, tok_last, &first_block, &n_blocks);
   const int seen_by_all = work.prefix + tok_first + 1;
 
   const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadB;
@@ -221,7 +247,7 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
   // What the last turn loads (its own block again) nobody uses.
   auto next_after = [&](int b) __attribute__((always_inline)) { return b + kWaves < n_blocks ? b + kWaves : b; };
   int pid[kBlockPages];
-  int block = wave;
+  int block = first_block + wave;
   if (block < n_blocks) {
     walk.pages_of(block, pid);
     stage.load(walk, kbase, pid);
@@ -352,7 +378,8 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
   const int tok_first = work.row0 / G;
   int tok_last = (work.row0 + kRows - 1) / G;
   tok_last = tok_last < work.chunk - 1 ? tok_last : work.chunk - 1;
-  const int n_blocks = (work.prefix + tok_last + kBlockKeys) / kBlockKeys;
+  int first_block, n_blocks;
+  blocks_of(work, tok_last, &first_block, &n_blocks);
   const int seen_by_all = work.prefix + tok_first + 1;
 
   const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadBytes;
@@ -379,7 +406,7 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
   // What the last turn loads (its own block again) nobody uses.
   auto next_after = [&](int b) __attribute__((always_inline)) { return b + kWaves < n_blocks ? b + kWaves : b; };
   int pid[kBlockPages];
-  int block = wave;
+  int block = first_block + wave;
   if (block < n_blocks) {
     walk.pages_of(block, pid);
     stage.load(walk, kbase, pid);

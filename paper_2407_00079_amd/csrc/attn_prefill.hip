@@ -36,7 +36,7 @@
 //   * Launches of few or short row tiles take 128 rows per workgroup: one wave of each SIMD
 //     computes, the other only copies tiles (see Rows).  Twice the workgroups to cut, half the
 //     matrix work on a workgroup's critical path, and the copies off it.
-//   * Whole rows of still fewer rows, or of few keys, take 32 (fp32: 16) rows per workgroup, whose
+//   * Launches of still fewer rows, or of few keys, take 32 (fp32: 16) rows per workgroup, whose
 //     waves share out the keys (attn_narrow.hip).
 #include <type_traits>
 

@@ -278,10 +278,10 @@ struct FormCost {
 FormCost form_cost_of(const mc_attn_params* p, int64_t tile_rows) {
   const bool few = tile_rows == kAttnFewRows, full = tile_rows == kAttnTileRows;
   if (p->dtype == MC_DTYPE_F32)
-    return full ? FormCost{0, 9, 7.0, 3, 0.36} : few ? FormCost{0, 8.4, 3.8, 2.6, 0.36} : FormCost{0, 4.2, 0.58, 0, 0};
+    return full ? FormCost{0, 9, 7.0, 3, 0.36} : few ? FormCost{0, 8.4, 3.8, 2.6, 0.36} : FormCost{0, 4.2, 0.58, 4.1, 0.22};
   if (p->head_dim == 128)
-    return full ? FormCost{1, 4, 1.37, 3, 0.25} : few ? FormCost{2.1, 5.5, 0.72, 2, 0.31} : FormCost{0, 4.65, 0.315, 0, 0};
-  return full ? FormCost{1, 1, 0.94, 5, 0.25} : few ? FormCost{1.5, 4.2, 0.55, 2.6, 0.44} : FormCost{0, 4.2, 0.21, 0, 0};
+    return full ? FormCost{1, 4, 1.37, 3, 0.25} : few ? FormCost{2.1, 5.5, 0.72, 2, 0.31} : FormCost{0, 4.65, 0.315, 4.6, 0.5};
+  return full ? FormCost{1, 1, 0.94, 5, 0.25} : few ? FormCost{1.5, 4.2, 0.55, 2.6, 0.44} : FormCost{0, 4.2, 0.21, 3.9, 0.1};
 }
 // K and V bytes per microsecond: the most any form reads, and what the narrow one's time grows by beyond what the caches hold
 // (it has no tiles in flight beyond the next block, and row tiles of a request that do not run together read their keys again).
@@ -429,7 +429,7 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 // placing ends where the best does (same plans; host time of a call of 63 requests, 8/1 heads, C up to 300: 219 us with every
 // trial placed, 20 now; of 63 one-token requests 41 and 16; of one to three requests 1 us of planning).
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                  int64_t max_part_rows, ClassPlan* plan) {
+                  int64_t max_part_rows, ClassPlan* plan, bool keep_room) {
   const int64_t G = p->num_q_heads / p->num_kv_heads, Hkv = p->num_kv_heads;
   struct Active {
     int32_t req, q_off, prefix, chunk;
@@ -570,10 +570,12 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       best_k = plain;
     }
   }
-  // The narrow form, beside what has been chosen so far: no cut, no merge, the keys of a row tile at several times the pace,
-  // and, with so few rows a workgroup, more rounds of them.  Both are estimated row tile by row tile (in up to 16 steps a run).
+  // The narrow form, beside what has been chosen so far: the keys of a row tile at several times the pace, and, with so few rows
+  // a workgroup, more rounds of them; whole rows, or cut where that was cut.  Both are estimated row tile by row tile (in up to
+  // 16 steps a run).
   const int64_t narrow_rows = p->dtype == MC_DTYPE_F32 ? kAttnNarrowRowsF32 : kAttnNarrowRows;
   plan->narrow_wgs = 0;
+  plan->narrow_pieces = 1;
   const int64_t narrow_items = items_of(narrow_rows);
   if (narrow_items <= kMostNarrow) {
     auto place = [&](Units& units, const Run& run, int64_t cut, int64_t tile_rows, const FormCost& cost, double limit) {
@@ -586,46 +588,74 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       }
       return true;
     };
+    auto merge_of = [&](const FormCost& cost, int64_t part_rows) {
+      return part_rows > 0 ? cost.merge + cost.part_mb * (double)part_rows * (double)(p->head_dim + 1) * 8e-6 : 0.0;
+    };
     const double bytes = (double)kv_bytes(p, prefix_lens, new_lens, batch);
     const FormCost cost = form_cost_of(p, best_rows);
     const int uncut = lay_out(best_whole, best_rows);
     Units chosen;
-    double part_rows = 0.0;
+    int64_t part_rows = 0, longest = 0, longest_piece = 0;
     for (int i = 0; i < n_runs; ++i) {
       const int64_t cut = i < uncut || best_of == 0 ? 1 : runs[i].pieces(best_of, best_k);
       place(chosen, runs[i], cut, best_rows, cost, HUGE_VAL);
-      if (cut > 1) part_rows += (double)(cut * runs[i].rows);
+      if (cut > 1) part_rows += cut * runs[i].rows;
+      longest = std::max(longest, runs[i].longest);
+      longest_piece = std::max(longest_piece, (runs[i].longest + cut - 1) / cut);
     }
-    const double merge = part_rows > 0.0 ? cost.merge + cost.part_mb * part_rows * (double)(p->head_dim + 1) * 8e-6 : 0.0;
-    double end = cost.launch + std::max(chosen.end(), bytes / kReadPerUs) + merge;
+    double end = cost.launch + std::max(chosen.end(), bytes / kReadPerUs) + merge_of(cost, part_rows);
+    if (part_rows > 0) end /= kNarrowSlack;
     const FormCost narrow = form_cost_of(p, narrow_rows);
     const double missed = std::max(0.0, bytes - kNarrowHeld) / kNarrowMissPerUs;
-    Units units;
+    const int64_t room = keep_room ? max_part_rows : part_rows;
     // (a row tile of one key tile is one block for each of two waves: the 128-row form has that done as soon)
-    int64_t longest = 0;
-    for (int i = 0; i < n; ++i) longest = std::max(longest, (act[i].prefix + act[i].chunk + kAttnTileKeys - 1) / (int64_t)kAttnTileKeys);
-    if (narrow_items > kComputeUnits) end /= bytes > kXcdCaches ? kNarrowApartSlack : kNarrowRoundsSlack;
-    else if (merge > 0.0) end /= kNarrowSlack;
-    bool sooner = longest > 1 && (p->dtype != MC_DTYPE_F32 || longest <= kNarrowTilesF32) &&
-                  narrow.launch + bytes / kNarrowReadPerUs < end;
-    for (int i = 0; i < n && sooner; ++i) {
-      const int64_t last = (act[i].chunk * G - 1) / narrow_rows;
-      sooner = place(units, make_run(p, i, act[i].prefix, act[i].chunk, 0, last, narrow_rows), 1, narrow_rows, narrow,
-                     end - narrow.launch - missed);
+    const bool may = longest > 1 && bytes / kNarrowReadPerUs < end && (p->dtype != MC_DTYPE_F32 || longest_piece <= kNarrowTilesF32);
+    n_runs = 0;
+    double work = 0.0;
+    for (int i = 0; i < n && may; ++i) {
+      runs[n_runs] = make_run(p, i, act[i].prefix, act[i].chunk, 0, (act[i].chunk * G - 1) / narrow_rows, narrow_rows);
+      work += (double)runs[n_runs].items * narrow.tile * runs[n_runs].mean();
+      ++n_runs;
     }
-    if (sooner) {
+    int64_t narrow_k = 0, n_before = 0;
+    for (int64_t k = 1; may && k <= longest && k <= MC_MAX_KV_SPLITS; k += k < 8 ? 1 : k < 32 ? 4 : 16) {
+      if (p->dtype == MC_DTYPE_F32 && (longest + k - 1) / k > kNarrowTilesF32) continue;
+      int64_t n_pieces = 0, parts = 0;
+      for (int i = 0; i < n_runs; ++i) {
+        const int64_t cut = runs[i].pieces(longest, k);
+        n_pieces += runs[i].items * cut;
+        if (cut > 1) parts += cut * runs[i].rows;
+      }
+      if (n_pieces > kMostNarrow || (k > 1 && parts > room)) break;
+      if (n_pieces == n_before) continue;
+      n_before = n_pieces;
+      const double rest = narrow.launch + missed + merge_of(narrow, parts);
+      double by = end;                                     // when it has to have ended
+      if (n_pieces > kComputeUnits) by /= bytes > kXcdCaches ? kNarrowApartSlack : kNarrowRoundsSlack;
+      if (rest + std::max(narrow.fixed, (work + narrow.fixed * (double)n_pieces) / kComputeUnits) >= by) continue;
+      Units units;
+      bool sooner = true;
+      for (int i = 0; i < n_runs && sooner; ++i)
+        sooner = place(units, runs[i], runs[i].pieces(longest, k), narrow_rows, narrow, by - rest);
+      if (!sooner) continue;
+      end = rest + units.end();
+      narrow_k = k;
+    }
+    if (narrow_k > 0) {
       AttnClasses& t = plan->narrow;
       t.n = n;
       t.rows = (int32_t)narrow_rows;
       t.once = 0;
-      int64_t wg = 0;
+      int64_t wg = 0, parts = 0;
       for (int i = 0; i < kMaxAttnClasses; ++i) {
         t.first[i] = i < n ? (int32_t)wg : 0;
         t.c[i] = AttnClass{};
         if (i >= n) continue;
-        const int64_t tiles = (act[i].chunk * G + narrow_rows - 1) / narrow_rows;
-        t.c[i] = AttnClass{act[i].req, act[i].q_off, act[i].prefix, act[i].chunk, 0, (int32_t)(tiles - 1), 1, 0};
-        wg += tiles * Hkv;
+        const int64_t cut = runs[i].pieces(longest, narrow_k);
+        t.c[i] = AttnClass{act[i].req, act[i].q_off, act[i].prefix, act[i].chunk, 0, (int32_t)runs[i].tile_hi, (int32_t)cut, (int32_t)parts};
+        wg += runs[i].items * cut;
+        if (cut > 1) parts += cut * runs[i].rows;
+        plan->narrow_pieces = std::max<int32_t>(plan->narrow_pieces, (int32_t)cut);
       }
       plan->narrow_wgs = (int32_t)wg;
       if (max_part_rows == 0) {
@@ -681,12 +711,12 @@ bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int3
     }
     lay->room = available >= lay->total;
   };
-  auto plan_with = [&](int64_t max_part_rows) {
-    lay->by_classes = plan_classes(p, prefix_lens, new_lens, batch, max_part_rows, &lay->plan);
+  auto plan_with = [&](int64_t max_part_rows, bool keep_room = false) {
+    lay->by_classes = plan_classes(p, prefix_lens, new_lens, batch, max_part_rows, &lay->plan, keep_room);
   };
   if (s > 1) {
     place(s * rows);
-    plan_with(lay->room ? s * rows : 0);
+    plan_with(lay->room ? s * rows : 0, true);
     return true;
   }
   // a launch of few workgroups may be cut all the same, and finer: at most 64 parts of a row

@@ -83,16 +83,17 @@ int32_t suggest_kv_splits(const mc_attn_params* p, const int32_t* prefix_lens, c
 // false: more requests with new tokens than a launch has classes for.
 struct ClassPlan {
   AttnClasses classes;
-  // Workgroups of the narrow form, if that is sooner (0: it is not); `narrow` are its classes, whole rows, and the launch takes
-  // them instead.  (Without room for partial results `classes` are then the whole rows of 128-row tiles.)
-  int32_t narrow_wgs;
+  // Workgroups of the narrow form, if that is sooner (0: it is not); `narrow` are its classes, whole rows or cut into up to
+  // narrow_pieces pieces, and the launch takes them instead.  Their partial results take no more room than those of `classes`
+  // or, with `keep_room`, than max_part_rows.  (Without room for partial results `classes` are the whole rows of 128-row tiles.)
+  int32_t narrow_wgs, narrow_pieces;
   AttnClasses narrow;
   int32_t n_wgs;          // workgroups of the attention launch
   int32_t most_pieces;    // 1: nothing is cut, no partial results, no merge
   int64_t part_rows;      // rows of partial results
 };
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                  int64_t max_part_rows, ClassPlan* plan);
+                  int64_t max_part_rows, ClassPlan* plan, bool keep_room = false);
 
 // Workspace of the automatic form: [work list + request table | o_parts | lse_parts], each part
 // starting at a multiple of 256 bytes.  The partial results have room for kv_splits parts of every row (kv_splits > 1)

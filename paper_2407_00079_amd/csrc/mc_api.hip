@@ -275,14 +275,14 @@ mc_status launch_class_plan(const mc_attn_params* p, const ClassPlan& plan, cons
   args.n_items = plan.narrow_wgs > 0 ? plan.narrow_wgs : plan.n_wgs;
   args.o_parts = o_parts;
   args.lse_parts = lse_parts;
-  if (plan.narrow_wgs > 0)
-    return mc::launch_attn_narrow(p->dtype, args, &plan.narrow, stream) == hipSuccess ? MC_OK : MC_ERR_HIP;
-  if (mc::launch_attn_classes(p->dtype, args, plan.classes, stream) != hipSuccess) return MC_ERR_HIP;
-  if (plan.most_pieces > 1 &&
-      mc::launch_attn_merge_classes(p->dtype, p->head_dim, o_parts, lse_parts, plan.classes, p->num_q_heads,
-                                    p->num_kv_heads, out, lse, stream) != hipSuccess)
-    return MC_ERR_HIP;
-  return MC_OK;
+  const bool narrow = plan.narrow_wgs > 0;
+  const mc::AttnClasses& classes = narrow ? plan.narrow : plan.classes;
+  hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, &classes, stream)
+                         : mc::launch_attn_classes(p->dtype, args, classes, stream);
+  if (st == hipSuccess && (narrow ? plan.narrow_pieces : plan.most_pieces) > 1)
+    st = mc::launch_attn_merge_classes(p->dtype, p->head_dim, o_parts, lse_parts, classes, p->num_q_heads, p->num_kv_heads, out,
+                                       lse, stream);
+  return st == hipSuccess ? MC_OK : MC_ERR_HIP;
 }
 
 // One-shot whole-row attention, over pieces of the keys where the workspace has room for partial results.  need_room:

@@ -42,8 +42,8 @@ hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t stream);
 hipError_t launch_attn_classes(int dtype, const AttnArgs& args, const AttnClasses& t, hipStream_t stream);
 hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream);
 
-// the narrow form, whole rows: args.n_items workgroups described by classes of its row tiles, or (t null) the row tiles of
-// the list's args.n_items items
+// the narrow form: args.n_items workgroups described by classes of its row tiles, or (t null) the row tiles of the list's
+// args.n_items items, whole
 hipError_t launch_attn_narrow(int dtype, const AttnArgs& args, const AttnClasses* t, hipStream_t stream);
 
 // enqueue the merge of the classes that were cut into pieces (nothing if none was)

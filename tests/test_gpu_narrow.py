@@ -53,3 +53,35 @@ def test_narrow_form_matches_oracle(oracle, dtype, Hq, Hkv, D, prefix, new, q_sc
         bits = dc.out.clone(), dc.lse.clone()
         first = first or bits
         assert torch.equal(bits[0], first[0]) and torch.equal(bits[1], first[1])
+
+
+# one call with room for partial results: narrow row tiles cut into pieces, and (the second half) shapes whose row tiles of 128
+# and of 256 rows are cut all the same
+PIECES = [
+    (W.BF16, 8, 1, 128, [9000], [4]), (W.BF16, 4, 1, 128, [5531, 300], [70, 20]), (W.BF16, 8, 1, 128, [15000, 0, 63], [1, 9, 5]),
+    (W.BF16, 16, 2, 64, [6001], [17]), (W.BF16, 12, 3, 128, [4100, 64], [33, 1]),
+    (W.F32, 8, 2, 64, [4091], [6]), (W.F32, 4, 1, 64, [9000, 17], [9, 40]), (W.F32, 16, 16, 64, [2100], [17]),
+    (W.BF16, 8, 2, 128, [401, 10503], [70, 1]), (W.BF16, 4, 1, 128, [250, 6614, 142], [80, 9, 76]), (W.BF16, 64, 8, 128, [7, 7908], [370, 2]),
+    (W.BF16, 64, 8, 64, [10515, 118], [2, 120]), (W.BF16, 64, 8, 64, [53, 1495], [419, 21]), (W.F32, 64, 8, 64, [68, 304], [147, 45]),
+    (W.F32, 64, 8, 64, [103, 704], [180, 33]),
+]
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,prefix,new", PIECES)
+def test_cut_row_tiles_match_oracle(oracle, dtype, Hq, Hkv, D, prefix, new):
+    print(f"cut case {dtype} Hq={Hq} Hkv={Hkv} D={D} prefix={prefix} new={new}", flush=True)
+    pages = sum(-(-(p + c) // 16) for p, c in zip(prefix, new)) + 5
+    case = W.make_attn_case(96, dtype, Hq, Hkv, D, 16, prefix, new, pages, q_scale=4.0)
+    dc = DeviceCase(case)
+    need = B.mc_prefill_attn_auto_workspace_bytes(dc.params, prefix, new)
+    assert need > B.mc_prefill_attn_workspace_bytes(dc.params, case.batch, case.total_new)
+    # the workspace between NaNs, and NaN itself: a write outside it, or a read of a part that was not written, shows
+    guard = 1 << 16
+    buf = torch.full(((need + 2 * guard) // 4 + 4,), float("nan"), dtype=torch.float32, device="cuda:0").view(torch.uint8)
+    B.mc_prefill_attn_paged(dc.params, dc.q, dc.k_pool, dc.v_pool, dc.block_tables, prefix, new, dc.out, dc.lse, buf[guard:guard + need])
+    out, lse = dc.result()
+    ref_out, ref_lse, _ = oracle.case_full(case)
+    check_close(out, ref_out, dtype, "cut")
+    assert np.abs(lse - ref_lse).max() <= TOL[dtype]["lse_abs"]
+    first = (guard + need + 3) // 4 * 4
+    assert torch.isnan(buf[:guard].view(torch.float32)).all() and torch.isnan(buf[first:first + guard].view(torch.float32)).all()
