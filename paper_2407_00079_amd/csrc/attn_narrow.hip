@@ -1,4 +1,4 @@
-// Narrow form of the attention kernels: a workgroup owns 32 (fp32: 16) stacked query rows of one (request,
+// Narrow form of the attention kernels: a workgroup owns 32 (fp32, or no more of them: 16) stacked query rows of one (request,
 // KV head) and its eight waves share out the KEYS of those rows, each walking every eighth 32-key block by itself; their
 // results meet in LDS once, at the end (paper Section 5.1: attention is associative over key slices).
 //
@@ -183,10 +183,14 @@ struct StageK {
   }
 };
 
-template <int D>
+// RT: 16-row tiles of a wave.  Two share every K and V fragment; one where no request has more rows (us, two / one: 64/8 heads,
+// P 30000, C 1 149 / 139; P 1023, C 2 10.3 / 8.8; 16/16 heads, P 300, C 16 6.7 / 5.9; head_dim 64, 64/8 heads, P 30000, C 2
+// 104 / 85).  250 random batches, one-shot and planned: 34 calls of at most 16 rows are 1.04-1.22
+// times as fast, none loses.
+template <int D, int RT>
 __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work) {
   constexpr int kBlockKeys = 32, kBlockPages = kBlockKeys / kPageTokens;
-  constexpr int kRows = 32, kSteps = D / 32, kVec = D / 16, kRowB = D * 2, kPageHeadB = kPageTokens * kRowB;
+  constexpr int kRows = 16 * RT, kSteps = D / 32, kVec = D / 16, kRowB = D * 2, kPageHeadB = kPageTokens * kRowB;
   typedef Narrow<kRows, D, kBlockKeys, __bf16> N;
   typedef uint32_t vvec __attribute__((ext_vector_type(kVec / 2)));
   __shared__ __attribute__((aligned(256))) typename N::Shared sh;
@@ -197,10 +201,10 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
   const int G = a.G, n_rows = work.chunk * G;
   const Walk walk(a, work, kPageHeadB);
 
-  int tok[2];
-  bf16x8 qf[kSteps][2];
+  int tok[RT];
+  bf16x8 qf[kSteps][RT];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
+  for (int rt = 0; rt < RT; ++rt) {
     int row = work.row0 + rt * 16 + j;
     row = row < n_rows ? row : n_rows - 1;                 // rows past the chunk's end compute the last one again
     tok[rt] = row / G;
@@ -230,13 +234,14 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
     }
   };
 
-  f32x4 o[kVec][2], l_acc[2];
-  float m_run[2] = {-INFINITY, -INFINITY};
+  f32x4 o[kVec][RT], l_acc[RT];
+  float m_run[RT];
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
+  for (int rt = 0; rt < RT; ++rt) {
+    m_run[rt] = -INFINITY;
     l_acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < kVec; ++e) o[e][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -258,9 +263,9 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
     stage.put(k_lds);
     stage.load(walk, kbase, pid);
     __builtin_amdgcn_sched_barrier(0);
-    f32x4 s[2][kBlockPages];                               // keys 16 kt + 4 g + r of the block
+    f32x4 s[RT][kBlockPages];                               // keys 16 kt + 4 g + r of the block
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int kt = 0; kt < kBlockPages; ++kt) s[rt][kt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -269,12 +274,12 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
       for (int kt = 0; kt < kBlockPages; ++kt) {
         const bf16x8 kf = stage.template fragment<bf16x8>(k_lds, kt, st);
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt) s[rt][kt] = mma(kf, qf[st][rt], s[rt][kt]);
+        for (int rt = 0; rt < RT; ++rt) s[rt][kt] = mma(kf, qf[st][rt], s[rt][kt]);
       }
     if ((block + 1) * kBlockKeys > seen_by_all) {
       asm volatile("");                                    // (a branch, not selects on every block's path)
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
+      for (int rt = 0; rt < RT; ++rt) {
         const int lim = work.prefix + tok[rt] - block * kBlockKeys - 4 * g;
 #pragma unroll
         for (int kt = 0; kt < kBlockPages; ++kt)
@@ -288,14 +293,14 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
       for (int q = 0; q < 8; ++q)
         if (block * kBlockKeys + (q >> 2) * 16 + 4 * g + (q & 3) >= walk.L) vr[q] = vvec{};
     }
-    float mx[2];
+    float mx[RT];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
       mx[rt] = max_over_groups(max8(s[rt][0], s[rt][1])) * c;
     }
-    if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] + kRescaleSlack || mx[1] > m_run[1] + kRescaleSlack) != 0) {
+    if (__builtin_amdgcn_ballot_w64(mx[0] > m_run[0] + kRescaleSlack || mx[RT - 1] > m_run[RT - 1] + kRescaleSlack) != 0) {
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
+      for (int rt = 0; rt < RT; ++rt) {
         const float m_new = fmaxf(m_run[rt], mx[rt]);
         const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run[rt] - m_new);
         m_run[rt] = m_new;
@@ -304,9 +309,9 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
         for (int e = 0; e < kVec; ++e) o[e][rt] *= alpha;
       }
     }
-    u32x4 p[2];
+    u32x4 p[RT];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
       const float ref = fmaxf(m_run[rt], kNoKeyYet);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -327,7 +332,7 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
       for (int k = 0; k < 4; ++k)
         w[k] = __builtin_amdgcn_perm(vr[2 * k + 1][e >> 1], vr[2 * k][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
         o[e][rt] = mma(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, p[rt]), o[e][rt]);
     }
     load_v(pid);
@@ -337,7 +342,7 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
 
   // column kVec (4 g + r) + e of row 16 rt + j
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
+  for (int rt = 0; rt < RT; ++rt) {
     const int row = rt * 16 + j;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -481,44 +486,48 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
 }
 
 // BF16_D: head_dim of the bf16 forms, 0: fp32
-template <int BF16_D>
+template <int BF16_D, int ROWS>
 __device__ __forceinline__ void narrow_body(const AttnArgs& a, const Work& work) {
   if constexpr (BF16_D == 0) narrow_f32(a, work);
-  else narrow_bf16<BF16_D>(a, work);
+  else narrow_bf16<BF16_D, ROWS / 16>(a, work);
 }
-template <int BF16_D>
-constexpr int kNarrowRowsOf = BF16_D == 0 ? kAttnNarrowRowsF32 : kAttnNarrowRows;
 
-template <int BF16_D>
+template <int BF16_D, int ROWS>
 __global__ __launch_bounds__(kWaves * 64) void attn_narrow_classes_kernel(const AttnArgs a, const AttnClasses t) {
-  narrow_body<BF16_D>(a, work_of<kNarrowRowsOf<BF16_D>>(t, blockIdx.x, a.Hkv, a.G));
+  narrow_body<BF16_D, ROWS>(a, work_of<ROWS>(t, blockIdx.x, a.Hkv, a.G));
 }
 
-// workgroups n_items k .. take the k-th kNarrowRowsOf rows of the items
-template <int BF16_D>
+// workgroups n_items k .. take the k-th ROWS rows of the items
+template <int BF16_D, int ROWS>
 __global__ __launch_bounds__(kWaves * 64) void attn_narrow_list_kernel(const AttnArgs a) {
   const int part = (int)blockIdx.x / a.n_items;
   const AttnItem item = a.items[(int)blockIdx.x - part * a.n_items];
   const AttnReq rq = a.reqs[item.req];
-  const int row0 = item.row0 + part * kNarrowRowsOf<BF16_D>;
+  const int row0 = item.row0 + part * ROWS;
   if (row0 >= rq.chunk * a.G) return;
-  narrow_body<BF16_D>(a, Work{item.req, item.kv_head, row0, rq.q_off, rq.prefix, rq.chunk, 0, 1, 0, false});
+  narrow_body<BF16_D, ROWS>(a, Work{item.req, item.kv_head, row0, rq.q_off, rq.prefix, rq.chunk, 0, 1, 0, false});
 }
 
-template <int BF16_D>
-void enqueue(const AttnArgs& args, const AttnClasses* t, hipStream_t stream) {
-  if (t != nullptr) attn_narrow_classes_kernel<BF16_D><<<args.n_items, kWaves * 64, 0, stream>>>(args, *t);
-  else attn_narrow_list_kernel<BF16_D><<<args.n_items * (kAttnTileRows / kNarrowRowsOf<BF16_D>), kWaves * 64, 0, stream>>>(args);
+template <int BF16_D, int ROWS>
+void enqueue(const AttnArgs& args, int parts, const AttnClasses* t, hipStream_t stream) {
+  if (t != nullptr) attn_narrow_classes_kernel<BF16_D, ROWS><<<args.n_items, kWaves * 64, 0, stream>>>(args, *t);
+  else attn_narrow_list_kernel<BF16_D, ROWS><<<args.n_items * parts, kWaves * 64, 0, stream>>>(args);
 }
 
 }  // namespace
 
-hipError_t launch_attn_narrow(int dtype, const AttnArgs& args, const AttnClasses* t, hipStream_t stream) {
+hipError_t launch_attn_narrow(int dtype, const AttnArgs& args, int rows, int parts, const AttnClasses* t, hipStream_t stream) {
   (void)hipGetLastError();
-  if (dtype == MC_DTYPE_F32 && args.head_dim == 64) enqueue<0>(args, t, stream);
-  else if (dtype == MC_DTYPE_BF16 && args.head_dim == 128) enqueue<128>(args, t, stream);
-  else if (dtype == MC_DTYPE_BF16 && args.head_dim == 64) enqueue<64>(args, t, stream);
-  else return hipErrorInvalidValue;
+  const bool bf16 = dtype == MC_DTYPE_BF16, least = rows == kAttnLeastRows;
+  if (!least && !(bf16 && rows == kAttnNarrowRows)) return hipErrorInvalidValue;
+  if (dtype == MC_DTYPE_F32 && args.head_dim == 64)
+    enqueue<0, kAttnLeastRows>(args, parts, t, stream);
+  else if (bf16 && args.head_dim == 128)
+    least ? enqueue<128, kAttnLeastRows>(args, parts, t, stream) : enqueue<128, kAttnNarrowRows>(args, parts, t, stream);
+  else if (bf16 && args.head_dim == 64)
+    least ? enqueue<64, kAttnLeastRows>(args, parts, t, stream) : enqueue<64, kAttnNarrowRows>(args, parts, t, stream);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

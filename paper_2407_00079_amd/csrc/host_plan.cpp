@@ -181,7 +181,7 @@ int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int
                   int32_t kv_splits, int64_t n_items) {
   ClassPlan plan;
   const bool planned = kv_splits == 0 && plan_classes(p, prefix_lens, new_lens, batch, 0, &plan);
-  if (planned && plan.narrow_wgs > 0) return kListNarrow;
+  if (planned && plan.narrow_wgs > 0) return few_rows(p, new_lens, batch, kAttnLeastRows) ? kListNarrowLeast : kListNarrow;
   if (few_rows(p, new_lens, batch, kAttnFewRows))
     return reads_once(p, prefix_lens, new_lens, batch, kAttnFewRows) ? kListFewOnce : kListFew;
   if (planned) return plan.classes.rows == kAttnFewRows ? kListHalves : 0;
@@ -276,12 +276,13 @@ struct FormCost {
   double launch, fixed, tile, merge, part_mb;
 };
 FormCost form_cost_of(const mc_attn_params* p, int64_t tile_rows) {
-  const bool few = tile_rows == kAttnFewRows, full = tile_rows == kAttnTileRows;
-  if (p->dtype == MC_DTYPE_F32)
-    return full ? FormCost{0, 9, 7.0, 3, 0.36} : few ? FormCost{0, 8.4, 3.8, 2.6, 0.36} : FormCost{0, 4.2, 0.58, 4.1, 0.22};
-  if (p->head_dim == 128)
-    return full ? FormCost{1, 4, 1.37, 3, 0.25} : few ? FormCost{2.1, 5.5, 0.72, 2, 0.31} : FormCost{0, 4.65, 0.315, 4.6, 0.5};
-  return full ? FormCost{1, 1, 0.94, 5, 0.25} : few ? FormCost{1.5, 4.2, 0.55, 2.6, 0.44} : FormCost{0, 4.2, 0.21, 3.9, 0.1};
+  const int form = tile_rows == kAttnTileRows ? 0 : tile_rows == kAttnFewRows ? 1 : tile_rows == kAttnNarrowRows ? 2 : 3;
+  static constexpr FormCost kF32[4] = {{0, 9, 7.0, 3, 0.36}, {0, 8.4, 3.8, 2.6, 0.36}, {}, {0, 4.2, 0.58, 4.1, 0.22}};
+  static constexpr FormCost kBf16[4] = {{1, 4, 1.37, 3, 0.25}, {2.1, 5.5, 0.72, 2, 0.31}, {0, 4.65, 0.315, 4.6, 0.5},
+                                        {0, 4.0, 0.29, 4.4, 0.4}};
+  static constexpr FormCost kBf16D64[4] = {{1, 1, 0.94, 5, 0.25}, {1.5, 4.2, 0.55, 2.6, 0.44}, {0, 4.2, 0.21, 3.9, 0.1},
+                                           {0, 3.8, 0.18, 3.8, 0.1}};
+  return (p->dtype == MC_DTYPE_F32 ? kF32 : p->head_dim == 128 ? kBf16 : kBf16D64)[form];
 }
 // K and V bytes per microsecond: the most any form reads, and what the narrow one's time grows by beyond what the caches hold
 // (it has no tiles in flight beyond the next block, and row tiles of a request that do not run together read their keys again).
@@ -573,7 +574,8 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   // The narrow form, beside what has been chosen so far: the keys of a row tile at several times the pace, and, with so few rows
   // a workgroup, more rounds of them; whole rows, or cut where that was cut.  Both are estimated row tile by row tile (in up to
   // 16 steps a run).
-  const int64_t narrow_rows = p->dtype == MC_DTYPE_F32 ? kAttnNarrowRowsF32 : kAttnNarrowRows;
+  const int64_t narrow_rows =
+      p->dtype == MC_DTYPE_F32 || few_rows(p, new_lens, batch, kAttnLeastRows) ? kAttnLeastRows : kAttnNarrowRows;
   plan->narrow_wgs = 0;
   plan->narrow_pieces = 1;
   const int64_t narrow_items = items_of(narrow_rows);
@@ -652,7 +654,8 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         t.c[i] = AttnClass{};
         if (i >= n) continue;
         const int64_t cut = runs[i].pieces(longest, narrow_k);
-        t.c[i] = AttnClass{act[i].req, act[i].q_off, act[i].prefix, act[i].chunk, 0, (int32_t)runs[i].tile_hi, (int32_t)cut, (int32_t)parts};
+        t.c[i] = AttnClass{act[i].req, act[i].q_off, act[i].prefix, act[i].chunk, 0, (int32_t)runs[i].tile_hi, (int32_t)cut,
+                           (int32_t)parts};
         wg += runs[i].items * cut;
         if (cut > 1) parts += cut * runs[i].rows;
         plan->narrow_pieces = std::max<int32_t>(plan->narrow_pieces, (int32_t)cut);

@@ -222,8 +222,11 @@ mc_status launch_planned_attn(const mc_attn_params* p, const mc_attn_plan* plan,
   args.rows_total = plan->total_new_tokens * p->num_q_heads;
   args.o_parts = o_parts;
   args.lse_parts = lse_parts;
-  const bool narrow = plan->reserved == kListNarrow && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
-  const hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, nullptr, stream) : mc::launch_attn(p->dtype, args, stream);
+  const bool least = plan->reserved == kListNarrowLeast;
+  const bool narrow = (plan->reserved == kListNarrow || least) && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
+  const int rows = least || p->dtype == MC_DTYPE_F32 ? mc::kAttnLeastRows : mc::kAttnNarrowRows;
+  const hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, rows, least ? 1 : mc::kAttnTileRows / rows, nullptr, stream)
+                               : mc::launch_attn(p->dtype, args, stream);
   return st == hipSuccess ? MC_OK : MC_ERR_HIP;
 }
 
@@ -277,7 +280,7 @@ mc_status launch_class_plan(const mc_attn_params* p, const ClassPlan& plan, cons
   args.lse_parts = lse_parts;
   const bool narrow = plan.narrow_wgs > 0;
   const mc::AttnClasses& classes = narrow ? plan.narrow : plan.classes;
-  hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, &classes, stream)
+  hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, classes.rows, 1, &classes, stream)
                          : mc::launch_attn_classes(p->dtype, args, classes, stream);
   if (st == hipSuccess && (narrow ? plan.narrow_pieces : plan.most_pieces) > 1)
     st = mc::launch_attn_merge_classes(p->dtype, p->head_dim, o_parts, lse_parts, classes, p->num_q_heads, p->num_kv_heads, out,

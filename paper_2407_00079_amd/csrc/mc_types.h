@@ -68,8 +68,9 @@ constexpr int kShortHashBlocks = 32;
 constexpr int kAttnTileRows = 256;
 // ... and of the form for launches whose row tiles are few or short: 4 waves compute (one per SIMD), 4 copy tiles
 constexpr int kAttnFewRows = 128;
-// ... and of the narrow form, whose waves share out keys instead of rows (attn_narrow.hip)
-constexpr int kAttnNarrowRows = 32, kAttnNarrowRowsF32 = 16;
+// ... and of the narrow form, whose waves share out keys instead of rows (attn_narrow.hip): bf16, or fp32 and bf16 where no
+// request has more rows
+constexpr int kAttnNarrowRows = 32, kAttnLeastRows = 16;
 // keys of one LDS tile; key slices of the split form are whole tiles
 constexpr int kAttnTileKeys = 64;
 // 16-byte vectors of a page one copy workgroup moves (512 threads, one vector each)

@@ -12,7 +12,7 @@ from gpu_util import TOL, DeviceCase, check_close
 
 pytestmark = pytest.mark.gpu
 
-NARROW = 0x4d434634                            # mc_attn_plan.reserved of a list that is launched so
+NARROW, LEAST = 0x4d434634, 0x4d434635         # mc_attn_plan.reserved of a list that is launched so; no request has more than 16 rows
 
 # dtype, Hq, Hkv, D, prefix, new
 CASES = [(W.BF16, 8, 1, 128, [keys - 4], [4]) for keys in (65, 95, 96, 97, 255, 256, 257, 288, 289, 511, 513, 545)]    # 32 rows; blocks per wave
@@ -20,6 +20,8 @@ CASES += [(W.BF16, 8, 2, 64, [keys - 9], [9]) for keys in (66, 256, 257, 300)]  
 CASES += [(W.F32, 4, 1, 64, [keys - 5], [5]) for keys in (67, 96, 255, 256, 257, 290)]                               # 20 rows: 16 and 4
 CASES += [
     (W.BF16, 8, 1, 128, [300], [1]),                          # 8 rows
+    (W.BF16, 4, 1, 128, [255, 900, 0], [1, 4, 3]), (W.BF16, 16, 16, 128, [285], [16]), (W.BF16, 16, 16, 64, [77, 640], [16, 1]),
+    (W.BF16, 16, 16, 128, [285, 30], [17, 16]), (W.F32, 8, 2, 64, [100, 513], [4, 1]),       # 16 rows, and one more
     (W.BF16, 16, 1, 128, [70], [2]),                          # exactly a row tile of 16 heads a group
     (W.BF16, 64, 8, 128, [1023], [33]),                       # 264 rows: more than one item of the list, the last of 8 rows
     (W.BF16, 12, 3, 128, [999, 1, 0], [130, 0, 257]),         # three heads, an empty request, no prefix: row tiles of one to five key tiles
@@ -38,7 +40,7 @@ def test_narrow_form_matches_oracle(oracle, dtype, Hq, Hkv, D, prefix, new, q_sc
     dc = DeviceCase(case)
     plan_ws = torch.empty_like(dc.workspace)
     plan = B.mc_prefill_attn_prepare(dc.params, prefix, new, 0, plan_ws)
-    assert plan.reserved == NARROW
+    assert plan.reserved == (LEAST if max(new) * (Hq // Hkv) <= 16 else NARROW)
     args = (dc.q, dc.k_pool, dc.v_pool, dc.block_tables)
     ref_out, ref_lse, _ = oracle.case_full(case)
     first = None
@@ -58,6 +60,7 @@ def test_narrow_form_matches_oracle(oracle, dtype, Hq, Hkv, D, prefix, new, q_sc
 # one call with room for partial results: narrow row tiles cut into pieces, and (the second half) shapes whose row tiles of 128
 # and of 256 rows are cut all the same
 PIECES = [
+    (W.BF16, 8, 1, 128, [12000], [2]), (W.BF16, 16, 16, 64, [5000, 90], [16, 3]),
     (W.BF16, 8, 1, 128, [9000], [4]), (W.BF16, 4, 1, 128, [5531, 300], [70, 20]), (W.BF16, 8, 1, 128, [15000, 0, 63], [1, 9, 5]),
     (W.BF16, 16, 2, 64, [6001], [17]), (W.BF16, 12, 3, 128, [4100, 64], [33, 1]),
     (W.F32, 8, 2, 64, [4091], [6]), (W.F32, 4, 1, 64, [9000, 17], [9, 40]), (W.F32, 16, 16, 64, [2100], [17]),

@@ -23,7 +23,7 @@ int main() {
   mc::host::ClassPlan plan;
   if (!mc::host::plan_classes(&p, P.data(), C.data(), batch, room, &plan)) return 2;
   const int32_t form = mc::host::list_form(&p, P.data(), C.data(), batch, 0, mc::host::count_items(&p, C.data(), batch));
-  std::printf("%d %d %d %lld", plan.narrow_wgs, plan.narrow_pieces, form == mc::host::kListNarrow, (long long)plan.part_rows);
+  std::printf("%d %d %d %lld", plan.narrow_wgs, plan.narrow_pieces, form == mc::host::kListNarrow || form == mc::host::kListNarrowLeast, (long long)plan.part_rows);
   for (int i = 0; plan.narrow_wgs > 0 && i < plan.narrow.n; ++i) {
     const mc::AttnClass& k = plan.narrow.c[i];
     std::printf(" %d %d %d %d %d %d %d %d %d", plan.narrow.first[i], k.req, k.q_off, k.prefix, k.chunk, k.tile_lo, k.tile_hi, k.pieces,
@@ -52,6 +52,8 @@ def driver(tmp_path_factory):
     (12, 3, 128, 0, [999, 1, 0], [130, 0, 257], True, 1),
     (64, 8, 128, 0, [131056], [16], True, 0),                 # bound by the memory
     (8, 1, 128, 0, [123051], [4], True, 64),
+    (16, 16, 128, 0, [300, 20], [16, 3], True, 1),            # 16 rows a workgroup
+    (16, 16, 128, 0, [300, 20], [17, 3], True, 1),            # one request has more
     (4, 1, 128, 0, [24530, 300], [118, 20], True, 16),        # pieces in proportion
     (64, 8, 128, 0, [8192], [8192], False, 0),                # many rounds of full row tiles
     (64, 8, 128, 0, [6144, 6144], [811, 328], False, 0),
@@ -62,7 +64,8 @@ def driver(tmp_path_factory):
     (8, 2, 128, 0, [200] * 63, [7] * 63, True, 1),            # as many requests as there are classes
 ])
 def test_the_narrow_form_is_taken_where_it_is_sooner(driver, Hq, Hkv, D, dtype, prefix, new, without, pieces):
-    G, rows = Hq // Hkv, 16 if dtype else 32
+    G = Hq // Hkv
+    rows = 16 if dtype or max(new) * G <= 16 else 32
     for room, most in ((0, 1 if without else 0), (64 * sum(new) * Hq, pieces)):
         line = " ".join(str(x) for x in [Hq, Hkv, D, dtype, room, len(prefix), *prefix, *new])
         v = [int(x) for x in subprocess.run([driver], input=line, capture_output=True, text=True, check=True).stdout.split()]
