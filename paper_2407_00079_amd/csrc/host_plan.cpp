@@ -293,7 +293,9 @@ constexpr int64_t kMostNarrow = 3 * kComputeUnits;
 
 // How much sooner the narrow form has to end than a cut, and than anything if it takes more than one round (the estimate's
 // errors), and if its rounds walk more keys than the XCDs' caches hold, at paces of their own (12/3 heads, C 1210 behind 32143:
-// 0.46 us a tile instead of 0.315, 382 -> 478 us).
+// 0.46 us a tile instead of 0.315, 382 -> 478 us).  The same where the row tiles of a request are cut and (heads x pieces) is no
+// multiple of the XCDs: each reads the keys past its own L2 (12/3 heads, P 9720 and 13066, C 19 and 3: 128-row form 17.3, 18
+// pieces 18.1, now 16.0; P 30000, C 30 21.5, 22.6, 21.6).
 constexpr double kNarrowSlack = 1.06, kNarrowRoundsSlack = 1.12, kNarrowApartSlack = 1.3, kXcdCaches = 32 << 20;
 // Longest row tile the fp32 narrow form takes, in key tiles (4096 keys).  Beyond, whole rows are one long chain of roundings in
 // the other forms (6.3e-6 off 64 bits at 127262 keys, 1.0e-6 at 3000) and eight shorter ones here (2.3e-6, 4.5e-7): better, but
@@ -623,17 +625,20 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
     for (int64_t k = 1; may && k <= longest && k <= MC_MAX_KV_SPLITS; k += k < 8 ? 1 : k < 32 ? 4 : 16) {
       if (p->dtype == MC_DTYPE_F32 && (longest + k - 1) / k > kNarrowTilesF32) continue;
       int64_t n_pieces = 0, parts = 0;
+      bool apart = false;                                  // cut row tiles of one request lie on different XCDs
       for (int i = 0; i < n_runs; ++i) {
         const int64_t cut = runs[i].pieces(longest, k);
         n_pieces += runs[i].items * cut;
         if (cut > 1) parts += cut * runs[i].rows;
+        apart = apart || (cut > 1 && runs[i].tile_hi > runs[i].tile_lo && Hkv * cut % kXcds != 0);
       }
       if (n_pieces > kMostNarrow || (k > 1 && parts > room)) break;
       if (n_pieces == n_before) continue;
       n_before = n_pieces;
       const double rest = narrow.launch + missed + merge_of(narrow, parts);
       double by = end;                                     // when it has to have ended
-      if (n_pieces > kComputeUnits) by /= bytes > kXcdCaches ? kNarrowApartSlack : kNarrowRoundsSlack;
+      if (bytes > kXcdCaches && (apart || n_pieces > kComputeUnits)) by /= kNarrowApartSlack;
+      else if (n_pieces > kComputeUnits) by /= kNarrowRoundsSlack;
       if (rest + std::max(narrow.fixed, (work + narrow.fixed * (double)n_pieces) / kComputeUnits) >= by) continue;
       Units units;
       bool sooner = true;
