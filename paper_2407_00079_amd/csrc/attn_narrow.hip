@@ -113,6 +113,11 @@ __device__ __forceinline__ float max8(f32x4 a, f32x4 b) {
   return m;
 }
 
+// Between one lane's write of LDS and another lane's read of it, and between that read and the next write of the place: a wave's
+// LDS accesses are carried out in the order they are issued, so nothing has to be waited for, but the compiler, which sees one
+// lane, may not move them past each other.
+__device__ __forceinline__ void wave_sees_lds() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // Where a request's keys lie.
 struct Walk {
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
@@ -262,6 +267,7 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
   for (; block < n_blocks; block += kWaves) {
     stage.put(k_lds);
     stage.load(walk, kbase, pid);
+    wave_sees_lds();
     __builtin_amdgcn_sched_barrier(0);
     f32x4 s[RT][kBlockPages];                               // keys 16 kt + 4 g + r of the block
 #pragma unroll
@@ -337,6 +343,7 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
     }
     load_v(pid);
     walk.pages_of(next_after(next_after(block)), pid);
+    wave_sees_lds();
     __builtin_amdgcn_sched_barrier(0);
   }
 
@@ -421,6 +428,7 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
   for (; block < n_blocks; block += kWaves) {
     stage.put(k_lds);
     stage.load(walk, kbase, pid);
+    wave_sees_lds();
     __builtin_amdgcn_sched_barrier(0);
     f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
@@ -469,6 +477,7 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
       for (int e = 0; e < 4; ++e) o[e] = mma(vr[q][e], s[q >> 2][q & 3], o[e]);
     load_v(pid);
     walk.pages_of(next_after(next_after(block)), pid);
+    wave_sees_lds();
     __builtin_amdgcn_sched_barrier(0);
   }
 
