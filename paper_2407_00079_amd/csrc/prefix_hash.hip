@@ -185,29 +185,34 @@ __global__ __launch_bounds__(1024) void prefix_pour_kernel(const int32_t* __rest
   __builtin_amdgcn_s_setprio(3);                          // the chain is what the others are early for
   uint64_t salt = kFirstSalt;
   chain_range(keys + k0, keys + k0, 0, nk < first ? nk : first, salt, lane);
-  // The count and the digests of the next group are read before this one's links, the count first (a wave's LDS accesses keep
-  // their order): if it is complete by then, its digests are what has been read.
-  const volatile int* const counts = done;
-  const volatile uint64_t* const from = digests + (lane & 15);
-  int ready = counts[0];
-  uint64_t ahead = from[0];
-  for (int base = 0; base < rest; base += 16) {
-    const int n = rest - base < 16 ? rest - base : 16;
-    while (__builtin_amdgcn_readfirstlane(ready) < n) {
-      __builtin_amdgcn_s_sleep(1);
-      ready = counts[base >> 4];
-      ahead = from[base];
+  // A group's digests are read once its count has been seen complete and a fence passed.  The count is read two groups ahead and
+  // the digests one, before links that take longer than either; a group that was not complete by then is waited for.
+  auto count = [&](int group) {
+    return __hip_atomic_load(&done[group < kPourBlocks / 16 ? group : 0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  auto digests_of = [&](int group) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    return digests[group * 16 + (lane & 15)];
+  };
+  int later = count(1);
+  bool held = false;                                      // `ahead` are this group's
+  uint64_t ahead = 0;
+  for (int group = 0; group * 16 < rest; ++group) {
+    const int left = rest - group * 16, n = left < 16 ? left : 16;
+    if (!held) {
+      while (__builtin_amdgcn_readfirstlane(count(group)) < n) __builtin_amdgcn_s_sleep(1);
+      ahead = digests_of(group);
     }
     const uint64_t digest = ahead;
-    const int next = base + 16 < kPourBlocks ? base + 16 : base;
-    ready = counts[next >> 4];
-    ahead = from[next];
+    held = left > 16 && __builtin_amdgcn_readfirstlane(later) >= (left < 32 ? left - 16 : 16);
+    if (held) ahead = digests_of(group + 1);
+    later = count(group + 2);
     uint32_t kl = 0, kh = 0;
     chain_four<0>(digest, salt, kl, kh);
     if (n > 4) chain_four<4>(digest, salt, kl, kh);
     if (n > 8) chain_four<8>(digest, salt, kl, kh);
     if (n > 12) chain_four<12>(digest, salt, kl, kh);
-    if (lane < n) keys[k0 + first + base + lane] = ((uint64_t)kh << 32) | kl;
+    if (lane < n) keys[k0 + first + group * 16 + lane] = ((uint64_t)kh << 32) | kl;
   }
 }
 
