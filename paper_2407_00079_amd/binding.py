@@ -198,6 +198,15 @@ def _current_stream() -> int:
     return raw(device())
 
 
+def _ask_torch_again() -> None:
+    """In a forked child: torch, not the parent's runtime, says whether the GPU can be used there."""
+    global _raw_stream, _device
+    _raw_stream = _device = None
+
+
+os.register_at_fork(after_in_child=_ask_torch_again)
+
+
 def _on(stream) -> int:
     return _current_stream() if stream is None else stream.cuda_stream
 

@@ -1,8 +1,10 @@
 """How the binding hands the arguments of a call over (csrc/pycall.cpp), seen from a C callback in the library's place."""
 import ctypes
+import os
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2407_00079_amd import binding as B
 
@@ -79,3 +81,30 @@ def test_lists_and_what_stands_for_them():
         B.mc_prefill_attn_run(B.attn_params(8, 1, 128, 16, 4, "bf16"), None, None, None, None, None, None, None, None, 0)
     with pytest.raises(B.McError):
         B.mc_kv_pack_layer(None, None, 4, 32, None, 1, None, None, type("S", (), {"cuda_stream": 0})())
+
+
+def test_a_forked_child_asks_torch_for_its_stream(monkeypatch):
+    """The parent's stream getters are not used in a child: torch refuses the GPU there once the parent has used it."""
+    for name, value in (("_cuda_getCurrentRawStream", lambda device: 70 + device), ("_cuda_getDevice", lambda: 7)):
+        monkeypatch.setattr(torch._C, name, value, raising=False)
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(B, "_device", None)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    assert B._on(None) == 77 and B._on(None) == 77
+
+    def refused():
+        raise RuntimeError("no GPU in a forked child")
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    monkeypatch.setattr(torch.cuda, "current_stream", refused)
+    pid = os.fork()
+    if pid == 0:
+        status = 1
+        try:
+            B._on(None)
+        except RuntimeError:
+            status = 0
+        finally:
+            os._exit(status)
+    assert os.waitpid(pid, 0)[1] == 0
+    assert B._on(None) == 77                                  # the parent's stay
