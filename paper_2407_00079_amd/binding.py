@@ -208,7 +208,7 @@ os.register_at_fork(after_in_child=_ask_torch_again)
 
 
 def _on(stream) -> int:
-    return _current_stream() if stream is None else stream.cuda_stream
+    return _current_stream() if stream is None else stream.cuda_stream or 0
 
 
 class _Ints:

@@ -108,3 +108,7 @@ def test_a_forked_child_asks_torch_for_its_stream(monkeypatch):
             os._exit(status)
     assert os.waitpid(pid, 0)[1] == 0
     assert B._on(None) == 77                                  # the parent's stay
+
+
+def test_a_stream_without_a_handle_is_the_default_one():
+    assert B._on(type("S", (), {"cuda_stream": None})()) == 0
