@@ -1,4 +1,4 @@
-"""Binding of ``libmooncake_hip.so`` (ctypes, and ``_mccall.so`` for the calls that enqueue work): argument marshalling only.
+"""Binding of ``libmooncake_hip.so`` (ctypes, and ``_mccall`` for the calls that enqueue work): argument marshalling only.
 
 Function names and argument order are those of ``include/mc.h``.  torch is used
 for device memory and streams; every step of the path runs in the library's
@@ -128,24 +128,40 @@ def lib():
         l.mc_attn_merge_lse.argtypes = [vp, vp, i32, i64, i32, i32, vp, vp, vp]
         try:
             from . import _mccall
-        except ImportError as e:
-            raise RuntimeError("_mccall.so is missing: build it with `python -m paper_2407_00079_amd.build`") from e
-        for name in EXPORTS:
-            _address[name] = ctypes.cast(getattr(l, name), ctypes.c_void_p).value
-        _call = _mccall.call
+        except ModuleNotFoundError:                        # none was built for this Python
+            _function.update((name, getattr(l, name)) for name in EXPORTS)
+            _call = _call_by_ctypes
+        else:
+            _function.update((name, ctypes.cast(getattr(l, name), ctypes.c_void_p).value) for name in EXPORTS)
+            _call = _mccall.call
         _lib = l
     return _lib
 
 
-_address: dict = {}            # of the library's functions
-_call = None                   # csrc/pycall.cpp
+_function: dict = {}           # the library's functions, as `_call` takes them
+_call = None                   # csrc/pycall.cpp, or _call_by_ctypes
+
+
+def _call_by_ctypes(function, kinds: str, *args) -> int:
+    """What csrc/pycall.cpp does, for an interpreter it was not built for."""
+    keep, given = [], []
+    for kind, a in zip(kinds, args):
+        if kind == "p":
+            a = _dev_ptr(a)
+        elif kind == "s" and a is not None:
+            a = ctypes.byref(a)
+        elif kind in "IQ":
+            keep.append(a if isinstance(a, _Ints) else _Ints("i" if kind == "I" else "q", a, len(a)))
+            a = keep[-1].at
+        given.append(a)
+    return function(*given)
 
 
 def _enqueue(name: str, kinds: str, *args) -> None:
     """The library's function ``name``; ``kinds`` says how each argument is handed over (csrc/pycall.cpp)."""
     if _call is None:
         lib()
-    st = _call(_address[name], kinds, *args)
+    st = _call(_function[name], kinds, *args)
     if st != MC_OK:
         raise McError(st, name)
 

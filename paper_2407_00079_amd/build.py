@@ -1,8 +1,10 @@
-"""Build ``libmooncake_hip.so`` (hipcc for gfx950, cross-compiles without a GPU) and ``_mccall.so``, through which the binding
+"""Build ``libmooncake_hip.so`` (hipcc for gfx950, cross-compiles without a GPU) and ``_mccall``, through which the binding
 calls it, in-tree."""
 from __future__ import annotations
 
 import os
+import platform
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -13,7 +15,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmooncake_hip.so")
-CALLER = os.path.join(PKG, "_mccall.so")
+# the name says which interpreter it is for: others do not load it
+CALLER = os.path.join(PKG, "_mccall" + sysconfig.get_config_var("EXT_SUFFIX"))
 # host_plan.cpp holds no device code: hipcc compiles it as plain C++
 SOURCES = ["mc_api.hip", "host_plan.cpp", "attn_prefill.hip", "attn_prefill_bf16.hip", "attn_narrow.hip", "attn_noalloc.hip", "kv_copy.hip", "prefix_hash.hip"]
 
@@ -38,8 +41,16 @@ def _compile(src: str) -> str:
 
 
 def _build_caller() -> None:
-    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", "-I",
-                    sysconfig.get_paths()["include"], "-o", CALLER, os.path.join(CSRC, "pycall.cpp")], check=True)
+    """Where it cannot be built (no headers of this Python, another processor) the binding calls through ctypes."""
+    untagged = os.path.join(PKG, "_mccall.so")           # any Python would load it
+    if os.path.exists(untagged):
+        os.remove(untagged)
+    include, cxx = sysconfig.get_paths()["include"], os.environ.get("CXX", "g++")
+    if not os.path.exists(os.path.join(include, "Python.h")) or shutil.which(cxx) is None or platform.machine() != "x86_64":
+        sys.stderr.write(f"no _mccall for this Python (needs x86-64, {cxx} and {include}/Python.h): calls go through ctypes\n")
+        return
+    subprocess.run([cxx, "-O2", "-std=c++17", "-fPIC", "-Wall", "-shared", "-I", include, "-o", CALLER,
+                    os.path.join(CSRC, "pycall.cpp")], check=True)
 
 
 def build(verbose: bool = False) -> str:

@@ -1,6 +1,9 @@
 """How the binding hands the arguments of a call over (csrc/pycall.cpp), seen from a C callback in the library's place."""
 import ctypes
 import os
+import subprocess
+import sys
+import sysconfig
 
 import numpy as np
 import pytest
@@ -112,3 +115,56 @@ def test_a_forked_child_asks_torch_for_its_stream(monkeypatch):
 
 def test_a_stream_without_a_handle_is_the_default_one():
     assert B._on(type("S", (), {"cuda_stream": None})()) == 0
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_the_caller_is_for_one_python(call):
+    """Its name says which: an extension of another interpreter's ABI must not be loaded."""
+    from paper_2407_00079_amd import _mccall, build
+    assert _mccall.__file__ == build.CALLER and build.CALLER.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert not os.path.exists(os.path.join(build.PKG, "_mccall.so"))
+
+
+def test_without_a_caller_calls_go_through_ctypes():
+    """As from an interpreter it was not built for: every argument check of the library is reached with the same results.  (No
+    call here passes all of them with anything to do: nothing is launched, with or without a GPU.)"""
+    code = """
+import sys
+sys.path.insert(0, %r)
+sys.modules["paper_2407_00079_amd._mccall"] = None if len(sys.argv) > 1 else __import__("paper_2407_00079_amd._mccall")._mccall
+from paper_2407_00079_amd import binding as B
+class S: cuda_stream = 0
+class T:
+    nbytes = 8
+    def data_ptr(self): return 1 << 40
+    def dim(self): return 2
+    def size(self, i): return 4
+p, t, s, plan = B.attn_params(8, 2, 128, 16, 64, "bf16"), T(), S(), B.McAttnPlan()
+def status(f):
+    try:
+        return f()
+    except B.McError as e:
+        return str(e)
+    except Exception as e:
+        return "refused"
+lens = [[16, 3], [5, 2]]
+for f in (lambda: B.mc_prefill_attn_paged(p, t, t, t, t, *lens, t, None, t, s), lambda: B.mc_prefill_attn_paged(p, t, t, t, t, [16, 300], [5, 2], t, None, t, s),
+          lambda: B.mc_prefill_attn_paged(None, t, t, t, t, *lens, t, None, t, s), lambda: B.mc_prefill_attn_auto(p, t, t, t, t, (16, 3), [5, 2], t, t, None, s),
+          lambda: B.mc_prefill_attn_paged(p, t, t, t, t, [0], [0], t, None, t, s), lambda: B.mc_prefill_attn_paged_noalloc(p, t, t, t, t, [-1], [5], t, None, s),
+          lambda: B.mc_prefill_attn_run(p, plan, t, t, t, t, t, None, t, s), lambda: B.mc_kv_append_run(p, plan, t, t, t, t, t, t, s),
+          lambda: B.mc_kv_append_paged(p, t, t, t, t, t, *lens, t, s), lambda: B.mc_kv_append_paged(p, t, None, t, t, t, *lens, t, s),
+          lambda: B.mc_kv_pack_layer(t, t, 4, 33, t, 2, t, t, s), lambda: B.mc_kv_pack_layer(t, t, 4, 32.0, t, 2, t, t, s),
+          lambda: B.mc_kv_unpack_layer(t, t, 4, 32, None, 2, t, t, s), lambda: B.mc_kv_page_order(t, -1, t, s),
+          lambda: B.mc_kv_pack_layer_ordered(t, t, -4, 32, t, t, 2, t, t, s), lambda: B.mc_kv_unpack_layer_ordered(t, t, 4, 24, t, None, 2, t, t, s),
+          lambda: B.mc_prefix_hash(t, [0, 700], 512, t, t, s), lambda: B.mc_prefix_hash(t, [0, -7], 512, t, t, s), lambda: B.mc_prefix_hash(t, [0, "x"], 512, t, t, s),
+          lambda: B.mc_prefix_match(t, [0, 2], t, [0, -9], t, t, t, t, s), lambda: B.mc_prefix_match(t, [0, 2], None, [0, 9], t, t, t, t, s)):
+    print(status(f))
+print(B._call.__name__, file=sys.stderr)
+""" % ROOT
+    native, by_ctypes = (subprocess.run([sys.executable, "-c", code, *arg], capture_output=True, text=True, timeout=120) for arg in ([], ["x"]))
+    assert native.returncode == 0 and by_ctypes.returncode == 0, (native.stderr, by_ctypes.stderr)
+    assert native.stderr.split()[-1] == "call" and by_ctypes.stderr.split()[-1] == "_call_by_ctypes"
+    assert native.stdout == by_ctypes.stdout and len(native.stdout.splitlines()) == 21, (native.stdout, by_ctypes.stdout)
+    assert "mc_status 7" not in native.stdout and len(set(native.stdout.splitlines())) > 6         # statuses of several kinds, and refusals
