@@ -157,11 +157,29 @@ def _call_by_ctypes(function, kinds: str, *args) -> int:
     return function(*given)
 
 
-def _enqueue(name: str, kinds: str, *args) -> None:
-    """The library's function ``name``; ``kinds`` says how each argument is handed over (csrc/pycall.cpp)."""
+# How each argument of the calls that enqueue work is handed over, one letter an argument (csrc/pycall.cpp says what they mean).
+_KINDS = {
+    "mc_prefill_attn_paged": "sppppiIIipppii",
+    "mc_prefill_attn_auto": "sppppiIIipppii",
+    "mc_prefill_attn_paged_noalloc": "sppppiIIippi",
+    "mc_prefill_attn_run": "ssppppipppi",
+    "mc_kv_append_run": "sspppppipi",
+    "mc_kv_pack_layer": "ppiipippi",
+    "mc_kv_unpack_layer": "ppiipippi",
+    "mc_kv_page_order": "pipi",
+    "mc_kv_pack_layer_ordered": "ppiippippi",
+    "mc_kv_unpack_layer_ordered": "ppiippippi",
+    "mc_prefix_hash": "pQiippii",
+    "mc_prefix_match": "pQipQippppii",
+    "mc_kv_append_paged": "spppppiIIipii",
+}
+
+
+def _enqueue(name: str, *args) -> None:
+    """The library's function ``name`` with arguments as _KINDS has them."""
     if _call is None:
         lib()
-    st = _call(_function[name], kinds, *args)
+    st = _call(_function[name], _KINDS[name], *args)
     if st != MC_OK:
         raise McError(st, name)
 
@@ -279,7 +297,7 @@ def mc_prefill_attn_paged(params: McAttnParams, q, k_pool, v_pool, block_tables,
     workspace: uint8 device tensor of at least the size the library asks for.
     """
     n = len(prefix_lens)
-    _enqueue("mc_prefill_attn_paged", "sppppiIIipppii", _params(params), q, k_pool, v_pool, block_tables,
+    _enqueue("mc_prefill_attn_paged", _params(params), q, k_pool, v_pool, block_tables,
              _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, out, lse, workspace,
              _nbytes(workspace), _on(stream))
 
@@ -298,7 +316,7 @@ def mc_prefill_attn_auto(params: McAttnParams, q, k_pool, v_pool, block_tables, 
                          workspace, stream=None) -> None:
     """mc_prefill_attn_paged with the whole-row / key-slices choice made by the library (larger workspace)."""
     n = len(prefix_lens)
-    _enqueue("mc_prefill_attn_auto", "sppppiIIipppii", _params(params), q, k_pool, v_pool, block_tables,
+    _enqueue("mc_prefill_attn_auto", _params(params), q, k_pool, v_pool, block_tables,
              _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, out, lse, workspace,
              _nbytes(workspace), _on(stream))
 
@@ -315,7 +333,7 @@ def mc_prefill_attn_paged_noalloc(params: McAttnParams, q, k_pool, v_pool, block
     """mc_prefill_attn_paged without a workspace: the work list is built on the device in the library's own
     fixed array (no allocation, no upload)."""
     n = len(prefix_lens)
-    _enqueue("mc_prefill_attn_paged_noalloc", "sppppiIIippi", _params(params), q, k_pool, v_pool, block_tables,
+    _enqueue("mc_prefill_attn_paged_noalloc", _params(params), q, k_pool, v_pool, block_tables,
              _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, out, lse, _on(stream))
 
 
@@ -339,7 +357,7 @@ def mc_prefill_attn_prepare(params: McAttnParams, prefix_lens, new_lens, kv_spli
 
 def mc_prefill_attn_run(params: McAttnParams, plan: McAttnPlan, q, k_pool, v_pool, block_tables, out, lse, workspace,
                         stream=None) -> None:
-    _enqueue("mc_prefill_attn_run", "ssppppipppi", _params(params), _plan(plan), q, k_pool, v_pool, block_tables,
+    _enqueue("mc_prefill_attn_run", _params(params), _plan(plan), q, k_pool, v_pool, block_tables,
              _max_pages(block_tables), out, lse, workspace, _on(stream))
 
 
@@ -355,7 +373,7 @@ def mc_prefill_attn_run_split(params: McAttnParams, plan: McAttnPlan, q, k_pool,
 
 def mc_kv_append_run(params: McAttnParams, plan: McAttnPlan, k_new, v_new, k_pool, v_pool, block_tables, workspace,
                      stream=None) -> None:
-    _enqueue("mc_kv_append_run", "sspppppipi", _params(params), _plan(plan), k_new, v_new, k_pool, v_pool, block_tables,
+    _enqueue("mc_kv_append_run", _params(params), _plan(plan), k_new, v_new, k_pool, v_pool, block_tables,
              _max_pages(block_tables), workspace, _on(stream))
 
 
@@ -424,17 +442,17 @@ def mc_kv_unpack_layer_raw(k_in, v_in, num_pages, page_bytes, page_ids, n, k_poo
 
 def mc_kv_pack_layer(k_pool_layer, v_pool_layer, num_pages: int, page_bytes: int, page_ids, n: int,
                      k_out, v_out, stream=None) -> None:
-    _enqueue("mc_kv_pack_layer", "ppiipippi", k_pool_layer, v_pool_layer, num_pages, page_bytes, page_ids, n, k_out, v_out, _on(stream))
+    _enqueue("mc_kv_pack_layer", k_pool_layer, v_pool_layer, num_pages, page_bytes, page_ids, n, k_out, v_out, _on(stream))
 
 
 def mc_kv_unpack_layer(k_in, v_in, num_pages: int, page_bytes: int, page_ids, n: int,
                        k_pool_layer, v_pool_layer, stream=None) -> None:
-    _enqueue("mc_kv_unpack_layer", "ppiipippi", k_in, v_in, num_pages, page_bytes, page_ids, n, k_pool_layer, v_pool_layer, _on(stream))
+    _enqueue("mc_kv_unpack_layer", k_in, v_in, num_pages, page_bytes, page_ids, n, k_pool_layer, v_pool_layer, _on(stream))
 
 
 def mc_kv_page_order(page_ids, n: int, order, stream=None) -> None:
     """Enqueue order[r] = position of the r-th smallest page id (int32 device tensors)."""
-    _enqueue("mc_kv_page_order", "pipi", page_ids, n, order, _on(stream))
+    _enqueue("mc_kv_page_order", page_ids, n, order, _on(stream))
 
 
 def mc_kv_check_page_ids(page_ids, n: int, num_pages: int, report, stream=None) -> None:
@@ -447,13 +465,13 @@ def mc_kv_check_page_ids(page_ids, n: int, num_pages: int, report, stream=None) 
 
 def mc_kv_pack_layer_ordered(k_pool_layer, v_pool_layer, num_pages: int, page_bytes: int, page_ids, order, n: int,
                              k_out, v_out, stream=None) -> None:
-    _enqueue("mc_kv_pack_layer_ordered", "ppiippippi", k_pool_layer, v_pool_layer, num_pages, page_bytes, page_ids, order, n, k_out, v_out,
+    _enqueue("mc_kv_pack_layer_ordered", k_pool_layer, v_pool_layer, num_pages, page_bytes, page_ids, order, n, k_out, v_out,
              _on(stream))
 
 
 def mc_kv_unpack_layer_ordered(k_in, v_in, num_pages: int, page_bytes: int, page_ids, order, n: int, k_pool_layer,
                                v_pool_layer, stream=None) -> None:
-    _enqueue("mc_kv_unpack_layer_ordered", "ppiippippi", k_in, v_in, num_pages, page_bytes, page_ids, order, n, k_pool_layer, v_pool_layer,
+    _enqueue("mc_kv_unpack_layer_ordered", k_in, v_in, num_pages, page_bytes, page_ids, order, n, k_pool_layer, v_pool_layer,
              _on(stream))
 
 
@@ -506,7 +524,7 @@ def mc_prefix_hash(tokens, tok_offsets, block_tokens: int, keys, workspace, stre
     """Enqueue the block keys of every request: ``tokens`` int32 device tensor, ``tok_offsets`` host sequence of
     batch + 1 ints, ``keys`` int64 device tensor (the uint64 bit patterns) with one entry per block."""
     n = len(tok_offsets)
-    _enqueue("mc_prefix_hash", "pQiippii", tokens, _ints("q", tok_offsets, n), n - 1, block_tokens, keys, workspace,
+    _enqueue("mc_prefix_hash", tokens, _ints("q", tok_offsets, n), n - 1, block_tokens, keys, workspace,
              _nbytes(workspace), _on(stream))
 
 
@@ -520,7 +538,7 @@ def mc_prefix_match(keys, key_offsets, cache_keys, cache_offsets, prefix_len, be
                     stream=None) -> None:
     """Enqueue the longest-prefix match of every request against every instance (device tensors; offsets on the host)."""
     n, m = len(key_offsets), len(cache_offsets)
-    _enqueue("mc_prefix_match", "pQipQippppii", keys, _ints("q", key_offsets, n), n - 1, cache_keys,
+    _enqueue("mc_prefix_match", keys, _ints("q", key_offsets, n), n - 1, cache_keys,
              _ints("q", cache_offsets, m), m - 1, prefix_len, best_len, best_inst, workspace, _nbytes(workspace), _on(stream))
 
 
@@ -539,7 +557,7 @@ def mc_kv_append_paged(params: McAttnParams, k_new, v_new, k_pool, v_pool, block
                        workspace, stream=None) -> None:
     """Enqueue the scatter of the new tokens' K/V rows into their page slots (torch device tensors)."""
     n = len(prefix_lens)
-    _enqueue("mc_kv_append_paged", "spppppiIIipii", _params(params), k_new, v_new, k_pool, v_pool, block_tables,
+    _enqueue("mc_kv_append_paged", _params(params), k_new, v_new, k_pool, v_pool, block_tables,
              _max_pages(block_tables), _ints("i", prefix_lens, n), _ints("i", new_lens, n), n, workspace,
              _nbytes(workspace), _on(stream))
 

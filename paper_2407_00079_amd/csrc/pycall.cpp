@@ -14,6 +14,10 @@
 
 #include <vector>
 
+#if !defined(__x86_64__)
+#error "Function below rests on the x86-64 System V calling convention"
+#endif
+
 namespace {
 
 constexpr int kMaxArgs = 20;

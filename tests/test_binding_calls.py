@@ -1,6 +1,7 @@
 """How the binding hands the arguments of a call over (csrc/pycall.cpp), seen from a C callback in the library's place."""
 import ctypes
 import os
+import re
 import subprocess
 import sys
 import sysconfig
@@ -168,3 +169,27 @@ print(B._call.__name__, file=sys.stderr)
     assert native.stderr.split()[-1] == "call" and by_ctypes.stderr.split()[-1] == "_call_by_ctypes"
     assert native.stdout == by_ctypes.stdout and len(native.stdout.splitlines()) == 21, (native.stdout, by_ctypes.stdout)
     assert "mc_status 7" not in native.stdout and len(set(native.stdout.splitlines())) > 6         # statuses of several kinds, and refusals
+
+
+def declarations():
+    """The parameters that include/mc.h declares: function -> (type, name) of each."""
+    text = re.sub(r"/\*.*?\*/", "", open(os.path.join(ROOT, "include", "mc.h")).read(), flags=re.S)
+    found = re.findall(r"\b(mc_[a-z_0-9]+)\s*\(([^)]*)\)\s*;", text)
+    return {f: [re.fullmatch(r"(.*?)\s*(\w+)", p.strip(), flags=re.S).groups() for p in params.split(",")] for f, params in found}
+
+
+def test_the_kinds_are_those_of_the_declared_parameters():
+    """One letter a parameter: a call with fewer would leave the rest of them zero, with no one to notice."""
+    host = {"prefix_lens", "new_lens", "tok_offsets", "key_offsets", "cache_offsets"}
+    declared = declarations()
+    assert len(B._KINDS) == 13
+    for function, kinds in B._KINDS.items():
+        want = ""
+        for type_, name in declared[function]:
+            if name in host:
+                want += {"const int32_t*": "I", "const int64_t*": "Q"}[type_]
+            elif type_.startswith("const mc_attn_"):
+                want += "s"
+            else:                                             # the stream's handle comes as an integer
+                want += "p" if type_.endswith("*") and name != "hip_stream" else "i"
+        assert kinds == want and len(getattr(B.lib(), function).argtypes) == len(want), function
