@@ -120,6 +120,21 @@ def test_copy_argument_errors(lib, fn):
     assert run(n=0, a=None, b=None, c=None, d=None, ids=None) == B.MC_OK
 
 
+def test_address_forms_of_append_and_prefix_calls(lib):
+    """The calls that take plain addresses, as a program without tensors makes them: refused like the others."""
+    p, lens, off = good_params(), (ctypes.c_int32 * 1)(16), (ctypes.c_int64 * 2)(0, 700)
+    i32, i64 = ctypes.addressof(lens), ctypes.addressof(off)
+    assert B.mc_kv_append_paged_raw(p, FAKE, None, FAKE, FAKE, FAKE, 4, i32, i32, 1, FAKE, 1 << 20, None) == B.MC_ERR_NULL
+    assert B.mc_kv_append_paged_raw(p, FAKE, FAKE, FAKE, FAKE, FAKE, 1, i32, i32, 1, FAKE, 1 << 20, None) == B.MC_ERR_SHAPE
+    assert B.mc_kv_append_paged_raw(p, FAKE, FAKE, FAKE, FAKE, FAKE, 4, i32, i32, 1, FAKE, 1, None) == B.MC_ERR_WORKSPACE
+    assert B.mc_prefix_hash_raw(None, i64, 1, 512, FAKE, FAKE, 1 << 20, None) == B.MC_ERR_NULL
+    assert B.mc_prefix_hash_raw(FAKE, i64, 1, 0, FAKE, FAKE, 1 << 20, None) == B.MC_ERR_SHAPE
+    assert B.mc_prefix_hash_raw(FAKE, i64, 1, 512, FAKE, FAKE, 1, None) == B.MC_ERR_WORKSPACE
+    assert B.mc_prefix_match_raw(FAKE, i64, 1, None, i64, 1, FAKE, FAKE, FAKE, FAKE, 1 << 20, None) == B.MC_ERR_NULL
+    assert B.mc_prefix_match_raw(FAKE, i64, -1, FAKE, i64, 1, FAKE, FAKE, FAKE, FAKE, 1 << 20, None) == B.MC_ERR_SHAPE
+    assert B.mc_prefix_match_raw(FAKE, i64, 1, FAKE, i64, 1, FAKE, FAKE, FAKE, FAKE, 1, None) == B.MC_ERR_WORKSPACE
+
+
 def test_suggested_key_slices(lib):
     """Host arithmetic only: the slice count with the fewest rounds of 256 work items (1 % per extra slice),
     capped by MC_MAX_KV_SPLITS and by 8 tiles of 64 keys per slice of the longest request."""
