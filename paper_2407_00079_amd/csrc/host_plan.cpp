@@ -666,11 +666,6 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         plan->narrow_pieces = std::max<int32_t>(plan->narrow_pieces, (int32_t)cut);
       }
       plan->narrow_wgs = (int32_t)wg;
-      if (max_part_rows == 0) {
-        best_rows = kAttnFewRows;
-        best_whole = items_of(best_rows);
-        best_of = 0;
-      }
     }
   }
   const int uncut = lay_out(best_whole, best_rows);

@@ -87,7 +87,7 @@ struct ClassPlan {
   AttnClasses classes;
   // Workgroups of the narrow form, if that is sooner (0: it is not); `narrow` are its classes, whole rows or cut into up to
   // narrow_pieces pieces, and the launch takes them instead.  Their partial results take no more room than those of `classes`
-  // or, with `keep_room`, than max_part_rows.  (Without room for partial results `classes` are the whole rows of 128-row tiles.)
+  // or, with `keep_room`, than max_part_rows.
   int32_t narrow_wgs, narrow_pieces;
   AttnClasses narrow;
   int32_t n_wgs;          // workgroups of the attention launch

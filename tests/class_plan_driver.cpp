@@ -1,7 +1,7 @@
 // Prints the class plan of each batch read from stdin, one line per plan (tests/test_class_plan.py checks them).
 // input:  Hq Hkv D dtype max_part_rows batch P... C...
 // output: n n_wgs most_pieces part_rows tile_rows [first req q_off prefix chunk tile_lo tile_hi pieces part_base]...
-//         and the rows of a workgroup of the prepared list of the batch
+//         and the rows of a workgroup of the launch (of its narrow form, if it takes that) and of the prepared list of the batch
 #include <cstdio>
 #include <vector>
 
@@ -29,7 +29,11 @@ int main() {
                   k.pieces, k.part_base);
     }
     const int32_t form = mc::host::list_form(&p, P.data(), C.data(), batch, 0, mc::host::count_items(&p, C.data(), batch));
-    std::printf(" %d\n", form == 0 ? mc::kAttnTileRows : mc::kAttnFewRows);
+    // as launch_planned_attn and launch_attn read it
+    const int narrow = dtype == MC_DTYPE_F32 ? mc::kAttnLeastRows : mc::kAttnNarrowRows;
+    const int list = form == 0 ? mc::kAttnTileRows : form == mc::host::kListNarrowLeast ? mc::kAttnLeastRows
+                   : form == mc::host::kListNarrow ? narrow : mc::kAttnFewRows;
+    std::printf(" %d %d\n", plan.narrow_wgs > 0 ? plan.narrow.rows : plan.classes.rows, list);
   }
   return 0;
 }

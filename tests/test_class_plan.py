@@ -28,7 +28,7 @@ def plan(driver, Hq, Hkv, D, dtype, room, prefix, new):
         return None
     v = [int(x) for x in out]
     names = ("first", "req", "q_off", "prefix", "chunk", "tile_lo", "tile_hi", "pieces", "part_base")
-    return dict(n_wgs=v[1], most_pieces=v[2], part_rows=v[3], rows=v[4], list_rows=v[-1],
+    return dict(n_wgs=v[1], most_pieces=v[2], part_rows=v[3], rows=v[4], launch_rows=v[-2], list_rows=v[-1],
                 classes=[dict(zip(names, v[5 + 9 * i:14 + 9 * i])) for i in range(v[0])])
 
 
@@ -92,13 +92,14 @@ SAME_ROWS = [
     (16, 16, 128, 0, [22, 700], [6965, 300]),
     (32, 32, 128, 0, [100] * 60, [40] * 60),
     (64, 8, 128, 0, [8192], [8192]),
+    (16, 16, 128, 0, [300, 20], [16, 3]),             # narrow, no request with more than 16 rows
 ]
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,dtype,prefix,new", BATCHES + SAME_ROWS)
 def test_prepared_lists_take_the_row_tiles_of_an_uncut_call(driver, Hq, Hkv, D, dtype, prefix, new):
     p = plan(driver, Hq, Hkv, D, dtype, 0, prefix, new)
-    assert p["most_pieces"] == 1 and p["list_rows"] == p["rows"]
+    assert p["most_pieces"] == 1 and p["list_rows"] == p["launch_rows"]
 
 
 def launch_end(workgroups):
