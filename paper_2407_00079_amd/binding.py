@@ -228,7 +228,7 @@ def _current_stream() -> int:
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
     if raw is None or device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    _raw_stream, _device = raw, device
+    _device, _raw_stream = device, raw                     # in this order: a thread that sees the second uses both
     return raw(device())
 
 

@@ -114,6 +114,44 @@ def test_a_forked_child_asks_torch_for_its_stream(monkeypatch):
     assert B._on(None) == 77                                  # the parent's stay
 
 
+def test_threads_that_make_the_first_call_together(monkeypatch):
+    """Between any two bytecodes of the first call that asks for the stream, another thread's call finds getters it can use."""
+    for name, value in (("_cuda_getCurrentRawStream", lambda device: 70 + device), ("_cuda_getDevice", lambda: 7)):
+        monkeypatch.setattr(torch._C, name, value, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(B, "_device", None)
+    seen = 0
+
+    def first_call(interrupted_at):
+        nonlocal seen
+        B._raw_stream = B._device = None
+        seen = 0
+
+        def trace(frame, event, arg):
+            nonlocal seen
+            if frame.f_code is not B._current_stream.__code__:
+                return None
+            frame.f_trace_opcodes = True
+            if event == "opcode":
+                seen += 1
+                if seen == interrupted_at:
+                    assert B._current_stream() == 77              # (not traced in here)
+            return trace
+
+        before = sys.gettrace()
+        sys.settrace(trace)
+        try:
+            assert B._current_stream() == 77
+        finally:
+            sys.settrace(before)
+
+    first_call(0)
+    assert seen > 20
+    for at in range(1, seen + 1):
+        first_call(at)
+
+
 def test_a_stream_without_a_handle_is_the_default_one():
     assert B._on(type("S", (), {"cuda_stream": None})()) == 0
 
