@@ -1,7 +1,9 @@
 """GPU parity: mc_prefill_attn_paged against the fp64 CPU oracle.
 
 Tolerances (vs the fp64 oracle on the same stored inputs): bf16 max-abs 2e-2 and
-relative L2 1e-2; f32 max-abs 1e-4 and relative L2 1e-5.
+relative L2 1e-2; f32 max-abs 1e-4 and relative L2 1e-5.  The small shapes run the
+narrow form of the kernels almost all of them, the full-size ones the wide form;
+test_gpu_wide_rows.py holds the same hard cases for the latter.
 """
 import dataclasses
 
@@ -55,7 +57,7 @@ def test_bf16_small_shapes(oracle, Hq, Hkv, P, C):
     (16, 2, [100], [37]),              # prefix not page aligned, partial last page
     (4, 4, [64], [130]),               # MHA
     (4, 2, [33, 0, 512, 16], [5, 17, 1, 70]),   # varlen batch incl. a single-row request
-    (8, 1, [2000], [300]),             # many pipelined tiles
+    (8, 1, [2000], [300]),             # many key tiles
 ])
 def test_bf16_head_dim_64_small_shapes(oracle, Hq, Hkv, P, C):
     case = W.make_attn_case(300 + Hq + sum(C), W.BF16, Hq, Hkv, 64, 16, P, C, 256)
@@ -158,7 +160,7 @@ def test_bf16_head_dim_64_at_full_size_on_sampled_rows(oracle):
 def test_scores_that_keep_outgrowing_the_reference(oracle):
     """Scores that rise along the keys at eight different rates, one per head (from 0.3 to 20 log2 units per 32-key
     block): the lazy softmax reference is outgrown by just under and just over its margin again and again, in the
-    pipelined tiles (long prefix) and in the diagonal ones."""
+    blocks of the prefix and in the diagonal ones."""
     Hq, Hkv, D, S, P, C = 8, 1, 128, 16, 2000, 150
     L = P + C
     rng = np.random.default_rng(11)

@@ -11,7 +11,9 @@ from gpu_util import TOL, DeviceCase, dev
 
 pytestmark = pytest.mark.gpu
 
-# dtype, Hq, Hkv, D, prefix, new: all of them cut into pieces where the workspace has room
+# dtype, Hq, Hkv, D, prefix, new: all of them in the narrow form, the second, third and fifth cut into pieces where the workspace
+# has room (against whole narrow row tiles), and all against key slices of 128- and 256-row tiles; cut wide row tiles are in
+# test_gpu_wide_rows.py
 SHAPES = [(W.F32, 4, 1, 64, [256], [128]), (W.BF16, 64, 8, 128, [4000], [16]), (W.BF16, 16, 2, 64, [3000], [40]),
           (W.BF16, 8, 2, 128, [700, 1500], [90, 3]), (W.F32, 8, 2, 64, [3000, 5], [33, 2])]
 

@@ -1,5 +1,7 @@
 """GPU parity of the one-shot attention call with room for partial results: row tiles cut into pieces along the keys
-(classes in the kernel argument) and their merge, against the oracle, at the edges of row tiles, key tiles and pieces."""
+(classes in the kernel argument) and their merge, against the oracle, at the edges of row tiles, key tiles and pieces.  All but
+two of the shapes (one key; 127, 128 with 1000, 60) take narrow row tiles; the wide ones, cut, are in test_gpu_wide_rows.py and
+in the second half of PIECES in test_gpu_narrow.py."""
 import numpy as np
 import pytest
 import torch
@@ -13,18 +15,18 @@ pytestmark = pytest.mark.gpu
 
 # dtype, Hq, Hkv, D, prefix, new
 CASES = [
-    (W.F32, 4, 1, 64, [256], [128]),                          # two row tiles of six key tiles each
+    (W.F32, 4, 1, 64, [256], [128]),                          # row tiles of six key tiles and less
     (W.F32, 4, 4, 64, [0, 65], [257, 1]),                     # no prefix; a row tile of one row; one key tile and a key
     (W.BF16, 8, 1, 128, [0], [1]),                            # one row, one key
-    (W.BF16, 64, 8, 128, [1023, 64], [1, 33]),                # a tile of 8 rows; 33 tokens = one row tile and 8 rows
+    (W.BF16, 64, 8, 128, [1023, 64], [1, 33]),                # a tile of 8 rows; 33 tokens: 264 rows, the last tile of 8
     (W.BF16, 8, 2, 128, [919], [355]),                        # early row tiles see fewer key tiles than there are pieces
     (W.BF16, 16, 16, 128, [538, 0, 7], [94, 0, 300]),         # one head per group, an empty request, row tiles at 256 rows
     (W.BF16, 12, 3, 128, [2000, 3], [40, 86]),                # groups of 4 heads, three KV heads
     (W.BF16, 16, 2, 64, [1500, 31], [17, 129]),               # 128-byte rows
     (W.BF16, 64, 8, 128, [127, 128], [1000, 60]),             # one full round of row tiles and a rest that is cut
-    (W.BF16, 8, 1, 128, [40000], [9]),                        # 72 rows: a wave without rows; pieces of several key tiles
-    (W.BF16, 16, 1, 128, [9000, 63, 320], [8, 1, 5]),         # 128-row tiles exactly full and nearly empty
-    (W.BF16, 64, 8, 64, [9999], [17]),                        # 136 rows: two row tiles, the second of 8 rows
+    (W.BF16, 8, 1, 128, [40000], [9]),                        # 72 rows; pieces of several key tiles
+    (W.BF16, 16, 1, 128, [9000, 63, 320], [8, 1, 5]),         # 128, 16 and 80 rows
+    (W.BF16, 64, 8, 64, [9999], [17]),                        # 136 rows: the last row tile of 8
     (W.F32, 8, 2, 64, [3000], [33]),
 ]
 
@@ -51,9 +53,10 @@ def test_pieces_match_oracle(oracle, dtype, Hq, Hkv, D, prefix, new):
 
 @pytest.mark.parametrize("dtype,D,tiles", [(W.BF16, 128, n) for n in (1, 2, 3, 4, 5, 6, 7, 11)] + [(W.BF16, 64, 6), (W.F32, 64, 5)])
 def test_few_rows_without_room(oracle, dtype, D, tiles):
-    """No room for partial results: one workgroup per KV head walks all key tiles, as many as there are LDS buffers and
-    around that; rows for one, two and four of its waves, and for more than one workgroup."""
-    for new in (1, 7, 16, 33):                                # 33 tokens: a full row tile and one of 8 rows, in halves
+    """No room for partial results: a workgroup walks all key tiles of its rows, one tile and up to eleven (narrow row tiles but for
+    one key tile; the key slices below take 128-row ones, over as many tiles as there are LDS buffers and around that); rows for
+    one row tile and for several."""
+    for new in (1, 7, 16, 33):                                # 33 tokens: the last row tile of 8 rows
         print(f"few rows case {dtype} D={D} tiles={tiles} new={new}", flush=True)
         case = W.make_attn_case(72 + tiles, dtype, 16, 2, D, 16, [64 * tiles - new - 3], [new], 4 * tiles + 3)
         dc = DeviceCase(case)

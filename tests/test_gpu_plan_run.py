@@ -1,6 +1,6 @@
 """GPU: prepare once, run per layer (mc_prefill_attn_prepare / _run / _run_split, mc_kv_append_run) gives bit for bit
 what the one-shot calls give (whole rows: with the minimal workspace, or without one), also when the runs are replayed
-from a HIP graph."""
+from a HIP graph.  (PREFIX, NEW are narrow lists; test_gpu_wide_rows.py has wide ones.)"""
 import numpy as np
 import pytest
 import torch
