@@ -41,7 +41,7 @@ struct AttnClass {
 constexpr int kMaxAttnClasses = 64;          // one lane of a wave each when a workgroup looks for its class
 struct AttnClasses {
   int32_t n;
-  int32_t rows;                              // stacked rows of a row tile: kAttnTileRows or kAttnFewRows
+  int32_t rows;                              // stacked rows of a row tile: kAttnTileRows, kAttnFewRows, kAttnNarrowRows or kAttnLeastRows
   int32_t once;                              // K and V are streamed: one row tile per head, more bytes than the caches hold
   int32_t first[kMaxAttnClasses];            // first workgroup of each class (of the attention launch or of the merge)
   AttnClass c[kMaxAttnClasses];
