@@ -25,7 +25,7 @@
 // hint: 0.53.  64 keys a block (head_dim 64): no change; two workgroups a compute unit (128 registers): 0.27 and fp32 0.73.
 // Whole calls before / now, us: planned, 64/8 heads, P 30000, C 90 350 / 148; P 131056, C 16 1490 / 908; 16/16 heads, P 7206,
 // C 200 93 / 41; head_dim 64, 64/8 heads, P 30000, C 90 301 / 104; fp32, 8/2 heads, P 2798, C 62 183 / 31; one call with room
-// for pieces, fp32, 4/1 heads, P 256, C 128, append included: 18.8 / 14.2.  450 random one-shot calls whose narrow row tiles may
+// for pieces, fp32, 4/1 heads, P 256, C 128, append included, both calls through ctypes: 18.8 / 14.2.  450 random one-shot calls whose narrow row tiles may
 // be cut, against only whole ones: geometric mean x1.05 (fp32 x1.25), the slowest x0.96.  When it is taken: plan_classes
 // (host_plan.cpp).
 #include "attn_device.h"

@@ -156,8 +156,9 @@ __global__ __launch_bounds__(256) void prefix_stage_kernel(const int32_t* __rest
 // in its first wave while the others digest the blocks behind them, into LDS, in order.  A group of 16 digests is complete when
 // its count says so; the chain waits for that, and only for waves of its own workgroup, which wait for nothing.
 // Bound by the chain where `first` is large enough (see hash_with): a compute unit digests a block of 512 tokens in 0.15 us, a
-// link takes 0.1.  Keys, launches of whole ranges before / this now, us: 64 prompts of 256 blocks of 512 tokens 31.0 / 28.6, 128
-// blocks 19.5 / 16.9; 200 prompts of 256 blocks 52.5 / 45.1; 128 of 59 20.9 / 17.1; 100 of 71 blocks of 128 tokens 21.1 / 18.0.
+// link takes 0.1.  Keys, launches of whole ranges / this, us: 64 prompts of 256 blocks of 512 tokens 30.5 / 28.3, 128 blocks
+// 19.6 / 16.6; 200 prompts of 256 blocks 51.0 / 43.8; 128 of 59 20.8 / 18.4; 100 of 71 blocks of 128 tokens 21.1 / 18.9; 64 of
+// 512 blocks of 256 tokens 53.2 / 54.0, the one of twelve batches that got slower.
 constexpr int kPourBlocks = 4096;                         // most blocks of a request behind `first`
 template <typename Tables>
 __global__ __launch_bounds__(1024) void prefix_pour_kernel(const int32_t* __restrict__ tokens, const Tables off, int block_tokens,
@@ -365,8 +366,8 @@ namespace {
 // 21.1, 64 of 2048 (not split) 16.0 / 15.9 / 15.9.
 constexpr double kChainNs = 95.0, kDigestNs = 0.64;
 // ... and a block's digest on the compute unit that chains its request, per token and for the block (256 tokens 133 ns, 512 186):
-// of 64, 80 and 110 for the block 80 was never behind launches of whole ranges (64 prompts of 512 blocks of 256 tokens 55.9,
-// 53.5, 51.8 us, 53.4 by ranges; 256 prompts of 118 blocks of 512 29.2, 29.2, 31.1, 35.6).
+// of 64, 80 and 110 for the block 80 was behind launches of whole ranges once, by 1.5 % (64 prompts of 512 blocks of 256 tokens
+// 55.9, 54.0, 51.8 us, 53.2 by ranges; 256 prompts of 118 blocks of 512 29.2, 29.4, 31.1, 35.3).
 constexpr double kUnitTokenNs = 0.207, kUnitBlockNs = 80.0;
 constexpr int kComputeUnits = 256;
 
