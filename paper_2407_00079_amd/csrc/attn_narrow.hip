@@ -16,6 +16,9 @@
 //     tile e holds the columns kVec i + e, so the kVec consecutive columns of a V row that a lane loads are one element of each
 //     tile.  bf16: the eight keys of a contraction come from eight registers, two at a time by v_perm; fp32: a register is an
 //     operand.
+//   * Where the row tiles leave most of the chip idle, several workgroups take a row tile, each a share of the output's columns: all
+//     of K, all scores and probabilities, its share of V and of P V.  Every column is summed as it is by one workgroup, so the
+//     results are the same bits.  Which: narrow_shares (host_plan.cpp).
 //   * True maxima per block, reference raised when a score outgrows it by 8 log2 units (see attn_prefill.hip).
 //
 // What bounds it: the loads of one compute unit (16 KiB in flight a wave).  One workgroup a compute unit, us a 64-key tile,
@@ -35,9 +38,10 @@ namespace mc {
 namespace {
 
 // What both dtypes share: a wave's corner of LDS and the meeting of the eight waves.
-template <int ROWS, int D, int BLOCK_KEYS, typename Out>
+template <int ROWS, int D, int SPLIT, int BLOCK_KEYS, typename Out>
 struct Narrow {
-  static constexpr int kStride = D + 4;                    // floats from row to row in LDS: 16 rows of a column spread over the banks
+  static constexpr int kCols = D / SPLIT;                  // columns of the workgroup's share of the output
+  static constexpr int kStride = kCols + 4;                // floats from row to row in LDS: 16 rows of a column spread over the banks
   // A wave's corner holds its block of keys in turn and, when it is done with them, its unnormalised output.
   static constexpr int kKeyBytes = BLOCK_KEYS * D * (int)sizeof(Out), kOutBytes = ROWS * kStride * 4;
   static constexpr int kCorner = ((kKeyBytes > kOutBytes ? kKeyBytes : kOutBytes) + 255) & ~255;
@@ -49,11 +53,11 @@ struct Narrow {
     }
     __device__ __forceinline__ float* o(int wave, int row) { return reinterpret_cast<float*>(corner[wave]) + row * kStride; }
   };
-  // Rows row0 .. of the chunk, over the waves' references, sums and unnormalised outputs in sh.
-  static __device__ __forceinline__ void finish(const Shared& sh, const AttnArgs& a, const Work& work, int n_rows) {
-    constexpr int kPer = ROWS * D / (kWaves * 64);         // columns of a thread
-    const int row = threadIdx.x / (D / kPer), col = threadIdx.x % (D / kPer) * kPer;
-    if (work.row0 + row >= n_rows) return;
+  // Rows row0 .. of the chunk, columns share kCols .., over the waves' references, sums and unnormalised outputs in sh.
+  static __device__ __forceinline__ void finish(const Shared& sh, const AttnArgs& a, const Work& work, int share, int n_rows) {
+    constexpr int kShare = ROWS * kCols / (kWaves * 64), kPer = kShare > 0 ? kShare : 1;       // columns of a thread
+    const int row = threadIdx.x / (kCols / kPer), col = threadIdx.x % (kCols / kPer) * kPer, out_col = share * kCols + col;
+    if ((kShare == 0 && row >= ROWS) || work.row0 + row >= n_rows) return;
     float top = sh.m[0][row];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) top = fmaxf(top, sh.m[w][row]);
@@ -78,16 +82,16 @@ struct Narrow {
       float v __attribute__((ext_vector_type(kPer)));
 #pragma unroll
       for (int e = 0; e < kPer; ++e) v[e] = acc[e] * inv;
-      *reinterpret_cast<decltype(v)*>(a.o_parts + part * D + col) = v;
-      if (col == 0) a.lse_parts[part] = l == 0.f ? -INFINITY : (top + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+      *reinterpret_cast<decltype(v)*>(a.o_parts + part * D + out_col) = v;
+      if (out_col == 0) a.lse_parts[part] = l == 0.f ? -INFINITY : (top + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
       return;
     }
     const float inv = 1.0f / l;
     Out v __attribute__((ext_vector_type(kPer)));
 #pragma unroll
     for (int e = 0; e < kPer; ++e) v[e] = (Out)(acc[e] * inv);
-    *reinterpret_cast<decltype(v)*>(reinterpret_cast<Out*>(a.out) + dst * D + col) = v;
-    if (a.lse != nullptr && col == 0) a.lse[dst] = (top + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+    *reinterpret_cast<decltype(v)*>(reinterpret_cast<Out*>(a.out) + dst * D + out_col) = v;
+    if (a.lse != nullptr && out_col == 0) a.lse[dst] = (top + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
   }
 };
 
@@ -192,11 +196,11 @@ struct StageK {
 // P 30000, C 1 149 / 139; P 1023, C 2 10.3 / 8.8; 16/16 heads, P 300, C 16 6.7 / 5.9; head_dim 64, 64/8 heads, P 30000, C 2
 // 104 / 85).  250 random batches, one-shot and planned: 34 calls of at most 16 rows are 1.04-1.22
 // times as fast, none loses.
-template <int D, int RT>
-__device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work) {
+template <int D, int RT, int SPLIT>
+__device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work, int share) {
   constexpr int kBlockKeys = 32, kBlockPages = kBlockKeys / kPageTokens;
-  constexpr int kRows = 16 * RT, kSteps = D / 32, kVec = D / 16, kRowB = D * 2, kPageHeadB = kPageTokens * kRowB;
-  typedef Narrow<kRows, D, kBlockKeys, __bf16> N;
+  constexpr int kRows = 16 * RT, kSteps = D / 32, kVec = D / 16 / SPLIT, kRowB = D * 2, kPageHeadB = kPageTokens * kRowB;
+  typedef Narrow<kRows, D, SPLIT, kBlockKeys, __bf16> N;
   typedef uint32_t vvec __attribute__((ext_vector_type(kVec / 2)));
   __shared__ __attribute__((aligned(256))) typename N::Shared sh;
 
@@ -227,7 +231,7 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
 
   const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadB;
   const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)work.kv_head * kPageHeadB;
-  const uint32_t v_lane = (uint32_t)(4 * g * kRowB + j * (kVec * 2));
+  const uint32_t v_lane = (uint32_t)(4 * g * kRowB + share * (kRowB / SPLIT) + j * (kVec * 2));
   StageK<kRowB, kBlockPages> stage;
   vvec vr[8];                                              // 4 page + r: key 4 g + r of that page
   auto load_v = [&](const int (&pid)[kBlockPages]) __attribute__((always_inline)) {
@@ -347,28 +351,35 @@ __device__ __forceinline__ void narrow_bf16(const AttnArgs& a, const Work& work)
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // column kVec (4 g + r) + e of row 16 rt + j
+  // column kVec (4 g + r) + e of the share, row 16 rt + j
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     const int row = rt * 16 + j;
+    constexpr int kStore = kVec < 4 ? kVec : 4;
+    typedef float fvec __attribute__((ext_vector_type(kStore)));
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int e = 0; e < kVec; e += 4)
-        *reinterpret_cast<f32x4*>(sh.o(wave, row) + kVec * (4 * g + r) + e) =
-            f32x4{o[e][rt][r], o[e + 1][rt][r], o[e + 2][rt][r], o[e + 3][rt][r]};
+      for (int e = 0; e < kVec; e += kStore) {
+        fvec v;
+#pragma unroll
+        for (int i = 0; i < kStore; ++i) v[i] = o[e + i][rt][r];
+        *reinterpret_cast<fvec*>(sh.o(wave, row) + kVec * (4 * g + r) + e) = v;
+      }
     if (g == 0) {
       sh.m[wave][row] = m_run[rt];
       sh.l[wave][row] = l_acc[rt][0];
     }
   }
   __syncthreads();
-  N::finish(sh, a, work, n_rows);
+  N::finish(sh, a, work, share, n_rows);
 }
 
-__device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) {
-  constexpr int kRows = 16, D = 64, kBlockKeys = 32, kBlockPages = kBlockKeys / kPageTokens;
-  typedef Narrow<kRows, D, kBlockKeys, float> N;
+template <int SPLIT>
+__device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work, int share) {
+  constexpr int kRows = 16, D = 64, kVec = D / 16 / SPLIT, kBlockKeys = 32, kBlockPages = kBlockKeys / kPageTokens;
+  typedef Narrow<kRows, D, SPLIT, kBlockKeys, float> N;
+  typedef float fvec __attribute__((ext_vector_type(kVec)));
   __shared__ __attribute__((aligned(256))) typename N::Shared sh;
 
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
@@ -396,21 +407,21 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
 
   const char* kbase = reinterpret_cast<const char*>(a.k_pool) + (int64_t)work.kv_head * kPageHeadBytes;
   const char* vbase = reinterpret_cast<const char*>(a.v_pool) + (int64_t)work.kv_head * kPageHeadBytes;
-  const uint32_t v_lane = (uint32_t)(4 * g * kRowBytes + j * 16);
+  const uint32_t v_lane = (uint32_t)(4 * g * kRowBytes + share * (kRowBytes / SPLIT) + j * (kVec * 4));
   StageK<kRowBytes, kBlockPages> stage;
-  f32x4 vr[8];
+  fvec vr[8];
   auto load_v = [&](const int (&pid)[kBlockPages]) __attribute__((always_inline)) {
 #pragma unroll
     for (int h = 0; h < kBlockPages; ++h) {
       const char* page = vbase + (int64_t)pid[h] * walk.page_stride;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) vr[4 * h + r] = *reinterpret_cast<const f32x4*>(page + v_lane + r * kRowBytes);
+      for (int r = 0; r < 4; ++r) vr[4 * h + r] = *reinterpret_cast<const fvec*>(page + v_lane + r * kRowBytes);
     }
   };
 
-  f32x4 o[4];
+  f32x4 o[kVec];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < kVec; ++e) o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;                    // (l_run: this lane group's keys)
   const float c = a.scale_log2e;
 
@@ -452,7 +463,7 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
       asm volatile("");
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        if (block * kBlockKeys + (q >> 2) * 16 + 4 * g + (q & 3) >= walk.L) vr[q] = f32x4{};
+        if (block * kBlockKeys + (q >> 2) * 16 + 4 * g + (q & 3) >= walk.L) vr[q] = fvec{};
     }
     const float mx = max_over_groups(max8(s[0], s[1])) * c;
     if (__builtin_amdgcn_ballot_w64(mx > m_run + kRescaleSlack) != 0) {
@@ -461,7 +472,7 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
       m_run = m_new;
       l_run *= alpha;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] *= alpha;
+      for (int e = 0; e < kVec; ++e) o[e] *= alpha;
     }
     const float ref = fmaxf(m_run, kNoKeyYet);
 #pragma unroll
@@ -474,7 +485,7 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
 #pragma unroll
     for (int q = 0; q < 8; ++q)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = mma(vr[q][e], s[q >> 2][q & 3], o[e]);
+      for (int e = 0; e < kVec; ++e) o[e] = mma(vr[q][e], s[q >> 2][q & 3], o[e]);
     load_v(pid);
     walk.pages_of(next_after(next_after(block)), pid);
     wave_sees_lds();
@@ -484,57 +495,71 @@ __device__ __forceinline__ void narrow_f32(const AttnArgs& a, const Work& work) 
   l_run += __shfl_xor(l_run, 16, 64);
   l_run = sum_with_other_half(l_run);
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
-    *reinterpret_cast<f32x4*>(sh.o(wave, j) + 16 * g + 4 * r) = f32x4{o[0][r], o[1][r], o[2][r], o[3][r]};
+  for (int r = 0; r < 4; ++r) {
+    fvec v;
+#pragma unroll
+    for (int e = 0; e < kVec; ++e) v[e] = o[e][r];
+    *reinterpret_cast<fvec*>(sh.o(wave, j) + kVec * (4 * g + r)) = v;
+  }
   if (g == 0) {
     sh.m[wave][j] = m_run;
     sh.l[wave][j] = l_run;
   }
   __syncthreads();
-  N::finish(sh, a, work, n_rows);
+  N::finish(sh, a, work, share, n_rows);
 }
 
 // BF16_D: head_dim of the bf16 forms, 0: fp32
-template <int BF16_D, int ROWS>
-__device__ __forceinline__ void narrow_body(const AttnArgs& a, const Work& work) {
-  if constexpr (BF16_D == 0) narrow_f32(a, work);
-  else narrow_bf16<BF16_D, ROWS / 16>(a, work);
+template <int BF16_D, int ROWS, int SPLIT>
+__device__ __forceinline__ void narrow_body(const AttnArgs& a, const Work& work, int share) {
+  if constexpr (BF16_D == 0) narrow_f32<SPLIT>(a, work, share);
+  else narrow_bf16<BF16_D, ROWS / 16, SPLIT>(a, work, share);
 }
 
-template <int BF16_D, int ROWS>
+// workgroups n_items k .. take the k-th share of the columns
+template <int BF16_D, int ROWS, int SPLIT>
 __global__ __launch_bounds__(kWaves * 64) void attn_narrow_classes_kernel(const AttnArgs a, const AttnClasses t) {
-  narrow_body<BF16_D, ROWS>(a, work_of<ROWS>(t, blockIdx.x, a.Hkv, a.G));
+  const int share = SPLIT == 1 ? 0 : (int)blockIdx.x / a.n_items;
+  narrow_body<BF16_D, ROWS, SPLIT>(a, work_of<ROWS>(t, (int)blockIdx.x - share * a.n_items, a.Hkv, a.G), share);
 }
 
-// workgroups n_items k .. take the k-th ROWS rows of the items
-template <int BF16_D, int ROWS>
+// workgroups n_items k .. take the (k / SPLIT)-th ROWS rows of the items, and of their columns share k % SPLIT
+template <int BF16_D, int ROWS, int SPLIT>
 __global__ __launch_bounds__(kWaves * 64) void attn_narrow_list_kernel(const AttnArgs a) {
   const int part = (int)blockIdx.x / a.n_items;
   const AttnItem item = a.items[(int)blockIdx.x - part * a.n_items];
   const AttnReq rq = a.reqs[item.req];
-  const int row0 = item.row0 + part * ROWS;
+  const int row0 = item.row0 + part / SPLIT * ROWS;
   if (row0 >= rq.chunk * a.G) return;
-  narrow_body<BF16_D, ROWS>(a, Work{item.req, item.kv_head, row0, rq.q_off, rq.prefix, rq.chunk, 0, 1, 0, false});
+  narrow_body<BF16_D, ROWS, SPLIT>(a, Work{item.req, item.kv_head, row0, rq.q_off, rq.prefix, rq.chunk, 0, 1, 0, false}, part % SPLIT);
 }
 
-template <int BF16_D, int ROWS>
+template <int BF16_D, int ROWS, int SPLIT>
 void enqueue(const AttnArgs& args, int parts, const AttnClasses* t, hipStream_t stream) {
-  if (t != nullptr) attn_narrow_classes_kernel<BF16_D, ROWS><<<args.n_items, kWaves * 64, 0, stream>>>(args, *t);
-  else attn_narrow_list_kernel<BF16_D, ROWS><<<args.n_items * parts, kWaves * 64, 0, stream>>>(args);
+  if (t != nullptr) attn_narrow_classes_kernel<BF16_D, ROWS, SPLIT><<<args.n_items * SPLIT, kWaves * 64, 0, stream>>>(args, *t);
+  else attn_narrow_list_kernel<BF16_D, ROWS, SPLIT><<<args.n_items * parts * SPLIT, kWaves * 64, 0, stream>>>(args);
+}
+// (head_dim 64 in bf16: a quarter of the columns is no sooner than half of them)
+template <int BF16_D, int ROWS>
+void enqueue(const AttnArgs& args, int parts, int shares, const AttnClasses* t, hipStream_t stream) {
+  if (shares == 4 && BF16_D != 64) enqueue<BF16_D, ROWS, BF16_D == 64 ? 2 : 4>(args, parts, t, stream);
+  else if (shares > 1) enqueue<BF16_D, ROWS, 2>(args, parts, t, stream);
+  else enqueue<BF16_D, ROWS, 1>(args, parts, t, stream);
 }
 
 }  // namespace
 
-hipError_t launch_attn_narrow(int dtype, const AttnArgs& args, int rows, int parts, const AttnClasses* t, hipStream_t stream) {
+hipError_t launch_attn_narrow(int dtype, const AttnArgs& args, int rows, int parts, int shares, const AttnClasses* t,
+                              hipStream_t stream) {
   (void)hipGetLastError();
   const bool bf16 = dtype == MC_DTYPE_BF16, least = rows == kAttnLeastRows;
   if (!least && !(bf16 && rows == kAttnNarrowRows)) return hipErrorInvalidValue;
   if (dtype == MC_DTYPE_F32 && args.head_dim == 64)
-    enqueue<0, kAttnLeastRows>(args, parts, t, stream);
+    enqueue<0, kAttnLeastRows>(args, parts, shares, t, stream);
   else if (bf16 && args.head_dim == 128)
-    least ? enqueue<128, kAttnLeastRows>(args, parts, t, stream) : enqueue<128, kAttnNarrowRows>(args, parts, t, stream);
+    least ? enqueue<128, kAttnLeastRows>(args, parts, shares, t, stream) : enqueue<128, kAttnNarrowRows>(args, parts, shares, t, stream);
   else if (bf16 && args.head_dim == 64)
-    least ? enqueue<64, kAttnLeastRows>(args, parts, t, stream) : enqueue<64, kAttnNarrowRows>(args, parts, t, stream);
+    least ? enqueue<64, kAttnLeastRows>(args, parts, shares, t, stream) : enqueue<64, kAttnNarrowRows>(args, parts, shares, t, stream);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -199,8 +199,9 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
     args.scale_log2e = attn_scale_log2e(p);
     args.n_items = plan.narrow_wgs > 0 ? plan.narrow_wgs : plan.n_wgs;
     const hipStream_t on = reinterpret_cast<hipStream_t>(hip_stream);
-    const hipError_t launched = plan.narrow_wgs > 0 ? launch_attn_narrow(p->dtype, args, plan.narrow.rows, 1, &plan.narrow, on)
-                                                    : launch_attn_classes(p->dtype, args, plan.classes, on);
+    const hipError_t launched =
+        plan.narrow_wgs > 0 ? launch_attn_narrow(p->dtype, args, plan.narrow.rows, 1, narrow_shares(p, plan.narrow_wgs), &plan.narrow, on)
+                            : launch_attn_classes(p->dtype, args, plan.classes, on);
     return launched == hipSuccess ? MC_OK : MC_ERR_HIP;
   }
 

@@ -188,6 +188,19 @@ int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int
   return 2 * n_items <= kComputeUnits ? kListHalves : 0;
 }
 
+// Shares of the columns cost every workgroup the scores and spare it what is left of V and P V, so they pay while they land on idle
+// compute units: up to 256 workgroups in fp32, which is bound by its MFMAs; in bf16 up to about 192, beyond which the K rows
+// that all of them load press on the L2s (head_dim 64 has half of them, but only halves are sooner: a row of V in quarters is 32 bytes).
+// Planned, us, one workgroup a row tile / two / four: 64/8 heads, P 131056, C 16 (32 row tiles) 909 / 745 / 629; P 20000, C 24
+// (48) 98 / 92 / 88, C 32 (64) 99 / 93 / 99, C 48 (96) 99 / 95 / 168, C 64 (128) 99 / 107 / 180; P 600, C 24 9.0 / 8.5 / 7.8;
+// head_dim 64, P 20000, C 48 (96) 71 / 70, C 64 71 / 73, P 600, C 32 (64) 6.8 / 6.0; fp32, 4/1 heads, P 3000, C 256 (64) 35 / 29 / 27, C 512
+// (128) 37 / 32 / 51, C 768 (192) 40 / 59 / 75; P 256, C 128 (32) 8.4 / 7.6 / 6.9.
+int32_t narrow_shares(const mc_attn_params* p, int64_t row_tiles) {
+  const bool f32 = p->dtype == MC_DTYPE_F32;
+  if (row_tiles <= (f32 ? 64 : 48) && (f32 || p->head_dim == 128)) return 4;
+  return row_tiles <= (f32 ? 128 : 96) ? 2 : 1;
+}
+
 mc_status check_plan(const mc_attn_params* p, const mc_attn_plan* plan, bool want_split) {
   if (plan == nullptr) return MC_ERR_NULL;
   if (plan->num_q_heads != p->num_q_heads || plan->num_kv_heads != p->num_kv_heads || plan->dtype != (int32_t)p->dtype ||

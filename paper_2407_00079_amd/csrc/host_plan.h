@@ -69,6 +69,9 @@ constexpr int32_t kMostNarrowItems = INT32_MAX / (kAttnTileRows / kAttnLeastRows
 int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                   int32_t kv_splits, int64_t n_items);
 
+// Workgroups that take a row tile of the narrow form, each a share of its columns, where there are `row_tiles` (x pieces) of them.
+int32_t narrow_shares(const mc_attn_params* p, int64_t row_tiles);
+
 // A plan handed back by the caller: made for these params, of the wanted form, not empty.
 mc_status check_plan(const mc_attn_params* p, const mc_attn_plan* plan, bool want_split);
 

@@ -225,7 +225,9 @@ mc_status launch_planned_attn(const mc_attn_params* p, const mc_attn_plan* plan,
   const bool least = plan->reserved == kListNarrowLeast;
   const bool narrow = (plan->reserved == kListNarrow || least) && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
   const int rows = least || p->dtype == MC_DTYPE_F32 ? mc::kAttnLeastRows : mc::kAttnNarrowRows;
-  const hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, rows, least ? 1 : mc::kAttnTileRows / rows, nullptr, stream)
+  // (at most so many row tiles: of every request the last may be short)
+  const int shares = narrow_shares(p, args.Hkv * (plan->total_new_tokens * args.G / rows + plan->batch));
+  const hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, rows, least ? 1 : mc::kAttnTileRows / rows, shares, nullptr, stream)
                                : mc::launch_attn(p->dtype, args, stream);
   return st == hipSuccess ? MC_OK : MC_ERR_HIP;
 }
@@ -280,7 +282,7 @@ mc_status launch_class_plan(const mc_attn_params* p, const ClassPlan& plan, cons
   args.lse_parts = lse_parts;
   const bool narrow = plan.narrow_wgs > 0;
   const mc::AttnClasses& classes = narrow ? plan.narrow : plan.classes;
-  hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, classes.rows, 1, &classes, stream)
+  hipError_t st = narrow ? mc::launch_attn_narrow(p->dtype, args, classes.rows, 1, narrow_shares(p, args.n_items), &classes, stream)
                          : mc::launch_attn_classes(p->dtype, args, classes, stream);
   if (st == hipSuccess && (narrow ? plan.narrow_pieces : plan.most_pieces) > 1)
     st = mc::launch_attn_merge_classes(p->dtype, p->head_dim, o_parts, lse_parts, classes, p->num_q_heads, p->num_kv_heads, out,

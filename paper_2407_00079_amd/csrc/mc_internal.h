@@ -43,9 +43,10 @@ hipError_t launch_attn_classes(int dtype, const AttnArgs& args, const AttnClasse
 hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream);
 
 // the narrow form: args.n_items workgroups described by classes of its row tiles, or (t null) the row tiles of the list's
-// args.n_items items, whole, `parts` row
-// tiles an item; rows of a workgroup: kAttnNarrowRows (bf16) or kAttnLeastRows
-hipError_t launch_attn_narrow(int dtype, const AttnArgs& args, int rows, int parts, const AttnClasses* t, hipStream_t stream);
+// args.n_items items, whole, `parts` row tiles an item; rows of a workgroup: kAttnNarrowRows (bf16) or kAttnLeastRows;
+// `shares` workgroups a row tile, each for as many of the output's columns: 1, 2 or 4
+hipError_t launch_attn_narrow(int dtype, const AttnArgs& args, int rows, int parts, int shares, const AttnClasses* t,
+                              hipStream_t stream);
 
 // enqueue the merge of the classes that were cut into pieces (nothing if none was)
 hipError_t launch_attn_merge_classes(int dtype, int head_dim, const float* o_parts, const float* lse_parts,
