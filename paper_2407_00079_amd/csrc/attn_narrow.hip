@@ -516,16 +516,20 @@ __device__ __forceinline__ void narrow_body(const AttnArgs& a, const Work& work,
   else narrow_bf16<BF16_D, ROWS / 16, SPLIT>(a, work, share);
 }
 
+template <int BF16_D, int ROWS>
+__global__ __launch_bounds__(kWaves * 64) void attn_narrow_classes_kernel(const AttnArgs a, const AttnClasses t) {
+  narrow_body<BF16_D, ROWS, 1>(a, work_of<ROWS>(t, blockIdx.x, a.Hkv, a.G), 0);
+}
 // workgroups n_items k .. take the k-th share of the columns
 template <int BF16_D, int ROWS, int SPLIT>
-__global__ __launch_bounds__(kWaves * 64) void attn_narrow_classes_kernel(const AttnArgs a, const AttnClasses t) {
-  const int share = SPLIT == 1 ? 0 : (int)blockIdx.x / a.n_items;
+__global__ __launch_bounds__(kWaves * 64) void attn_narrow_shared_classes_kernel(const AttnArgs a, const AttnClasses t) {
+  const int share = (int)blockIdx.x / a.n_items;
   narrow_body<BF16_D, ROWS, SPLIT>(a, work_of<ROWS>(t, (int)blockIdx.x - share * a.n_items, a.Hkv, a.G), share);
 }
 
 // workgroups n_items k .. take the (k / SPLIT)-th ROWS rows of the items, and of their columns share k % SPLIT
 template <int BF16_D, int ROWS, int SPLIT>
-__global__ __launch_bounds__(kWaves * 64) void attn_narrow_list_kernel(const AttnArgs a) {
+__device__ __forceinline__ void narrow_list(const AttnArgs& a) {
   const int part = (int)blockIdx.x / a.n_items;
   const AttnItem item = a.items[(int)blockIdx.x - part * a.n_items];
   const AttnReq rq = a.reqs[item.req];
@@ -533,11 +537,24 @@ __global__ __launch_bounds__(kWaves * 64) void attn_narrow_list_kernel(const Att
   if (row0 >= rq.chunk * a.G) return;
   narrow_body<BF16_D, ROWS, SPLIT>(a, Work{item.req, item.kv_head, row0, rq.q_off, rq.prefix, rq.chunk, 0, 1, 0, false}, part % SPLIT);
 }
+template <int BF16_D, int ROWS>
+__global__ __launch_bounds__(kWaves * 64) void attn_narrow_list_kernel(const AttnArgs a) {
+  narrow_list<BF16_D, ROWS, 1>(a);
+}
+template <int BF16_D, int ROWS, int SPLIT>
+__global__ __launch_bounds__(kWaves * 64) void attn_narrow_shared_list_kernel(const AttnArgs a) {
+  narrow_list<BF16_D, ROWS, SPLIT>(a);
+}
 
 template <int BF16_D, int ROWS, int SPLIT>
 void enqueue(const AttnArgs& args, int parts, const AttnClasses* t, hipStream_t stream) {
-  if (t != nullptr) attn_narrow_classes_kernel<BF16_D, ROWS, SPLIT><<<args.n_items * SPLIT, kWaves * 64, 0, stream>>>(args, *t);
-  else attn_narrow_list_kernel<BF16_D, ROWS, SPLIT><<<args.n_items * parts * SPLIT, kWaves * 64, 0, stream>>>(args);
+  if constexpr (SPLIT == 1) {
+    if (t != nullptr) attn_narrow_classes_kernel<BF16_D, ROWS><<<args.n_items, kWaves * 64, 0, stream>>>(args, *t);
+    else attn_narrow_list_kernel<BF16_D, ROWS><<<args.n_items * parts, kWaves * 64, 0, stream>>>(args);
+  } else {
+    if (t != nullptr) attn_narrow_shared_classes_kernel<BF16_D, ROWS, SPLIT><<<args.n_items * SPLIT, kWaves * 64, 0, stream>>>(args, *t);
+    else attn_narrow_shared_list_kernel<BF16_D, ROWS, SPLIT><<<args.n_items * parts * SPLIT, kWaves * 64, 0, stream>>>(args);
+  }
 }
 // (head_dim 64 in bf16: a quarter of the columns is no sooner than half of them)
 template <int BF16_D, int ROWS>
