@@ -413,6 +413,9 @@ mc_status mc_kv_unpack_layer_ordered(const void* k_in, const void* v_in, int64_t
  *          = two host-to-device copies, then mc_kv_unpack_layer
  *   store: pages page_ids[i] of the pools -> k_stage/v_stage -> k_host/v_host
  *          = mc_kv_pack_layer, then two device-to-host copies
+ *   At most 512 slices of 4 KiB (2 MiB of K, if pages are that long) between pinned memory and the
+ *   pools are moved by one kernel, which reads or writes the host memory itself; the staging buffers
+ *   hold the packed form afterwards either way.
  *
  *   k_host, v_host    host  n * page_bytes each.  For the copies to be asynchronous the memory
  *                           must be pinned (hipHostMalloc); pageable memory works but blocks.

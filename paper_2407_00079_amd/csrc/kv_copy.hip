@@ -63,6 +63,48 @@ __global__ __launch_bounds__(kThreads) void kv_copy_kernel(const u32x4* __restri
   }
 }
 
+// A layer's load or store in one launch, where it is small: the kernel reads or writes pinned host memory itself and leaves the
+// packed form in the staging buffers on the way.  What bounds it: the host link (55 GB/s).  The copy engine's way is two copies and
+// a kernel, each waiting for the one before through a signal (20-130 us of an idle link between them), and copies of several
+// streams wait for each other where they share an engine.  Four layers of K and V each way on two streams, three such pairs of
+// streams in turn, us by the copy engine / so: 64 KiB a copy 178-203 / 157, 512 KiB 438 / 178, 1 MiB 656 / 321, 2 MiB 940 / 596;
+// 12.6 MB in by the engine and 1.67 MB out 2837 / 2204.
+// Few workgroups, small enough to run beside attention's on a compute unit: 16 keep 256 KiB of reads in flight, and 8 write as
+// fast as the link takes it while fewer of attention's wait behind them.  A step of 231 us of attention a layer (64/8 heads, P 8192,
+// C 1024) that stores 2 MiB of K and of V 376 by the engine, with 64 workgroups 304, 16 296, 8 292; one of 1010 us of attention
+// 1047, 1079, 1060, 1057 (loads make no difference).  So not beyond 2 MiB: the engine disturbs a long attention less.
+constexpr int kHostThreads = 256, kHostPer = 4, kHostLoadGrid = 16, kHostStoreGrid = 8;
+static_assert(kHostThreads * 16 == kHostSliceBytes, "a workgroup moves a slice at a time");
+template <bool kLoad>
+__global__ __launch_bounds__(kHostThreads) void kv_host_kernel(u32x4* k_host, u32x4* v_host, u32x4* k_stage, u32x4* v_stage,
+                                                               u32x4* k_pool, u32x4* v_pool,
+                                                               const int32_t* __restrict__ page_ids, int page_vecs,
+                                                               int slices_per_page, int slices) {
+  for (int base = blockIdx.x; base < 2 * slices; base += kHostPer * gridDim.x) {
+    u32x4 v[kHostPer];
+    // slice `at` of K, then of V: page, vector of the page, and whether the thread has one
+    auto each = [&](auto&& move) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < kHostPer; ++u) {
+        const int at = base + u * (int)gridDim.x;
+        if (at >= 2 * slices) break;
+        const bool second = at >= slices;
+        const int rest = second ? at - slices : at, page = rest / slices_per_page;
+        const int vec = (rest - page * slices_per_page) * kHostThreads + (int)threadIdx.x;
+        if (vec < page_vecs) move(v[u], second, (int64_t)page * page_vecs + vec, (int64_t)page_ids[page] * page_vecs + vec);
+      }
+    };
+    each([&](u32x4& x, bool second, int64_t packed, int64_t paged) __attribute__((always_inline)) {
+      x = kLoad ? (second ? v_host : k_host)[packed] : (second ? v_pool : k_pool)[paged];
+    });
+    each([&](u32x4& x, bool second, int64_t packed, int64_t paged) __attribute__((always_inline)) {
+      (second ? v_stage : k_stage)[packed] = x;
+      if (kLoad) (second ? v_pool : k_pool)[paged] = x;
+      else (second ? v_host : k_host)[packed] = x;
+    });
+  }
+}
+
 // order[r] = the list position whose pool page is the r-th smallest (ties: lower position first),
 // i.e. the rank of the 64-bit key (page id, list position).  Rank by counting, the ids staged
 // through LDS in chunks: O(n^2) compares, meant to be run once per request - the list is the same
@@ -216,6 +258,18 @@ hipError_t launch_kv_append(const void* k_new, const void* v_new, void* k_pool, 
     kv_append_kernel<const AttnReq*><<<blocks, 256, 0, stream>>>(
         (const u32x4*)k_new, (const u32x4*)v_new, (u32x4*)k_pool, (u32x4*)v_pool, block_tables, max_pages, reqs, batch,
         total_vecs, Hkv, gran_shift);
+  return hipGetLastError();
+}
+
+hipError_t launch_kv_host(bool load, void* k_host, void* v_host, void* k_stage, void* v_stage, void* k_pool, void* v_pool,
+                          const int32_t* page_ids, int64_t n, int64_t page_bytes, hipStream_t stream) {
+  const int per_page = (int)((page_bytes + kHostSliceBytes - 1) / kHostSliceBytes), slices = (int)n * per_page;
+  const int most = load ? kHostLoadGrid : kHostStoreGrid;
+  const unsigned grid = (unsigned)(2 * slices < most ? 2 * slices : most);
+  auto kernel = load ? kv_host_kernel<true> : kv_host_kernel<false>;
+  (void)hipGetLastError();
+  kernel<<<grid, kHostThreads, 0, stream>>>((u32x4*)k_host, (u32x4*)v_host, (u32x4*)k_stage, (u32x4*)v_stage, (u32x4*)k_pool,
+                                            (u32x4*)v_pool, page_ids, (int)(page_bytes / 16), per_page, slices);
   return hipGetLastError();
 }
 

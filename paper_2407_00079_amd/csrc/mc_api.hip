@@ -105,6 +105,35 @@ mc_status upload(void* dst, const void* src, size_t bytes, hipStream_t stream) {
   return g_staging.release_after(slot, stream) ? MC_OK : MC_ERR_HIP;
 }
 
+// Where the device sees `bytes` of pinned host memory, or null: memory of another kind, or less of it.
+void* host_view(const void* host, size_t bytes) {
+  hipPointerAttribute_t attr = {};
+  void* start = nullptr;
+  size_t size = 0;
+  void* const at = const_cast<void*>(host);
+  const bool known = hipPointerGetAttributes(&attr, at) == hipSuccess && attr.type == hipMemoryTypeHost &&
+                     attr.devicePointer != nullptr && (attr.allocationFlags & hipHostMallocNonCoherent) == 0 &&
+                     hipPointerGetAttribute(&start, HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, at) == hipSuccess &&
+                     hipPointerGetAttribute(&size, HIP_POINTER_ATTRIBUTE_RANGE_SIZE, at) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  const uintptr_t offset = reinterpret_cast<uintptr_t>(attr.devicePointer) - reinterpret_cast<uintptr_t>(start);
+  return known && offset <= size && bytes <= size - offset ? attr.devicePointer : nullptr;
+}
+
+// Small loads and stores: one launch that reads or writes the host memory itself.  *done: it has been enqueued.
+mc_status host_copy(bool load, const void* k_host, const void* v_host, void* k_stage, void* v_stage, void* k_pool, void* v_pool,
+                    const int32_t* page_ids, int64_t n, int64_t page_bytes, hipStream_t stream, bool* done) {
+  *done = false;
+  const int64_t slices = n * ((page_bytes + mc::kHostSliceBytes - 1) / mc::kHostSliceBytes);
+  if (slices > mc::kMostHostSlices) return MC_OK;
+  void* k = host_view(k_host, (size_t)(n * page_bytes));
+  void* v = host_view(v_host, (size_t)(n * page_bytes));
+  if (k == nullptr || v == nullptr) return MC_OK;
+  *done = true;
+  return mc::launch_kv_host(load, k, v, k_stage, v_stage, k_pool, v_pool, page_ids, n, page_bytes, stream) == hipSuccess ? MC_OK
+                                                                                                                       : MC_ERR_HIP;
+}
+
 // Two offset tables for a prefix call: in `arg` if they fit, else uploaded to the workspace back to back.
 mc_status place_tables(const int64_t* a, size_t n_a, const int64_t* b, size_t n_b, void* workspace, hipStream_t stream,
                        mc::OffsetTables* arg, mc::PrefixTables* out) {
@@ -611,6 +640,9 @@ mc_status mc_kv_load_layer(const void* k_host, const void* v_host, void* k_stage
   if (k_host == nullptr || v_host == nullptr) return MC_ERR_NULL;
   if (!aligned16(k_host) || !aligned16(v_host)) return MC_ERR_ALIGN;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
+  bool done = false;
+  st = host_copy(true, k_host, v_host, k_stage, v_stage, k_pool_layer, v_pool_layer, page_ids, n, page_bytes, stream, &done);
+  if (done || st != MC_OK) return st;
   const size_t bytes = (size_t)n * (size_t)page_bytes;
   if (hipMemcpyAsync(k_stage, k_host, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return MC_ERR_HIP;
   if (hipMemcpyAsync(v_stage, v_host, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return MC_ERR_HIP;
@@ -628,6 +660,10 @@ mc_status mc_kv_store_layer(const void* k_pool_layer, const void* v_pool_layer, 
   if (k_host == nullptr || v_host == nullptr) return MC_ERR_NULL;
   if (!aligned16(k_host) || !aligned16(v_host)) return MC_ERR_ALIGN;
   hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
+  bool done = false;
+  st = host_copy(false, k_host, v_host, k_stage, v_stage, const_cast<void*>(k_pool_layer), const_cast<void*>(v_pool_layer), page_ids,
+                 n, page_bytes, stream, &done);
+  if (done || st != MC_OK) return st;
   const size_t bytes = (size_t)n * (size_t)page_bytes;
   if (mc::launch_kv_copy(true, k_pool_layer, v_pool_layer, k_stage, v_stage, page_ids, nullptr, n, page_bytes, stream) !=
       hipSuccess)

@@ -62,6 +62,11 @@ hipError_t launch_kv_copy(bool pack, const void* k_src, const void* v_src, void*
                           const int32_t* page_ids, const int32_t* order, int64_t n, int64_t page_bytes,
                           hipStream_t stream);
 
+// enqueue a layer's load from (or store to) host memory that the device sees at k_host, v_host: host and stage hold the n pages
+// in list order.  For small n (2 n ceil(page_bytes / kHostSliceBytes) has to fit 32 bits).
+hipError_t launch_kv_host(bool load, void* k_host, void* v_host, void* k_stage, void* v_stage, void* k_pool, void* v_pool,
+                          const int32_t* page_ids, int64_t n, int64_t page_bytes, hipStream_t stream);
+
 // enqueue the computation of order[r] = position of the r-th smallest page id (stable)
 hipError_t launch_kv_page_order(const int32_t* page_ids, int64_t n, int32_t* order, hipStream_t stream);
 

@@ -75,6 +75,10 @@ constexpr int kAttnNarrowRows = 32, kAttnLeastRows = 16;
 constexpr int kAttnTileKeys = 64;
 // 16-byte vectors of a page one copy workgroup moves (512 threads, one vector each)
 constexpr int kKvCopySliceVecs = 512;
+// bytes of a page that a workgroup of a small load or store against host memory moves at a time, and the most such slices of K
+// of a call that goes that way: 2 MiB (kv_host_kernel in kv_copy.hip)
+constexpr int kHostSliceBytes = 4096;
+constexpr int64_t kMostHostSlices = 512;
 // the work list is kept in this many lists, one per XCD of the chip
 constexpr int kXcds = 8;
 
