@@ -43,12 +43,14 @@ constexpr float kNoKeyYet = -1e30f;
 // Full tiles / few rows, one call, bf16 head_dim 128, 64/8 heads unless said: P 131056, C 16 111 / 96 us; P 131056, C 1
 // 101 / 86; P 1000, C 100 28 / 22; P 256, C 128 17 / 13; P 30000, C 300 245 / 275; head_dim 64, P 131056, C 16 69 / 60;
 // fp32, 4/1 heads, P 256, C 128 24 / 17, P 6955, C 200 80 / 46.
-enum Rows { kFullRows = 0, kFewRows = 1 };
+// Pair rows (64): as few rows, but the four that compute are two pairs, one for the first 32 keys of every tile and one for the
+// others; their results meet in LDS at the end.
+enum Rows { kFullRows = 0, kFewRows = 1, kPairRows = 2 };
 constexpr int kFetchWaves = 4;
 template <Rows R>
-constexpr int kTileRowsOf = R == kFewRows ? kAttnFewRows : kAttnTileRows;
+constexpr int kTileRowsOf = R == kPairRows ? kAttnPairRows : R == kFewRows ? kAttnFewRows : kAttnTileRows;
 template <Rows R>
-__device__ __forceinline__ bool wave_copies(int wave) { return R == kFewRows ? wave >= kFetchWaves : wave < kFetchWaves; }
+__device__ __forceinline__ bool wave_copies(int wave) { return R != kFullRows ? wave >= kFetchWaves : wave < kFetchWaves; }
 template <Rows R>
 __device__ __forceinline__ bool wave_computes(int wave) { return R == kFullRows || wave < kFetchWaves; }
 
@@ -66,9 +68,18 @@ struct Work {
   bool once;                             // K and V are streamed (AttnClasses::once)
 };
 
-// list launches; workgroups n_items .. take the second halves of the items' row tiles (few rows only)
+// list launches; workgroups n_items .. take the second halves of the items' row tiles (few rows).  Pair rows: the quarters of eight
+// items together, in the order of the list and each on its item's XCD (the last n_items % 8 items: one quarter after another).
 template <Rows R, typename Args>
 __device__ __forceinline__ Work work_of(const Args& a, int wg) {
+  if constexpr (R == kPairRows) {
+    constexpr int kParts = kAttnTileRows / kAttnPairRows;
+    const int rest = a.n_items % kXcds, whole = (a.n_items - rest) * kParts, behind = wg - whole;
+    const int part = behind < 0 ? wg / kXcds % kParts : behind / rest;
+    const AttnItem item = a.items[behind < 0 ? wg / (kXcds * kParts) * kXcds + wg % kXcds : a.n_items - rest + behind % rest];
+    const AttnReq rq = a.reqs[item.req];
+    return Work{item.req, item.kv_head, item.row0 + part * kAttnPairRows, rq.q_off, rq.prefix, rq.chunk, 0, 1, 0, false};
+  }
   const bool second = R == kFewRows && wg >= a.n_items;
   const AttnItem item = a.items[second ? wg - a.n_items : wg];
   const AttnReq rq = a.reqs[item.req];

@@ -222,7 +222,7 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
                                                                             p->page_size, items, reqs, (int)n_items);
   if (hipGetLastError() != hipSuccess) return MC_ERR_HIP;
 
-  AttnArgs args;
+  AttnArgs args = {};
   args.q = q;
   args.k_pool = k_pool;
   args.v_pool = v_pool;

@@ -31,6 +31,11 @@
 //     score MFMAs of block j+1, row tile 0 of block j+1 under the P V MFMAs of block j.  The row
 //     sums of the rounded probabilities come from two more MFMAs per block (ones x P^T), and the
 //     guard of the lazy reference is an OR over the packed probabilities (see kRefLift).
+//   * Pair rows (64-row workgroups): for launches whose 128-row tiles leave compute units idle and whose 32-row ones would take
+//     several rounds.  A tile is one block for each wave: 0.44-0.47 us (head_dim 64: 0.36), of which the copies hold the compute unit
+//     for 0.29; 0.72 (0.55) with 128 rows.  The two pairs meet in LDS once, at the end.  Planned, us, before / so: 64/8 heads,
+//     P 8192, C 192 103 / 64; P 120000, C 200 1370 / 880 (head_dim 64 1170 / 690); 16/2 heads, P 23838, C 599 240 / 165; 8/1 heads,
+//     P 24084, C 1839 260 / 188.  When it is taken: plan_classes (host_plan.cpp).
 //   * What bounds it at head_dim 128: the board's power limit.  7.0 % less time on all-zero operands,
 //     which run at the full clock (128k-context shape, 2.58 -> 2.40 ms; 6.1 % fewer cycles by the
 //     counters), came out as 1.3 % less on random ones (3.20 -> 3.16 ms): the clock falls as the stream
@@ -164,6 +169,7 @@ __device__ __forceinline__ uint32_t round_pair(const Scores& p, int e) {
 template <int D, Rows ROWS, Form FORM>
 __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& work) {
   constexpr bool SPLIT = FORM != kWhole;       // the result may be partial
+  constexpr bool kByPairs = ROWS == kPairRows;   // every wave sees 32 of the 64 keys of a tile
   typedef Geo<D> X;
   // (these names hide the 256-byte-row constants of attn_device.h inside this kernel)
   constexpr int kD = D, kSteps = X::kSteps, kDTiles = X::kDTiles, kRing = X::kRing, kRowBytes = X::kRowB,
@@ -174,10 +180,14 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   // three buffers, 97 with four or five; a short call, 1000 + 16 tokens: 16.9, 17.0, 17.4).
   constexpr int kBufs = ROWS == kFullRows ? kBuffers : kDeepBuffers;
   constexpr int kAhead = kBufs - 1;
-  constexpr int kVBase = kBufs * kKTileBytes;            // the K tiles of the buffers, then the V tiles
+  // Pair rows: a wave goes through a tile in one step, its scores run a tile ahead and their fragments one more, so K needs three
+  // tiles where V needs one; with three and two more on their way that is 144 KiB (four buffers of V, 160 KiB and a loop of twelve
+  // tiles: 1 % sooner).
+  constexpr int kKBufs = kByPairs ? 6 : kBufs, kVBufs = kByPairs ? 3 : kBufs;
+  constexpr int kVBase = kKBufs * kKTileBytes;           // the K tiles of the buffers, then the V tiles
   // tile bases are multiples of 8 KiB from a 256-byte aligned start: the XOR constants of the swizzle (< 256)
   // never reach a tile base
-  __shared__ __attribute__((aligned(256))) char smem[kBufs * (kKTileBytes + kVTileBytes)];
+  __shared__ __attribute__((aligned(256))) char smem[kKBufs * kKTileBytes + kVBufs * kVTileBytes];
   constexpr int kTileRows = kTileRowsOf<ROWS>;
 
   const int tid = threadIdx.x;
@@ -195,7 +205,9 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   // a wave that copies no tiles and whose 32 rows all lie past the end of the chunk ends here
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const bool fetcher = wave_copies<ROWS>(wave_u);
-  if (!fetcher && work.row0 + wave_u * 32 >= n_rows) return;
+  const int row_wave = kByPairs ? wave & 1 : wave, row_wave_u = kByPairs ? wave_u & 1 : wave_u;
+  const int key_half = kByPairs ? wave_u >> 1 & 1 : 0;
+  if (!fetcher && work.row0 + row_wave_u * 32 >= n_rows) return;
 
   // ---- this lane's two query rows: their Q fragments stay in registers for the whole KV loop
   frag qf[kSteps][2];
@@ -204,7 +216,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   int64_t orow_idx[2], prow[2];                   // rows of the output and of the partial results
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
-    int row = work.row0 + wave * 32 + rt * 16 + j;
+    int row = work.row0 + row_wave * 32 + rt * 16 + j;
     live[rt] = row < n_rows;
     row = live[rt] ? row : n_rows - 1;            // dead rows recompute the last row, never stored
     tok[rt] = row / G;
@@ -323,8 +335,8 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) o[dt][rt] = acc4{0.f, 0.f, 0.f, 0.f};
   const float c = a.scale_log2e;
-  const uint32_t k_lane = smem_base + X::k_lane_off(lane);
-  const uint32_t v_lane = smem_base + kVBase + X::v_lane_off(lane);
+  const uint32_t k_lane = smem_base + key_half * 32 * kRowBytes + X::k_lane_off(lane);
+  const uint32_t v_lane = smem_base + kVBase + key_half * 32 * kRowBytes + X::v_lane_off(lane);
   uint32_t kx[kSteps], vx[kDTiles];
 #pragma unroll
   for (int i = 0; i < kSteps; ++i) kx[i] = k_lane ^ (uint32_t)(i << 6);
@@ -367,11 +379,12 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
         const float m_new = fmaxf(m_run[rt], mx[rt] + kRefLift);
-        // a row that has seen no key yet keeps -inf (only in a slice that starts beyond the row's diagonal)
-        const float alpha = (SPLIT && m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run[rt] - m_new);
+        // a row that has seen no key yet keeps -inf (only in a slice that starts beyond the row's diagonal, or in the later keys
+        // of a tile)
+        const float alpha = ((SPLIT || kByPairs) && m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_run[rt] - m_new);
         l_acc[rt] *= alpha;
         m_run[rt] = m_new;
-        m_ref[rt] = SPLIT ? fmaxf(m_new, kNoKeyYet) : m_new;
+        m_ref[rt] = SPLIT || kByPairs ? fmaxf(m_new, kNoKeyYet) : m_new;
 #pragma unroll
         for (int dt = 0; dt < kDTiles; ++dt) o[dt][rt] *= alpha;
       }
@@ -446,7 +459,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
     }
   };
   auto phase_a = [&](int buf_cur, int kb_cur) __attribute__((always_inline)) {
-    const int off_v = buf_cur * kVTileBytes + kb_cur * 32 * kRowBytes;
+    const int off_v = buf_cur % kVBufs * kVTileBytes + kb_cur * 32 * kRowBytes;
     s_cur = s_next;
     s_next.zero();
     pb.w[0] = pb_ahead;
@@ -503,7 +516,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   };
   auto plain_block = [&](int buf, int kb, int key0, Scores& s, bool have_scores) __attribute__((always_inline)) {
     if (!have_scores) scores_of(buf, kb, s);
-    const int off = buf * kVTileBytes + kb * 32 * kRowBytes;
+    const int off = (kByPairs ? buf % kVBufs : buf) * kVTileBytes + kb * 32 * kRowBytes;
 #pragma unroll
     for (int dt = 0; dt < kDTiles; ++dt) ring[dt] = X::load_v(vx, off, dt);
     settle_reference(s, key0, std::true_type{});
@@ -543,6 +556,65 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   // Tile `tile` begins: the copy of the next one has landed everywhere (the scores run a block ahead), the buffer of the
   // one before is free and takes tile + kAhead, whose ids were loaded a tile ago.
   int buf = 0;
+  // Pair rows: what the waves that copy do.  When tile t begins, K of tile t + 2 and V of tile t have landed everywhere, and the
+  // buffers of tile t - 1 are free: they take K of tile t + 5 and V of tile t + 2.
+  auto copy_pair_tiles = [&]() __attribute__((always_inline)) {
+    auto ids_of = [&](int tile) __attribute__((always_inline)) {
+      const int lp = tile * (kTileKeys / kPageTokens) + fetch_wave;
+      return (int)btc[lp < last_page ? lp : last_page];
+    };
+    // one half of a tile's copies: K or V
+    auto fetch_half = [&](const char* base, const uint32_t (&src)[X::kPageChunks], uint32_t tiles_at, int tile, int id) __attribute__((always_inline)) {
+      const uint32_t dst = smem_base + tiles_at + fetch_wave * kPageHeadBytes;
+      const int64_t page_off = (int64_t)id * page_stride;
+      if ((tile + 1) * kTileKeys <= L) {
+        dma16_page<false>(base + page_off, src, dst);
+      } else {
+#pragma unroll
+        for (int i = 0; i < X::kPageChunks; ++i) {           // (see fetch)
+          const int row = fetch_wave * kPageTokens + i * X::kChunkRows + lane / X::kGran;
+          const bool in_seq = tile * kTileKeys + row < L;
+          dma16(base + (in_seq ? page_off + i * 1024 + src[i] : first_page_off + (src[i] & (kRowBytes - 1))), dst + i * 1024);
+        }
+      }
+    };
+    auto fetch_k = [&](int tile, int b, int id) __attribute__((always_inline)) {
+      if (tile < n_tiles) fetch_half(kbase, k_src, b * kKTileBytes, tile, id);
+    };
+    auto fetch_v = [&](int tile, int b, int id) __attribute__((always_inline)) {
+      if (tile < n_tiles) fetch_half(vbase, v_src, kVBase + b * kVTileBytes, tile, id);
+    };
+    int id[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) id[i] = ids_of(t_lo + i);
+    fetch_k(t_lo, 0, id[0]);
+    fetch_v(t_lo, 0, id[0]);
+    fetch_k(t_lo + 1, 1, id[1]);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    fetch_k(t_lo + 2, 2, id[2]);
+    fetch_v(t_lo + 1, 1, id[1]);
+    fetch_k(t_lo + 3, 3, id[3]);
+    fetch_k(t_lo + 4, 4, id[4]);
+    int v_id = id[2], id_3 = id[3], id_4 = id[4], k_id = id[5], k_buf = 5, v_buf = 2;
+    for (int tile = t_lo; tile < n_tiles; ++tile) {
+      const int next_id = ids_of(tile + 6);
+      // enqueued last: K of tile + 4 and V of tile + 1, as far as there are such tiles (at the start K of the tiles before, too)
+      constexpr int kHalf = X::kPageChunks;
+      if (tile + 4 < n_tiles) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * kHalf);
+      else if (tile + 1 < n_tiles) __builtin_amdgcn_s_waitcnt(0x0F70 | kHalf);
+      else __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+      fetch_k(tile + 5, k_buf, k_id);
+      fetch_v(tile + 2, v_buf, v_id);
+      v_id = id_3;
+      id_3 = id_4;
+      id_4 = k_id;
+      k_id = next_id;
+      k_buf = k_buf == kKBufs - 1 ? 0 : k_buf + 1;
+      v_buf = v_buf == kVBufs - 1 ? 0 : v_buf + 1;
+    }
+  };
   auto copy_sync = [&](int tile) __attribute__((always_inline)) {
     const bool ahead = tile + kAhead < n_tiles;
     if (ahead) load_ids(tile + kAhead + 1);
@@ -559,7 +631,13 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
     if constexpr (ROWS == kFullRows) copy_sync(tile);
     else __syncthreads();
   };
-  if constexpr (ROWS == kFewRows) {
+  if constexpr (kByPairs) {
+    if (fetcher) {
+      copy_pair_tiles();
+      return;
+    }
+    __syncthreads();
+  } else if constexpr (ROWS == kFewRows) {
     if (fetcher) {
       first_copies();
       for (int tile = t_lo; tile < n_tiles; ++tile) {
@@ -577,7 +655,8 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
   scores_of(0, 0, s_next);
   if (tile < n_plain) {
     settle_reference(s_next, 0, std::false_type{});
-    load_k_ring(0, 1);
+    if constexpr (kByPairs) load_k_ring(1, 0);
+    else load_k_ring(0, 1);
 #pragma unroll
     for (int e = 0; e < 8; ++e) s_next.set(e, __builtin_amdgcn_exp2f(__builtin_fmaf(s_next.get(e), c, -m_ref[0])));
 #pragma unroll
@@ -586,10 +665,20 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
     // (few rows: the waves that would be late only copy.  The compiler is not told: with the barrier unconditional the
     // phases become one basic block, in which it keeps 28 registers too many alive and spills 52.)
     int w = wave_u;
-    if constexpr (ROWS == kFewRows) asm volatile("" : "+s"(w));
+    if constexpr (ROWS != kFullRows) asm volatile("" : "+s"(w));
     const bool late_barrier = w >= kFetchWaves;
     auto pipelined_tile = [&](auto buf_tag) __attribute__((always_inline)) {
       constexpr int b = decltype(buf_tag)::value, bn = (b + 1) % kBufs;
+      if constexpr (kByPairs) {
+        buf = b;
+        if (!late_barrier) tile_sync(tile);
+        phase_a(b, 0);
+        if (late_barrier) tile_sync(tile);
+        phase_b((b + 2) % kKBufs, 0);
+        buf = (b + 1) % kKBufs;
+        ++tile;
+        return;
+      }
       buf = b;
       if (!late_barrier) tile_sync(tile);
       phase_a(b, 0);
@@ -611,20 +700,54 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
       pipelined_tile(std::integral_constant<int, 1>{});
       if (tile >= n_plain) break;
       pipelined_tile(std::integral_constant<int, 2>{});
-      if constexpr (kBufs == 4) {
+      if constexpr (kKBufs >= 4) {
         if (tile >= n_plain) break;
         pipelined_tile(std::integral_constant<int, 3>{});
+      }
+      if constexpr (kKBufs == 6) {
+        if (tile >= n_plain) break;
+        pipelined_tile(std::integral_constant<int, 4>{});
+        if (tile >= n_plain) break;
+        pipelined_tile(std::integral_constant<int, 5>{});
       }
     }
   }
   bool have_scores = n_plain <= t_lo;
   for (; tile < n_tiles; ++tile) {
-    const int buf_next = buf == kBufs - 1 ? 0 : buf + 1;
+    const int buf_next = buf == kKBufs - 1 ? 0 : buf + 1;
     tile_sync(tile);
-    plain_block(buf, 0, tile * kTileKeys, s_next, have_scores);
+    plain_block(buf, 0, tile * kTileKeys + key_half * 32, s_next, have_scores);
     have_scores = false;
-    plain_block(buf, 1, tile * kTileKeys + 32, s_next, false);
+    if constexpr (!kByPairs) plain_block(buf, 1, tile * kTileKeys + 32, s_next, false);
     buf = buf_next;
+  }
+
+  // ---- pair rows: the other pair's references, sums and outputs of the same rows, lane by lane through LDS
+  if constexpr (kByPairs) {
+    constexpr int kLaneB = (kDTiles * 2 + 1) * 16;           // bytes of a lane: its output, and (m, l) of both row tiles
+    static_assert(2 * 64 * kLaneB <= sizeof(smem), "room for two waves");
+    char* const mine = smem + row_wave_u * (64 * kLaneB) + lane * 16;
+    __syncthreads();                                         // (the tiles are done with)
+    if (key_half == 1) {
+#pragma unroll
+      for (int dt = 0; dt < kDTiles; ++dt)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) *reinterpret_cast<acc4*>(mine + (2 * dt + rt) * 1024) = o[dt][rt];
+      *reinterpret_cast<acc4*>(mine + 2 * kDTiles * 1024) = acc4{m_run[0], l_acc[0][0], m_run[1], l_acc[1][0]};
+    }
+    __syncthreads();
+    if (key_half == 1) return;
+    const acc4 other = *reinterpret_cast<const acc4*>(mine + 2 * kDTiles * 1024);
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      const float top = fmaxf(m_run[rt], other[2 * rt]), ref = top == -INFINITY ? 0.f : top;
+      const float here = __builtin_amdgcn_exp2f(m_run[rt] - ref), there = __builtin_amdgcn_exp2f(other[2 * rt] - ref);
+      m_run[rt] = top;
+      l_acc[rt][0] = l_acc[rt][0] * here + other[2 * rt + 1] * there;
+#pragma unroll
+      for (int dt = 0; dt < kDTiles; ++dt)
+        o[dt][rt] = o[dt][rt] * here + *reinterpret_cast<const acc4*>(mine + (2 * dt + rt) * 1024) * there;
+    }
   }
 
   // ---- epilogue: normalise, round, store; a lane holds 4 consecutive columns per (dt, rt)
@@ -664,7 +787,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs& a, const Work& wo
 template <int D, Rows ROWS, bool SPLIT>
 __global__ __launch_bounds__(kWaves * 64) void attn_prefill_bf16_kernel(const AttnArgs a) {
   const Work work = work_of<ROWS>(a, blockIdx.x);
-  if (ROWS == kFewRows && work.row0 >= work.chunk * a.G) return;      // a second half without rows
+  if (ROWS != kFullRows && work.row0 >= work.chunk * a.G) return;     // a second half (later quarter) without rows
   attn_bf16_body<D, ROWS, SPLIT ? kSlices : kWhole>(a, work);
 }
 
@@ -677,8 +800,9 @@ __global__ __launch_bounds__(kWaves * 64) void attn_prefill_bf16_classes_kernel(
 
 template <int D, Rows ROWS>
 static void enqueue_list(const AttnArgs& args, hipStream_t stream) {
-  const int wgs = args.n_items << args.halves;
-  if (args.kv_splits > 0) attn_prefill_bf16_kernel<D, ROWS, true><<<wgs, kWaves * 64, 0, stream>>>(args);
+  const int wgs = ROWS == kPairRows ? args.n_items * (kAttnTileRows / kAttnPairRows) : args.n_items << args.halves;
+  if constexpr (ROWS == kPairRows) attn_prefill_bf16_kernel<D, ROWS, false><<<wgs, kWaves * 64, 0, stream>>>(args);
+  else if (args.kv_splits > 0) attn_prefill_bf16_kernel<D, ROWS, true><<<wgs, kWaves * 64, 0, stream>>>(args);
   else attn_prefill_bf16_kernel<D, ROWS, false><<<wgs, kWaves * 64, 0, stream>>>(args);
 }
 template <int D, Rows ROWS>
@@ -688,8 +812,10 @@ static void enqueue_classes(const AttnArgs& args, const AttnClasses& t, hipStrea
 
 hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, hipStream_t stream) {
   (void)hipGetLastError();
-  const bool few = t.rows == kAttnFewRows;
-  if (args.head_dim == 128) few ? enqueue_classes<128, kFewRows>(args, t, stream) : enqueue_classes<128, kFullRows>(args, t, stream);
+  const bool few = t.rows == kAttnFewRows, pairs = t.rows == kAttnPairRows;
+  if (pairs && args.head_dim == 128) enqueue_classes<128, kPairRows>(args, t, stream);
+  else if (pairs && args.head_dim == 64) enqueue_classes<64, kPairRows>(args, t, stream);
+  else if (args.head_dim == 128) few ? enqueue_classes<128, kFewRows>(args, t, stream) : enqueue_classes<128, kFullRows>(args, t, stream);
   else if (args.head_dim == 64) few ? enqueue_classes<64, kFewRows>(args, t, stream) : enqueue_classes<64, kFullRows>(args, t, stream);
   else return hipErrorInvalidValue;
   return hipGetLastError();
@@ -697,7 +823,9 @@ hipError_t launch_attn_bf16_classes(const AttnArgs& args, const AttnClasses& t, 
 
 hipError_t launch_attn_bf16(const AttnArgs& args, hipStream_t stream) {
   (void)hipGetLastError();   // drop any stale error of earlier, unrelated runtime calls
-  if (args.head_dim == 128) args.few_rows ? enqueue_list<128, kFewRows>(args, stream) : enqueue_list<128, kFullRows>(args, stream);
+  if (args.pair_rows && args.head_dim == 128) enqueue_list<128, kPairRows>(args, stream);
+  else if (args.pair_rows && args.head_dim == 64) enqueue_list<64, kPairRows>(args, stream);
+  else if (args.head_dim == 128) args.few_rows ? enqueue_list<128, kFewRows>(args, stream) : enqueue_list<128, kFullRows>(args, stream);
   else if (args.head_dim == 64) args.few_rows ? enqueue_list<64, kFewRows>(args, stream) : enqueue_list<64, kFullRows>(args, stream);
   else return hipErrorInvalidValue;
   return hipGetLastError();

@@ -181,6 +181,7 @@ int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int
                   int32_t kv_splits, int64_t n_items) {
   ClassPlan plan;
   const bool planned = kv_splits == 0 && plan_classes(p, prefix_lens, new_lens, batch, 0, &plan);
+  if (planned && plan.classes.rows == kAttnPairRows) return kListPairs;
   if (planned && plan.narrow_wgs > 0) return few_rows(p, new_lens, batch, kAttnLeastRows) ? kListNarrowLeast : kListNarrow;
   if (few_rows(p, new_lens, batch, kAttnFewRows))
     return reads_once(p, prefix_lens, new_lens, batch, kAttnFewRows) ? kListFewOnce : kListFew;
@@ -289,12 +290,13 @@ struct FormCost {
   double launch, fixed, tile, merge, part_mb;
 };
 FormCost form_cost_of(const mc_attn_params* p, int64_t tile_rows) {
-  const int form = tile_rows == kAttnTileRows ? 0 : tile_rows == kAttnFewRows ? 1 : tile_rows == kAttnNarrowRows ? 2 : 3;
-  static constexpr FormCost kF32[4] = {{0, 9, 7.0, 3, 0.36}, {0, 8.4, 3.8, 2.6, 0.36}, {}, {0, 4.2, 0.58, 4.1, 0.22}};
-  static constexpr FormCost kBf16[4] = {{1, 4, 1.37, 3, 0.25}, {2.1, 5.5, 0.72, 2, 0.31}, {0, 4.65, 0.315, 4.6, 0.5},
-                                        {0, 4.0, 0.29, 4.4, 0.4}};
-  static constexpr FormCost kBf16D64[4] = {{1, 1, 0.94, 5, 0.25}, {1.5, 4.2, 0.55, 2.6, 0.44}, {0, 4.2, 0.21, 3.9, 0.1},
-                                           {0, 3.8, 0.18, 3.8, 0.1}};
+  const int form = tile_rows == kAttnTileRows ? 0 : tile_rows == kAttnFewRows ? 1 : tile_rows == kAttnNarrowRows ? 2
+                   : tile_rows == kAttnLeastRows ? 3 : 4;
+  static constexpr FormCost kF32[5] = {{0, 9, 7.0, 3, 0.36}, {0, 8.4, 3.8, 2.6, 0.36}, {}, {0, 4.2, 0.58, 4.1, 0.22}, {}};
+  static constexpr FormCost kBf16[5] = {{1, 4, 1.37, 3, 0.25}, {2.1, 5.5, 0.72, 2, 0.31}, {0, 4.65, 0.315, 4.6, 0.5},
+                                        {0, 4.0, 0.29, 4.4, 0.4}, {2.1, 4.6, 0.44, 0, 0}};
+  static constexpr FormCost kBf16D64[5] = {{1, 1, 0.94, 5, 0.25}, {1.5, 4.2, 0.55, 2.6, 0.44}, {0, 4.2, 0.21, 3.9, 0.1},
+                                           {0, 3.8, 0.18, 3.8, 0.1}, {1.5, 3.2, 0.36, 0, 0}};
   return (p->dtype == MC_DTYPE_F32 ? kF32 : p->head_dim == 128 ? kBf16 : kBf16D64)[form];
 }
 // K and V bytes per microsecond: the most any form reads, and what the narrow one's time grows by beyond what the caches hold
@@ -303,6 +305,17 @@ constexpr double kReadPerUs = 6.2e6, kNarrowReadPerUs = 5.8e6, kNarrowMissPerUs 
 // Launches of more narrow workgroups than this are not worth weighing: the other forms fill the chip (of 20 random launches of
 // more the estimate chose, the narrow form won 13 by 17 % on average and lost 7 by up to 20 %).
 constexpr int64_t kMostNarrow = 3 * kComputeUnits;
+
+// The same for 64-row workgroups (bf16), and how much sooner they have to end than what they are weighed against, by where the
+// workgroups of the list really go; more than two rounds of them, where full row tiles do better than estimated, by more.  260
+// random lists (64/8 to 4/1 heads, 60-900 workgroups): of the 106 for which the plain estimate is sooner 14 got slower (425 -> 519
+// us the worst: 240 workgroups and as many short of rows, nine on some of the queues of eight units); of the 86 taken so one did,
+// by 3 %, and they run x1.43 faster, the others 4 % slower.
+constexpr int64_t kMostPairs = 3 * kComputeUnits;
+constexpr double kPairSlack = 1.03, kPairRoundsSlack = 1.15;
+// Fewer key tiles (2560 keys) are left to 128-row workgroups, which are tested there; they would gain a few microseconds a launch
+// (64/8 heads, P 600, C 200 17.7 / 12.9).
+constexpr int64_t kLeastPairTiles = 40;
 
 // How much sooner the narrow form has to end than a cut, and than anything if it takes more than one round (the estimate's
 // errors), and if its rounds walk more keys than the XCDs' caches hold, at paces of their own (12/3 heads, C 1210 behind 32143:
@@ -408,6 +421,30 @@ class Queues {
   int next_ = 0;
   double end_ = 0.0;
 };
+// The same for the 64-row workgroups of a list, in the order that its launch has them (work_of in attn_device.h).
+double pairs_really_end(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                        const FormCost& cost) {
+  constexpr int kParts = kAttnTileRows / kAttnPairRows;
+  const int64_t G = p->num_q_heads / p->num_kv_heads;
+  std::vector<AttnReq> reqs;
+  std::vector<AttnItem> items;
+  build_work_list(p, prefix_lens, new_lens, batch, 0, reqs, items);
+  const size_t n = items.size(), rest = n % kXcds, even = n - rest;
+  Queues queues;
+  auto place = [&](const AttnItem& item, int part) {
+    const AttnReq& rq = reqs[(size_t)item.req];
+    const int64_t row0 = item.row0 + part * kAttnPairRows;
+    const bool empty = row0 >= rq.chunk * G;
+    const int64_t tok_last = std::min<int64_t>(rq.chunk - 1, (row0 + kAttnPairRows - 1) / G);
+    queues.place(1, empty ? 1.0 : cost.fixed + cost.tile * (double)((rq.prefix + tok_last + kAttnTileKeys) / kAttnTileKeys));
+  };
+  for (size_t at = 0; at < even; at += kXcds)
+    for (int part = 0; part < kParts; ++part)
+      for (size_t i = at; i < at + kXcds; ++i) place(items[i], part);
+  for (int part = 0; part < kParts; ++part)
+    for (size_t i = even; i < n; ++i) place(items[i], part);
+  return cost.launch + queues.end();
+}
 // how much sooner the plain cut has to end to be taken instead
 constexpr double kPlainSlack = 1.02;
 
@@ -594,7 +631,8 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   plan->narrow_wgs = 0;
   plan->narrow_pieces = 1;
   const int64_t narrow_items = items_of(narrow_rows);
-  if (narrow_items <= kMostNarrow) {
+  const bool by_pairs = p->dtype == MC_DTYPE_BF16 && narrow_rows == kAttnNarrowRows && items_of(kAttnPairRows) <= kMostPairs;
+  if (narrow_items <= kMostNarrow || by_pairs) {
     auto place = [&](Units& units, const Run& run, int64_t cut, int64_t tile_rows, const FormCost& cost, double limit) {
       const Active& a = act[run.active];
       const int64_t step = (run.tile_hi - run.tile_lo) / 16 + 1;
@@ -626,7 +664,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
     const double missed = std::max(0.0, bytes - kNarrowHeld) / kNarrowMissPerUs;
     const int64_t room = keep_room ? max_part_rows : part_rows;
     // (a row tile of one key tile is one block for each of two waves: the 128-row form has that done as soon)
-    const bool may = longest > 1 && bytes / kNarrowReadPerUs < end && (p->dtype != MC_DTYPE_F32 || longest_piece <= kNarrowTilesF32);
+    const bool may = narrow_items <= kMostNarrow && longest > 1 && bytes / kNarrowReadPerUs < end && (p->dtype != MC_DTYPE_F32 || longest_piece <= kNarrowTilesF32);
     n_runs = 0;
     double work = 0.0;
     for (int i = 0; i < n && may; ++i) {
@@ -679,6 +717,22 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         plan->narrow_pieces = std::max<int32_t>(plan->narrow_pieces, (int32_t)cut);
       }
       plan->narrow_wgs = (int32_t)wg;
+    }
+    // 64-row workgroups, all rows whole, beside that.
+    if (by_pairs && longest >= kLeastPairTiles) {
+      const FormCost pairs = form_cost_of(p, kAttnPairRows);
+      const double slack = items_of(kAttnPairRows) > 2 * kComputeUnits ? kPairRoundsSlack : kPairSlack, by = end / slack - pairs.launch;
+      Units units;
+      bool sooner = bytes / kReadPerUs < by;
+      lay_out(items_of(kAttnPairRows), kAttnPairRows);
+      for (int i = 0; i < n_runs && sooner; ++i) sooner = place(units, runs[i], 1, kAttnPairRows, pairs, by);
+      if (sooner && pairs_really_end(p, prefix_lens, new_lens, batch, pairs) * slack < end) {
+        best_rows = kAttnPairRows;
+        best_whole = items_of(kAttnPairRows);
+        best_of = 0;
+        plan->narrow_wgs = 0;
+        plan->narrow_pieces = 1;
+      }
     }
   }
   const int uncut = lay_out(best_whole, best_rows);

@@ -59,12 +59,12 @@ bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, i
 bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
 
 // How a list of n_items workgroups is launched, kept in a plan: as row tiles of 256 rows (0), by workgroups of 128 rows, one
-// per item or two, or by those of the narrow form, as many per item as it may have rows for, or one of the
+// per item or two, by workgroups of 64 rows, four per item, or by those of the narrow form, as many per item as it may have rows for, or one of the
 // fewest rows (kListNarrowLeast: no item has more).  Marks that no caller's own zeroed or filled struct holds by accident: a
 // list of longer row tiles launched one workgroup per item would leave rows out.
 constexpr int32_t kListFew = 0x4d434631, kListFewOnce = 0x4d434632, kListHalves = 0x4d434633, kListNarrow = 0x4d434634,
-                  kListNarrowLeast = 0x4d434635;
-// (items of a plan that is launched so: their workgroups have to be counted with 32 bits)
+                  kListNarrowLeast = 0x4d434635, kListPairs = 0x4d434636;
+// (items of a plan that is launched narrow or by pairs: their workgroups have to be counted with 32 bits)
 constexpr int32_t kMostNarrowItems = INT32_MAX / (kAttnTileRows / kAttnLeastRows);
 int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                   int32_t kv_splits, int64_t n_items);

@@ -247,6 +247,7 @@ mc_status launch_planned_attn(const mc_attn_params* p, const mc_attn_plan* plan,
   args.halves = plan->reserved == kListHalves;
   args.few_rows = args.halves || plan->reserved == kListFew || plan->reserved == kListFewOnce;
   args.once = plan->reserved == kListFewOnce;
+  args.pair_rows = plan->reserved == kListPairs && p->dtype == MC_DTYPE_BF16 && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
   args.kv_splits = plan->kv_splits;
   args.rows_total = plan->total_new_tokens * p->num_q_heads;
   args.o_parts = o_parts;

@@ -23,6 +23,7 @@ struct AttnArgs {
   int32_t n_items;
   int32_t few_rows;    // list launches: 128-row workgroups, one per item (no item has more rows) or two (halves)
   int32_t halves;
+  int32_t pair_rows;   // list launches (bf16): 64-row workgroups, four per item
   int32_t once;        // list launches: as AttnClasses::once
   // split launches (kv_splits > 0): partial results go to o_parts [kv_splits, rows_total, D] fp32 and
   // lse_parts [kv_splits, rows_total] instead of out / lse

@@ -68,6 +68,8 @@ constexpr int kShortHashBlocks = 32;
 constexpr int kAttnTileRows = 256;
 // ... and of the form for launches whose row tiles are few or short: 4 waves compute (one per SIMD), 4 copy tiles
 constexpr int kAttnFewRows = 128;
+// ... and of the one between that and the narrow form: the waves that compute are two pairs, each for every other 32 keys (bf16)
+constexpr int kAttnPairRows = 64;
 // ... and of the narrow form, whose waves share out keys instead of rows (attn_narrow.hip): bf16, or fp32 and bf16 where no
 // request has more rows
 constexpr int kAttnNarrowRows = 32, kAttnLeastRows = 16;
