@@ -197,11 +197,17 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
     args.max_pages = max_pages_per_req;
     args.head_dim = p->head_dim;
     args.scale_log2e = attn_scale_log2e(p);
-    args.n_items = plan.narrow_wgs > 0 ? plan.narrow_wgs : plan.n_wgs;
     const hipStream_t on = reinterpret_cast<hipStream_t>(hip_stream);
-    const hipError_t launched =
-        plan.narrow_wgs > 0 ? launch_attn_narrow(p->dtype, args, plan.narrow.rows, 1, narrow_shares(p, plan.narrow_wgs), &plan.narrow, on)
-                            : launch_attn_classes(p->dtype, args, plan.classes, on);
+    auto launch = [&](const ClassPlan& of) {
+      args.n_items = of.narrow_wgs > 0 ? of.narrow_wgs : of.n_wgs;
+      return of.narrow_wgs > 0
+                 ? launch_attn_narrow(p->dtype, args, of.narrow.rows, 1, narrow_shares(p, of.narrow_wgs), &of.narrow, on)
+                 : launch_attn_classes(p->dtype, args, of.classes, on);
+    };
+    ApartPlan apart;
+    const bool two = plan_apart(p, prefix_lens, new_lens, batch, plan, &apart);
+    hipError_t launched = launch(two ? apart.few : plan);
+    if (two && launched == hipSuccess) launched = launch(apart.many);
     return launched == hipSuccess ? MC_OK : MC_ERR_HIP;
   }
 

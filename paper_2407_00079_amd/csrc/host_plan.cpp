@@ -482,7 +482,7 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 // placing ends where the best does (same plans; host time of a call of 63 requests, 8/1 heads, C up to 300: 219 us with every
 // trial placed, 20 now; of 63 one-token requests 41 and 16; of one to three requests 1 us of planning).
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                  int64_t max_part_rows, ClassPlan* plan, bool keep_room) {
+                  int64_t max_part_rows, ClassPlan* plan, bool keep_room, const int32_t* placed) {
   const int64_t G = p->num_q_heads / p->num_kv_heads, Hkv = p->num_kv_heads;
   struct Active {
     int32_t req, q_off, prefix, chunk;
@@ -494,7 +494,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       if (n == kMaxAttnClasses - 1) return false;      // one request may take two classes
       act[n++] = {r, (int32_t)q_off, prefix_lens[r], new_lens[r]};
     }
-    q_off += new_lens[r];
+    q_off += (placed != nullptr ? placed : new_lens)[r];
   }
   auto items_of = [&](int64_t tile_rows) {
     int64_t items = 0;
@@ -632,7 +632,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   plan->narrow_pieces = 1;
   const int64_t narrow_items = items_of(narrow_rows);
   const bool by_pairs = p->dtype == MC_DTYPE_BF16 && narrow_rows == kAttnNarrowRows && items_of(kAttnPairRows) <= kMostPairs;
-  if (narrow_items <= kMostNarrow || by_pairs) {
+  {
     auto place = [&](Units& units, const Run& run, int64_t cut, int64_t tile_rows, const FormCost& cost, double limit) {
       const Active& a = act[run.active];
       const int64_t step = (run.tile_hi - run.tile_lo) / 16 + 1;
@@ -726,7 +726,9 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       bool sooner = bytes / kReadPerUs < by;
       lay_out(items_of(kAttnPairRows), kAttnPairRows);
       for (int i = 0; i < n_runs && sooner; ++i) sooner = place(units, runs[i], 1, kAttnPairRows, pairs, by);
-      if (sooner && pairs_really_end(p, prefix_lens, new_lens, batch, pairs) * slack < end) {
+      const double really = sooner ? pairs_really_end(p, prefix_lens, new_lens, batch, pairs) : end;
+      if (really * slack < end) {
+        end = really;
         best_rows = kAttnPairRows;
         best_whole = items_of(kAttnPairRows);
         best_of = 0;
@@ -734,6 +736,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
         plan->narrow_pieces = 1;
       }
     }
+    plan->ends = end;
   }
   const int uncut = lay_out(best_whole, best_rows);
   AttnClasses& t = plan->classes;
@@ -761,6 +764,87 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
   }
   plan->n_wgs = (int32_t)wg;
   return true;
+}
+
+// Requests of few rows behind long prefixes beside requests of many rows: in one form either the former walk their keys at the pace
+// of a 128- or 256-row workgroup or the latter are too many narrow workgroups.  One launch behind the other, the line between
+// them at a power of two of new tokens.
+// Planned, us, one launch / two: 64/8 heads, P 6000 and 0, C 3 and 900 72 / 60; P 19657, 31 and 50, C 2, 2 and 829 213 / 149;
+// P 51199 and 647, C 7 and 1187 552 / 335; fp32, 16/16 heads, P 3900, 0, 40, C 3, 900, 5 243 / 99.
+// What both launches take at least, by the longest row tile of either and the work of the second, says which line is tried; it is
+// planned only if that is sooner than one launch, which most batches end at.
+// Where the line lies, by 66 random batches that the plain estimate divides: a first launch of more than one round of workgroups (5
+// of 7 got slower, 196 -> 267 us the worst), one whose row tiles share keys that the XCDs' caches do not hold (12/3 heads, C 664
+// behind 27003 211 -> 319), and full row tiles in several rounds, which do better than estimated (261 -> 298, 157 -> 187).
+// Of 22 others by these rules with a slack of 1.1, 20 run x1.0-2.1 and two x0.96, both within 15 % by the estimate.
+constexpr double kApartLeast = 40.0, kApartSecond = 3.0, kApartSlack = 1.15, kApartRoundsSlack = 1.35, kApartMiss = 1.5;
+bool plan_apart(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, const ClassPlan& one,
+                ApartPlan* apart) {
+  if (one.ends < kApartLeast) return false;
+  const int64_t G = p->num_q_heads / p->num_kv_heads;
+  const FormCost full = form_cost_of(p, kAttnTileRows), half = form_cost_of(p, kAttnFewRows),
+                 pairs = form_cost_of(p, p->dtype == MC_DTYPE_BF16 ? kAttnPairRows : kAttnFewRows),
+                 narrow = form_cost_of(p, kAttnLeastRows);
+  const bool rounds = one.narrow_wgs == 0 && one.classes.rows == kAttnTileRows && one.n_wgs > kComputeUnits;
+  const double limit = one.ends / (rounds ? kApartRoundsSlack : kApartSlack) - kApartSecond;
+  double best = limit;
+  int32_t line = 0, most = 0;
+  for (int32_t r = 0; r < batch; ++r) most = std::max(most, new_lens[r]);
+  for (int64_t at = 1; at < most; at *= 2) {
+    int64_t few_longest = 0, few_items = 0, many_longest = 0;
+    double many_work = 0.0;
+    for (int32_t r = 0; r < batch; ++r) {
+      if (new_lens[r] == 0) continue;
+      const int64_t tiles = ((int64_t)prefix_lens[r] + new_lens[r] + kAttnTileKeys - 1) / kAttnTileKeys, rows = new_lens[r] * G;
+      if (new_lens[r] <= at) {
+        few_longest = std::max(few_longest, tiles);
+        few_items += (rows + kAttnNarrowRows - 1) / kAttnNarrowRows * p->num_kv_heads;
+      } else {
+        many_longest = std::max(many_longest, tiles);
+        many_work += (double)(rows * p->num_kv_heads) / kAttnTileRows * full.tile *
+                     ((double)prefix_lens[r] + 0.5 * (double)new_lens[r]) / kAttnTileKeys;
+      }
+    }
+    if (few_items == 0 || few_items > kComputeUnits) continue;
+    const double least = narrow.fixed + narrow.tile * (double)few_longest + pairs.fixed +
+                         std::max(std::min(pairs.tile, half.tile) * (double)many_longest, many_work / kComputeUnits);
+    if (least >= best) continue;
+    best = least;
+    line = (int32_t)at;
+  }
+  if (line == 0) return false;
+  apart->few_lens.assign(new_lens, new_lens + batch);
+  apart->many_lens.assign(new_lens, new_lens + batch);
+  for (int32_t r = 0; r < batch; ++r) (new_lens[r] <= line ? apart->many_lens : apart->few_lens)[(size_t)r] = 0;
+  if (!plan_classes(p, prefix_lens, apart->few_lens.data(), batch, 0, &apart->few, false, new_lens)) return false;
+  const ClassPlan& few = apart->few;
+  std::vector<int32_t> several = apart->few_lens;          // requests of several row tiles a head
+  for (int32_t& c : several) c = c * G > few.narrow.rows ? c : 0;
+  const bool miss = few.narrow_wgs > 0 && kv_bytes(p, prefix_lens, several.data(), batch) > kXcdCaches;
+  const double few_ends = few.ends * (miss ? kApartMiss : 1.0);
+  return few.narrow_wgs > 0 && few.narrow_wgs <= kComputeUnits && few_ends < limit &&
+         plan_classes(p, prefix_lens, apart->many_lens.data(), batch, 0, &apart->many, false, new_lens) &&
+         apart->many.narrow_wgs == 0 && few_ends + apart->many.ends < limit;
+}
+
+int32_t apart_list(const mc_attn_params* p, const int32_t* prefix_lens, const ApartPlan& apart, int32_t batch,
+                   std::vector<AttnItem>& items) {
+  std::vector<AttnReq> reqs;
+  std::vector<AttnItem> behind;
+  build_work_list(p, prefix_lens, apart.few_lens.data(), batch, 0, reqs, items);
+  build_work_list(p, prefix_lens, apart.many_lens.data(), batch, 0, reqs, behind);
+  const int32_t n_few = (int32_t)items.size();
+  items.insert(items.end(), behind.begin(), behind.end());
+  const int32_t form = apart.many.classes.rows == kAttnPairRows ? kListPairs
+                       : few_rows(p, apart.many_lens.data(), batch, kAttnFewRows)
+                           ? (reads_once(p, prefix_lens, apart.many_lens.data(), batch, kAttnFewRows) ? kListFewOnce : kListFew)
+                       : apart.many.classes.rows == kAttnFewRows ? kListHalves : 0;
+  ApartMark mark;
+  mark.n_few = n_few;
+  mark.least = apart.few.narrow.rows == kAttnLeastRows;
+  mark.shares = narrow_shares(p, apart.few.narrow_wgs);
+  mark.form = form;
+  return mark.packed();
 }
 
 bool auto_layout(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,

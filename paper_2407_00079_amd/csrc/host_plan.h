@@ -64,6 +64,7 @@ bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32
 // list of longer row tiles launched one workgroup per item would leave rows out.
 constexpr int32_t kListFew = 0x4d434631, kListFewOnce = 0x4d434632, kListHalves = 0x4d434633, kListNarrow = 0x4d434634,
                   kListNarrowLeast = 0x4d434635, kListPairs = 0x4d434636;
+constexpr int32_t kListApart = 0x4d44;        // upper half of the mark of a list of two launches (ApartMark)
 // (items of a plan that is launched narrow or by pairs: their workgroups have to be counted with 32 bits)
 constexpr int32_t kMostNarrowItems = INT32_MAX / (kAttnTileRows / kAttnLeastRows);
 int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
@@ -96,9 +97,45 @@ struct ClassPlan {
   int32_t n_wgs;          // workgroups of the attention launch
   int32_t most_pieces;    // 1: nothing is cut, no partial results, no merge
   int64_t part_rows;      // rows of partial results
+  double ends;            // us, by the estimate
 };
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                  int64_t max_part_rows, ClassPlan* plan, bool keep_room = false);
+                  int64_t max_part_rows, ClassPlan* plan, bool keep_room = false, const int32_t* placed = nullptr);
+// (`placed`: the new tokens of every request in q and out, where new_lens leaves some requests out.)
+
+// Whole rows as two launches: the requests of few rows by the narrow form, then the others by a form of theirs.  false: one
+// launch (`one`, whole rows) is as soon.  A prepared list holds the items of the first launch, then those of the second
+// (apart_list, which returns the mark of such a list); calls without room for partial results launch the same two by classes, so
+// that both compute the same bits.
+struct ApartPlan {
+  std::vector<int32_t> few_lens, many_lens;     // new tokens of every request in the first and in the second launch
+  ClassPlan few, many;
+};
+bool plan_apart(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, const ClassPlan& one,
+                ApartPlan* apart);
+int32_t apart_list(const mc_attn_params* p, const int32_t* prefix_lens, const ApartPlan& apart, int32_t batch,
+                   std::vector<AttnItem>& items);
+struct ApartMark {
+  int32_t n_few, shares;                        // items of the first launch, workgroups a row tile
+  bool least;                                   // 16-row workgroups there
+  int32_t form;                                 // of the second
+  static constexpr int32_t kForms[5] = {0, kListFew, kListFewOnce, kListHalves, kListPairs};
+  int32_t packed() const {
+    int32_t at = 0;
+    while (kForms[at] != form) ++at;
+    return kListApart << 16 | at << 13 | (int32_t)least << 12 | (shares >> 1) << 10 | n_few;
+  }
+  // false: another mark, or one that does not fit a list of n_items
+  bool unpack(int32_t mark, int32_t n_items) {
+    const int32_t at = mark >> 13 & 7, share = mark >> 10 & 3;
+    if (mark >> 16 != kListApart || at >= 5 || share == 3) return false;
+    n_few = mark & 1023;
+    shares = share == 0 ? 1 : 2 * share;
+    least = (mark >> 12 & 1) != 0;
+    form = kForms[at];
+    return n_few > 0 && n_few < n_items;
+  }
+};
 
 // Workspace of the automatic form: [work list + request table | o_parts | lse_parts], each part
 // starting at a multiple of 256 bytes.  The partial results have room for kv_splits parts of every row (kv_splits > 1)

@@ -193,6 +193,12 @@ mc_status prepare_attn(const mc_attn_params* p, const int32_t* prefix_lens, cons
   std::vector<mc::AttnReq> reqs;
   std::vector<mc::AttnItem> items;
   build_work_list(p, prefix_lens, new_lens, batch, split ? kv_splits : 0, reqs, items);
+  ApartPlan apart;
+  ClassPlan one;
+  const bool two = !split && plan_classes(p, prefix_lens, new_lens, batch, 0, &one) &&
+                   plan_apart(p, prefix_lens, new_lens, batch, one, &apart);
+  const int32_t form = two ? apart_list(p, prefix_lens, apart, batch, items)
+                           : list_form(p, prefix_lens, new_lens, batch, split ? kv_splits : 0, (int64_t)items.size());
   const size_t n_items = items.size();
 
   // one pinned, asynchronous copy of work list + request table
@@ -219,7 +225,7 @@ mc_status prepare_attn(const mc_attn_params* p, const int32_t* prefix_lens, cons
   plan->num_q_heads = p->num_q_heads;
   plan->num_kv_heads = p->num_kv_heads;
   plan->dtype = (int32_t)p->dtype;
-  plan->reserved = list_form(p, prefix_lens, new_lens, batch, plan->kv_splits, plan->n_items);
+  plan->reserved = form;
   return MC_OK;
 }
 
@@ -244,14 +250,27 @@ mc_status launch_planned_attn(const mc_attn_params* p, const mc_attn_plan* plan,
   args.head_dim = p->head_dim;
   args.scale_log2e = attn_scale_log2e(p);
   args.n_items = plan->n_items;
-  args.halves = plan->reserved == kListHalves;
-  args.few_rows = args.halves || plan->reserved == kListFew || plan->reserved == kListFewOnce;
-  args.once = plan->reserved == kListFewOnce;
-  args.pair_rows = plan->reserved == kListPairs && p->dtype == MC_DTYPE_BF16 && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
+  // a list of two launches: its first items by the narrow form, the rest as its mark says
+  ApartMark apart;
+  const bool two = plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems && apart.unpack(plan->reserved, plan->n_items);
+  const int32_t form = two ? apart.form : plan->reserved;
+  args.halves = form == kListHalves;
+  args.few_rows = args.halves || form == kListFew || form == kListFewOnce;
+  args.once = form == kListFewOnce;
+  args.pair_rows = form == kListPairs && p->dtype == MC_DTYPE_BF16 && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
   args.kv_splits = plan->kv_splits;
   args.rows_total = plan->total_new_tokens * p->num_q_heads;
   args.o_parts = o_parts;
   args.lse_parts = lse_parts;
+  if (two) {
+    const int rows = apart.least ? mc::kAttnLeastRows : mc::kAttnNarrowRows;
+    args.n_items = apart.n_few;
+    const int parts = apart.least && p->dtype == MC_DTYPE_BF16 ? 1 : mc::kAttnTileRows / rows;
+    if (mc::launch_attn_narrow(p->dtype, args, rows, parts, apart.shares, nullptr, stream) != hipSuccess) return MC_ERR_HIP;
+    args.items += apart.n_few;
+    args.n_items = plan->n_items - apart.n_few;
+    return mc::launch_attn(p->dtype, args, stream) == hipSuccess ? MC_OK : MC_ERR_HIP;
+  }
   const bool least = plan->reserved == kListNarrowLeast;
   const bool narrow = (plan->reserved == kListNarrow || least) && plan->kv_splits == 0 && plan->n_items <= kMostNarrowItems;
   const int rows = least || p->dtype == MC_DTYPE_F32 ? mc::kAttnLeastRows : mc::kAttnNarrowRows;
@@ -348,6 +367,15 @@ mc_status attn_one_shot(const mc_attn_params* p, const void* q, const void* k_po
   char* ws = reinterpret_cast<char*>(workspace);
   float* o_parts = reinterpret_cast<float*>(ws + lay.o_off);
   float* lse_parts = reinterpret_cast<float*>(ws + lay.lse_off);
+  ApartPlan apart;
+  if (lay.by_classes && (lay.plan.narrow_wgs > 0 ? lay.plan.narrow_pieces : lay.plan.most_pieces) == 1 &&
+      plan_apart(p, prefix_lens, new_lens, batch, lay.plan, &apart)) {
+    st = launch_class_plan(p, apart.few, q, k_pool, v_pool, block_tables, max_pages_per_req, out, lse, nullptr, nullptr,
+                           reinterpret_cast<hipStream_t>(hip_stream));
+    if (st != MC_OK) return st;
+    return launch_class_plan(p, apart.many, q, k_pool, v_pool, block_tables, max_pages_per_req, out, lse, nullptr, nullptr,
+                             reinterpret_cast<hipStream_t>(hip_stream));
+  }
   if (lay.by_classes)
     return launch_class_plan(p, lay.plan, q, k_pool, v_pool, block_tables, max_pages_per_req, out, lse, o_parts,
                              lse_parts, reinterpret_cast<hipStream_t>(hip_stream));
