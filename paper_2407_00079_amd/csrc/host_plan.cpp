@@ -818,12 +818,12 @@ bool plan_apart(const mc_attn_params* p, const int32_t* prefix_lens, const int32
   for (int32_t r = 0; r < batch; ++r) (new_lens[r] <= line ? apart->many_lens : apart->few_lens)[(size_t)r] = 0;
   if (!plan_classes(p, prefix_lens, apart->few_lens.data(), batch, 0, &apart->few, false, new_lens)) return false;
   const ClassPlan& few = apart->few;
+  if (few.narrow_wgs == 0 || few.narrow_wgs > kComputeUnits) return false;      // (0: `narrow` has not been written)
   std::vector<int32_t> several = apart->few_lens;          // requests of several row tiles a head
   for (int32_t& c : several) c = c * G > few.narrow.rows ? c : 0;
-  const bool miss = few.narrow_wgs > 0 && kv_bytes(p, prefix_lens, several.data(), batch) > kXcdCaches;
+  const bool miss = kv_bytes(p, prefix_lens, several.data(), batch) > kXcdCaches;
   const double few_ends = few.ends * (miss ? kApartMiss : 1.0);
-  return few.narrow_wgs > 0 && few.narrow_wgs <= kComputeUnits && few_ends < limit &&
-         plan_classes(p, prefix_lens, apart->many_lens.data(), batch, 0, &apart->many, false, new_lens) &&
+  return few_ends < limit && plan_classes(p, prefix_lens, apart->many_lens.data(), batch, 0, &apart->many, false, new_lens) &&
          apart->many.narrow_wgs == 0 && few_ends + apart->many.ends < limit;
 }
 
