@@ -76,7 +76,7 @@ mc_status check_list_range(const mc_attn_params* p, int32_t batch, int64_t total
   return MC_OK;
 }
 
-void build_work_list(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+void build_work_list(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
                      int32_t kv_splits, std::vector<AttnReq>& reqs, std::vector<AttnItem>& items) {
   const bool split = kv_splits > 0;
   const int G = p->num_q_heads / p->num_kv_heads;
@@ -91,7 +91,7 @@ void build_work_list(const mc_attn_params* p, const int32_t* prefix_lens, const 
   for (int32_t r = 0; r < batch; ++r) {
     const int32_t P = prefix_lens[r], C = new_lens[r];
     reqs[(size_t)r] = {(int32_t)q_off, P, C, (int32_t)(((int64_t)P + C + p->page_size - 1) / p->page_size)};
-    q_off += C;
+    q_off += new_lens.of[r];
     const int64_t n_rows = (int64_t)C * G;
     for (int32_t g = 0; g < p->num_kv_heads; ++g)
       for (int64_t row0 = 0; row0 < n_rows; row0 += rows) {
@@ -140,14 +140,14 @@ int64_t count_items(const mc_attn_params* p, const int32_t* new_lens, int32_t ba
   return n;
 }
 
-bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, int64_t tile_rows) {
+bool few_rows(const mc_attn_params* p, NewLens new_lens, int32_t batch, int64_t tile_rows) {
   const int64_t G = p->num_q_heads / p->num_kv_heads;
   for (int32_t r = 0; r < batch; ++r)
     if (new_lens[r] * G > tile_rows) return false;
   return true;
 }
 
-int64_t kv_bytes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch) {
+int64_t kv_bytes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch) {
   int64_t keys = 0;
   for (int32_t r = 0; r < batch; ++r)
     if (new_lens[r] > 0) keys += (int64_t)prefix_lens[r] + new_lens[r];
@@ -162,7 +162,7 @@ int64_t kv_bytes(const mc_attn_params* p, const int32_t* prefix_lens, const int3
 // Requests may share pages, which the host does not see: they are counted as if they were apart.  Those that do read them at
 // about the same time and find them in the caches either way: 16 requests on one 16k document 127 / 128, 32 on 8k 121 / 121,
 // 8 on 32k 129 / 129, 2 on 128k 148 / 149; the one clear loss of the shapes tried is 32 on 32k with 8/1 heads, 71.6 / 73.5.
-bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
                 int64_t tile_rows) {
   constexpr int64_t kLastLevelBytes = (int64_t)256 << 20;
   return few_rows(p, new_lens, batch, tile_rows) && kv_bytes(p, prefix_lens, new_lens, batch) > kLastLevelBytes;
@@ -422,7 +422,7 @@ class Queues {
   double end_ = 0.0;
 };
 // The same for the 64-row workgroups of a list, in the order that its launch has them (work_of in attn_device.h).
-double pairs_really_end(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+double pairs_really_end(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
                         const FormCost& cost) {
   constexpr int kParts = kAttnTileRows / kAttnPairRows;
   const int64_t G = p->num_q_heads / p->num_kv_heads;
@@ -481,8 +481,8 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 // Every one-shot call pays for the search on the host, so a trial that the work alone puts behind the best is not placed, and
 // placing ends where the best does (same plans; host time of a call of 63 requests, 8/1 heads, C up to 300: 219 us with every
 // trial placed, 20 now; of 63 one-token requests 41 and 16; of one to three requests 1 us of planning).
-bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                  int64_t max_part_rows, ClassPlan* plan, bool keep_room, const int32_t* placed) {
+bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
+                  int64_t max_part_rows, ClassPlan* plan, bool keep_room) {
   const int64_t G = p->num_q_heads / p->num_kv_heads, Hkv = p->num_kv_heads;
   struct Active {
     int32_t req, q_off, prefix, chunk;
@@ -494,7 +494,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       if (n == kMaxAttnClasses - 1) return false;      // one request may take two classes
       act[n++] = {r, (int32_t)q_off, prefix_lens[r], new_lens[r]};
     }
-    q_off += (placed != nullptr ? placed : new_lens)[r];
+    q_off += new_lens.of[r];
   }
   auto items_of = [&](int64_t tile_rows) {
     int64_t items = 0;
@@ -612,7 +612,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int
       return queues.end() + merge;
     };
     const double end = really_ends(best_whole, best_rows, best_of, best_k, HUGE_VAL) / kPlainSlack;
-    const int32_t plain = suggest_kv_splits(p, prefix_lens, new_lens, batch);
+    const int32_t plain = suggest_kv_splits(p, prefix_lens, new_lens.of, batch);      // (a cut is of all requests)
     lay_out(0, kAttnTileRows);
     int64_t longest = 0;
     for (int i = 0; i < n_runs; ++i) longest = std::max(longest, runs[i].longest);
@@ -813,31 +813,31 @@ bool plan_apart(const mc_attn_params* p, const int32_t* prefix_lens, const int32
     line = (int32_t)at;
   }
   if (line == 0) return false;
-  apart->few_lens.assign(new_lens, new_lens + batch);
-  apart->many_lens.assign(new_lens, new_lens + batch);
-  for (int32_t r = 0; r < batch; ++r) (new_lens[r] <= line ? apart->many_lens : apart->few_lens)[(size_t)r] = 0;
-  if (!plan_classes(p, prefix_lens, apart->few_lens.data(), batch, 0, &apart->few, false, new_lens)) return false;
+  apart->line = line;
+  const NewLens few_lens(new_lens, 0, line), many_lens(new_lens, line, INT32_MAX);
+  if (!plan_classes(p, prefix_lens, few_lens, batch, 0, &apart->few)) return false;
   const ClassPlan& few = apart->few;
   if (few.narrow_wgs == 0 || few.narrow_wgs > kComputeUnits) return false;      // (0: `narrow` has not been written)
-  std::vector<int32_t> several = apart->few_lens;          // requests of several row tiles a head
-  for (int32_t& c : several) c = c * G > few.narrow.rows ? c : 0;
-  const bool miss = kv_bytes(p, prefix_lens, several.data(), batch) > kXcdCaches;
+  const int32_t one_tile = (int32_t)std::min<int64_t>(few.narrow.rows / G, line);
+  const NewLens several(new_lens, one_tile, line);         // requests of several row tiles a head
+  const bool miss = kv_bytes(p, prefix_lens, several, batch) > kXcdCaches;
   const double few_ends = few.ends * (miss ? kApartMiss : 1.0);
-  return few_ends < limit && plan_classes(p, prefix_lens, apart->many_lens.data(), batch, 0, &apart->many, false, new_lens) &&
-         apart->many.narrow_wgs == 0 && few_ends + apart->many.ends < limit;
+  return few_ends < limit && plan_classes(p, prefix_lens, many_lens, batch, 0, &apart->many) && apart->many.narrow_wgs == 0 &&
+         few_ends + apart->many.ends < limit;
 }
 
-int32_t apart_list(const mc_attn_params* p, const int32_t* prefix_lens, const ApartPlan& apart, int32_t batch,
-                   std::vector<AttnItem>& items) {
+int32_t apart_list(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, const ApartPlan& apart,
+                   int32_t batch, std::vector<AttnItem>& items) {
+  const NewLens few_lens(new_lens, 0, apart.line), many_lens(new_lens, apart.line, INT32_MAX);
   std::vector<AttnReq> reqs;
   std::vector<AttnItem> behind;
-  build_work_list(p, prefix_lens, apart.few_lens.data(), batch, 0, reqs, items);
-  build_work_list(p, prefix_lens, apart.many_lens.data(), batch, 0, reqs, behind);
+  build_work_list(p, prefix_lens, few_lens, batch, 0, reqs, items);
+  build_work_list(p, prefix_lens, many_lens, batch, 0, reqs, behind);
   const int32_t n_few = (int32_t)items.size();
   items.insert(items.end(), behind.begin(), behind.end());
   const int32_t form = apart.many.classes.rows == kAttnPairRows ? kListPairs
-                       : few_rows(p, apart.many_lens.data(), batch, kAttnFewRows)
-                           ? (reads_once(p, prefix_lens, apart.many_lens.data(), batch, kAttnFewRows) ? kListFewOnce : kListFew)
+                       : few_rows(p, many_lens, batch, kAttnFewRows)
+                           ? (reads_once(p, prefix_lens, many_lens, batch, kAttnFewRows) ? kListFewOnce : kListFew)
                        : apart.many.classes.rows == kAttnFewRows ? kListHalves : 0;
   ApartMark mark;
   mark.n_few = n_few;

@@ -43,11 +43,21 @@ mc_status check_attn_buffers(bool split, const void* q, const void* k_pool, cons
 // sizes that must hold before a work list is built: row and item counts the kernels index with 32 bits
 mc_status check_list_range(const mc_attn_params* p, int32_t batch, int64_t total_new, int32_t kv_splits);
 
+// New tokens that the requests of a batch bring to a launch: all of them, or (a batch that is two launches) those of the requests
+// with more than `above` and at most `most`, while q and out hold the rows of all.
+struct NewLens {
+  const int32_t* of;                  // [batch]
+  int32_t above, most;
+  NewLens(const int32_t* all) : NewLens(all, 0, INT32_MAX) {}
+  NewLens(const int32_t* all, int32_t above, int32_t most) : of(all), above(above), most(most) {}
+  int32_t operator[](int32_t r) const { return of[r] > above && of[r] <= most ? of[r] : 0; }
+};
+
 // Work list of an attention launch: one item per (request, KV head, tile of stacked rows) and, for
 // split launches (kv_splits >= 1), per key slice - most keys first, dealt round-robin so that
 // consecutive workgroup ids (which land on different XCDs) take different (request, KV head)
 // streams and each XCD's L2 keeps one stream hot.  Lengths have been validated by the caller.
-void build_work_list(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+void build_work_list(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
                      int32_t kv_splits, std::vector<AttnReq>& reqs, std::vector<AttnItem>& items);
 
 // number of whole-row work items of a batch (the size of the list build_work_list makes for kv_splits == 0)
@@ -55,8 +65,8 @@ int64_t count_items(const mc_attn_params* p, const int32_t* new_lens, int32_t ba
 
 // Every request's stacked rows of a KV head fit one row tile; and then, whether the K and V rows the requests read outgrow
 // the last-level cache.
-bool few_rows(const mc_attn_params* p, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
-bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, int64_t tile_rows);
+bool few_rows(const mc_attn_params* p, NewLens new_lens, int32_t batch, int64_t tile_rows);
+bool reads_once(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch, int64_t tile_rows);
 
 // How a list of n_items workgroups is launched, kept in a plan: as row tiles of 256 rows (0), by workgroups of 128 rows, one
 // per item or two, by workgroups of 64 rows, four per item, or by those of the narrow form, as many per item as it may have rows for, or one of the
@@ -99,22 +109,21 @@ struct ClassPlan {
   int64_t part_rows;      // rows of partial results
   double ends;            // us, by the estimate
 };
-bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
-                  int64_t max_part_rows, ClassPlan* plan, bool keep_room = false, const int32_t* placed = nullptr);
-// (`placed`: the new tokens of every request in q and out, where new_lens leaves some requests out.)
+bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
+                  int64_t max_part_rows, ClassPlan* plan, bool keep_room = false);
 
 // Whole rows as two launches: the requests of few rows by the narrow form, then the others by a form of theirs.  false: one
 // launch (`one`, whole rows) is as soon.  A prepared list holds the items of the first launch, then those of the second
 // (apart_list, which returns the mark of such a list); calls without room for partial results launch the same two by classes, so
 // that both compute the same bits.
 struct ApartPlan {
-  std::vector<int32_t> few_lens, many_lens;     // new tokens of every request in the first and in the second launch
+  int32_t line;           // most new tokens of a request of the first launch
   ClassPlan few, many;
 };
 bool plan_apart(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, const ClassPlan& one,
                 ApartPlan* apart);
-int32_t apart_list(const mc_attn_params* p, const int32_t* prefix_lens, const ApartPlan& apart, int32_t batch,
-                   std::vector<AttnItem>& items);
+int32_t apart_list(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, const ApartPlan& apart,
+                   int32_t batch, std::vector<AttnItem>& items);
 struct ApartMark {
   int32_t n_few, shares;                        // items of the first launch, workgroups a row tile
   bool least;                                   // 16-row workgroups there

@@ -1,10 +1,25 @@
 // Plans each batch read from stdin as a call without room for partial results does (plan_classes, then plan_apart); one line a
-// batch: "none" (more requests than classes), "one" or "two" launches.
+// batch: "none" (more requests than classes), "one" or "two" launches, and the allocations on the host heap that both planning
+// functions made.
 // input:  Hq Hkv D dtype batch P... C...
 #include <cstdio>
+#include <cstdlib>
+#include <new>
 #include <vector>
 
 #include "host_plan.h"
+
+static long news = 0;
+#ifdef COUNT_NEWS            // (MemorySanitizer has its own)
+void* operator new(size_t bytes) {
+  ++news;
+  void* p = std::malloc(bytes);
+  if (p == nullptr) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+#endif
 
 int main() {
   int Hq, Hkv, D, dtype, batch;
@@ -17,11 +32,11 @@ int main() {
     const mc_attn_params p{Hq, Hkv, D, 16, 1 << 20, dtype, 0.f};
     mc::host::ClassPlan one;
     mc::host::ApartPlan apart;
-    if (!mc::host::plan_classes(&p, P.data(), C.data(), batch, 0, &one)) {
-      std::puts("none");
-      continue;
-    }
-    std::puts(mc::host::plan_apart(&p, P.data(), C.data(), batch, one, &apart) ? "two" : "one");
+    const long before = news;
+    const bool planned = mc::host::plan_classes(&p, P.data(), C.data(), batch, 0, &one);
+    const long by_classes = news - before;
+    const bool two = planned && mc::host::plan_apart(&p, P.data(), C.data(), batch, one, &apart);
+    std::printf("%s %ld %ld\n", !planned ? "none" : two ? "two" : "one", by_classes, news - before - by_classes);
   }
   return 0;
 }

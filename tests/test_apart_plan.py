@@ -31,7 +31,7 @@ def ask(exe, batches):
     text = "".join(" ".join(str(x) for x in [*b[:4], len(b[4]), *b[4], *b[5]]) + "\n" for b in batches)
     res = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0 and res.stderr == "", res.stderr[-2000:]
-    out = res.stdout.splitlines()
+    out = [line.split() for line in res.stdout.splitlines()]
     assert len(out) == len(batches)
     return out
 
@@ -41,5 +41,15 @@ def test_no_choice_reads_what_no_plan_has_written(tmp_path):
     """A first launch whose plan is not narrow has no narrow classes to look at."""
     exe = build(tmp_path, "-O0", "-g", "-fsanitize=memory", cxx=CLANG)
     rng = random.Random(5)
-    out = ask(exe, [draw(rng) for _ in range(1500)])
-    assert out.count("two") > 20 and out.count("one") > 20
+    launches = [what for what, *_ in ask(exe, [draw(rng) for _ in range(1500)])]
+    assert launches.count("two") > 20 and launches.count("one") > 20
+
+
+def test_the_choice_of_two_launches_uses_no_heap(tmp_path):
+    """mc_prefill_attn_paged_noalloc plans with these functions and promises to allocate nothing, on the host heap either."""
+    rng = random.Random(6)
+    # one launch by the narrow or a wide form, or two: no batch here weighs 64-row workgroups
+    batches = [b for b in (draw(rng) for _ in range(6000)) if b[3] == 1] + [(64, 8, 128, 0, [6000, 0], [3, 900])]
+    out = ask(build(tmp_path, "-O2", "-DCOUNT_NEWS"), batches)
+    assert sum(what == "two" for what, *_ in out) > 20
+    assert [b for b, (_, _, by_apart) in zip(batches, out) if by_apart != "0"] == []
