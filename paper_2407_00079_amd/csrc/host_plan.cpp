@@ -334,6 +334,11 @@ double merge_time(const mc_attn_params* p, int64_t part_rows) {
   return part_rows > 0 ? kMergeFixed + 2.0 * (double)part_rows * (double)(p->head_dim + 1) * 4.0 / kPartBytesPerUs : 0.0;
 }
 
+// A request with new tokens.
+struct Active {
+  int32_t req, q_off, prefix, chunk;
+};
+
 // A set of row tiles of one request: `items` workgroups if uncut, of `shortest` to `longest` key tiles.
 struct Run {
   int active;               // which of the requests with new tokens, in launch order
@@ -402,47 +407,113 @@ class Units {
 // 236 of 430: 1761 / 1760 / 1388; 256 and 236: 1391 / 1390 / 1385; 354 of 290 instead of 236: 1520 / 1519 / 1506.)
 class Queues {
  public:
+  static constexpr int kQueues = 32;
   // n workgroups next in launch order
   void place(int64_t n, double dur) {
     for (; n > 0; --n) {
-      double* t = t_[next_];
+      place_on(next_, dur);
       next_ = (next_ + 1) % kQueues;
-      int at = 0;
-      for (int u = 1; u < kUnits; ++u) at = t[u] < t[at] ? u : at;
-      t[at] += dur;
-      end_ = t[at] > end_ ? t[at] : end_;
     }
+  }
+  // a workgroup of which the launch order says that it goes to this queue
+  void place_on(int queue, double dur) {
+    double* t = t_[queue];
+    int at = 0;
+    for (int u = 1; u < kUnits; ++u) at = t[u] < t[at] ? u : at;
+    t[at] += dur;
+    end_ = t[at] > end_ ? t[at] : end_;
   }
   double end() const { return end_; }
 
  private:
-  static constexpr int kQueues = 32, kUnits = (int)kComputeUnits / kQueues;
+  static constexpr int kUnits = (int)kComputeUnits / kQueues;
   double t_[kQueues][kUnits] = {{0.0}};
   int next_ = 0;
   double end_ = 0.0;
 };
-// The same for the 64-row workgroups of a list, in the order that its launch has them (work_of in attn_device.h).
-double pairs_really_end(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
-                        const FormCost& cost) {
+// The same for the 64-row workgroups of a list (build_work_list), in the order that its launch has them (work_of in attn_device.h);
+// `limit`: as late as that or later.  The list is not made for that: its row tiles, in the order that all its eight lanes have
+// them, and where each lane is among them say which item comes next.  Where the heads fill the lanes evenly one XCD goes for all
+// of them.  (Planning whole rows, 64/8 heads, P 8192, C 192: 3.1 us with the list built and sorted, 0.9 so.)
+double pairs_really_end(const mc_attn_params* p, const Active* act, int n, const FormCost& cost, double limit) {
   constexpr int kParts = kAttnTileRows / kAttnPairRows;
   const int64_t G = p->num_q_heads / p->num_kv_heads;
-  std::vector<AttnReq> reqs;
-  std::vector<AttnItem> items;
-  build_work_list(p, prefix_lens, new_lens, batch, 0, reqs, items);
-  const size_t n = items.size(), rest = n % kXcds, even = n - rest;
-  Queues queues;
-  auto place = [&](const AttnItem& item, int part) {
-    const AttnReq& rq = reqs[(size_t)item.req];
-    const int64_t row0 = item.row0 + part * kAttnPairRows;
-    const bool empty = row0 >= rq.chunk * G;
-    const int64_t tok_last = std::min<int64_t>(rq.chunk - 1, (row0 + kAttnPairRows - 1) / G);
-    queues.place(1, empty ? 1.0 : cost.fixed + cost.tile * (double)((rq.prefix + tok_last + kAttnTileKeys) / kAttnTileKeys));
+  const int32_t Hkv = p->num_kv_heads;
+  // row tiles, most keys first, of the same keys that of the earlier request, and the time of each quarter's workgroup
+  struct Next {
+    int64_t keys;
+    const Active* of;
+    int64_t row_tile;
+  } next[kMaxAttnClasses];
+  struct Tile {
+    int32_t req;
+    double us[kParts];
+  } tiles[kMostPairs];
+  auto later = [](const Next& a, const Next& b) { return a.keys != b.keys ? a.keys < b.keys : a.of->req > b.of->req; };
+  auto last_token = [&](const Active& a, int64_t row) { return std::min<int64_t>(a.chunk - 1, row / G); };
+  auto tile_of = [&](const Active& a, int64_t t) {
+    return Next{a.prefix + last_token(a, t * kAttnTileRows + kAttnTileRows - 1) + 1, &a, t};
   };
-  for (size_t at = 0; at < even; at += kXcds)
+  int32_t n_tiles = 0;
+  for (int i = 0; i < n; ++i) next[i] = tile_of(act[i], (act[i].chunk * G - 1) / kAttnTileRows);
+  std::make_heap(next, next + n, later);
+  for (int left = n; left > 0;) {
+    std::pop_heap(next, next + left, later);
+    const Active& a = *next[left - 1].of;
+    const int64_t t = next[left - 1].row_tile;
+    Tile& tile = tiles[n_tiles++];
+    tile.req = a.req;
+    for (int part = 0; part < kParts; ++part) {
+      const int64_t row0 = t * kAttnTileRows + part * kAttnPairRows;
+      const int64_t keys = a.prefix + last_token(a, row0 + kAttnPairRows - 1) + 1;
+      tile.us[part] = row0 >= a.chunk * G ? 1.0 : cost.fixed + cost.tile * (double)((keys + kAttnTileKeys - 1) / kAttnTileKeys);
+    }
+    if (t > 0) {
+      next[left - 1] = tile_of(a, t - 1);
+      std::push_heap(next, next + left, later);
+    } else {
+      --left;
+    }
+  }
+  // the items of a tile in a lane: as many as the request has heads there
+  const bool even = Hkv % kXcds == 0;
+  auto heads_in = [&](const Tile& tile, int lane) {
+    if (even) return Hkv / kXcds;
+    const int first = (int)(((int64_t)lane - (int64_t)tile.req * Hkv % kXcds + kXcds) % kXcds);
+    return Hkv > first ? (Hkv - first - 1) / kXcds + 1 : 0;
+  };
+  struct Lane {
+    int32_t at, heads;                // its next item's tile, and the items of that tile that are left
+  } lanes[kXcds];
+  auto settle = [&](int lane) {
+    while (lanes[lane].heads == 0 && ++lanes[lane].at < n_tiles) lanes[lane].heads = heads_in(tiles[lanes[lane].at], lane);
+  };
+  for (int x = 0; x < kXcds; ++x) {
+    lanes[x] = {-1, 0};
+    settle(x);
+  }
+  Queues queues;
+  int lane = 0;
+  for (;;) {
+    // the next eight items, from the lanes in turn; fewer at the end.  A part of them is a row of workgroups on consecutive queues.
+    const Tile* items[kXcds];
+    int n_items = 0;
+    for (int empty = 0; n_items < (even ? 1 : kXcds) && empty < kXcds; lane = even ? 0 : (lane + 1) % kXcds) {
+      Lane& l = lanes[lane];
+      if (l.at >= n_tiles) {
+        ++empty;
+        continue;
+      }
+      empty = 0;
+      items[n_items++] = &tiles[l.at];
+      --l.heads;
+      settle(lane);
+    }
+    if (n_items == 0) break;
     for (int part = 0; part < kParts; ++part)
-      for (size_t i = at; i < at + kXcds; ++i) place(items[i], part);
-  for (int part = 0; part < kParts; ++part)
-    for (size_t i = even; i < n; ++i) place(items[i], part);
+      for (int i = 0; i < n_items; ++i) queues.place_on(part * (even ? kXcds : n_items) + i, items[i]->us[part]);
+    if (cost.launch + queues.end() >= limit) return limit;
+  }
   return cost.launch + queues.end();
 }
 // how much sooner the plain cut has to end to be taken instead
@@ -484,9 +555,7 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
                   int64_t max_part_rows, ClassPlan* plan, bool keep_room) {
   const int64_t G = p->num_q_heads / p->num_kv_heads, Hkv = p->num_kv_heads;
-  struct Active {
-    int32_t req, q_off, prefix, chunk;
-  } act[kMaxAttnClasses];
+  Active act[kMaxAttnClasses];
   int n = 0;
   int64_t q_off = 0;
   for (int32_t r = 0; r < batch; ++r) {
@@ -721,13 +790,13 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
     // 64-row workgroups, all rows whole, beside that.
     if (by_pairs && longest >= kLeastPairTiles) {
       const FormCost pairs = form_cost_of(p, kAttnPairRows);
-      const double slack = items_of(kAttnPairRows) > 2 * kComputeUnits ? kPairRoundsSlack : kPairSlack, by = end / slack - pairs.launch;
+      const double limit = end / (items_of(kAttnPairRows) > 2 * kComputeUnits ? kPairRoundsSlack : kPairSlack), by = limit - pairs.launch;
       Units units;
       bool sooner = bytes / kReadPerUs < by;
       lay_out(items_of(kAttnPairRows), kAttnPairRows);
       for (int i = 0; i < n_runs && sooner; ++i) sooner = place(units, runs[i], 1, kAttnPairRows, pairs, by);
-      const double really = sooner ? pairs_really_end(p, prefix_lens, new_lens, batch, pairs) : end;
-      if (really * slack < end) {
+      const double really = sooner ? pairs_really_end(p, act, n, pairs, limit) : limit;
+      if (really < limit) {
         end = really;
         best_rows = kAttnPairRows;
         best_whole = items_of(kAttnPairRows);

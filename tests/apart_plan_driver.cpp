@@ -1,6 +1,6 @@
 // Plans each batch read from stdin as a call without room for partial results does (plan_classes, then plan_apart); one line a
-// batch: "none" (more requests than classes), "one" or "two" launches, and the allocations on the host heap that both planning
-// functions made.
+// batch: "none" (more requests than classes), "one" or "two" launches, the allocations on the host heap that both planning functions
+// made, and of one launch the rows of its workgroups (0: narrow) and its estimated end in microseconds.
 // input:  Hq Hkv D dtype batch P... C...
 #include <cstdio>
 #include <cstdlib>
@@ -36,7 +36,8 @@ int main() {
     const bool planned = mc::host::plan_classes(&p, P.data(), C.data(), batch, 0, &one);
     const long by_classes = news - before;
     const bool two = planned && mc::host::plan_apart(&p, P.data(), C.data(), batch, one, &apart);
-    std::printf("%s %ld %ld\n", !planned ? "none" : two ? "two" : "one", by_classes, news - before - by_classes);
+    std::printf("%s %ld %ld", !planned ? "none" : two ? "two" : "one", by_classes, news - before - by_classes);
+    std::printf(" %d %.9g\n", planned && one.narrow_wgs == 0 ? one.classes.rows : 0, planned ? one.ends : 0.0);
   }
   return 0;
 }

@@ -5,6 +5,9 @@ import subprocess
 
 import pytest
 
+from paper_2407_00079_amd import binding as B
+from test_class_plan import launch_end
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2407_00079_amd", "csrc")
 CLANG = "/opt/rocm/llvm/bin/clang++"
@@ -45,11 +48,40 @@ def test_no_choice_reads_what_no_plan_has_written(tmp_path):
     assert launches.count("two") > 20 and launches.count("one") > 20
 
 
-def test_the_choice_of_two_launches_uses_no_heap(tmp_path):
+def test_planning_uses_no_heap(tmp_path):
     """mc_prefill_attn_paged_noalloc plans with these functions and promises to allocate nothing, on the host heap either."""
     rng = random.Random(6)
-    # one launch by the narrow or a wide form, or two: no batch here weighs 64-row workgroups
-    batches = [b for b in (draw(rng) for _ in range(6000)) if b[3] == 1] + [(64, 8, 128, 0, [6000, 0], [3, 900])]
+    batches = [draw(rng) for _ in range(3000)] + [(64, 8, 128, 0, [6000, 0], [3, 900]), (64, 8, 128, 0, [8192], [192])]
     out = ask(build(tmp_path, "-O2", "-DCOUNT_NEWS"), batches)
-    assert sum(what == "two" for what, *_ in out) > 20
-    assert [b for b, (_, _, by_apart) in zip(batches, out) if by_apart != "0"] == []
+    assert sum(what == "two" for what, *_ in out) > 20 and sum(rows == "64" for *_, rows, _ in out) > 20
+    assert [b for b, (_, by_classes, by_apart, *_) in zip(batches, out) if (by_classes, by_apart) != ("0", "0")] == []
+
+
+def pairs_end(Hq, Hkv, D, dtype, prefix, new):
+    """End of a launch of 64-row workgroups, the quarters of eight items of the list after the other, each quarter's workgroups
+    where they go."""
+    launch, fixed, tile = (2.1, 4.6, 0.44) if D == 128 else (1.5, 3.2, 0.36)
+    G = Hq // Hkv
+    items = B.mc_prefill_attn_plan(B.attn_params(Hq, Hkv, D, 16, 1 << 20, "bf16"), prefix, new, 0)
+    rest = len(items) % 8
+    order = [(items[at + i], part) for at in range(0, len(items) - rest, 8) for part in range(4) for i in range(8)]
+    order += [(item, part) for part in range(4) for item in items[len(items) - rest:]]
+
+    def us(item, part):
+        row0 = item[2] + 64 * part
+        P, C = prefix[item[0]], new[item[0]]
+        return fixed + tile * -(-(P + min(C - 1, (row0 + 63) // G) + 1) // 64) if row0 < C * G else 1.0
+    return launch + launch_end([us(*w) for w in order])
+
+
+def test_64_row_workgroups_are_weighed_by_where_those_of_the_list_go(tmp_path):
+    """Heads that fill the eight lists evenly and heads that do not, requests with the same keys, requests without new tokens."""
+    rng = random.Random(8)
+    batches = [(*rng.choice([h for h in HEADS if h[3] == 0] + [(40, 40, 128, 0), (4, 1, 64, 0), (24, 8, 128, 0)]),
+                [rng.choice((2600, 9000, rng.randrange(30000))) for _ in range(n)], [rng.choice((0, 200, rng.randint(1, 900))) for _ in range(n)])
+               for n in (rng.choice((1, 2, 3, 6)) for _ in range(1200))]
+    out = ask(build(tmp_path, "-O2"), batches)
+    pairs = [(b, float(ends)) for b, (*_, rows, ends) in zip(batches, out) if rows == "64"]
+    assert len(pairs) > 150 and {b[1] for b, _ in pairs} >= {8, 2, 3, 1}
+    for b, ends in pairs:
+        assert ends == pytest.approx(pairs_end(*b), rel=1e-6), b
