@@ -797,6 +797,8 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
       for (int i = 0; i < n_runs && sooner; ++i) sooner = place(units, runs[i], 1, kAttnPairRows, pairs, by);
       const double really = sooner ? pairs_really_end(p, act, n, pairs, limit) : limit;
       if (really < limit) {
+        // (sooner than a cut: whether also than other whole rows, is what a call without room weighs)
+        if (part_rows > 0 || plan->narrow_pieces > 1) return plan_classes(p, prefix_lens, new_lens, batch, 0, plan);
         end = really;
         best_rows = kAttnPairRows;
         best_whole = items_of(kAttnPairRows);

@@ -1,9 +1,11 @@
 // Plans each batch read from stdin as a call without room for partial results does (plan_classes, then plan_apart); one line a
 // batch: "none" (more requests than classes), "one" or "two" launches, the allocations on the host heap that both planning functions
-// made, and of one launch the rows of its workgroups (0: narrow) and its estimated end in microseconds.
+// made, and of one launch the rows of its workgroups (0: narrow) and its estimated end in microseconds;
+// then the same rows of a call with room for partial results (-1: it cuts some), and whether it is that launch.
 // input:  Hq Hkv D dtype batch P... C...
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <new>
 #include <vector>
 
@@ -37,7 +39,15 @@ int main() {
     const long by_classes = news - before;
     const bool two = planned && mc::host::plan_apart(&p, P.data(), C.data(), batch, one, &apart);
     std::printf("%s %ld %ld", !planned ? "none" : two ? "two" : "one", by_classes, news - before - by_classes);
-    std::printf(" %d %.9g\n", planned && one.narrow_wgs == 0 ? one.classes.rows : 0, planned ? one.ends : 0.0);
+    std::printf(" %d %.9g", planned && one.narrow_wgs == 0 ? one.classes.rows : 0, planned ? one.ends : 0.0);
+    mc::host::AutoLayout lay;
+    mc::host::auto_layout(&p, P.data(), C.data(), batch, &lay);
+    const mc::host::ClassPlan& roomy = lay.plan;
+    const bool whole = planned && lay.by_classes && (roomy.narrow_wgs > 0 ? roomy.narrow_pieces : roomy.most_pieces) == 1;
+    const bool same = whole && roomy.narrow_wgs == one.narrow_wgs && roomy.ends == one.ends &&
+                      (one.narrow_wgs > 0 ? std::memcmp(&roomy.narrow, &one.narrow, sizeof one.narrow) == 0
+                                          : std::memcmp(&roomy.classes, &one.classes, sizeof one.classes) == 0);
+    std::printf(" %d %d\n", !whole ? -1 : roomy.narrow_wgs > 0 ? 0 : roomy.classes.rows, same);
   }
   return 0;
 }

@@ -53,7 +53,7 @@ def test_planning_uses_no_heap(tmp_path):
     rng = random.Random(6)
     batches = [draw(rng) for _ in range(3000)] + [(64, 8, 128, 0, [6000, 0], [3, 900]), (64, 8, 128, 0, [8192], [192])]
     out = ask(build(tmp_path, "-O2", "-DCOUNT_NEWS"), batches)
-    assert sum(what == "two" for what, *_ in out) > 20 and sum(rows == "64" for *_, rows, _ in out) > 20
+    assert sum(what == "two" for what, *_ in out) > 20 and sum(line[3] == "64" for line in out) > 20
     assert [b for b, (_, by_classes, by_apart, *_) in zip(batches, out) if (by_classes, by_apart) != ("0", "0")] == []
 
 
@@ -81,7 +81,18 @@ def test_64_row_workgroups_are_weighed_by_where_those_of_the_list_go(tmp_path):
                 [rng.choice((2600, 9000, rng.randrange(30000))) for _ in range(n)], [rng.choice((0, 200, rng.randint(1, 900))) for _ in range(n)])
                for n in (rng.choice((1, 2, 3, 6)) for _ in range(1200))]
     out = ask(build(tmp_path, "-O2"), batches)
-    pairs = [(b, float(ends)) for b, (*_, rows, ends) in zip(batches, out) if rows == "64"]
+    pairs = [(b, float(line[4])) for b, line in zip(batches, out) if line[3] == "64"]
     assert len(pairs) > 150 and {b[1] for b, _ in pairs} >= {8, 2, 3, 1}
     for b, ends in pairs:
         assert ends == pytest.approx(pairs_end(*b), rel=1e-6), b
+
+
+def test_a_call_that_could_cut_takes_64_row_workgroups_where_whole_rows_do(tmp_path):
+    """They are weighed against a cut, too; other whole rows may be as soon, and a prepared list takes those."""
+    rng = random.Random(9)
+    batches = [(8, 2, 128, 0, [4948], [3490]), (16, 2, 128, 0, [1900, 3178, 27, 0], [597, 2, 12, 8])]
+    batches += [(*rng.choice([h for h in HEADS if h[3] == 0] + [(8, 2, 128, 0)]), [int(2 ** rng.uniform(6, 14)) for _ in range(n)],
+                 [int(2 ** rng.uniform(0, 12)) for _ in range(n)]) for n in (rng.choice((1, 1, 2, 4)) for _ in range(6000))]
+    out = ask(build(tmp_path, "-O2"), batches)
+    assert sum(line[-2] == "64" for line in out) > 20
+    assert [b for b, line in zip(batches, out) if line[-2] == "64" and (line[3], line[-1]) != ("64", "1")] == []
