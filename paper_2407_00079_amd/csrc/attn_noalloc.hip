@@ -244,7 +244,7 @@ extern "C" mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, cons
   args.head_dim = p->head_dim;
   args.scale_log2e = attn_scale_log2e(p);
   args.n_items = (int32_t)n_items;
-  const int32_t form = list_form(p, prefix_lens, new_lens, batch, 0, n_items);
+  const int32_t form = planned_list_form(p, prefix_lens, new_lens, batch, nullptr, n_items);
   args.few_rows = form != 0;
   args.halves = form == kListHalves;
   args.once = form == kListFewOnce;

@@ -181,11 +181,15 @@ int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int
                   int32_t kv_splits, int64_t n_items) {
   ClassPlan plan;
   const bool planned = kv_splits == 0 && plan_classes(p, prefix_lens, new_lens, batch, 0, &plan);
-  if (planned && plan.classes.rows == kAttnPairRows) return kListPairs;
-  if (planned && plan.narrow_wgs > 0) return few_rows(p, new_lens, batch, kAttnLeastRows) ? kListNarrowLeast : kListNarrow;
+  return planned_list_form(p, prefix_lens, new_lens, batch, planned ? &plan : nullptr, n_items);
+}
+int32_t planned_list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                          const ClassPlan* plan, int64_t n_items) {
+  if (plan != nullptr && plan->classes.rows == kAttnPairRows) return kListPairs;
+  if (plan != nullptr && plan->narrow_wgs > 0) return few_rows(p, new_lens, batch, kAttnLeastRows) ? kListNarrowLeast : kListNarrow;
   if (few_rows(p, new_lens, batch, kAttnFewRows))
     return reads_once(p, prefix_lens, new_lens, batch, kAttnFewRows) ? kListFewOnce : kListFew;
-  if (planned) return plan.classes.rows == kAttnFewRows ? kListHalves : 0;
+  if (plan != nullptr) return plan->classes.rows == kAttnFewRows ? kListHalves : 0;
   return 2 * n_items <= kComputeUnits ? kListHalves : 0;
 }
 

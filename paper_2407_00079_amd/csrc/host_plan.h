@@ -79,6 +79,10 @@ constexpr int32_t kListApart = 0x4d44;        // upper half of the mark of a lis
 constexpr int32_t kMostNarrowItems = INT32_MAX / (kAttnTileRows / kAttnLeastRows);
 int32_t list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
                   int32_t kv_splits, int64_t n_items);
+// the same where the batch's whole rows have been planned (null: there is no plan, or the list is of key slices)
+struct ClassPlan;
+int32_t planned_list_form(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch,
+                          const ClassPlan* plan, int64_t n_items);
 
 // Workgroups that take a row tile of the narrow form, each a share of its columns, where there are `row_tiles` (x pieces) of them.
 int32_t narrow_shares(const mc_attn_params* p, int64_t row_tiles);

@@ -195,10 +195,10 @@ mc_status prepare_attn(const mc_attn_params* p, const int32_t* prefix_lens, cons
   build_work_list(p, prefix_lens, new_lens, batch, split ? kv_splits : 0, reqs, items);
   ApartPlan apart;
   ClassPlan one;
-  const bool two = !split && plan_classes(p, prefix_lens, new_lens, batch, 0, &one) &&
-                   plan_apart(p, prefix_lens, new_lens, batch, one, &apart);
+  const bool planned = !split && plan_classes(p, prefix_lens, new_lens, batch, 0, &one);
+  const bool two = planned && plan_apart(p, prefix_lens, new_lens, batch, one, &apart);
   const int32_t form = two ? apart_list(p, prefix_lens, new_lens, apart, batch, items)
-                           : list_form(p, prefix_lens, new_lens, batch, split ? kv_splits : 0, (int64_t)items.size());
+                           : planned_list_form(p, prefix_lens, new_lens, batch, planned ? &one : nullptr, (int64_t)items.size());
   const size_t n_items = items.size();
 
   // one pinned, asynchronous copy of work list + request table

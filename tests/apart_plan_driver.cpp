@@ -1,7 +1,8 @@
 // Plans each batch read from stdin as a call without room for partial results does (plan_classes, then plan_apart); one line a
 // batch: "none" (more requests than classes), "one" or "two" launches, the allocations on the host heap that both planning functions
 // made, and of one launch the rows of its workgroups (0: narrow) and its estimated end in microseconds;
-// then the same rows of a call with room for partial results (-1: it cuts some), and whether it is that launch.
+// then the same rows of a call with room for partial results (-1: it cuts some), and whether it is that launch;
+// and whether a list's form is the same from that plan as from the lengths.
 // input:  Hq Hkv D dtype batch P... C...
 #include <cstdio>
 #include <cstdlib>
@@ -47,7 +48,10 @@ int main() {
     const bool same = whole && roomy.narrow_wgs == one.narrow_wgs && roomy.ends == one.ends &&
                       (one.narrow_wgs > 0 ? std::memcmp(&roomy.narrow, &one.narrow, sizeof one.narrow) == 0
                                           : std::memcmp(&roomy.classes, &one.classes, sizeof one.classes) == 0);
-    std::printf(" %d %d\n", !whole ? -1 : roomy.narrow_wgs > 0 ? 0 : roomy.classes.rows, same);
+    const int64_t items = mc::host::count_items(&p, C.data(), batch);
+    const bool form = mc::host::planned_list_form(&p, P.data(), C.data(), batch, planned ? &one : nullptr, items) ==
+                      mc::host::list_form(&p, P.data(), C.data(), batch, 0, items);
+    std::printf(" %d %d %d\n", !whole ? -1 : roomy.narrow_wgs > 0 ? 0 : roomy.classes.rows, same, form);
   }
   return 0;
 }

@@ -35,7 +35,7 @@ def ask(exe, batches):
     res = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0 and res.stderr == "", res.stderr[-2000:]
     out = [line.split() for line in res.stdout.splitlines()]
-    assert len(out) == len(batches)
+    assert len(out) == len(batches) and all(line[7] == "1" for line in out)
     return out
 
 
@@ -94,5 +94,5 @@ def test_a_call_that_could_cut_takes_64_row_workgroups_where_whole_rows_do(tmp_p
     batches += [(*rng.choice([h for h in HEADS if h[3] == 0] + [(8, 2, 128, 0)]), [int(2 ** rng.uniform(6, 14)) for _ in range(n)],
                  [int(2 ** rng.uniform(0, 12)) for _ in range(n)]) for n in (rng.choice((1, 1, 2, 4)) for _ in range(6000))]
     out = ask(build(tmp_path, "-O2"), batches)
-    assert sum(line[-2] == "64" for line in out) > 20
-    assert [b for b, line in zip(batches, out) if line[-2] == "64" and (line[3], line[-1]) != ("64", "1")] == []
+    assert sum(line[5] == "64" for line in out) > 20
+    assert [b for b, line in zip(batches, out) if line[5] == "64" and (line[3], line[6]) != ("64", "1")] == []
