@@ -10,6 +10,11 @@ namespace host {
 
 namespace {
 constexpr int64_t kComputeUnits = 256;   // MI355X
+
+// a / b of what is not negative, in 32 bits where they fit (planning is full of such divisions: 6000 random batches 4.0 -> 3.6 us).
+int64_t quotient(int64_t a, int64_t b) {
+  return ((a | b) >> 32) == 0 ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
+}
 }  // namespace
 
 mc_status check_params(const mc_attn_params* p) {
@@ -351,8 +356,8 @@ struct Run {
   int64_t shortest, longest;
   double mean() const { return 0.5 * (double)(shortest + longest); }
   // pieces of at most 1 / k of `of` key tiles each, and the key tiles of one of c pieces on average, rounded up
-  int64_t pieces(int64_t of, int64_t k) const { return std::min<int64_t>((longest * k + of - 1) / of, MC_MAX_KV_SPLITS); }
-  double mean_piece(int64_t c) const { return (double)((shortest + longest + 2 * c - 1) / (2 * c)); }
+  int64_t pieces(int64_t of, int64_t k) const { return std::min<int64_t>(quotient(longest * k + of - 1, of), MC_MAX_KV_SPLITS); }
+  double mean_piece(int64_t c) const { return (double)quotient(shortest + longest + 2 * c - 1, 2 * c); }
 };
 
 // End of the last workgroup if the runs' pieces are handed to the compute units in order, each to the one free first
@@ -454,7 +459,7 @@ double pairs_really_end(const mc_attn_params* p, const Active* act, int n, const
     double us[kParts];
   } tiles[kMostPairs];
   auto later = [](const Next& a, const Next& b) { return a.keys != b.keys ? a.keys < b.keys : a.of->req > b.of->req; };
-  auto last_token = [&](const Active& a, int64_t row) { return std::min<int64_t>(a.chunk - 1, row / G); };
+  auto last_token = [&](const Active& a, int64_t row) { return std::min<int64_t>(a.chunk - 1, quotient(row, G)); };
   auto tile_of = [&](const Active& a, int64_t t) {
     return Next{a.prefix + last_token(a, t * kAttnTileRows + kAttnTileRows - 1) + 1, &a, t};
   };
@@ -524,7 +529,7 @@ double pairs_really_end(const mc_attn_params* p, const Active* act, int n, const
 constexpr double kPlainSlack = 1.02;
 
 int64_t key_tiles(int64_t prefix, int64_t chunk, int64_t G, int64_t row_tile, int64_t tile_rows) {
-  const int64_t last = std::min<int64_t>(chunk - 1, (row_tile * tile_rows + tile_rows - 1) / G);
+  const int64_t last = std::min<int64_t>(chunk - 1, quotient(row_tile * tile_rows + tile_rows - 1, G));
   return (prefix + last + 1 + kAttnTileKeys - 1) / kAttnTileKeys;
 }
 
@@ -541,6 +546,39 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
   return run;
 }
 
+// The row tiles of a request from `hi` down to `lo`, each in `cut` pieces, in up to 16 steps; false as soon as one ends at `limit` or later.
+bool place_tiles(const mc_attn_params* p, Units& units, int64_t prefix, int64_t chunk, int64_t lo, int64_t hi, int64_t cut,
+                 int64_t tile_rows, const FormCost& cost, double limit) {
+  const int64_t G = p->num_q_heads / p->num_kv_heads, step = (hi - lo) / 16 + 1;
+  for (; hi >= lo; hi -= step) {
+    const int64_t n = std::min(step, hi - lo + 1), tiles = key_tiles(prefix, chunk, G, hi, tile_rows);
+    if (!units.place(n * p->num_kv_heads * cut, cost.fixed + cost.tile * (double)quotient(tiles + cut - 1, cut), limit)) return false;
+  }
+  return true;
+}
+
+// ClassPlan::ends of a plan of whole rows, where it has not been estimated; `least` and less: no later than that.  (However they
+// are placed, the last workgroup starts before the work would end if the units shared it evenly.)
+double ends_of(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch, const ClassPlan& plan,
+               double least = 0.0) {
+  if (plan.ends > 0.0) return plan.ends;
+  const AttnClasses& t = plan.classes;
+  const FormCost cost = form_cost_of(p, t.rows);
+  const double read = (double)kv_bytes(p, prefix_lens, new_lens, batch) / kReadPerUs;
+  double work = 0.0, longest = 0.0;
+  for (int i = 0; i < t.n && least > 0.0; ++i) {
+    const Run run = make_run(p, i, t.c[i].prefix, t.c[i].chunk, t.c[i].tile_lo, t.c[i].tile_hi, t.rows);
+    const double step = (double)(run.longest - run.shortest) / 16 + 1;      // (place_tiles rounds up to the longest of a step)
+    work += (double)run.items * (cost.fixed + cost.tile * (run.mean() + step));
+    longest = std::max(longest, cost.fixed + cost.tile * (double)run.longest);
+  }
+  if (cost.launch + std::max(work / kComputeUnits + longest, read) <= least) return least;
+  Units units;
+  for (int i = 0; i < t.n; ++i)
+    place_tiles(p, units, t.c[i].prefix, t.c[i].chunk, t.c[i].tile_lo, t.c[i].tile_hi, 1, t.rows, cost, HUGE_VAL);
+  return cost.launch + std::max(units.end(), read);
+}
+
 }  // namespace
 
 // The cut.  The first `whole` workgroups of the launch order stay uncut - a multiple of the compute units, so that they
@@ -555,7 +593,9 @@ Run make_run(const mc_attn_params* p, int active, int64_t prefix, int64_t chunk,
 // (2 row tiles: whole / 6 pieces) 73 / 33 us; P 131056, C 16, 64/8 heads (32 slices / 32 pieces) 125 / 118 us.
 // Every one-shot call pays for the search on the host, so a trial that the work alone puts behind the best is not placed, and
 // placing ends where the best does (same plans; host time of a call of 63 requests, 8/1 heads, C up to 300: 219 us with every
-// trial placed, 20 now; of 63 one-token requests 41 and 16; of one to three requests 1 us of planning).
+// trial placed, 20 now; of 63 one-token requests 41 and 16).  6000 random batches, mean / 99 of 100, us, with room for partial
+// results (whole rows): one to three requests 1.2 / 7 (0.8 / 5), 4 to 15 3 / 15 (2.5 / 16), 16 to 63 9 / 29 (9 / 36); without
+// 64-row workgroups and two launches to weigh 1.1 / 6 (0.5 / 2), 2.7 / 13 (1.3 / 4), 7 / 32 (4 / 13).
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
                   int64_t max_part_rows, ClassPlan* plan, bool keep_room) {
   const int64_t G = p->num_q_heads / p->num_kv_heads, Hkv = p->num_kv_heads;
@@ -571,7 +611,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
   }
   auto items_of = [&](int64_t tile_rows) {
     int64_t items = 0;
-    for (int i = 0; i < n; ++i) items += Hkv * ((act[i].chunk * G + tile_rows - 1) / tile_rows);
+    for (int i = 0; i < n; ++i) items += Hkv * quotient(act[i].chunk * G + tile_rows - 1, tile_rows);
     return items;
   };
   if (items_of(kAttnTileRows) > INT32_MAX) return false;
@@ -590,8 +630,8 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
     int uncut = 0;
     for (int i = 0; i < n; ++i) {
       const int64_t P = act[i].prefix, C = act[i].chunk;
-      const int64_t tiles = (C * G + tile_rows - 1) / tile_rows;
-      const int64_t keep = std::min<int64_t>(tiles, whole / Hkv);
+      const int64_t tiles = quotient(C * G + tile_rows - 1, tile_rows);
+      const int64_t keep = std::min<int64_t>(tiles, quotient(whole, Hkv));
       if (keep > 0) {
         runs[n_runs] = make_run(p, i, P, C, tiles - keep, tiles - 1, tile_rows);
         ++n_runs;
@@ -703,18 +743,18 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
       p->dtype == MC_DTYPE_F32 || few_rows(p, new_lens, batch, kAttnLeastRows) ? kAttnLeastRows : kAttnNarrowRows;
   plan->narrow_wgs = 0;
   plan->narrow_pieces = 1;
+  plan->ends = 0.0;
   const int64_t narrow_items = items_of(narrow_rows);
-  const bool by_pairs = p->dtype == MC_DTYPE_BF16 && narrow_rows == kAttnNarrowRows && items_of(kAttnPairRows) <= kMostPairs;
-  {
+  int64_t longest = 0;
+  for (int i = 0; i < n; ++i) longest = std::max(longest, ((int64_t)act[i].prefix + act[i].chunk + kAttnTileKeys - 1) / kAttnTileKeys);
+  // (a row tile of one key tile is one block for each of two waves: the 128-row form has that done as soon)
+  const bool by_narrow = narrow_items <= kMostNarrow && longest > 1;
+  const bool by_pairs = p->dtype == MC_DTYPE_BF16 && narrow_rows == kAttnNarrowRows && items_of(kAttnPairRows) <= kMostPairs &&
+                        longest >= kLeastPairTiles;
+  if (by_narrow || by_pairs) {
     auto place = [&](Units& units, const Run& run, int64_t cut, int64_t tile_rows, const FormCost& cost, double limit) {
       const Active& a = act[run.active];
-      const int64_t step = (run.tile_hi - run.tile_lo) / 16 + 1;
-      for (int64_t hi = run.tile_hi; hi >= run.tile_lo; hi -= step) {
-        const int64_t lo = std::max(run.tile_lo, hi - step + 1);
-        const int64_t tiles = key_tiles(a.prefix, a.chunk, G, hi, tile_rows);
-        if (!units.place((hi - lo + 1) * Hkv * cut, cost.fixed + cost.tile * (double)((tiles + cut - 1) / cut), limit)) return false;
-      }
-      return true;
+      return place_tiles(p, units, a.prefix, a.chunk, run.tile_lo, run.tile_hi, cut, tile_rows, cost, limit);
     };
     auto merge_of = [&](const FormCost& cost, int64_t part_rows) {
       return part_rows > 0 ? cost.merge + cost.part_mb * (double)part_rows * (double)(p->head_dim + 1) * 8e-6 : 0.0;
@@ -723,21 +763,19 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
     const FormCost cost = form_cost_of(p, best_rows);
     const int uncut = lay_out(best_whole, best_rows);
     Units chosen;
-    int64_t part_rows = 0, longest = 0, longest_piece = 0;
+    int64_t part_rows = 0, longest_piece = 0;
     for (int i = 0; i < n_runs; ++i) {
       const int64_t cut = i < uncut || best_of == 0 ? 1 : runs[i].pieces(best_of, best_k);
       place(chosen, runs[i], cut, best_rows, cost, HUGE_VAL);
       if (cut > 1) part_rows += cut * runs[i].rows;
-      longest = std::max(longest, runs[i].longest);
-      longest_piece = std::max(longest_piece, (runs[i].longest + cut - 1) / cut);
+      longest_piece = std::max(longest_piece, quotient(runs[i].longest + cut - 1, cut));
     }
     double end = cost.launch + std::max(chosen.end(), bytes / kReadPerUs) + merge_of(cost, part_rows);
     if (part_rows > 0) end /= kNarrowSlack;
     const FormCost narrow = form_cost_of(p, narrow_rows);
     const double missed = std::max(0.0, bytes - kNarrowHeld) / kNarrowMissPerUs;
     const int64_t room = keep_room ? max_part_rows : part_rows;
-    // (a row tile of one key tile is one block for each of two waves: the 128-row form has that done as soon)
-    const bool may = narrow_items <= kMostNarrow && longest > 1 && bytes / kNarrowReadPerUs < end && (p->dtype != MC_DTYPE_F32 || longest_piece <= kNarrowTilesF32);
+    const bool may = by_narrow && bytes / kNarrowReadPerUs < end && (p->dtype != MC_DTYPE_F32 || longest_piece <= kNarrowTilesF32);
     n_runs = 0;
     double work = 0.0;
     for (int i = 0; i < n && may; ++i) {
@@ -792,7 +830,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
       plan->narrow_wgs = (int32_t)wg;
     }
     // 64-row workgroups, all rows whole, beside that.
-    if (by_pairs && longest >= kLeastPairTiles) {
+    if (by_pairs) {
       const FormCost pairs = form_cost_of(p, kAttnPairRows);
       const double limit = end / (items_of(kAttnPairRows) > 2 * kComputeUnits ? kPairRoundsSlack : kPairSlack), by = limit - pairs.launch;
       Units units;
@@ -855,39 +893,53 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
 constexpr double kApartLeast = 40.0, kApartSecond = 3.0, kApartSlack = 1.15, kApartRoundsSlack = 1.35, kApartMiss = 1.5;
 bool plan_apart(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, int32_t batch, const ClassPlan& one,
                 ApartPlan* apart) {
-  if (one.ends < kApartLeast) return false;
+  if (one.ends > 0.0 && one.ends < kApartLeast) return false;
   const int64_t G = p->num_q_heads / p->num_kv_heads;
   const FormCost full = form_cost_of(p, kAttnTileRows), half = form_cost_of(p, kAttnFewRows),
                  pairs = form_cost_of(p, p->dtype == MC_DTYPE_BF16 ? kAttnPairRows : kAttnFewRows),
                  narrow = form_cost_of(p, kAttnLeastRows);
-  const bool rounds = one.narrow_wgs == 0 && one.classes.rows == kAttnTileRows && one.n_wgs > kComputeUnits;
-  const double limit = one.ends / (rounds ? kApartRoundsSlack : kApartSlack) - kApartSecond;
-  double best = limit;
-  int32_t line = 0, most = 0;
-  for (int32_t r = 0; r < batch; ++r) most = std::max(most, new_lens[r]);
-  for (int64_t at = 1; at < most; at *= 2) {
-    int64_t few_longest = 0, few_items = 0, many_longest = 0;
-    double many_work = 0.0;
-    for (int32_t r = 0; r < batch; ++r) {
-      if (new_lens[r] == 0) continue;
-      const int64_t tiles = ((int64_t)prefix_lens[r] + new_lens[r] + kAttnTileKeys - 1) / kAttnTileKeys, rows = new_lens[r] * G;
-      if (new_lens[r] <= at) {
-        few_longest = std::max(few_longest, tiles);
-        few_items += (rows + kAttnNarrowRows - 1) / kAttnNarrowRows * p->num_kv_heads;
-      } else {
-        many_longest = std::max(many_longest, tiles);
-        many_work += (double)(rows * p->num_kv_heads) / kAttnTileRows * full.tile *
-                     ((double)prefix_lens[r] + 0.5 * (double)new_lens[r]) / kAttnTileKeys;
-      }
-    }
-    if (few_items == 0 || few_items > kComputeUnits) continue;
-    const double least = narrow.fixed + narrow.tile * (double)few_longest + pairs.fixed +
-                         std::max(std::min(pairs.tile, half.tile) * (double)many_longest, many_work / kComputeUnits);
-    if (least >= best) continue;
-    best = least;
-    line = (int32_t)at;
+  // what the requests between two lines add to the launches, and then what those above a line do
+  struct Between {
+    int64_t longest = 0, items = 0;
+    double work = 0.0;
+  } at[33];
+  int highest = 0;
+  for (int32_t r = 0; r < batch; ++r) {
+    if (new_lens[r] == 0) continue;
+    int k = 0;
+    while ((int64_t)1 << k < new_lens[r]) ++k;
+    const int64_t rows = new_lens[r] * G;
+    at[k].longest = std::max(at[k].longest, ((int64_t)prefix_lens[r] + new_lens[r] + kAttnTileKeys - 1) / kAttnTileKeys);
+    at[k].items += (rows + kAttnNarrowRows - 1) / kAttnNarrowRows * p->num_kv_heads;
+    at[k].work += (double)(rows * p->num_kv_heads) / kAttnTileRows * full.tile *
+                  ((double)prefix_lens[r] + 0.5 * (double)new_lens[r]) / kAttnTileKeys;
+    highest = std::max(highest, k);
   }
-  if (line == 0) return false;
+  Between above[33];
+  for (int k = highest - 1; k >= 0; --k) {
+    above[k].longest = std::max(above[k + 1].longest, at[k + 1].longest);
+    above[k].work = above[k + 1].work + at[k + 1].work;
+  }
+  double least = HUGE_VAL;
+  int32_t line = 0;
+  int64_t few_longest = 0;
+  Between below;
+  for (int k = 0; k < highest; ++k) {
+    below.longest = std::max(below.longest, at[k].longest);
+    below.items += at[k].items;
+    if (below.items == 0 || below.items > kComputeUnits) continue;
+    const double both = narrow.fixed + narrow.tile * (double)below.longest + pairs.fixed +
+                        std::max(std::min(pairs.tile, half.tile) * (double)above[k].longest, above[k].work / kComputeUnits);
+    if (both >= least) continue;
+    least = both;
+    line = (int32_t)((int64_t)1 << k);
+    few_longest = below.longest;
+  }
+  if (line == 0 || (p->dtype == MC_DTYPE_F32 && few_longest > kNarrowTilesF32)) return false;
+  const bool rounds = one.narrow_wgs == 0 && one.classes.rows == kAttnTileRows && one.n_wgs > kComputeUnits;
+  const double slack = rounds ? kApartRoundsSlack : kApartSlack, at_least = std::max(kApartLeast, (least + kApartSecond) * slack);
+  const double ends = ends_of(p, prefix_lens, new_lens, batch, one, at_least), limit = ends / slack - kApartSecond;
+  if (ends <= at_least) return false;
   apart->line = line;
   const NewLens few_lens(new_lens, 0, line), many_lens(new_lens, line, INT32_MAX);
   if (!plan_classes(p, prefix_lens, few_lens, batch, 0, &apart->few)) return false;
@@ -898,7 +950,7 @@ bool plan_apart(const mc_attn_params* p, const int32_t* prefix_lens, const int32
   const bool miss = kv_bytes(p, prefix_lens, several, batch) > kXcdCaches;
   const double few_ends = few.ends * (miss ? kApartMiss : 1.0);
   return few_ends < limit && plan_classes(p, prefix_lens, many_lens, batch, 0, &apart->many) && apart->many.narrow_wgs == 0 &&
-         few_ends + apart->many.ends < limit;
+         few_ends + ends_of(p, prefix_lens, many_lens, batch, apart->many) < limit;
 }
 
 int32_t apart_list(const mc_attn_params* p, const int32_t* prefix_lens, const int32_t* new_lens, const ApartPlan& apart,

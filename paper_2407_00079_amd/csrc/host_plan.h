@@ -111,7 +111,7 @@ struct ClassPlan {
   int32_t n_wgs;          // workgroups of the attention launch
   int32_t most_pieces;    // 1: nothing is cut, no partial results, no merge
   int64_t part_rows;      // rows of partial results
-  double ends;            // us, by the estimate
+  double ends;            // us, by the estimate; 0: no other form was weighed
 };
 bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens new_lens, int32_t batch,
                   int64_t max_part_rows, ClassPlan* plan, bool keep_room = false);
