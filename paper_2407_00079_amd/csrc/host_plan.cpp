@@ -1017,6 +1017,10 @@ bool hash_in_one_launch(int64_t max_blocks, int64_t max_tokens) {
   return max_blocks <= kShortHashBlocks && (max_tokens <= kShortTokens || max_blocks <= kSimds);
 }
 
+bool kernel_may_reach(uint32_t flags, uintptr_t at, uintptr_t start, size_t size, size_t bytes) {
+  return (flags & ~kPlainHostFlags) == 0 && at >= start && at - start <= size && bytes <= size - (at - start);
+}
+
 mc_status check_copy(const void* a, const void* b, int64_t num_pages, int64_t page_bytes, const int32_t* ids,
                      int64_t n, const void* c, const void* d) {
   if (num_pages < 0 || page_bytes < 0 || n < 0) return MC_ERR_SHAPE;

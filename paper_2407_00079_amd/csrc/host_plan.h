@@ -172,6 +172,13 @@ bool hash_in_one_launch(int64_t max_blocks, int64_t max_tokens);
 mc_status check_copy(const void* a, const void* b, int64_t num_pages, int64_t page_bytes, const int32_t* ids,
                      int64_t n, const void* c, const void* d);
 
+// Whether a kernel may read and write `bytes` of pinned host memory at `at` itself: all of them lie in the allocation of `size`
+// bytes from `start`, and its flags are among those of plain pinned memory (portable, mapped, NUMA-local, coherent).  Memory that is
+// not coherent has a registered twin whose flag is another (coarse-grained: 0x8, also read-only); write-combined and I/O memory
+// share a flag.  What is not named here goes by the copy engine.
+constexpr uint32_t kPlainHostFlags = 0x60000003;
+bool kernel_may_reach(uint32_t flags, uintptr_t at, uintptr_t start, size_t size, size_t bytes);
+
 // Bookkeeping of the pinned host slots that work lists and tables are written to before their
 // asynchronous upload.  A slot is FREE, HELD by a call that is filling it (between acquire and
 // the event recorded behind its upload), or IN FLIGHT (its event decides when it is free again).

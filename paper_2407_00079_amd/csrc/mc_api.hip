@@ -105,19 +105,23 @@ mc_status upload(void* dst, const void* src, size_t bytes, hipStream_t stream) {
   return g_staging.release_after(slot, stream) ? MC_OK : MC_ERR_HIP;
 }
 
-// Where the device sees `bytes` of pinned host memory, or null: memory of another kind, or less of it.
+// Where the device sees `bytes` of host memory that a kernel may reach, or null.
 void* host_view(const void* host, size_t bytes) {
+  static_assert(kPlainHostFlags ==
+                (hipHostMallocPortable | hipHostMallocMapped | hipHostMallocNumaUser | hipHostMallocCoherent), "HIP's flags");
   hipPointerAttribute_t attr = {};
   void* start = nullptr;
   size_t size = 0;
   void* const at = const_cast<void*>(host);
   const bool known = hipPointerGetAttributes(&attr, at) == hipSuccess && attr.type == hipMemoryTypeHost &&
-                     attr.devicePointer != nullptr && (attr.allocationFlags & hipHostMallocNonCoherent) == 0 &&
+                     attr.devicePointer != nullptr &&
                      hipPointerGetAttribute(&start, HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, at) == hipSuccess &&
                      hipPointerGetAttribute(&size, HIP_POINTER_ATTRIBUTE_RANGE_SIZE, at) == hipSuccess;
   if (!known) (void)hipGetLastError();
-  const uintptr_t offset = reinterpret_cast<uintptr_t>(attr.devicePointer) - reinterpret_cast<uintptr_t>(start);
-  return known && offset <= size && bytes <= size - offset ? attr.devicePointer : nullptr;
+  return known && kernel_may_reach(attr.allocationFlags, reinterpret_cast<uintptr_t>(attr.devicePointer),
+                                   reinterpret_cast<uintptr_t>(start), size, bytes)
+             ? attr.devicePointer
+             : nullptr;
 }
 
 // Small loads and stores: one launch that reads or writes the host memory itself.  *done: it has been enqueued.

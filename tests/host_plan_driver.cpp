@@ -122,6 +122,20 @@ static void test_hash_rule() {
 }
 
 // The slot bookkeeping, driven the way the staging ring drives it: `done` stands in for hipEventQuery.
+static void test_kernel_may_reach() {
+  const uintptr_t at = 0x7F0000001000ull;
+  EXPECT(kernel_may_reach(0, at, at, 4096, 4096) && kernel_may_reach(0, at + 16, at, 4096, 4080));
+  EXPECT(kernel_may_reach(0, at + 4096, at, 4096, 0));
+  EXPECT(kernel_may_reach(0x3, at, at, 4096, 1) && kernel_may_reach(0x60000000, at, at, 4096, 1));   // portable, mapped; coherent, NUMA
+  // memory shorter than the call says, and an address that is not in the range it is said to be in
+  EXPECT(!kernel_may_reach(0, at, at, 4096, 4097) && !kernel_may_reach(0, at + 16, at, 4096, 4096));
+  EXPECT(!kernel_may_reach(0, at - 16, at, 4096, 16) && !kernel_may_reach(0, at + 4112, at, 4096, 0));
+  EXPECT(!kernel_may_reach(0, at, at, 4096, SIZE_MAX));
+  // allocated non-coherent, registered as coarse-grained or read-only (0x8), write-combined or registered as I/O memory (0x4),
+  // uncached, and what a later runtime may add
+  for (uint32_t flags : {0x80000000u, 0x8u, 0x4u, 0x10000000u, 0x10u, 0x80000003u, 0xBu}) EXPECT(!kernel_may_reach(flags, at, at, 4096, 16));
+}
+
 static void test_slot_ring() {
   SlotRing ring;
   std::vector<char> finished(SlotRing::kMaxSlots, 0);
@@ -235,6 +249,7 @@ int main(int argc, char** argv) {
   if (argc > 1 && std::string(argv[1]) == "plan") return run_plans();
   test_rejections();
   test_hash_rule();
+  test_kernel_may_reach();
   test_slot_ring();
   if (failures == 0) std::printf("selftest ok\n");
   return failures == 0 ? 0 : 1;

@@ -1,5 +1,7 @@
 """GPU parity of small loads and stores against host memory (kv_host_kernel in csrc/kv_copy.hip), byte for byte: both sides of the
 line to the copy engine's way, slices that end inside a page, host memory that the kernel may not touch itself, and replays."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -89,3 +91,60 @@ def test_streams_and_replays():
         torch.cuda.synchronize()
         layer.check_loaded()
         assert torch.equal(layer.k_out, layer.k) and torch.equal(layer.v_out, layer.v)
+
+
+def _hip():
+    torch.cuda.init()
+    with open("/proc/self/maps") as maps:
+        return ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+
+
+def _recorded(call):
+    """What a call enqueues, by the kinds of the nodes of a graph that records it (0: kernel, 1: copy).  The graph is never run."""
+    hip = _hip()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    handle, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(n)) == 0
+    kinds = []
+    for node in nodes:
+        kind = ctypes.c_int(-1)
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        kinds.append(kind.value)
+    return sorted(kinds)
+
+
+def _allocated(flags, n, page_bytes):
+    """Host memory of hipHostMalloc with these flags, freed at the end of the process"""
+    at = ctypes.c_void_p()
+    assert _hip().hipHostMalloc(ctypes.byref(at), ctypes.c_size_t(n * page_bytes), ctypes.c_uint(flags)) == 0
+    array = np.ctypeslib.as_array(ctypes.cast(at, ctypes.POINTER(ctypes.c_uint8)), (n, page_bytes))
+    return torch.from_numpy(array)
+
+
+@pytest.mark.parametrize("page_bytes,n,by_kernel", [(16, 1, True), (16, 512, True), (16, 513, False), (4112, 256, True), (4112, 257, False),
+                                                    (32768, 64, True), (32768, 65, False)])
+def test_which_way_a_call_goes(page_bytes, n, by_kernel):
+    layer = Layer(page_bytes, n, True)
+    for call in (layer.load, layer.store):
+        assert _recorded(call) == ([0] if by_kernel else [0, 1, 1])
+
+
+# plain, portable and mapped, NUMA-local, coherent; not coherent, write-combined
+@pytest.mark.parametrize("flags,by_kernel", [(0, True), (0x3, True), (0x20000000, True), (0x40000000, True), (0x80000000, False), (0x4, False)])
+def test_memory_that_a_kernel_may_not_touch_goes_by_the_copy_engine(flags, by_kernel):
+    layer = Layer(4096, 24, True)
+    want = layer.k.clone(), layer.v.clone()
+    layer.k, layer.v, layer.k_out, layer.v_out = (_allocated(flags, 24, 4096) for _ in range(4))
+    layer.k.copy_(want[0])
+    layer.v.copy_(want[1])
+    for call in (layer.load, layer.store):
+        assert _recorded(call) == ([0] if by_kernel else [0, 1, 1])
+    layer.load()
+    layer.store()
+    torch.cuda.synchronize()
+    layer.check_loaded()
+    assert torch.equal(layer.k_out, want[0]) and torch.equal(layer.v_out, want[1])
