@@ -3,6 +3,8 @@
 // made, and of one launch the rows of its workgroups (0: narrow) and its estimated end in microseconds;
 // then the same rows of a call with room for partial results (-1: it cuts some), and whether it is that launch;
 // and whether a list's form is the same from that plan as from the lengths.
+// With an argument, of each batch of two launches only: "line | rows of a workgroup, then classes, of the first launch | the same
+// of the second | the list's mark, then what it is read as | the list's items", numbers all.
 // input:  Hq Hkv D dtype batch P... C...
 #include <cstdio>
 #include <cstdlib>
@@ -24,7 +26,29 @@ void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, size_t) noexcept { std::free(p); }
 #endif
 
-int main() {
+static void print(const mc::AttnClasses& t) {
+  std::printf(" | %d", t.rows);
+  for (int i = 0; i < t.n; ++i)
+    std::printf(" %d %d %d %d %d %d %d %d", t.first[i], t.c[i].req, t.c[i].q_off, t.c[i].prefix, t.c[i].chunk, t.c[i].tile_lo,
+                t.c[i].tile_hi, t.c[i].pieces);
+}
+
+static void print_two(const mc_attn_params& p, const std::vector<int32_t>& P, const std::vector<int32_t>& C,
+                      const mc::host::ApartPlan& apart) {
+  std::printf("%d", apart.line);
+  print(apart.few.narrow);
+  print(apart.many.classes);
+  std::vector<mc::AttnItem> items;
+  const int32_t packed = mc::host::apart_list(&p, P.data(), C.data(), apart, (int32_t)P.size(), items);
+  mc::host::ApartMark mark;
+  const bool read = mark.unpack(packed, (int32_t)items.size()), small = mark.unpack(packed, mark.n_few);
+  std::printf(" | %d %d %d %d %d %d %d", packed, read, small, mark.n_few, mark.shares, mark.least, mark.form);
+  std::printf(" %d |", mc::host::narrow_shares(&p, apart.few.narrow_wgs));
+  for (const mc::AttnItem& it : items) std::printf(" %d %d %d %d", it.req, it.kv_head, it.row0, it.slice);
+  std::puts("");
+}
+
+int main(int argc, char**) {
   int Hq, Hkv, D, dtype, batch;
   while (std::scanf("%d %d %d %d %d", &Hq, &Hkv, &D, &dtype, &batch) == 5) {
     std::vector<int32_t> P(batch), C(batch);
@@ -39,6 +63,11 @@ int main() {
     const bool planned = mc::host::plan_classes(&p, P.data(), C.data(), batch, 0, &one);
     const long by_classes = news - before;
     const bool two = planned && mc::host::plan_apart(&p, P.data(), C.data(), batch, one, &apart);
+    if (argc > 1) {
+      if (two) print_two(p, P, C, apart);
+      else std::puts("");
+      continue;
+    }
     std::printf("%s %ld %ld", !planned ? "none" : two ? "two" : "one", by_classes, news - before - by_classes);
     std::printf(" %d %.9g", planned && one.narrow_wgs == 0 ? one.classes.rows : 0, planned ? one.ends : 0.0);
     mc::host::AutoLayout lay;

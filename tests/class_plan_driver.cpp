@@ -32,7 +32,8 @@ int main() {
     // as launch_planned_attn and launch_attn read it
     const int narrow = dtype == MC_DTYPE_F32 ? mc::kAttnLeastRows : mc::kAttnNarrowRows;
     const int list = form == 0 ? mc::kAttnTileRows : form == mc::host::kListNarrowLeast ? mc::kAttnLeastRows
-                   : form == mc::host::kListNarrow ? narrow : mc::kAttnFewRows;
+                   : form == mc::host::kListNarrow ? narrow
+                   : form == mc::host::kListPairs ? mc::kAttnPairRows : mc::kAttnFewRows;
     std::printf(" %d %d\n", plan.narrow_wgs > 0 ? plan.narrow.rows : plan.classes.rows, list);
   }
   return 0;

@@ -30,12 +30,18 @@ def draw(rng):
     return (*rng.choice(HEADS), prefix, new)
 
 
-def ask(exe, batches):
+def lines_of(exe, batches, *args):
     text = "".join(" ".join(str(x) for x in [*b[:4], len(b[4]), *b[4], *b[5]]) + "\n" for b in batches)
-    res = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=300)
+    res = subprocess.run([exe, *args], input=text, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0 and res.stderr == "", res.stderr[-2000:]
-    out = [line.split() for line in res.stdout.splitlines()]
-    assert len(out) == len(batches) and all(line[7] == "1" for line in out)
+    lines = res.stdout.splitlines()
+    assert len(lines) == len(batches)
+    return lines
+
+
+def ask(exe, batches):
+    out = [line.split() for line in lines_of(exe, batches)]
+    assert all(line[7] == "1" for line in out)
     return out
 
 
@@ -96,3 +102,47 @@ def test_a_call_that_could_cut_takes_64_row_workgroups_where_whole_rows_do(tmp_p
     out = ask(build(tmp_path, "-O2"), batches)
     assert sum(line[5] == "64" for line in out) > 20
     assert [b for b, line in zip(batches, out) if line[5] == "64" and (line[3], line[6]) != ("64", "1")] == []
+
+
+FORMS = {0: 256, 0x4d434631: 128, 0x4d434632: 128, 0x4d434633: 128, 0x4d434636: 64}       # rows of the second launch's workgroups
+
+
+def test_two_launches_and_their_list_cover_every_row_tile_once(tmp_path):
+    """Under AddressSanitizer and UBSan: the classes of both launches, at the rows of the whole batch in q and out, the list of the
+    same two launches, and its mark."""
+    exe = build(tmp_path, "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all")
+    rng = random.Random(11)
+    batches = [draw(rng) for _ in range(4000)]
+    # (of test_gpu_apart.py)
+    batches += [(64, 8, 128, 0, [6000, 0], [3, 900]), (64, 8, 128, 0, [0, 7001], [1100, 33]), (64, 8, 128, 0, [17, 5, 12000, 3], [900, 0, 3, 5]),
+                (16, 2, 128, 0, [108, 14659, 1947], [2942, 299, 183]), (64, 8, 64, 0, [12007, 17, 0, 3], [17, 600, 0, 5])]
+    forms, leasts = set(), set()
+    for (Hq, Hkv, D, dtype, prefix, new), line in zip(batches, lines_of(exe, batches, "two")):
+        if line == "":
+            continue
+        (at,), few, many, mark, items = ([int(x) for x in part.split()] for part in line.split("|"))
+        G = Hq // Hkv
+        seen = {}
+        for launch, (rows, *classes) in enumerate((few, many)):
+            wg = 0
+            for i in range(0, len(classes), 8):
+                first, r, q_off, P, C, lo, hi, pieces = classes[i:i + 8]
+                assert (q_off, P, C, pieces, first) == (sum(new[:r]), prefix[r], new[r], 1, wg)
+                assert (0 < C <= at) if launch == 0 else C > at
+                wg += (hi - lo + 1) * Hkv
+                for t in range(lo, hi + 1):
+                    assert (r, t) not in seen
+                    seen[r, t] = rows
+        assert set(seen) == {(r, t) for r, C in enumerate(new) for t in range(-(-C * G // (few if C <= at else many)[0]))}
+        packed, read, small, n_few, shares, least, form, want_shares = mark
+        assert packed >> 16 == 0x4d44 and (read, small, shares) == (1, 0, want_shares)
+        assert few[0] == (16 if least or dtype == 1 else 32) and many[0] == FORMS[form]
+        items = [tuple(items[i:i + 4]) for i in range(0, len(items), 4)]
+        whole = B.mc_prefill_attn_plan(B.attn_params(Hq, Hkv, D, 16, 1 << 20, ("bf16", "f32")[dtype]), prefix, new, 0)
+        assert len(set(items)) == len(items) and set(items) == set(whole)
+        assert all(new[r] <= at for r, *_ in items[:n_few]) and all(new[r] > at for r, *_ in items[n_few:])
+        if least:
+            assert dtype == 1 or max(new[r] for r, *_ in items[:n_few]) * G <= 16          # an item is one row tile
+        forms.add(form)
+        leasts.add((dtype, least))
+    assert forms >= {0, 0x4d434633, 0x4d434636} and leasts == {(0, 0), (0, 1), (1, 1)}

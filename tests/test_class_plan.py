@@ -74,6 +74,29 @@ def test_classes_cover_every_tile_once(driver, Hq, Hkv, D, dtype, prefix, new, r
     assert mins == sorted(mins, reverse=True)          # what starts last is short
 
 
+# whole rows by 64-row workgroups (of test_gpu_pair_rows.py: several requests, heads that do not divide the lists, rows that end anywhere)
+PAIRS = [
+    (64, 8, 128, 0, [2560], [130]),
+    (64, 8, 64, 0, [2620], [133]),
+    (12, 3, 128, 0, [2700], [700]),
+    (16, 16, 128, 0, [2570, 0], [543, 3]),
+    (64, 8, 128, 0, [2600, 0, 20, 60, 100, 150, 250, 300, 370], [130, 1, 3, 10, 33, 20, 9, 70, 1]),
+    (16, 2, 128, 0, [2540], [520]),
+]
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,dtype,prefix,new", PAIRS)
+def test_64_row_classes_cover_every_tile_once(driver, Hq, Hkv, D, dtype, prefix, new):
+    p = plan(driver, Hq, Hkv, D, dtype, 0, prefix, new)
+    assert p["rows"] == p["launch_rows"] == p["list_rows"] == 64 and (p["most_pieces"], p["part_rows"]) == (1, 0)
+    wg, seen = 0, []
+    for c in p["classes"]:
+        assert (c["first"], c["q_off"], c["prefix"], c["chunk"]) == (wg, sum(new[:c["req"]]), prefix[c["req"]], new[c["req"]])
+        wg += (c["tile_hi"] - c["tile_lo"] + 1) * Hkv
+        seen += [(c["req"], t) for t in range(c["tile_lo"], c["tile_hi"] + 1)]
+    assert wg == p["n_wgs"] and sorted(seen) == [(r, t) for r in range(len(new)) for t in range(-(-new[r] * (Hq // Hkv) // 64))]
+
+
 def test_cuts_that_matter(driver):
     assert plan(driver, 64, 8, 128, 0, 32 * 16 * 64, [131056], [16])["most_pieces"] == 32
     p = plan(driver, 64, 8, 128, 0, 6 * 1139 * 64, [6144, 6144], [811, 328])
