@@ -1,14 +1,12 @@
 // Plans each batch read from stdin as a call without room for partial results does (plan_classes, then plan_apart); one line a
 // batch: "none" (more requests than classes), "one" or "two" launches, the allocations on the host heap that both planning functions
-// made, and of one launch the rows of its workgroups (0: narrow) and its estimated end in microseconds;
-// then the same rows of a call with room for partial results (-1: it cuts some), and whether it is that launch;
+// made, and of one launch the rows of its workgroups (0: narrow) and its estimated end in microseconds,
 // and whether a list's form is the same from that plan as from the lengths.
 // With an argument, of each batch of two launches only: "line | rows of a workgroup, then classes, of the first launch | the same
 // of the second | the list's mark, then what it is read as | the list's items", numbers all.
 // input:  Hq Hkv D dtype batch P... C...
 #include <cstdio>
 #include <cstdlib>
-#include <cstring>
 #include <new>
 #include <vector>
 
@@ -70,17 +68,10 @@ int main(int argc, char**) {
     }
     std::printf("%s %ld %ld", !planned ? "none" : two ? "two" : "one", by_classes, news - before - by_classes);
     std::printf(" %d %.9g", planned && one.narrow_wgs == 0 ? one.classes.rows : 0, planned ? one.ends : 0.0);
-    mc::host::AutoLayout lay;
-    mc::host::auto_layout(&p, P.data(), C.data(), batch, &lay);
-    const mc::host::ClassPlan& roomy = lay.plan;
-    const bool whole = planned && lay.by_classes && (roomy.narrow_wgs > 0 ? roomy.narrow_pieces : roomy.most_pieces) == 1;
-    const bool same = whole && roomy.narrow_wgs == one.narrow_wgs && roomy.ends == one.ends &&
-                      (one.narrow_wgs > 0 ? std::memcmp(&roomy.narrow, &one.narrow, sizeof one.narrow) == 0
-                                          : std::memcmp(&roomy.classes, &one.classes, sizeof one.classes) == 0);
     const int64_t items = mc::host::count_items(&p, C.data(), batch);
     const bool form = mc::host::planned_list_form(&p, P.data(), C.data(), batch, planned ? &one : nullptr, items) ==
                       mc::host::list_form(&p, P.data(), C.data(), batch, 0, items);
-    std::printf(" %d %d %d\n", !whole ? -1 : roomy.narrow_wgs > 0 ? 0 : roomy.classes.rows, same, form);
+    std::printf(" %d\n", form);
   }
   return 0;
 }
