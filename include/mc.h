@@ -241,7 +241,7 @@ mc_status mc_prefill_attn_paged_noalloc(const mc_attn_params* p, const void* q, 
  * mc_kv_append_run takes either form of plan.
  */
 typedef struct {
-  int32_t n_items;            /* work items (workgroups) of the attention launch */
+  int32_t n_items;            /* work items of the attention launch or launches */
   int32_t batch;
   int32_t kv_splits;          /* 0 = whole-row form */
   int32_t need_pages;         /* most pages any request with new tokens spans */
@@ -266,17 +266,19 @@ mc_status mc_kv_append_run(const mc_attn_params* p, const mc_attn_plan* plan, co
                            const void* workspace, void* hip_stream);
 
 /*
- * The work list the two attention calls above launch for these lengths, in launch order, written
- * to HOST memory - for inspection and for tests of the host logic; no GPU call, nothing enqueued.
- * One work item = one workgroup = one tile of 256 stacked query rows (row = token * G + head in
- * group) of one (request, KV head), and for the split form one key slice of it:
+ * The work list of the two attention calls above for these lengths, written to HOST memory - for
+ * inspection and for tests of the host logic; no GPU call, nothing enqueued.
+ * One work item = one tile of 256 stacked query rows (row = token * G + head in group) of one
+ * (request, KV head), and for the split form one key slice of it; one workgroup takes it, or several
+ * of fewer rows each.
  *
  *   items[i] = { request, kv_head, first stacked row of the tile, key slice (0 if whole-row) }
  *
  * Order: items are keyed by the keys their last row sees (split form: by the keys of the slice),
  * kept in 8 lists by (request * Hkv + kv_head + slice) mod 8, longest first within a list, and
  * dealt out round-robin - consecutive workgroups land on different XCDs, so each XCD's L2 keeps
- * the K/V stream of one (request, KV head), and the longest items start first.
+ * the K/V stream of one (request, KV head), and the longest items start first.  Whole rows may be
+ * launched as two lists, the requests of few rows first and then the others: each is in this order.
  *
  *   kv_splits  0 = mc_prefill_attn_paged, 1 .. MC_MAX_KV_SPLITS = mc_prefill_attn_paged_split
  *   items      HOST int32 [capacity][4], or NULL (capacity 0) to count only
@@ -413,9 +415,10 @@ mc_status mc_kv_unpack_layer_ordered(const void* k_in, const void* v_in, int64_t
  *          = two host-to-device copies, then mc_kv_unpack_layer
  *   store: pages page_ids[i] of the pools -> k_stage/v_stage -> k_host/v_host
  *          = mc_kv_pack_layer, then two device-to-host copies
- *   At most 512 slices of 4 KiB (2 MiB of K, if pages are that long) between pinned memory and the
- *   pools are moved by one kernel, which reads or writes the host memory itself; the staging buffers
- *   hold the packed form afterwards either way.
+ *   At most 512 slices of 4 KiB (2 MiB of K, if pages are that long) between plain pinned memory (of
+ *   hipHostMalloc, not non-coherent or write-combined) and the pools are moved by one kernel, which
+ *   reads or writes the host memory itself; the staging buffers hold the packed form afterwards either
+ *   way.
  *
  *   k_host, v_host    host  n * page_bytes each.  For the copies to be asynchronous the memory
  *                           must be pinned (hipHostMalloc); pageable memory works but blocks.

@@ -2,7 +2,7 @@
 // (code under HIP graph capture, serving loops and harnesses that forbid hipMalloc).
 //
 // Batches of up to kMaxAttnClasses - 1 requests are described by classes in the kernel argument, as
-// in mc_prefill_attn_paged: no list at all, one launch.  For larger ones mc_prefill_attn_paged keeps
+// in mc_prefill_attn_paged: no list at all, one launch or two (plan_apart).  For larger ones mc_prefill_attn_paged keeps
 // its work list and request table in a caller-supplied workspace and uploads them from pinned host
 // memory; here both live in a file-scope device array, and the list is BUILT ON THE DEVICE by a
 // small kernel that gets the batch's lengths as a kernel argument: no workspace, no upload, no

@@ -34,7 +34,7 @@
 //   * Pair rows (64-row workgroups): for launches whose 128-row tiles leave compute units idle and whose 32-row ones would take
 //     several rounds.  A tile is one block for each wave: 0.44-0.47 us (head_dim 64: 0.36), of which the copies hold the compute unit
 //     for 0.29; 0.72 (0.55) with 128 rows.  The two pairs meet in LDS once, at the end.  Planned, us, before / so: 64/8 heads,
-//     P 8192, C 192 103 / 64; P 120000, C 200 1370 / 880 (head_dim 64 1170 / 690); 16/2 heads, P 23838, C 599 240 / 165; 8/1 heads,
+//     P 8192, C 192 103 / 67; P 120000, C 200 1375 / 869 (head_dim 64 1167 / 693); 16/2 heads, P 23838, C 599 240 / 165; 8/1 heads,
 //     P 24084, C 1839 260 / 188.  When it is taken: plan_classes (host_plan.cpp).
 //   * What bounds it at head_dim 128: the board's power limit.  7.0 % less time on all-zero operands,
 //     which run at the full clock (128k-context shape, 2.58 -> 2.40 ms; 6.1 % fewer cycles by the

@@ -322,8 +322,8 @@ constexpr int64_t kMostNarrow = 3 * kComputeUnits;
 // by 3 %, and they run x1.43 faster, the others 4 % slower.
 constexpr int64_t kMostPairs = 3 * kComputeUnits;
 constexpr double kPairSlack = 1.03, kPairRoundsSlack = 1.15;
-// Fewer key tiles (2560 keys) are left to 128-row workgroups, which are tested there; they would gain a few microseconds a launch
-// (64/8 heads, P 600, C 200 17.7 / 12.9).
+// Fewer key tiles (2560 keys) are left to 128-row workgroups: not where a measurement puts the line, but where the tests of that form
+// need it.  Shorter calls would gain a few microseconds a launch (64/8 heads, P 600, C 200 17.7 / 12.9).
 constexpr int64_t kLeastPairTiles = 40;
 
 // How much sooner the narrow form has to end than a cut, and than anything if it takes more than one round (the estimate's
@@ -881,7 +881,7 @@ bool plan_classes(const mc_attn_params* p, const int32_t* prefix_lens, NewLens n
 // Requests of few rows behind long prefixes beside requests of many rows: in one form either the former walk their keys at the pace
 // of a 128- or 256-row workgroup or the latter are too many narrow workgroups.  One launch behind the other, the line between
 // them at a power of two of new tokens.
-// Planned, us, one launch / two: 64/8 heads, P 6000 and 0, C 3 and 900 72 / 60; P 19657, 31 and 50, C 2, 2 and 829 213 / 149;
+// Planned, us, one launch / two: 64/8 heads, P 6000 and 0, C 3 and 900 69 / 57; P 19657, 31 and 50, C 2, 2 and 829 208 / 101;
 // P 51199 and 647, C 7 and 1187 552 / 335; fp32, 16/16 heads, P 3900, 0, 40, C 3, 900, 5 243 / 99.
 // What both launches take at least, by the longest row tile of either and the work of the second, says which line is tried; it is
 // planned only if that is sooner than one launch, which most batches end at.

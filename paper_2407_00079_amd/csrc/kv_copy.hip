@@ -72,7 +72,8 @@ __global__ __launch_bounds__(kThreads) void kv_copy_kernel(const u32x4* __restri
 // Few workgroups, small enough to run beside attention's on a compute unit: 16 keep 256 KiB of reads in flight, and 8 write as
 // fast as the link takes it while fewer of attention's wait behind them.  A step of 231 us of attention a layer (64/8 heads, P 8192,
 // C 1024) that stores 2 MiB of K and of V 376 by the engine, with 64 workgroups 304, 16 296, 8 292; one of 1010 us of attention
-// 1047, 1079, 1060, 1057 (loads make no difference).  So not beyond 2 MiB: the engine disturbs a long attention less.
+// 1047, 1079, 1060, 1057 (loads make no difference).  So no stores beyond 2 MiB: the engine disturbs a long attention less.  Loads
+// stop there too, without having been weighed by themselves.
 constexpr int kHostThreads = 256, kHostPer = 4, kHostLoadGrid = 16, kHostStoreGrid = 8;
 static_assert(kHostThreads * 16 == kHostSliceBytes, "a workgroup moves a slice at a time");
 template <bool kLoad>
